@@ -152,7 +152,7 @@ def tolerance(case):
 # ---- inputs
 
 
-def _make_index(case, g):
+def _arrays(case, g):
     dev, N, d, nlist = g.device, case["N"], case["d"], case["nlist"]
     unit = case["metric"] == "ip"
     cent = torch.nn.functional.normalize(torch.randn(nlist, d, generator=g, device=dev), dim=1)
@@ -169,8 +169,19 @@ def _make_index(case, g):
         x = torch.randn(min(step, N - r), d, generator=g, device=dev).mul_(NOISE / d ** 0.5).add_(cent[row_list[r:r + step]])
         vectors[r:r + step] = torch.nn.functional.normalize(x, dim=1) if unit else x
     ids = torch.randperm(N, generator=g, device=dev)
-    index = hr.IvfIndex(cent, offsets.cpu(), vectors, ids, row_tables=case["tables"])
-    return index, cent, offsets, rank_to_list, torch.from_numpy(_chance(case, sizes)).to(dev)
+    return cent, offsets, vectors, ids, rank_to_list, torch.from_numpy(_chance(case, sizes)).to(dev)
+
+
+def _queries(case, cent, rank_to_list, chance, g):
+    """The batch of queries and, for multi-hop requests, those of the hop after it (else None)."""
+    own = rank_to_list[torch.multinomial(chance, case["nq"], replacement=True, generator=g)]
+
+    def near(x, spread):
+        y = x + torch.randn(x.shape, generator=g, device=g.device) * (spread / case["d"] ** 0.5)
+        return torch.nn.functional.normalize(y, dim=1) if case["metric"] == "ip" else y
+
+    q = near(cent[own], NOISE)
+    return q, near(q, DRIFT) if case["op"] == "reuse" else None
 
 
 def _cold(case):
@@ -183,18 +194,19 @@ def _moved(case):
     return slice(n // 2, n // 2 + max(1, min(8, n // 16)))
 
 
-def prepare(case, seed):
+def _generator(seed):
     g = torch.Generator(device="cuda")
     g.manual_seed(int(seed))
-    index, cent, offsets, rank_to_list, chance = _make_index(case, g)
-    nq, d, k, nlist = case["nq"], case["d"], case["k"], case["nlist"]
-    own = rank_to_list[torch.multinomial(chance, nq, replacement=True, generator=g)]
+    return g
 
-    def near(x, spread):
-        y = x + torch.randn(x.shape, generator=g, device=g.device) * (spread / d ** 0.5)
-        return torch.nn.functional.normalize(y, dim=1) if case["metric"] == "ip" else y
 
-    s = dict(case=case, index=index, queries=near(cent[own], NOISE))
+def prepare(case, seed):
+    g = _generator(seed)
+    cent, offsets, vectors, ids, rank_to_list, chance = _arrays(case, g)
+    index = hr.IvfIndex(cent, offsets.cpu(), vectors, ids, row_tables=case["tables"])
+    nq, k, nlist = case["nq"], case["k"], case["nlist"]
+    queries, after = _queries(case, cent, rank_to_list, chance, g)
+    s = dict(case=case, index=index, queries=queries)
     if case["op"] == "static":
         s["ids"] = torch.empty(nq, k, dtype=torch.int64, device=g.device)
         s["scores"] = torch.empty(nq, k, dtype=torch.float32, device=g.device)
@@ -204,7 +216,7 @@ def prepare(case, seed):
         state = index.new_state_rows(nq, CARRIED)
         index.scan_step_rows(s["queries"], s["probed"], state, case["metric"])
         s["cached_rows"] = state[2]
-        s["queries"] = near(s["queries"], DRIFT)
+        s["queries"] = after
     if case["op"] == "swap":
         s["into"] = rank_to_list[_moved(case)].to(torch.int32)
         s["out"] = rank_to_list[nlist - _cold(case):].to(torch.int32)
@@ -251,3 +263,72 @@ def run(s):
     for a, b in s["ranges"]:
         index.refresh_rows(a, b)
     return (hot, hits) + _swap_batch(s)
+
+
+# ---- the same outputs in 64 bits
+
+
+def _operand(case, q):
+    """Queries as the list scan multiplies them: rounded to binary16 with binary16 rows, bfloat16 pairs with bfloat16 ones."""
+    if case["storage"] == "f16" or (case["storage"] == "bf16" and case["tables"]):
+        return q.half().double()
+    if case["storage"] == "bf16":
+        hi = q.bfloat16().float()
+        return hi.double() + (q - hi).bfloat16().double()
+    return q.double()
+
+
+def _keys(case, q, rows):
+    """Larger is better: inner products, or minus the squared distances; both arguments in 64 bits."""
+    dots = q @ rows.T
+    return dots if case["metric"] == "ip" else 2 * dots - (q * q).sum(1)[:, None] - (rows * rows).sum(1)
+
+
+def _closest(case, cent, q):
+    key, probe = torch.topk(_keys(case, q.double(), cent.double()), case["nprobe"], dim=1)
+    return probe, key if case["metric"] == "ip" else -key
+
+
+def _best(case, offsets, vectors, ids, q, probe, k):
+    """The k best rows of every query's probed lists (a probe of -1 is none): labels, scores, row numbers."""
+    nq, nprobe = probe.shape
+    op, host = _operand(case, q), offsets.tolist()
+    key = torch.full((nq * nprobe, k), -float("inf"), dtype=torch.float64, device=q.device)
+    row = torch.full((nq * nprobe, k), -1, dtype=torch.int64, device=q.device)
+    by_list, pair = torch.sort(probe.reshape(-1), stable=True)
+    ends = torch.searchsorted(by_list, torch.arange(-1, case["nlist"], device=q.device), right=True).tolist()
+    for x in range(case["nlist"]):
+        at = pair[ends[x]:ends[x + 1]]
+        a, b = host[x], host[x + 1]
+        for part in torch.split(at, max(1, (1 << 28) // (b - a))) if len(at) else ():
+            top = torch.topk(_keys(case, op[part // nprobe], vectors[a:b].double()), min(k, b - a), dim=1)
+            key[part, :min(k, b - a)] = top.values
+            row[part, :min(k, b - a)] = torch.where(top.values > -float("inf"), top.indices + a, -1)
+    key, at = torch.topk(key.view(nq, nprobe * k), k, dim=1)
+    row = row.view(nq, nprobe * k).gather(1, at)
+    return torch.where(row >= 0, ids[row.clamp(min=0)], -1), key if case["metric"] == "ip" else -key, row
+
+
+def exact(case, seed):
+    g = _generator(seed)
+    cent, offsets, vectors, ids, rank_to_list, chance = _arrays(case, g)
+    q, after = _queries(case, cent, rank_to_list, chance, g)
+    if case["op"] == "reuse":
+        # (a row that the hop before returned is a candidate whether its list is probed again or not)
+        cached = _best(case, offsets, vectors, ids, q, _closest(case, cent, q)[0], CARRIED)[2]
+        found = _best(case, offsets, vectors, ids, after, _closest(case, cent, after)[0], CARRIED)[2]
+        row = torch.cat([found, torch.where((cached[:, :, None] == found[:, None, :]).any(2), -1, cached)], 1)
+        op = _operand(case, after)
+        key = torch.stack([_keys(case, op[i:i + 1], vectors[row[i].clamp(min=0)].double())[0] for i in range(case["nq"])])
+        key = torch.topk(torch.where(row >= 0, key, -float("inf")), CARRIED, dim=1).values
+        return None, None, (None, key if case["metric"] == "ip" else -key, None)
+    probe, score = _closest(case, cent, q)
+    if case["op"] == "coarse":
+        return probe.int(), score
+    if case["op"] == "swap":
+        cold = torch.zeros(case["nlist"], dtype=torch.bool, device=q.device)
+        cold[rank_to_list[case["nlist"] - _cold(case):]] = True
+        cold[rank_to_list[_moved(case)]] = False
+        probe = torch.where(cold[probe], -1, probe)
+        return (None,) * 4 + _best(case, offsets, vectors, ids, q, probe, case["k"])[:2]
+    return _best(case, offsets, vectors, ids, q, probe, case["k"])[:2]
