@@ -830,43 +830,54 @@ __global__ __launch_bounds__(256) void k_topk_rows(TopkArgs a)
     Cand* ent = s_ent[wave];
     const int k = min(a.k, a.n);
 
-    // ---- the quick way, one pass over the row: a lower bound t0 from 512 keys spread over the
-    // row (their m-th largest, m chosen so that about 3k keys of the row are expected above
-    // it), every key >= t0 collected in LDS, the k best of those selected there.  It is exact
-    // whenever at least k and at most kCollect keys were collected (all keys >= the k-th best
-    // are then among them); otherwise the radix passes below do the work.
+    // ---- the quick way, one pass over the row: a lower bound t0 from up to 1024 keys spread over the row (their
+    // want-th largest), every key >= t0 collected in LDS, the k best of those selected there.  It is exact whenever at
+    // least k and at most kCollect keys were collected (all keys >= the k-th best are then among them); otherwise the
+    // radix passes below do the work, some eight times slower: the row that takes them is what the whole launch waits
+    // for.  How many sampled keys belong to the k best is close to Poisson with mean lambda = k S / n, so want lies
+    // 5.5 deviations above it: too few are collected for one row in some hundred thousand.  (16384 keys, k 128, 3001
+    // rows: with 3 k keys expected above t0, from 512 samples, about three rows took the radix passes and the call 537 us,
+    // now 445; the select over fewer bits is part of that.)
     bool done = false;
     {
         uint32_t t0 = 0;                            // (below every encoded key: short rows are collected whole)
-        if (a.n > kCollect) {
-            constexpr int S = 512;
-            uint32_t sv[S / 64];
+        auto sample = [&](auto per) __attribute__((always_inline)) {
+            constexpr int C = decltype(per)::value, S = C * 64;
+            uint32_t sv[C];
 #pragma unroll
-            for (int j = 0; j < S / 64; j++) sv[j] = enc_key(row[(int)(((long long)(j * 64 + lane) * a.n) / S)]);
-            int want = (int)((3LL * k * S + a.n - 1) / a.n);
+            for (int j = 0; j < C; j++) sv[j] = enc_key(row[(int)(((long long)(j * 64 + lane) * a.n) / S)]);
+            const float lambda = (float)k * (float)S / (float)a.n;
+            // (nor may more than kCollect be collected: for large k midway between the two)
+            int want = min((int)(lambda + 5.5f * sqrtf(lambda) + 3.0f), (int)((float)S * (float)(k + kCollect) * 0.5f / (float)a.n) + 1);
             want = max(2, min(S, want));
-            unsigned long long alive[S / 64];
+            unsigned long long alive[C];
 #pragma unroll
-            for (int j = 0; j < S / 64; j++) alive[j] = ~0ull;
-            for (int b = 31; b >= 0; b--) {
-                unsigned long long ones[S / 64];
+            for (int j = 0; j < C; j++) alive[j] = ~0ull;
+            for (int b = 31, left = S; b >= 0 && left != want; b--) {
+                unsigned long long ones[C];
                 int c1 = 0;
 #pragma unroll
-                for (int j = 0; j < S / 64; j++) {
+                for (int j = 0; j < C; j++) {
                     ones[j] = alive[j] & __builtin_amdgcn_ballot_w64((sv[j] >> b) & 1u);
                     c1 += __builtin_popcountll(ones[j]);
                 }
                 if (c1 >= want) {
                     t0 |= 1u << b;
+                    left = c1;
 #pragma unroll
-                    for (int j = 0; j < S / 64; j++) alive[j] = ones[j];
+                    for (int j = 0; j < C; j++) alive[j] = ones[j];
                 } else {
                     want -= c1;
+                    left -= c1;
 #pragma unroll
-                    for (int j = 0; j < S / 64; j++) alive[j] &= ~ones[j];
+                    for (int j = 0; j < C; j++) alive[j] &= ~ones[j];
                 }
             }
-        }
+        };
+        // (short rows: a sample of 256 is enough to spare the select over the whole of them)
+        if (a.n > 4 * kCollect) sample(std::integral_constant<int, 16>{});
+        else if (a.n > kCollect) sample(std::integral_constant<int, 8>{});
+        else if (a.n > 256) sample(std::integral_constant<int, 4>{});
         int cnt = 0;
         auto collect = [&](float key, int i, bool valid) __attribute__((always_inline)) {
             const uint32_t u = enc_key(key);
@@ -999,6 +1010,7 @@ __global__ __launch_bounds__(256) void k_topk_rows(TopkArgs a)
         int pos[PER];
 #pragma unroll
         for (int m = 0; m < PER; m++) { e[m] = lane + 64 * m < k ? ent[lane + 64 * m] : Cand{0u, 0u}; pos[m] = 0; }
+#pragma unroll 8
         for (int i = 0; i < k; i++) {
             const Cand o = ent[i];
 #pragma unroll

@@ -114,6 +114,22 @@ __device__ __forceinline__ int wave_prefix_sum(int v)
     return v;
 }
 
+// bitwise or / smallest value over the 64 lanes of a wave, to all lanes (the lane steps of the prefix sum above; lanes
+// that a step does not reach combine their value with itself)
+template <typename F>
+__device__ __forceinline__ uint32_t wave_fold(uint32_t v, F&& f)
+{
+    v = f(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x111, 0xf, 0xf, false));
+    v = f(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x112, 0xf, 0xf, false));
+    v = f(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x114, 0xf, 0xf, false));
+    v = f(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x118, 0xf, 0xf, false));
+    v = f(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x142, 0xa, 0xf, false));
+    v = f(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x143, 0xc, 0xf, false));
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ uint32_t wave_or(uint32_t v) { return wave_fold(v, [](uint32_t x, uint32_t y) { return x | y; }); }
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) { return wave_fold(v, [](uint32_t x, uint32_t y) { return x < y ? x : y; }); }
+
 // Lower edge of histogram bin b of a query whose bin 0 starts at base and whose bins are w
 // wide; one expression, used wherever a key is binned or a bound is derived, so that a key
 // counted in bin b is never below the edge that later readers compute for b.
@@ -122,8 +138,10 @@ __device__ __forceinline__ float hist_edge(float base, float w, int b) { return 
 // Keep the k best of the n (> k) candidates in buf[0..n): afterwards buf[0..k) holds them, in
 // no particular order.  Order: key descending, then label ascending (label = row number when
 // ids == nullptr; labels are only fetched when equal keys straddle the k-th place).
-// Binary radix select on the 32 key bits: the cost does not depend on n.  Called by a whole
-// converged wave with wave-uniform arguments.  Returns the k-th best key.
+// Binary radix select on the key bits.  What bounds it is a serial chain, one ballot and count per entry slot and bit,
+// so it walks as few bits as decide: from the highest bit in which two of the keys differ (keys of one query share
+// sign, exponent and more) down to where as many entries are left as are wanted, about log2 n + 2 bits instead of 32.
+// Called by a whole converged wave with wave-uniform arguments.  Returns the k-th best key.
 // Label of a candidate for tie-breaking and output: rows with the top bit set are entries of
 // a carried result (index into ext), the others stored rows.
 constexpr uint32_t kCarried = 0x80000000u;
@@ -147,9 +165,19 @@ __device__ __forceinline__ uint32_t wave_select(Cand* buf, int n, int k, const i
         alive[m] = __builtin_amdgcn_ballot_w64(valid);
         kept[m] = 0;
     }
+    // the bits above the highest one in which two keys differ decide nothing: start below them
+    uint32_t has1 = 0, has0 = 0;
+#pragma unroll
+    for (int m = 0; m < CAPE; m++)
+        if ((alive[m] >> lane) & 1) { has1 |= e[m].key; has0 |= ~e[m].key; }
+    has1 = wave_or(has1);
+    const uint32_t differ = has1 & wave_or(has0);
     int need = k;              // how many of the entries still alive belong to the k best
-    uint32_t T = 0;            // k-th best key, built from the top bit down
-    for (int b = 31; b >= 0; b--) {
+    int left = n;              // entries still alive
+    int b = differ ? 31 - __builtin_clz(differ) : -1;
+    uint32_t T = has1 & ~(uint32_t)((2ull << (b < 0 ? 0 : b)) - 1);     // k-th best key, built from bit b down
+    if (b < 0) T = has1;
+    for (; b >= 0 && left != need; b--) {
         const uint32_t bit = 1u << b;
         unsigned long long ones[CAPE];
         int c1 = 0;
@@ -160,19 +188,26 @@ __device__ __forceinline__ uint32_t wave_select(Cand* buf, int n, int k, const i
         }
         if (c1 >= need) {
             T |= bit;
+            left = c1;
 #pragma unroll
             for (int m = 0; m < CAPE; m++) alive[m] = ones[m];
         } else {
             need -= c1;
+            left -= c1;
 #pragma unroll
             for (int m = 0; m < CAPE; m++) { kept[m] |= ones[m]; alive[m] &= ~ones[m]; }
         }
     }
-    // alive = entries whose key equals T; `need` of them complete the k best
-    int n_eq = 0;
+    if (b >= 0) {
+        // everything still alive belongs to the k best: the k-th is the smallest of it
+        uint32_t low = ~0u;
 #pragma unroll
-    for (int m = 0; m < CAPE; m++) n_eq += __builtin_popcountll(alive[m]);
-    if (n_eq > need) {
+        for (int m = 0; m < CAPE; m++)
+            if ((alive[m] >> lane) & 1) low = min(low, e[m].key);
+        T = wave_min(low);
+    }
+    // `need` of the entries still alive complete the k best (more alive than that: their keys all equal T)
+    if (left > need) {
         // equal keys on both sides of the k-th place: take the lowest labels
         int64_t label[CAPE];
         int rank[CAPE];
