@@ -85,7 +85,7 @@ size_t scan_lds_bytes(int dtype, int d, int cap, int shape, int nbuf)
         const int chunks = kBlockRows * d * 2 / 16, threads = nw * 64;
         buf = (size_t)((chunks + threads - 1) / threads) * threads * 16;
     }
-    const size_t cw = (size_t)cols_per_set(dtype) * shape_sets(shape);
+    const size_t cw = (size_t)cols_per_set(dtype, d) * shape_sets(shape);
     return nbuf * buf + cw * cap * sizeof(Cand) + (size_t)nbuf * kBlockRows * sizeof(float) + 32;
 }
 }  // namespace hr
@@ -224,22 +224,25 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     for (int nbuf = 3; nbuf >= 2 && p.shape_c < 0; nbuf--)
         if (scan_lds_bytes(HR_F16X2, ix->d, 0, SCAN_WIDE, nbuf) <= (size_t)kLdsLimit) { p.shape_c = SCAN_WIDE; p.nbuf_c = nbuf; }
     p.shape_s = ps.shape; p.nbuf_s = ps.nbuf; p.cap_s = ps.cap; p.gsel_s = ps.gsel;
-    p.cw_c = cols_per_set(HR_F32) * shape_sets(p.shape_c < 0 ? 0 : p.shape_c);
+    p.cw_c = cols_per_set(HR_F16X2, ix->d) * shape_sets(p.shape_c < 0 ? 0 : p.shape_c);
     // queries per coarse chunk: the [chunk, nlist] key table stays within its limit, 512 MiB by default (the more
     // queries per launch the better both kernels fill the device: 16384 lists, four chunks of 2048 queries 1.88 ms,
     // one of 8192 1.45 ms)
-    p.cchunk = (int64_t)lim.ckeys_bytes / (nlist * 4) / p.cw_c * p.cw_c;
-    if (p.cchunk < p.cw_c) p.cchunk = p.cw_c;
+    p.cchunk = (int64_t)lim.ckeys_bytes / (nlist * 4) / 64 * 64;
+    if (p.cchunk < 64) p.cchunk = 64;
     if (p.cchunk > nq) p.cchunk = nq > 0 ? nq : 1;
     p.nqt_c = (int)((p.cchunk + p.cw_c - 1) / p.cw_c);
-    int64_t seg = (nlist * (int64_t)p.nqt_c + 511) / 512;
+    // rows of the centroid table per work item: as many items as two whole rounds over 256 compute units (eight where
+    // the tiles are too many to split that evenly), never a few more
+    const int64_t want = p.nqt_c <= 64 ? 512 : 2048;
+    int64_t seg = want / p.nqt_c;
+    seg = (nlist + (seg < 1 ? 1 : seg) - 1) / (seg < 1 ? 1 : seg);
     seg = (seg + 15) & ~15LL;
-    if (seg < 32) seg = 32;
-    if (seg > 1024) seg = 1024;
+    if (p.nqt_c > 1 && seg < 32) seg = 32;          // (a tile of queries is loaded per item: two blocks at least for it)
     p.seg_c = (int)seg;
     p.nseg_c = (int)((nlist + seg - 1) / seg);
     p.items_c = p.nseg_c * p.nqt_c;
-    p.cw_s = cols_per_set(scan_dtype(ix)) * shape_sets(p.shape_s < 0 ? 0 : p.shape_s);
+    p.cw_s = cols_per_set(scan_dtype(ix), ix->d) * shape_sets(p.shape_s < 0 ? 0 : p.shape_s);
     const int64_t pairs = nq * nprobe;
     // Work items: sum over probed lists of segments x query tiles.  Segments have at least C / item_target rows, C =
     // sum of rows x tiles, so there are at most item_target items plus one per (list, tile) for the ragged ends.
@@ -682,6 +685,9 @@ int hr_ivf_search(const hr_ivf_index* ix, const float* queries, int64_t nq, int3
 // Limits of a plan that has to fit the static scratch array: few, large work items (result slots are
 // what takes the room) and a small coarse key table.
 static constexpr PlanLimits kStaticLimits = {256, (size_t)4 << 20};
+// (result slots: item_target x queries of a tile.  Storage whose tiles have 128 queries since they hold both operand parts
+// in registers had 64 before: half the items are half the slots, so what used to fit still does.)
+static constexpr PlanLimits kStaticFewer = {128, (size_t)4 << 20};
 
 int hr_ivf_search_static(const hr_ivf_index* ix, const float* queries, int64_t nq, int32_t nprobe, int32_t k,
                          int32_t metric, int64_t* out_ids, float* out_scores, void* stream)
@@ -693,7 +699,8 @@ int hr_ivf_search_static(const hr_ivf_index* ix, const float* queries, int64_t n
     int dev = -1;
     HR_HIP(hipGetDevice(&dev));
     if (dev != ix->device) return fail(HR_ERR_ARG, "current device is %d, the index lives on device %d", dev, ix->device);
-    const Plan p = make_plan(ix, nq, nprobe, k, kStaticLimits);
+    Plan p = make_plan(ix, nq, nprobe, k, kStaticLimits);
+    if (p.total > (size_t)HR_STATIC_SCRATCH_BYTES && operand_parts(scan_dtype(ix), ix->d) == 2) p = make_plan(ix, nq, nprobe, k, kStaticFewer);
     if (p.total > (size_t)HR_STATIC_SCRATCH_BYTES)
         return fail(HR_ERR_WORKSPACE, "this batch (nq=%lld, nprobe=%d, k=%d) needs %zu bytes of scratch, the static array has %zu: "
                                       "use hr_ivf_search with a workspace", (long long)nq, nprobe, k, p.total, (size_t)HR_STATIC_SCRATCH_BYTES);

@@ -19,9 +19,19 @@ constexpr int kMinSegRows = 256;           // smallest rows-per-work-item
 constexpr int kItemTarget = 4096;          // aimed number of scan work items per batch
 constexpr int kHistBins = 64;              // per-query histogram of candidate keys (one bin per lane)
 
-// columns (queries) per 16-column MFMA set: 16 when the query operand is one binary16 row, 8
-// when it is a (hi, lo) pair occupying two MFMA columns.
-__host__ __device__ constexpr int cols_per_set(int dtype) { return dtype == HR_F16 ? 16 : 8; }
+// Parts of a query operand that a wave keeps in registers of their own.  A (hi, lo) pair either occupies two MFMA columns
+// (8 queries per wave) or, where two operands of d elements leave room for the rest in 256 registers, two operands of one
+// column (16 queries per wave): a tile then has twice the queries, so every row is moved into LDS half as often, and
+// every row fragment read from LDS feeds two MFMAs per plane instead of one.  Both were what the narrow form waited for:
+// 8192 queries x 16.8 M bfloat16 rows 17.9 -> 16.0 ms, 3001 queries x 16384 centroids 445 -> 355 us, float32 lists with
+// row tables (1024 queries) 705 -> 680 us; the same bits.  d = 1024 (256 registers of operand) keeps the two columns,
+// as do float32 rows split on the fly, whose rows pass through the registers.
+__host__ __device__ constexpr int operand_parts(int dtype, int d)
+{
+    return (dtype == HR_BF16 || dtype == HR_F16X2) && d <= 768 ? 2 : 1;
+}
+// columns (queries) per 16-column MFMA set
+__host__ __device__ constexpr int cols_per_set(int dtype, int d) { return dtype == HR_F16 || operand_parts(dtype, d) == 2 ? 16 : 8; }
 
 // Workgroup shapes of the scan kernel: waves x column sets per wave.  A work item covers
 // shape_sets(shape) * cols_per_set(dtype) queries of a bucket.
@@ -35,6 +45,9 @@ __host__ __device__ constexpr int scan_group(int dtype, int ksteps, int nw)
 {
     if (ksteps < 8) return ksteps < 4 ? ksteps : 4;
     if (nw == 8 && dtype == HR_F32 && ksteps >= 24) return 2;       // (leaves registers for a second row block in flight)
+    // (what a long operand in two parts leaves: 253 of 256 registers at 24 k-steps, none spilled)
+    if (nw == 8 && ksteps >= 16 && operand_parts(dtype, ksteps * 32) == 2)
+        return dtype == HR_F16X2 ? (ksteps >= 24 ? 1 : 2) : (ksteps >= 24 ? 2 : 4);
     if (nw == 8) return ((dtype == HR_F32 || dtype == HR_F16X2) && ksteps >= 32) ? 2 : 4;   // (256 registers per lane)
     return 8;
 }

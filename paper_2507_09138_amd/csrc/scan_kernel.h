@@ -11,8 +11,9 @@
 //
 // Storage types:
 //   HR_F16   rows are binary16; the query is rounded to binary16; one MFMA per k-step.
-//   HR_BF16  rows are bfloat16; the query is split into bfloat16 hi + lo parts that take two
-//            MFMA columns (lanes j and j+8 of each 16-lane row), summed after the MFMA.
+//   HR_BF16  rows are bfloat16; the query is split into bfloat16 hi + lo parts, each an operand in registers of its
+//            own (d <= 768), or the two in two MFMA columns (lanes j and j+8 of each 16-lane row); the same products
+//            in the same order either way, summed after the MFMA.
 //   HR_F32   rows are float32, split on the fly into binary16 hi + 2^11-scaled lo planes; the
 //            query likewise; the four partial products are recombined with their scales,
 //            which keeps about 22 bits of each factor with float32 accumulation.
@@ -47,6 +48,16 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
+
+// The lane number made anew where it is used.  What is computed from lane_id() does not change inside a loop, so the
+// compiler computes it before the loop and keeps it in registers for the whole of it; in paths that are taken once in
+// many blocks a few instructions are cheaper than registers that the multiplication has not got.
+__device__ __forceinline__ int lane_now()
+{
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(l));
+    return l;
+}
 
 __device__ __forceinline__ void wave_sync()
 {
@@ -152,9 +163,8 @@ __device__ __forceinline__ int64_t label_of(uint32_t row, const int64_t* ids, co
 }
 
 template <int CAPE>   // entries held per lane: CAPE * 64 >= n
-__device__ __forceinline__ uint32_t wave_select(Cand* buf, int n, int k, const int64_t* ids, const int64_t* ext = nullptr)
+__device__ __forceinline__ uint32_t wave_select(Cand* buf, int n, int k, const int64_t* ids, const int64_t* ext, const int lane)
 {
-    const int lane = lane_id();
     Cand e[CAPE];
     unsigned long long alive[CAPE], kept[CAPE];
 #pragma unroll
@@ -246,11 +256,17 @@ __device__ __forceinline__ uint32_t wave_select(Cand* buf, int n, int k, const i
     return T;
 }
 
+template <int CAPE>
+__device__ __forceinline__ uint32_t wave_select(Cand* buf, int n, int k, const int64_t* ids, const int64_t* ext = nullptr)
+{
+    return wave_select<CAPE>(buf, n, k, ids, ext, lane_id());
+}
+
 template <int DT> struct StoreTraits;
-template <> struct StoreTraits<HR_F32>  { static constexpr int esize = 4, planes = 2, nc = 8;  };
-template <> struct StoreTraits<HR_F16>  { static constexpr int esize = 2, planes = 1, nc = 16; };
-template <> struct StoreTraits<HR_BF16> { static constexpr int esize = 2, planes = 1, nc = 8;  };
-template <> struct StoreTraits<HR_F16X2> { static constexpr int esize = 2, planes = 2, nc = 8; };
+template <> struct StoreTraits<HR_F32>  { static constexpr int esize = 4, planes = 2; };
+template <> struct StoreTraits<HR_F16>  { static constexpr int esize = 2, planes = 1; };
+template <> struct StoreTraits<HR_BF16> { static constexpr int esize = 2, planes = 1; };
+template <> struct StoreTraits<HR_F16X2> { static constexpr int esize = 2, planes = 2; };
 
 // NW = waves per workgroup (4: one per SIMD, each may use all 512 registers; 8: two per SIMD
 // with 256 registers each, so that one wave's MFMAs run while the other selects or waits).
@@ -265,7 +281,6 @@ template <> struct StoreTraits<HR_F16X2> { static constexpr int esize = 2, plane
 //     all banks.  Up to four blocks are in flight or waiting in LDS ahead of the one in use.
 //   through registers (float32 storage): rows are split into binary16 hi and lo planes on the
 //     way, from a ring of prefetch registers into two padded buffers.
-constexpr int kAcc = 2;                       // accumulators per column set (independent MFMA chains)
 constexpr int kMaxAhead = 4;                  // most blocks staged ahead of the one in use (direct)
 
 template <int DT, int KSTEPS, int NCS, int NW>
@@ -273,6 +288,9 @@ struct ScanShape {
     static constexpr int nw = NW;
     static constexpr int threads = NW * 64;
     static constexpr int d = KSTEPS * 32;
+    static constexpr int nc = cols_per_set(DT, d);                 // query columns per 16-column MFMA set
+    static constexpr int qp = operand_parts(DT, d);                // parts of the query operand in registers of their own
+    static constexpr int na = 2 * qp;                              // accumulators per column set (independent MFMA chains)
     static constexpr int planes = StoreTraits<DT>::planes;
     static constexpr bool direct = DT != HR_F32;                   // (HR_F16X2: two planes, both moved directly)
     static constexpr int rowb = d * StoreTraits<DT>::esize;        // bytes of one stored row
@@ -291,7 +309,14 @@ struct ScanShape {
     static constexpr int grp = scan_group(DT, KSTEPS, NW);
     // register path: row blocks kept in flight in registers ahead of the one being staged
     static constexpr int pf = scan_prefetch(DT, KSTEPS, NCS, NW);
-    static constexpr int wcols = StoreTraits<DT>::nc * NCS;        // query columns per wave
+    static constexpr int wcols = nc * NCS;                         // query columns per wave
+    // a wave whose operand fills the register file: what the rare paths need is computed there (see lane_now), and
+    // the fragment addresses come from one register.  (Binary16 lists have registers to spare and lose by it: 4096
+    // queries x 4096 lists 2.46 -> 2.74 ms.)
+    static constexpr bool lean = qp * KSTEPS >= 32;
+    // two blocks of a pair as one MFMA chain (see mfma_pair): twice the accumulators, which a wave that holds both
+    // parts of a long operand has no registers for
+    static constexpr bool chain = NCS == 1 && (KSTEPS / grp) % 2 == 0 && grp * 2 <= KSTEPS && qp * planes * KSTEPS < 48;
     static constexpr int cw = wcols * NW;                          // query columns per item
 };
 
@@ -358,17 +383,16 @@ __device__ __forceinline__ void stage_block(char* buf, const u32x4 (&regs)[S::nl
 // with padded rows the four bases are 64 bytes apart, with the xor-ed chunk positions of the
 // direct staging they are permuted per lane.
 template <int DT, int KSTEPS, int NCS, int NA, typename S>
-__device__ __forceinline__ void mfma_block(const char* const (&ap)[4], const u32x4 (&bfrag)[NCS][KSTEPS], floatx4 (&acc)[NCS][kAcc])
+__device__ __forceinline__ void mfma_block(const char* const (&ap)[4], const u32x4 (&bfrag)[NCS * S::qp][KSTEPS], floatx4 (&acc)[NCS][S::na])
 {
     constexpr int G = S::grp;                        // k-steps per group
     constexpr int NG = KSTEPS / G;
-    constexpr int AM = (NA == 1 ? kAcc : 2) - 1;     // a lone set spreads over all accumulators
     constexpr int P = StoreTraits<DT>::planes;
     static_assert(KSTEPS % G == 0, "k-steps must split into whole groups");
 #pragma unroll
     for (int s = 0; s < NA; s++)
 #pragma unroll
-        for (int i = 0; i < kAcc; i++) acc[s][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < S::na; i++) acc[s][i] = floatx4{0.f, 0.f, 0.f, 0.f};
     u32x4 af[2][P][G];
 #pragma unroll
     for (int i = 0; i < G; i++)
@@ -389,16 +413,20 @@ __device__ __forceinline__ void mfma_block(const char* const (&ap)[4], const u32
             const int t = gi * G + i;
 #pragma unroll
             for (int s = 0; s < NA; s++) {
-                if constexpr (StoreTraits<DT>::planes == 2) {
-                    half8 b = __builtin_bit_cast(half8, bfrag[s][t]);
-                    acc[s][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gi & 1][0][i]), b, acc[s][0], 0, 0, 0);
-                    acc[s][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gi & 1][1][i]), b, acc[s][1], 0, 0, 0);
-                } else if constexpr (DT == HR_F16) {
-                    half8 b = __builtin_bit_cast(half8, bfrag[s][t]);
-                    acc[s][t & AM] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gi & 1][0][i]), b, acc[s][t & AM], 0, 0, 0);
-                } else {
-                    bf16x8 b = __builtin_bit_cast(bf16x8, bfrag[s][t]);
-                    acc[s][t & AM] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[gi & 1][0][i]), b, acc[s][t & AM], 0, 0, 0);
+#pragma unroll
+                for (int qp = 0; qp < S::qp; qp++) {
+                    const u32x4 bq = bfrag[s * S::qp + qp][t];
+                    if constexpr (StoreTraits<DT>::planes == 2) {
+                        half8 b = __builtin_bit_cast(half8, bq);
+                        acc[s][qp * 2] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gi & 1][0][i]), b, acc[s][qp * 2], 0, 0, 0);
+                        acc[s][qp * 2 + 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gi & 1][1][i]), b, acc[s][qp * 2 + 1], 0, 0, 0);
+                    } else if constexpr (DT == HR_F16) {
+                        half8 b = __builtin_bit_cast(half8, bq);
+                        acc[s][t & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gi & 1][0][i]), b, acc[s][t & 1], 0, 0, 0);
+                    } else {
+                        bf16x8 b = __builtin_bit_cast(bf16x8, bq);
+                        acc[s][qp * 2 + (t & 1)] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[gi & 1][0][i]), b, acc[s][qp * 2 + (t & 1)], 0, 0, 0);
+                    }
                 }
             }
         }
@@ -411,19 +439,18 @@ __device__ __forceinline__ void mfma_block(const char* const (&ap)[4], const u32
 // its own begins with a round trip to LDS during which the wave has nothing to issue), and `between` (the
 // filter of the first block) runs after the first MFMAs of the second block have been handed to the matrix pipe.
 template <int DT, int KSTEPS, int NCS, int NA, typename S, typename F>
-__device__ __forceinline__ void mfma_pair(const char* const (&ap0)[4], const char* const (&ap1)[4], const u32x4 (&bfrag)[NCS][KSTEPS],
-                                          floatx4 (&acc0)[NCS][kAcc], floatx4 (&acc1)[NCS][kAcc], F&& between)
+__device__ __forceinline__ void mfma_pair(const char* const (&ap0)[4], const char* const (&ap1)[4], const u32x4 (&bfrag)[NCS * S::qp][KSTEPS],
+                                          floatx4 (&acc0)[NCS][S::na], floatx4 (&acc1)[NCS][S::na], F&& between)
 {
     constexpr int G = S::grp;
     constexpr int NG = KSTEPS / G;
-    constexpr int AM = (NA == 1 ? kAcc : 2) - 1;
     constexpr int P = StoreTraits<DT>::planes;
     static_assert(KSTEPS % G == 0, "k-steps must split into whole groups");
     static_assert(NG % 2 == 0, "the fragment buffers alternate: an even number of groups per block");
 #pragma unroll
     for (int s = 0; s < NA; s++)
 #pragma unroll
-        for (int i = 0; i < kAcc; i++) { acc0[s][i] = floatx4{0.f, 0.f, 0.f, 0.f}; acc1[s][i] = floatx4{0.f, 0.f, 0.f, 0.f}; }
+        for (int i = 0; i < S::na; i++) { acc0[s][i] = floatx4{0.f, 0.f, 0.f, 0.f}; acc1[s][i] = floatx4{0.f, 0.f, 0.f, 0.f}; }
     u32x4 af[2][P][G];
     // (every index below is a compile-time constant: the loop over the groups is unrolled by the type system,
     // so that the operand and accumulator arrays stay in registers)
@@ -438,23 +465,27 @@ __device__ __forceinline__ void mfma_pair(const char* const (&ap0)[4], const cha
                 else                   af[gg & 1][pl][i] = *(const u32x4*)(ap1[(g0 + i) & 3] + pl * S::plane_bytes + ((g0 + i) >> 2) * 256);
             }
     };
-    auto group = [&](auto gc, floatx4 (&acc)[NCS][kAcc]) __attribute__((always_inline)) {
+    auto group = [&](auto gc, floatx4 (&acc)[NCS][S::na]) __attribute__((always_inline)) {
         constexpr int gg = decltype(gc)::value;
 #pragma unroll
         for (int i = 0; i < G; i++) {
             const int t = (gg < NG ? gg : gg - NG) * G + i;
 #pragma unroll
             for (int s = 0; s < NA; s++) {
-                if constexpr (StoreTraits<DT>::planes == 2) {
-                    half8 b = __builtin_bit_cast(half8, bfrag[s][t]);
-                    acc[s][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gg & 1][0][i]), b, acc[s][0], 0, 0, 0);
-                    acc[s][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gg & 1][1][i]), b, acc[s][1], 0, 0, 0);
-                } else if constexpr (DT == HR_F16) {
-                    half8 b = __builtin_bit_cast(half8, bfrag[s][t]);
-                    acc[s][t & AM] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gg & 1][0][i]), b, acc[s][t & AM], 0, 0, 0);
-                } else {
-                    bf16x8 b = __builtin_bit_cast(bf16x8, bfrag[s][t]);
-                    acc[s][t & AM] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[gg & 1][0][i]), b, acc[s][t & AM], 0, 0, 0);
+#pragma unroll
+                for (int qp = 0; qp < S::qp; qp++) {
+                    const u32x4 bq = bfrag[s * S::qp + qp][t];
+                    if constexpr (StoreTraits<DT>::planes == 2) {
+                        half8 b = __builtin_bit_cast(half8, bq);
+                        acc[s][qp * 2] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gg & 1][0][i]), b, acc[s][qp * 2], 0, 0, 0);
+                        acc[s][qp * 2 + 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gg & 1][1][i]), b, acc[s][qp * 2 + 1], 0, 0, 0);
+                    } else if constexpr (DT == HR_F16) {
+                        half8 b = __builtin_bit_cast(half8, bq);
+                        acc[s][t & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gg & 1][0][i]), b, acc[s][t & 1], 0, 0, 0);
+                    } else {
+                        bf16x8 b = __builtin_bit_cast(bf16x8, bq);
+                        acc[s][qp * 2 + (t & 1)] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[gg & 1][0][i]), b, acc[s][qp * 2 + (t & 1)], 0, 0, 0);
+                    }
                 }
             }
         }
@@ -471,11 +502,11 @@ __device__ __forceinline__ void mfma_pair(const char* const (&ap0)[4], const cha
 }
 
 // prune with as few register slots per lane as the buffer capacity needs
-__device__ __forceinline__ uint32_t select_k(Cand* buf, int n, int k, int cap, const int64_t* ids)
+__device__ __forceinline__ uint32_t select_k(Cand* buf, int n, int k, int cap, const int64_t* ids, int lane)
 {
-    if (cap <= 64) return wave_select<1>(buf, n, k, ids);
-    if (cap <= 128) return wave_select<2>(buf, n, k, ids);
-    return wave_select<3>(buf, n, k, ids);
+    if (cap <= 64) return wave_select<1>(buf, n, k, ids, nullptr, lane);
+    if (cap <= 128) return wave_select<2>(buf, n, k, ids, nullptr, lane);
+    return wave_select<3>(buf, n, k, ids, nullptr, lane);
 }
 
 template <int DT, int KSTEPS, int NCS, int NW, bool GS>   // GS = a.gsel
@@ -483,8 +514,12 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
 {
     using S = ScanShape<DT, KSTEPS, NCS, NW>;
     using T = StoreTraits<DT>;
-    constexpr int NC = T::nc;
+    constexpr int NC = S::nc;
+    constexpr int QP = S::qp;
     constexpr int WC = S::wcols;
+    // the coarse step: all queries against all rows, every key written out, nothing selected (lists split into two
+    // tables at load always keep their selection buffers in global memory)
+    constexpr bool DENSE = DT == HR_F16X2 && !GS;
     constexpr int PF = S::pf;
     constexpr int NLD = S::nld;
     extern __shared__ __align__(16) char smem[];
@@ -517,6 +552,8 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
     const int myx = blockIdx.x & 7;                // workgroups are dealt round-robin to the 8 XCDs
     int drained = 0;                               // thread 0: queues found empty
 
+    auto lane_here = [&]() __attribute__((always_inline)) { return S::lean ? lane_now() : lane; };
+
     // ---- per-lane constants of the staging layout
     // row fragment of k-step t of this lane: abase[t & 3] + (t >> 2) * 256 inside a buffer
     int abase[4];
@@ -526,8 +563,15 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
         const int i = lane & 15;
         if constexpr (S::direct) {
             const int hi = (i & S::swz) >> 2, lo = i & 3;
+            static_assert(!S::lean || S::rowp % 256 == 0, "the xor below stays inside a row");
+            if constexpr (S::lean) {
+                // (a row is a multiple of 256 bytes: the address of step j is that of step 0 with 64 j xor-ed in)
+                abase[0] = i * S::rowp + 64 * hi + 16 * (g ^ lo);
+                abase[1] = abase[2] = abase[3] = 0;
+            } else {
 #pragma unroll
-            for (int j = 0; j < 4; j++) abase[j] = i * S::rowp + 64 * (j ^ hi) + 16 * (g ^ lo);
+                for (int j = 0; j < 4; j++) abase[j] = i * S::rowp + 64 * (j ^ hi) + 16 * (g ^ lo);
+            }
 #pragma unroll
             for (int m = 0; m < NLD; m++) {
                 const int L = (m * S::nfw + wave) * 64 + lane;  // chunk position inside the buffer
@@ -545,7 +589,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
     for (;;) {
         if (threadIdx.x == 0) {
             int item = -1;
-            if (a.dense) {
+            if (DENSE) {
                 int i = atomicAdd(a.work_counter, 1);
                 if (i < a.dense_items) item = i;
             } else {
@@ -574,7 +618,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
 
         // ---- decode the work item
         int qt, row0, row_end, w, boff, slot0 = 0;
-        if (a.dense) {
+        if (DENSE) {
             const int seg = item / a.dense_nqt;
             qt = item - seg * a.dense_nqt;
             row0 = seg * seg_rows;
@@ -601,7 +645,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
         //
         // direct: block blk -> buffer buf, straight from HBM; the squared norms of its rows go
         // to a place of this wave's own (each wave fetches its own copy: 64 bytes)
-        const bool stream_once = !a.dense && w <= S::cw;   // the only work item that reads these rows
+        const bool stream_once = !DENSE && w <= S::cw;   // the only work item that reads these rows
         auto fill_direct = [&](int blk, int buf) __attribute__((always_inline)) {
             const int bl = min(blk, nblk - 1);
             const int valid = min(nrows - bl * kBlockRows, kBlockRows);
@@ -622,7 +666,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
                     // are masked out of the selection)
 #pragma unroll
                     for (int m = 0; m < NLD; m++) {
-                        const int L = (m * S::nfw + wave) * 64 + lane;
+                        const int L = (m * S::nfw + wave) * 64 + lane_here();
                         const int r = L / S::cpr, pos = L % S::cpr;
                         const uint32_t o = (uint32_t)(min(r, valid - 1) * S::cpr + (pos ^ (r & S::swz))) * 16u;
                         lds_dma16(bsrc, o, dst + m * S::nfw * 1024);
@@ -631,9 +675,12 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
             }
             // (every wave writes the same 16 norms: the same number of loads per wave; the inner
             // product needs none)
-            if (a.l2 && lane < kBlockRows)
-                lds_dma4(a.row_norm + row0 + bl * kBlockRows, (uint32_t)min(lane, valid - 1) * 4u,
-                         lds_addr(nstage) + buf * (kBlockRows * 4));
+            if (a.l2) {
+                const int ln = lane_here();
+                if (ln < kBlockRows)
+                    lds_dma4(a.row_norm + row0 + bl * kBlockRows, (uint32_t)min(ln, valid - 1) * 4u,
+                             lds_addr(nstage) + buf * (kBlockRows * 4));
+            }
         };
         // through registers: a ring of PF blocks in flight
         u32x4 ring[S::direct ? 1 : PF][NLD];
@@ -658,21 +705,24 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
         bool col_ok[NCS];
         int q[NCS];
         float thr[NCS];
-        u32x4 bfrag[NCS][KSTEPS];
+        u32x4 bfrag[NCS * QP][KSTEPS];
 #pragma unroll
         for (int s = 0; s < NCS; s++) {
             const int ecol = ecol0 + s * NC;
             col_ok[s] = ecol < w;
             q[s] = 0;
-            if (col_ok[s]) q[s] = a.dense ? ecol : a.bucket_q[boff + ecol];
+            if (col_ok[s]) q[s] = DENSE ? ecol : a.bucket_q[boff + ecol];
         }
 #pragma unroll
         for (int s = 0; s < NCS; s++) {
-            const size_t qrow = (NC == 8) ? ((size_t)q[s] * 2 + part) : (size_t)q[s];
-            const char* qp = (const char*)a.qop + qrow * (size_t)(S::d * 2) + g * 16;
+            const size_t qrow = (NC == 8) ? ((size_t)q[s] * 2 + part) : (size_t)q[s] * QP;
 #pragma unroll
-            for (int t = 0; t < KSTEPS; t++)
-                bfrag[s][t] = col_ok[s] ? *(const u32x4*)(qp + t * 64) : u32x4{0, 0, 0, 0};
+            for (int h = 0; h < QP; h++) {
+                const char* qp = (const char*)a.qop + (qrow + h) * (size_t)(S::d * 2) + g * 16;
+#pragma unroll
+                for (int t = 0; t < KSTEPS; t++)
+                    bfrag[s * QP + h][t] = col_ok[s] ? *(const u32x4*)(qp + t * 64) : u32x4{0, 0, 0, 0};
+            }
             thr[s] = (owner && col_ok[s]) ? dec_key(a.thr[q[s]]) : __builtin_inff();
         }
         // candidates buffered per column: kept in a register by every lane of the column (the
@@ -680,8 +730,6 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
         int ccnt[NCS];
 #pragma unroll
         for (int s = 0; s < NCS; s++) ccnt[s] = 0;
-        const unsigned long long colmask = 0x0001000100010001ULL << jcol;   // owner lanes of my column
-        const unsigned long long below = (1ULL << lane) - 1;
         // column sets of this wave that hold at least one query (sets fill in order); a wave
         // with none only helps to stage rows
         int nact = 0;
@@ -741,8 +789,8 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
         };
 
         // ---- selection over the scores of one block: acc = accumulators of the block, nrm =
-        // squared norms of this lane's 4 rows, rbase = first of those rows
-        auto select_block = [&](const floatx4 (&acc)[NCS][kAcc], const floatx4 nrm, const int rbase) __attribute__((always_inline)) {
+        // squared norms of this lane's 4 rows, brow = first row of the block
+        auto select_block = [&](const floatx4 (&acc)[NCS][S::na], const floatx4 nrm, const int brow) __attribute__((always_inline)) {
 #pragma unroll
             for (int s = 0; s < NCS; s++) {
                 if (s >= nact) break;
@@ -753,7 +801,11 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
 #pragma unroll
                 for (int r = 0; r < 4; r++) {
                     float dot;
-                    if constexpr (T::planes == 2) {
+                    if constexpr (T::planes == 2 && QP == 2) {
+                        dot = acc[s][0][r] + (acc[s][2][r] + acc[s][1][r]) * (1.0f / 2048.0f) + acc[s][3][r] * (1.0f / 4194304.0f);
+                    } else if constexpr (QP == 2) {
+                        dot = (acc[s][0][r] + acc[s][1][r]) + (acc[s][2][r] + acc[s][3][r]);
+                    } else if constexpr (T::planes == 2) {
                         float t0 = lane_xor8(acc[s][0][r]);      // hi rows x lo query
                         float t1 = lane_xor8(acc[s][1][r]);      // lo rows x lo query
                         dot = acc[s][0][r] + (t0 + acc[s][1][r]) * (1.0f / 2048.0f) + t1 * (1.0f / 4194304.0f);
@@ -769,16 +821,20 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
 #pragma unroll
                     for (int r = 0; r < 4; r++) key[r] = 2.0f * key[r] - nrm[r];
                 }
-                if (a.key_out != nullptr) {
+                if (DENSE) {
                     // dense scoring only: every key goes to its place in the [query, row] table,
                     // one block late (see flush_keys)
                     held[s] = floatx4{key[0], key[1], key[2], key[3]};
-                    held_rbase = rbase;
+                    held_rbase = brow + g * 4;
                     continue;
                 }
                 const float best = fmaxf(fmaxf(key[0], key[1]), fmaxf(key[2], key[3]));
                 // ---- append what reaches the column's threshold
                 if (__builtin_amdgcn_ballot_w64(best >= thr[s]) != 0) {
+                    const int lane = lane_here();
+                    const int jcol = lane & (NC - 1);
+                    const int rbase = brow + (lane >> 4) * 4;                           // first of this lane's rows
+                    const unsigned long long colmask = 0x0001000100010001ULL << jcol;   // owner lanes of my column
                     bool pass[4];
 #pragma unroll
                     for (int r = 0; r < 4; r++) pass[r] = key[r] >= thr[s] && (rbase + r < row_end);
@@ -791,7 +847,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
                     for (int r = 0; r < 4; r++) {
                         const unsigned long long mine = __builtin_amdgcn_ballot_w64(pass[r]) & colmask;
                         if (pass[r]) {
-                            const int pos = ccnt[s] + add + __builtin_popcountll(mine & below);
+                            const int pos = ccnt[s] + add + lanes_below(mine);
                             const Cand cd{enc_key(key[r]), (uint32_t)(rbase + r)};
                             if (GS) gs[jcol * a.cap + pos] = cd;
                             else ssel[jcol * a.cap + pos] = cd;
@@ -805,8 +861,8 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
                         int col = __builtin_ctzll(full);
                         full &= full - 1;
                         int n = __builtin_amdgcn_readlane(ccnt[s], col);
-                        uint32_t kth = GS ? select_k(gs + col * a.cap, n, a.k, a.cap, a.row_ids)
-                                              : select_k(ssel + col * a.cap, n, a.k, a.cap, a.row_ids);
+                        uint32_t kth = GS ? select_k(gs + col * a.cap, n, a.k, a.cap, a.row_ids, lane)
+                                              : select_k(ssel + col * a.cap, n, a.k, a.cap, a.row_ids, lane);
                         float nt = 0.f;
                         if (lane == col) {
                             uint32_t old = atomicMax(&a.thr[q[s]], kth);
@@ -819,8 +875,20 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
             }
         };
 
+        // where the row fragments of this lane start in a staged block (mfma_block's ap)
+        auto frag_bases = [&](const char* (&ap)[4], const char* cur) __attribute__((always_inline)) {
+            if constexpr (S::direct && S::lean) {
+                int a0 = abase[0];
+                asm volatile("" : "+v"(a0));                     // (one register across the loop instead of four)
+#pragma unroll
+                for (int j = 0; j < 4; j++) ap[j] = cur + (a0 ^ (64 * j));
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; j++) ap[j] = cur + abase[j];
+            }
+        };
         int bi = 0;                                              // blk % NB
-        floatx4 accs[2][NCS][kAcc];
+        floatx4 accs[2][NCS][S::na];
         floatx4 nrms[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
         // direct staging: (1) this wave's part of block blk has landed, (2) barrier: so has
         // everybody's, and nobody reads block blk-1 any more, (3) request block blk+D into the
@@ -843,15 +911,16 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
                 }
             }
             __builtin_amdgcn_s_barrier();
-            if (a.key_out != nullptr) flush_keys();
+            if (DENSE) flush_keys();
             fill_direct(blk + D, bi == 0 ? NB - 1 : bi - 1);
             if (nact > 0) {
                 const char* cur = stage + bi * S::buf_bytes;
-                if (a.l2) nrms[0] = *(const floatx4*)(nstage + bi * kBlockRows + g * 4);
-                const char* const ap[4] = {cur + abase[0], cur + abase[1], cur + abase[2], cur + abase[3]};
+                if (a.l2) nrms[0] = *(const floatx4*)(nstage + bi * kBlockRows + (lane_here() >> 4) * 4);
+                const char* ap[4];
+                frag_bases(ap, cur);
                 if (NCS == 2 && nact == 2) mfma_block<DT, KSTEPS, NCS, NCS, S>(ap, bfrag, accs[0]);
                 else                       mfma_block<DT, KSTEPS, NCS, 1, S>(ap, bfrag, accs[0]);
-                select_block(accs[0], nrms[0], row0 + blk * kBlockRows + g * 4);
+                select_block(accs[0], nrms[0], row0 + blk * kBlockRows);
             }
             bi = bi + 1 == NB ? 0 : bi + 1;
         };
@@ -873,34 +942,37 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
                 fill_direct(blk + D + 1, fb + 1);
             };
             if (early) requests();
-            if (NCS == 1 && S::grp * 2 <= KSTEPS && (KSTEPS / S::grp) % 2 == 0 && nact > 0 && blk + 1 < nblk) {
+            if (S::chain && nact > 0 && blk + 1 < nblk) {
                 // both blocks of the pair as one chain (see mfma_pair); the late requests go out with the
                 // filter of the first block
                 const char* c0 = stage + bi * S::buf_bytes;
                 const char* c1 = c0 + S::buf_bytes;
                 if (a.l2) {
-                    nrms[0] = *(const floatx4*)(nstage + bi * kBlockRows + g * 4);
-                    nrms[1] = *(const floatx4*)(nstage + (bi + 1) * kBlockRows + g * 4);
+                    nrms[0] = *(const floatx4*)(nstage + bi * kBlockRows + (lane_here() >> 4) * 4);
+                    nrms[1] = *(const floatx4*)(nstage + (bi + 1) * kBlockRows + (lane_here() >> 4) * 4);
                 }
-                const char* const ap0[4] = {c0 + abase[0], c0 + abase[1], c0 + abase[2], c0 + abase[3]};
-                const char* const ap1[4] = {c1 + abase[0], c1 + abase[1], c1 + abase[2], c1 + abase[3]};
-                if constexpr (NCS == 1 && (KSTEPS / S::grp) % 2 == 0 && S::grp * 2 <= KSTEPS) {
+                const char* ap0[4];
+                frag_bases(ap0, c0);
+                const char* ap1[4];
+                frag_bases(ap1, c1);
+                if constexpr (S::chain) {
                     mfma_pair<DT, KSTEPS, NCS, 1, S>(ap0, ap1, bfrag, accs[0], accs[1], [&]() __attribute__((always_inline)) {
                         if (!early) requests();
-                        select_block(accs[0], nrms[0], row0 + blk * kBlockRows + g * 4);
+                        select_block(accs[0], nrms[0], row0 + blk * kBlockRows);
                     });
                 }
-                select_block(accs[1], nrms[1], row0 + (blk + 1) * kBlockRows + g * 4);
+                select_block(accs[1], nrms[1], row0 + (blk + 1) * kBlockRows);
             } else {
 #pragma unroll
                 for (int h = 0; h < 2; h++) {
                     if (nact > 0 && blk + h < nblk) {
                         const char* cur = stage + (bi + h) * S::buf_bytes;
-                        if (a.l2) nrms[0] = *(const floatx4*)(nstage + (bi + h) * kBlockRows + g * 4);
-                        const char* const ap[4] = {cur + abase[0], cur + abase[1], cur + abase[2], cur + abase[3]};
+                        if (a.l2) nrms[0] = *(const floatx4*)(nstage + (bi + h) * kBlockRows + (lane_here() >> 4) * 4);
+                        const char* ap[4];
+                        frag_bases(ap, cur);
                         if (NCS == 2 && nact == 2) mfma_block<DT, KSTEPS, NCS, NCS, S>(ap, bfrag, accs[0]);
                         else                       mfma_block<DT, KSTEPS, NCS, 1, S>(ap, bfrag, accs[0]);
-                        select_block(accs[0], nrms[0], row0 + (blk + h) * kBlockRows + g * 4);
+                        select_block(accs[0], nrms[0], row0 + (blk + h) * kBlockRows);
                     }
                     if (h == 0 && !early) requests();
                 }
@@ -921,11 +993,12 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
             nring[pn] = load_norm(blk + 1 + PF);
             if (live && nact > 0) {
                 const char* cur = stage + bi * S::buf_bytes;
-                nrms[0] = *(const floatx4*)(nstage + bi * kBlockRows + g * 4);
-                const char* const ap[4] = {cur + abase[0], cur + abase[1], cur + abase[2], cur + abase[3]};
+                nrms[0] = *(const floatx4*)(nstage + bi * kBlockRows + (lane_here() >> 4) * 4);
+                const char* ap[4];
+                frag_bases(ap, cur);
                 if (NCS == 2 && nact == 2) mfma_block<DT, KSTEPS, NCS, NCS, S>(ap, bfrag, accs[0]);
                 else                       mfma_block<DT, KSTEPS, NCS, 1, S>(ap, bfrag, accs[0]);
-                select_block(accs[0], nrms[0], row0 + blk * kBlockRows + g * 4);
+                select_block(accs[0], nrms[0], row0 + blk * kBlockRows);
             }
             bi ^= 1;
         };
@@ -943,13 +1016,14 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
                 static_for<PF>([&](auto pc) __attribute__((always_inline)) { step_regs(b0 + decltype(pc)::value, pc); });
         }
 
-        if (a.key_out != nullptr) flush_keys();
+        if (DENSE) flush_keys();
         // ---- hand what is left to the item's slots: columns with more entries than a slot holds
         // (slot_stride: k, or the whole buffer for small k, when nothing has to be cut) are cut
         // down to the k best first (one at a time, whole wave), then every lane copies one
         // column's entries
         wave_sync();
-        if (a.key_out == nullptr) {
+        if (!DENSE) {
+            const int lane = lane_here();
             int c = 0;
 #pragma unroll
             for (int s = 0; s < NCS; s++) {
@@ -961,7 +1035,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
                 const int wc = __builtin_ctzll(over);
                 over &= over - 1;
                 const int n = __builtin_amdgcn_readlane(c, wc);
-                uint32_t kth = select_k(mysel + wc * a.cap, n, a.k, a.cap, a.row_ids);
+                uint32_t kth = select_k(mysel + wc * a.cap, n, a.k, a.cap, a.row_ids, lane);
                 // column wc = set wc / NC, lane wc % NC of that set holds its query
                 int qq = 0;
 #pragma unroll
@@ -1150,7 +1224,7 @@ template <int DT, int KSTEPS>
 __global__ __launch_bounds__(256) void k_seed(SeedArgs a)
 {
     using T = StoreTraits<DT>;
-    constexpr int NC = T::nc;
+    constexpr int NC = DT == HR_F16 ? 16 : 8;           // (hi and lo rows of an operand in two columns)
     constexpr int d = KSTEPS * 32;
     constexpr int rowb = d * T::esize;
     constexpr int QP = (NC == 8) ? 2 : 1;               // operand rows per query (bfloat16: hi and lo)

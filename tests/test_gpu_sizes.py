@@ -57,3 +57,38 @@ def test_coarse_takes_the_closest_centroids(nlist, nprobe, nq, metric):
     twin = (np.abs(p[:, 1:] - p[:, :-1]) == nlist // 2) & (np.minimum(p[:, 1:], p[:, :-1]) < nlist // 8)
     assert np.all(p[:, 1:][twin] > p[:, :-1][twin])
     ix.close()
+
+
+def _operand(q, storage):
+    """The query as the list scan multiplies it (float32 lists: as it is)."""
+    if storage == "bf16":
+        hi = q.bfloat16().float()
+        return hi.double() + (q - hi).bfloat16().double()
+    return q.half().double() if storage == "f16" else q.double()
+
+
+@pytest.mark.parametrize("storage,tables", [("bf16", False), ("f32", True), ("f32", False), ("f16", False)])
+@pytest.mark.parametrize("d", [64, 128, 256, 512, 768, 1024])
+@pytest.mark.parametrize("nq,k,metric", [(1, 1, "ip"), (15, 100, "l2"), (17, 10, "ip"), (64, 10, "l2"), (65, 128, "ip"), (128, 3, "l2"), (129, 24, "ip"),
+                                         (257, 100, "l2")])
+def test_scan_finds_the_best_rows_at_the_edges_of_query_tiles(storage, tables, d, nq, k, metric):
+    """Every query probes every list, so the buckets are as wide as the batch: on both sides of a wave's columns and of
+    a tile's; the lists end in the middle of a block of rows."""
+    dtype = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[storage]
+    ix, cent, off, vec, ids, g = _index(2000 + nq, d, 5, dtype, nq + d, tables=tables, zipf=0.7)
+    q = torch.randn(nq, d, generator=g, device="cuda")
+    found, score = ix.search(q, 5, k, metric)
+    op = _operand(q, storage)
+    key = _keys(op, vec.double(), metric)
+    best = torch.topk(key, k, dim=1).values
+    row = torch.empty_like(ids)
+    row[ids] = torch.arange(len(ids), device="cuda")
+    got = key.gather(1, row[found])
+    # sums of d products (and norms) of values near 1 in float32, in chains of at most d/32 steps: 2^-24 of the
+    # magnitudes, |q||x| + |x|^2 below 3 d, with room for the steps of a chain
+    tol = 3 * d * 2.0 ** -24 * 8
+    assert float((got - best).abs().max()) <= 2 * tol
+    want = best if metric == "ip" else (op * op).sum(1, keepdim=True) - best
+    assert float((score.double() - want).abs().max()) <= 2 * tol
+    assert all(len(set(r)) == k for r in found.cpu().tolist())
+    ix.close()
