@@ -197,7 +197,7 @@ struct Plan {
     size_t o_thr;                   // 2*nq ints set to "-inf"
     size_t o_qop_c, o_qnorm_c, o_qop_s, o_qnorm_s;
     size_t o_probe;
-    size_t o_pair_entry, o_bucket_off, o_bucket_q, o_item_base, o_slot_base, o_xq;
+    size_t o_pair_entry, o_bucket_off, o_bucket_q, o_slot_base, o_xq;
     size_t o_ckeys;                 // coarse step: [cchunk, nlist] keys of one chunk of queries
     int64_t cchunk;                 // queries per coarse chunk
     size_t o_slot_cnt, o_slot_ent;
@@ -273,7 +273,6 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     p.o_pair_entry = take((size_t)pairs * 4);
     p.o_bucket_off = take((size_t)(nlist + 1) * 4);
     p.o_bucket_q = take((size_t)pairs * 4);
-    p.o_item_base = take((size_t)(nlist + 1) * 4);
     p.o_slot_base = take((size_t)(nlist + 1) * 4);
     p.o_xq = take((size_t)p.item_cap * 8 * 2 * sizeof(int4));
     p.o_ckeys = take((size_t)p.cchunk * nlist * 4);
@@ -587,7 +586,6 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, int64_t
     b.pair_entry = (int*)(ws + p.o_pair_entry);
     b.bucket_off = (int*)(ws + p.o_bucket_off);
     b.bucket_q = (int*)(ws + p.o_bucket_q);
-    b.item_base = (int*)(ws + p.o_item_base);
     b.slot_base = (int*)(ws + p.o_slot_base);
     b.slot_cap = p.slot_cap;
     b.item_target = p.item_target;

@@ -297,35 +297,39 @@ __global__ void k_bucket_count(BucketArgs a)
     a.pair_entry[i] = here ? atomicAdd(&a.list_w[l], 1) : -1;
 }
 
-// Exclusive prefix sum over the 1024 threads of a workgroup (16 waves); total returned to all.
-__device__ __forceinline__ int block_scan_1024(int v, int* s_wave /* [17] */, int& total)
+// Exclusive prefix sums of N values over the 1024 threads of a workgroup (16 waves); totals returned to all.  One
+// barrier: every wave adds up the waves' sums for itself; s_wave is written by this call alone.
+template <int N>
+__device__ __forceinline__ void block_scan_1024(const int (&v)[N], int (&before)[N], int (&total)[N], int (*s_wave)[16])
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int incl = wave_prefix_sum(v);
-    __syncthreads();                                   // (s_wave may still be read from the last call)
-    if (lane == 63) s_wave[wave] = incl;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int run = 0;
-        for (int i = 0; i < 16; i++) { int x = s_wave[i]; s_wave[i] = run; run += x; }
-        s_wave[16] = run;
+    int incl[N];
+#pragma unroll
+    for (int n = 0; n < N; n++) {
+        incl[n] = wave_prefix_sum(v[n]);
+        if (lane == 63) s_wave[n][wave] = incl[n];
     }
     __syncthreads();
-    total = s_wave[16];
-    return s_wave[wave] + incl - v;
+#pragma unroll
+    for (int n = 0; n < N; n++) {
+        const int x = lane < 16 ? s_wave[n][lane] : 0, upto = wave_prefix_sum(x);
+        total[n] = __shfl(upto, 15);
+        before[n] = __shfl(upto - x, wave) + incl[n] - v[n];
+    }
 }
 
-__device__ __forceinline__ long long block_sum_1024(long long v, long long* s_wave /* [16] */)
+__device__ __forceinline__ long long wave_sum_ll(long long v)
 {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) s_wave[threadIdx.x >> 6] = v;
-    __syncthreads();
-    long long t = 0;
-    for (int i = 0; i < 16; i++) t += s_wave[i];
-    return t;
+    return v;
 }
+
+// Largest batch that one workgroup groups by itself: four pairs and four lists per thread stay in its registers and the
+// tables of the lists (64 KB) in LDS.  Beyond that its serial share grows while the five kernels spread over the device:
+// with the counting of rounds in one workgroup 16384 pairs over 4096 lists took 1.42 ms a call against 1.34.  On this side
+// of the line (measured at 10 .. 1088 pairs) the one launch was 4 .. 9 % of the call faster.
+constexpr int kWholePairs = 4096, kWholeLists = 4096;
 
 // Work items and their order of execution.  Items are numbered list-major (segment-major,
 // query tile minor inside a list).  The order of execution is given by eight queues, one per
@@ -352,16 +356,43 @@ __device__ __forceinline__ int round_of(int l, int s, int nseg, int R)
     return (int)((((long long)s << 16) + u) * R / ((long long)nseg << 16));
 }
 
-// One workgroup: bucket offsets, rows per segment for this batch, first work item and first
-// result slot of every list, and where every round of every queue starts.
+// Records of the query tiles of segment s of list l (w queries, len rows from row_first on) from place pos of queue x on.
+__device__ __forceinline__ void write_items(const BucketArgs& a, int x, int pos, int l, int s, int nqt, int w, int row_first, int len,
+                                            int seg, int boff, long long sbase)
+{
+    const int row0 = row_first + s * seg, nrows = min(len - s * seg, seg);
+    for (int t = 0; t < nqt; t++) {
+        // first result slot of the item: entries t*cw .. of segment s (the last tile of a bucket has fewer
+        // than cw entries; what lies behind them belongs to the next segment and is never touched)
+        const long long first = sbase + (long long)s * w + (long long)t * a.cw;
+        // (the guards cannot fail: the host sizes the tables from the same bounds)
+        if (pos + t < a.item_cap && first + min(a.cw, w - t * a.cw) <= a.slot_cap) {
+            int4* rec = a.xq_rec + ((size_t)x * a.item_cap + pos + t) * 2;
+            rec[0] = make_int4(row0, nrows, boff, w);
+            rec[1] = make_int4(t, (int)first, l, s);
+        }
+    }
+}
+
+// One workgroup: bucket offsets, rows per segment for this batch, first result slot of every list, rounds in use.
 // (PER > 0: every thread owns at most PER lists and reads their widths and lengths once, all loads in flight
 // together, into registers; the passes below then run without touching memory again.  PER == 0: any number of
 // lists per thread, read from memory in every pass.)
-template <int PER>
+// WHOLE: the whole grouping in this one workgroup (launch_bucketing says when): the pairs are counted in LDS before the
+// passes and put in place after them, and the work items are written with the (list, segment) units spread flat over the
+// threads.  Bound: latency; the four other kernels of the chain are each a launch, a drain and a few dependent loads.
+// With one barrier per group of sums (was three per sum): one request over 16 of 256 lists 118.6 -> 110.7 us a call, 64
+// requests 210.6 -> 201.5; 544 requests in four sub-stages of two lists 1381 -> 1346.
+template <int PER, bool WHOLE>
 __global__ __launch_bounds__(1024) void k_bucket_scan(BucketArgs a)
 {
-    __shared__ int s_wave[17];
-    __shared__ long long s_lwave[16];
+    static_assert(!WHOLE || PER == kWholeLists / 1024, "the lists of a thread sit in registers");
+    constexpr int NL = WHOLE ? kWholeLists : 1, NP = WHOLE ? kWholePairs / 1024 : 1;
+    __shared__ int s_w[NL], s_boff[NL], s_slot[NL], s_unit[NL + 1];      // width, bucket, first slot, first unit of every list
+    __shared__ int s_round[WHOLE ? 8 * kRounds : 1], s_cur[WHOLE ? 8 * kRounds : 1];
+    int pl[NP], pe[NP];                                // list (-1: none) of this thread's pairs, place inside its bucket
+    __shared__ int s_sums1[1][16], s_sums2[3][16];
+    __shared__ long long s_cost[16], s_rows[16];
     __shared__ int s_maxseg;
     const int t = threadIdx.x;
     if (t == 0) s_maxseg = 0;
@@ -370,11 +401,36 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketArgs a)
     constexpr int NR = PER > 0 ? PER : 1;
     constexpr int UN = NR;                              // loops over a thread's lists: unrolled when they sit in registers
     int wv[NR], lv[NR];
+    if constexpr (WHOLE) {
+        const int pairs = a.nq * a.nprobe;
+        for (int l = t; l < a.nlist; l += 1024) s_w[l] = 0;
+        for (int i = t; i < 8 * kRounds; i += 1024) { s_round[i] = 0; s_cur[i] = 0; }
+#pragma unroll
+        for (int j = 0; j < NP; j++) pl[j] = j * 1024 + t < pairs ? a.probe[j * 1024 + t] : -1;
+        int res[NP];
+#pragma unroll
+        for (int j = 0; j < NP; j++) {
+            if (pl[j] >= a.nlist) pl[j] = -1;
+            res[j] = pl[j] >= 0 ? a.resident[pl[j]] : 0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NP; j++) {
+            pe[j] = -1;
+            if (pl[j] >= 0) {
+                if (res[j] != 0) pe[j] = atomicAdd(&s_w[pl[j]], 1);
+                else if (a.hits != nullptr) atomicAdd(&a.hits[pl[j]], 1ull);       // (as in k_bucket_count)
+            }
+            if (j * 1024 + t < pairs) a.pair_entry[j * 1024 + t] = pe[j];
+        }
+        __syncthreads();
+        for (int l = t; l < a.nlist; l += 1024) a.list_w[l] = s_w[l];
+    }
     if constexpr (PER > 0) {
 #pragma unroll
         for (int i = 0; i < PER; i++) {
             const int l = min(l0 + i, a.nlist - 1);
-            wv[i] = a.list_w[l];
+            wv[i] = WHOLE ? s_w[l] : a.list_w[l];
             lv[i] = a.list_off[l + 1] - a.list_off[l];
         }
     }
@@ -413,18 +469,26 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketArgs a)
         cost += len * ((w + a.cw - 1) / a.cw);
         if (w > 0) rows += len;
     }
-    int total;
+    cost = wave_sum_ll(cost);
+    rows = wave_sum_ll(rows);
+    if ((t & 63) == 0) { s_cost[t >> 6] = cost; s_rows[t >> 6] = rows; }
     {
-        int run = block_scan_1024(w_sum, s_wave, total);
+        int v[1] = {w_sum}, before[1], total[1];
+        block_scan_1024(v, before, total, s_sums1);
+        int run = before[0];
 #pragma unroll UN
         for (int i = 0; i < (PER > 0 ? PER : per); i++) {
             const int l = l0 + i;
             if (l >= l1) break;
-            a.bucket_off[l] = run; run += width(l);
+            a.bucket_off[l] = run;
+            if constexpr (WHOLE) s_boff[l] = run;
+            run += width(l);
         }
-        if (t == 0) { a.bucket_off[a.nlist] = total; a.dyn[DYN_PAIRS] = total; }
+        if (t == 0) { a.bucket_off[a.nlist] = total[0]; a.dyn[DYN_PAIRS] = total[0]; }
     }
-    const long long c = block_sum_1024(cost, s_lwave);
+    long long c = 0, r = 0;
+#pragma unroll
+    for (int i = 0; i < 16; i++) { c += s_cost[i]; r += s_rows[i]; }
     // rows per segment: about item_target items at most; and, since every item costs some ten
     // microseconds whatever its size, segments of up to 1024 rows as long as that leaves 1024 items
     // (one million rows in 1024 lists: 1024 items of 1024 rows, 0.60 ms; 4096 items of 256 rows, 0.65 ms)
@@ -435,14 +499,13 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketArgs a)
     if (segll < kMinSegRows) segll = kMinSegRows;
     if (segll > 0x7ffffff0LL) segll = 0x7ffffff0LL;          // (a list has fewer than 2^31 rows: one segment then)
     const int seg = (int)segll;
-    const long long r = block_sum_1024(rows, s_lwave);
     if (t == 0) {
         a.dyn[DYN_SEG_ROWS] = seg;
         a.dyn[DYN_ROWS_LO] = (int)(r & 0xffffffffLL);
         a.dyn[DYN_ROWS_HI] = (int)(r >> 32);
     }
 
-    // pass 2: work items per list = segments * query tiles; result slots per list = segments * bucket width
+    // pass 2: work items of a list = segments * query tiles; result slots per list = segments * bucket width
     // (one slot per (segment, query of the bucket): slot of entry e of segment s = slot_base[l] + s * w + e)
     auto list_items = [&](int l, int& nseg, int& nqt) __attribute__((always_inline)) {
         const int w = width(l);
@@ -450,48 +513,86 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketArgs a)
         nseg = (w > 0 && len > 0) ? (len + seg - 1) / seg : 0;
         nqt = (w + a.cw - 1) / a.cw;
     };
-    int items = 0, slots = 0, maxseg = 0;
+    int items = 0, slots = 0, maxseg = 0, units = 0;
 #pragma unroll UN
     for (int i = 0; i < (PER > 0 ? PER : per); i++) {
         const int l = l0 + i;
         if (l >= l1) break;
         int nseg, nqt; list_items(l, nseg, nqt);
-        items += nseg * nqt; slots += nseg * width(l); maxseg = max(maxseg, nseg);
+        items += nseg * nqt; slots += nseg * width(l); maxseg = max(maxseg, nseg); units += nseg;
     }
     if (maxseg > 0) atomicMax(&s_maxseg, maxseg);
+    int v2[3] = {items, slots, units}, before[3], total[3];
+    block_scan_1024(v2, before, total, s_sums2);
     {
-        int run = block_scan_1024(items, s_wave, total);
-#pragma unroll UN
-        for (int i = 0; i < (PER > 0 ? PER : per); i++) {
-            const int l = l0 + i;
-            if (l >= l1) break;
-            a.item_base[l] = run;
-            int nseg, nqt; list_items(l, nseg, nqt);
-            run += nseg * nqt;
-        }
-        if (t == 0) {
-            a.item_base[a.nlist] = total;
-            // never more than the table holds (cannot happen: the host sizes it from the same bound)
-            a.dyn[DYN_ITEMS] = min(total, a.item_cap);
-        }
-    }
-    {
-        int run = block_scan_1024(slots, s_wave, total);
+        int run = before[1];
 #pragma unroll UN
         for (int i = 0; i < (PER > 0 ? PER : per); i++) {
             const int l = l0 + i;
             if (l >= l1) break;
             a.slot_base[l] = run;
+            if constexpr (WHOLE) s_slot[l] = run;
             int nseg, nqt; list_items(l, nseg, nqt);
             run += nseg * width(l);
         }
         if (t == 0) {
-            a.slot_base[a.nlist] = total;
-            a.dyn[DYN_SLOTS] = total;
+            a.slot_base[a.nlist] = total[1];
+            a.dyn[DYN_SLOTS] = total[1];
+            // never more than the table holds (cannot happen: the host sizes it from the same bound)
+            a.dyn[DYN_ITEMS] = min(total[0], a.item_cap);
         }
     }
     // rounds of the queues: the longest list has eight segments per round
-    if (t == 0) a.dyn[DYN_ROUNDS] = max(1, min(kRounds, (s_maxseg + 7) / 8));
+    const int R = max(1, min(kRounds, (s_maxseg + 7) / 8));
+    if (t == 0) a.dyn[DYN_ROUNDS] = R;
+    if constexpr (WHOLE) {
+        int run = before[2];
+#pragma unroll
+        for (int i = 0; i < PER; i++) {
+            const int l = l0 + i;
+            if (i >= per || l >= l1) break;
+            s_unit[l] = run;
+            int nseg, nqt; list_items(l, nseg, nqt);
+            run += nseg;
+        }
+        if (t == 0) s_unit[a.nlist] = total[2];
+        __syncthreads();
+        // pairs to their places
+#pragma unroll
+        for (int j = 0; j < NP; j++)
+            if (pe[j] >= 0) a.bucket_q[s_boff[pl[j]] + pe[j]] = (j * 1024 + t) / a.nprobe;
+        // list and segment of a unit: the last list whose first unit is not behind it (lists without units share theirs
+        // with the next one, so that one is never theirs)
+        auto unit = [&](int u, int& l, int& s, int& slot, int& nqt) __attribute__((always_inline)) {
+            int lo = 0, hi = a.nlist;                    // s_unit[lo] <= u < s_unit[hi]
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (s_unit[mid] <= u) lo = mid; else hi = mid;
+            }
+            l = lo; s = u - s_unit[lo];
+            slot = queue_of(l, s) * kRounds + round_of(l, s, s_unit[lo + 1] - s_unit[lo], R);
+            nqt = (s_w[l] + a.cw - 1) / a.cw;
+        };
+        for (int u = t; u < total[2]; u += 1024) {
+            int l, s, slot, nqt; unit(u, l, s, slot, nqt);
+            atomicAdd(&s_round[slot], nqt);
+        }
+        __syncthreads();
+        // one wave per queue: where every round starts in it
+        static_assert(kRounds == 64, "a lane per round");
+        if (t < 8 * kRounds) {
+            const int c = s_round[t], incl = wave_prefix_sum(c);
+            s_round[t] = incl - c;
+            if ((t & 63) == 63) a.xq_count[t >> 6] = min(incl, a.item_cap);
+        }
+        __syncthreads();
+        for (int u = t; u < total[2]; u += 1024) {
+            int l, s, slot, nqt; unit(u, l, s, slot, nqt);
+            const int w = s_w[l], row_first = a.list_off[l], len = a.list_off[l + 1] - row_first;
+            const int pos = s_round[slot] + atomicAdd(&s_cur[slot], nqt);
+            write_items(a, slot / kRounds, pos, l, s, nqt, w, row_first, len, seg, s_boff[l], s_slot[l]);
+        }
+    }
 }
 
 __global__ void k_bucket_scatter(BucketArgs a)
@@ -542,27 +643,13 @@ __global__ __launch_bounds__(256) void k_item_expand(BucketArgs a)
     int seg = a.dyn[DYN_SEG_ROWS];
     int nqt = (w + a.cw - 1) / a.cw;
     int nseg = (len + seg - 1) / seg;
-    long long base = a.item_base[l];
     const long long sbase = a.slot_base[l];
     const int R = a.dyn[DYN_ROUNDS];
     const int row_first = a.list_off[l], boff = a.bucket_off[l];
     for (int s = lane; s < nseg; s += 64) {
         const int x = queue_of(l, s), slot = x * kRounds + round_of(l, s, nseg, R);
         const int pos = s_start[slot] + atomicAdd(&a.round_cur[slot], nqt);
-        const int row0 = row_first + s * seg;
-        const int nrows = min(len - s * seg, seg);
-        for (int t = 0; t < nqt; t++) {
-            long long idx = base + (long long)s * nqt + t;
-            // first result slot of the item: entries t*cw .. of segment s (the last tile of a bucket has fewer
-            // than cw entries; what lies behind them belongs to the next segment and is never touched)
-            const long long first = sbase + (long long)s * w + (long long)t * a.cw;
-            // (the guards cannot fail: the host sizes the tables from the same bounds)
-            if (idx < a.item_cap && pos + t < a.item_cap && first + min(a.cw, w - t * a.cw) <= a.slot_cap) {
-                int4* rec = a.xq_rec + ((size_t)x * a.item_cap + pos + t) * 2;
-                rec[0] = make_int4(row0, nrows, boff, w);
-                rec[1] = make_int4(t, (int)first, l, s);
-            }
-        }
+        write_items(a, x, pos, l, s, nqt, w, row_first, len, seg, boff, sbase);
     }
 }
 
@@ -570,11 +657,15 @@ hipError_t launch_bucketing(const BucketArgs& a, hipStream_t s)
 {
     int64_t pairs = (int64_t)a.nq * a.nprobe;
     unsigned gp = (unsigned)((pairs + 255) / 256);
+    if (pairs <= kWholePairs && a.nlist <= kWholeLists) {
+        hipLaunchKernelGGL((k_bucket_scan<kWholeLists / 1024, true>), dim3(1), dim3(1024), 0, s, a);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(k_bucket_count, dim3(gp), dim3(256), 0, s, a);
     const int per = (a.nlist + 1023) / 1024;
-    if (per <= 4) hipLaunchKernelGGL(k_bucket_scan<4>, dim3(1), dim3(1024), 0, s, a);
-    else if (per <= 16) hipLaunchKernelGGL(k_bucket_scan<16>, dim3(1), dim3(1024), 0, s, a);
-    else hipLaunchKernelGGL(k_bucket_scan<0>, dim3(1), dim3(1024), 0, s, a);
+    if (per <= 4) hipLaunchKernelGGL((k_bucket_scan<4, false>), dim3(1), dim3(1024), 0, s, a);
+    else if (per <= 16) hipLaunchKernelGGL((k_bucket_scan<16, false>), dim3(1), dim3(1024), 0, s, a);
+    else hipLaunchKernelGGL((k_bucket_scan<0, false>), dim3(1), dim3(1024), 0, s, a);
     hipLaunchKernelGGL(k_bucket_scatter, dim3(gp), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_round_count, dim3((unsigned)((a.nlist + 3) / 4)), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_item_expand, dim3((unsigned)((a.nlist + 3) / 4)), dim3(256), 0, s, a);

@@ -197,7 +197,6 @@ struct BucketArgs {
     int* pair_entry;            // [nq*nprobe]
     int* bucket_off;            // [nlist+1]
     int* bucket_q;              // [nq*nprobe]
-    int* item_base;             // [nlist+1]
     int* slot_base;             // [nlist+1] first result slot of every list
     int* dyn;                   // device scalars
     int4* xq_rec;               // [8][item_cap][2] per-XCD queues of item records (see ScanArgs)

@@ -92,3 +92,41 @@ def test_scan_finds_the_best_rows_at_the_edges_of_query_tiles(storage, tables, d
     assert float((score.double() - want).abs().max()) <= 2 * tol
     assert all(len(set(r)) == k for r in found.cpu().tolist())
     ix.close()
+
+
+@pytest.mark.parametrize("nlist,nq,nprobe,N", [(1, 1, 1, 5000), (3, 1, 3, 2000000), (3, 1365, 3, 60000), (256, 64, 16, 65536), (1000, 241, 17, 100000),
+                                               (1024, 4096, 1, 40000), (1025, 1, 512, 60000), (4096, 128, 32, 100000), (4097, 128, 32, 100000),
+                                               (4095, 9, 455, 50000)])
+def test_grouping_keeps_every_pair_whatever_the_batch(nlist, nq, nprobe, N):
+    """Around the largest batch that one workgroup groups alone (4096 pairs, 4096 lists), with lists that are not in
+    place, probes of nothing, and one list of most of the rows; then the counters of the probes."""
+    ix, cent, off, vec, ids, g = _index(N, 64, nlist, torch.float16, nlist + nq, zipf=1.3)
+    q = torch.randn(nq, 64, generator=g, device="cuda")
+    probe = torch.rand(nq, nlist, generator=g, device="cuda").topk(nprobe, dim=1).indices.int()
+    away = torch.arange(1, nlist, 7, dtype=torch.int32, device="cuda")
+    none = torch.rand(nq, nprobe, generator=g, device="cuda") < 0.1
+    probe[none] = -1
+    if len(away):
+        ix.set_resident(away, False)
+    ix.list_hits(reset=True)
+    k = 7
+    found, score = ix.scan(q, probe, k, "ip")
+    hits = torch.bincount(probe[probe >= 0].long(), minlength=nlist)
+    assert torch.equal(ix.list_hits().cuda(), hits)
+    allowed = torch.zeros(nq, nlist + 1, dtype=torch.bool, device="cuda")
+    allowed.scatter_(1, torch.where(probe < 0, nlist, probe.long()), True)
+    allowed[:, away.long()] = False
+    of_row = torch.repeat_interleave(torch.arange(nlist), off[1:] - off[:-1]).cuda()
+    op, row = q.half().float(), torch.empty_like(ids)
+    row[ids] = torch.arange(N, device="cuda")
+    for i in range(0, nq, 256):
+        key = torch.where(allowed[i:i + 256][:, of_row], op[i:i + 256].double() @ vec.double().T, -float("inf"))
+        best = torch.topk(key, k, dim=1).values
+        f = found[i:i + 256]
+        got = torch.where(f >= 0, key.gather(1, row[f.clamp(min=0)]), -float("inf"))
+        assert torch.equal(f >= 0, best > -float("inf"))
+        ok = f >= 0
+        # float32 sums of 64 products of values near 1, |q||x| below 200: 2^-24 of that for each of a few roundings
+        assert float((got[ok] - best[ok]).abs().max() if ok.any() else 0.0) < 1e-4
+        assert float((score[i:i + 256][ok].double() - best[ok]).abs().max() if ok.any() else 0.0) < 1e-4
+    ix.close()
