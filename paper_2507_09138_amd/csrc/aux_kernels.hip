@@ -1101,7 +1101,9 @@ __global__ __launch_bounds__(256) void k_topk_rows(TopkArgs a)
         int pos[PER];
 #pragma unroll
         for (int m = 0; m < PER; m++) { e[m] = lane + 64 * m < k ? ent[lane + 64 * m] : Cand{0u, 0u}; pos[m] = 0; }
-#pragma unroll 8
+        // (what is in flight at a time: 16 comparisons with as few LDS reads as that needs.  8 entries per step whatever
+        // PER is, or one, took the 512 best of 4096 keys 141 us a call of 40 rows, 16 / PER 100)
+#pragma unroll (PER <= 2 ? 8 : 16 / PER)
         for (int i = 0; i < k; i++) {
             const Cand o = ent[i];
 #pragma unroll
