@@ -906,11 +906,13 @@ struct TopkArgs {
     int32_t* out_ids;           // [nq, k]
     float* out_scores;          // [nq, k] or nullptr
     int nq, n, k, l2;
+    TopkSample sample;          // (computed on the host: its square root and divisions cost each wave a microsecond)
 };
 
-__global__ __launch_bounds__(256) void k_topk_rows(TopkArgs a)
+__global__ __launch_bounds__(256, 4) void k_topk_rows(TopkArgs a)
 {
-    constexpr int kCollect = 1024;                  // entries one wave can collect in LDS (>= HR_NPROBE_MAX)
+    constexpr int kCollect = kTopkCollect;          // entries one wave can collect in LDS
+    static_assert(kCollect >= HR_NPROBE_MAX, "the best of a row must fit");
     __shared__ int s_hist[4][256];
     __shared__ Cand s_ent[4][kCollect];
     const int lane = lane_id(), wave = threadIdx.x >> 6;
@@ -921,29 +923,27 @@ __global__ __launch_bounds__(256) void k_topk_rows(TopkArgs a)
     Cand* ent = s_ent[wave];
     const int k = min(a.k, a.n);
 
-    // ---- the quick way, one pass over the row: a lower bound t0 from up to 1024 keys spread over the row (their
-    // want-th largest), every key >= t0 collected in LDS, the k best of those selected there.  It is exact whenever at
-    // least k and at most kCollect keys were collected (all keys >= the k-th best are then among them); otherwise the
-    // radix passes below do the work, some eight times slower: the row that takes them is what the whole launch waits
-    // for.  How many sampled keys belong to the k best is close to Poisson with mean lambda = k S / n, so want lies
-    // 5.5 deviations above it: too few are collected for one row in some hundred thousand.  (16384 keys, k 128, 3001
-    // rows: with 3 k keys expected above t0, from 512 samples, about three rows took the radix passes and the call 537 us,
-    // now 445; the select over fewer bits is part of that.)
+    // ---- the quick way, one pass over the row: a lower bound t0 from keys spread over the row (topk_sample says how
+    // many and which of them), every key >= t0 collected in LDS, the k best of those selected there.  It is exact
+    // whenever at least k and at most kCollect keys were collected (all keys >= the k-th best are then among them).
+    // Too few: a lower one of the sampled keys and another pass.  Too many: the k-th best of those that did fit is a
+    // bound that at least k keys reach and few others do, and another pass.  Only rows of many equal keys, or keys in
+    // an order that misleads the sample twice, are left to the radix passes below, some eight times slower, and one such
+    // row is what the whole launch waits for (65536 keys, k 16, 100 rows of which one collected too many: 567 us a call
+    // when that row took the radix passes, 160 with another pass over it).
     bool done = false;
     {
         uint32_t t0 = 0;                            // (below every encoded key: short rows are collected whole)
-        auto sample = [&](auto per) __attribute__((always_inline)) {
+        const TopkSample sm = a.sample;
+        auto sample = [&](auto per, int want, const int lane) __attribute__((always_inline)) {
             constexpr int C = decltype(per)::value, S = C * 64;
             uint32_t sv[C];
 #pragma unroll
             for (int j = 0; j < C; j++) sv[j] = enc_key(row[(int)(((long long)(j * 64 + lane) * a.n) / S)]);
-            const float lambda = (float)k * (float)S / (float)a.n;
-            // (nor may more than kCollect be collected: for large k midway between the two)
-            int want = min((int)(lambda + 5.5f * sqrtf(lambda) + 3.0f), (int)((float)S * (float)(k + kCollect) * 0.5f / (float)a.n) + 1);
-            want = max(2, min(S, want));
             unsigned long long alive[C];
 #pragma unroll
             for (int j = 0; j < C; j++) alive[j] = ~0ull;
+            uint32_t t = 0;
             for (int b = 31, left = S; b >= 0 && left != want; b--) {
                 unsigned long long ones[C];
                 int c1 = 0;
@@ -953,7 +953,7 @@ __global__ __launch_bounds__(256) void k_topk_rows(TopkArgs a)
                     c1 += __builtin_popcountll(ones[j]);
                 }
                 if (c1 >= want) {
-                    t0 |= 1u << b;
+                    t |= 1u << b;
                     left = c1;
 #pragma unroll
                     for (int j = 0; j < C; j++) alive[j] = ones[j];
@@ -964,58 +964,73 @@ __global__ __launch_bounds__(256) void k_topk_rows(TopkArgs a)
                     for (int j = 0; j < C; j++) alive[j] &= ~ones[j];
                 }
             }
+            return t;
         };
-        // (short rows: a sample of 256 is enough to spare the select over the whole of them)
-        if (a.n > 4 * kCollect) sample(std::integral_constant<int, 16>{});
-        else if (a.n > kCollect) sample(std::integral_constant<int, 8>{});
-        else if (a.n > 256) sample(std::integral_constant<int, 4>{});
-        int cnt = 0;
-        auto collect = [&](float key, int i, bool valid) __attribute__((always_inline)) {
-            const uint32_t u = enc_key(key);
-            const bool take = valid && u >= t0;
-            const unsigned long long m = __builtin_amdgcn_ballot_w64(take);
-            if (m == 0) return;
-            const int pos = cnt + lanes_below(m);
-            if (take && pos < kCollect) ent[pos] = Cand{u, (uint32_t)i};
-            cnt += __builtin_popcountll(m);
-        };
-        // (what hides the latency of the loads is how many are in flight: 8 of 16 bytes per
-        // lane when the rows allow it; the order of collection does not matter)
-        if ((a.n & 3) == 0) {
-            const float4* row4 = (const float4*)row;
-            const int n4 = a.n >> 2;
-            for (int i0 = 0; i0 < n4; i0 += 64 * 8) {
-                float4 v[8];
+        int want = sm.want;
+        bool look = sm.size > 0;                    // t0 comes from the sample (else: as it is)
+        for (int tries = 0; tries < 3 && !done; tries++) {
+            const int lane = lane_now();                // (what follows from it is not kept in registers from one pass to the next)
+            if (look) {
+                if (sm.size == 1024) t0 = sample(std::integral_constant<int, 16>{}, want, lane);
+                else if (sm.size == 512) t0 = sample(std::integral_constant<int, 8>{}, want, lane);
+                else t0 = sample(std::integral_constant<int, 4>{}, want, lane);
+            }
+            int cnt = 0;
+            auto collect = [&](float key, int i, bool valid) __attribute__((always_inline)) {
+                const uint32_t u = enc_key(key);
+                const bool take = valid && u >= t0;
+                const unsigned long long m = __builtin_amdgcn_ballot_w64(take);
+                if (m == 0) return;
+                const int pos = cnt + lanes_below(m);
+                if (take && pos < kCollect) ent[pos] = Cand{u, (uint32_t)i};
+                cnt += __builtin_popcountll(m);
+            };
+            // (what hides the latency of the loads is how many are in flight: 8 of 16 bytes per
+            // lane when the rows allow it; the order of collection does not matter)
+            if ((a.n & 3) == 0) {
+                const float4* row4 = (const float4*)row;
+                const int n4 = a.n >> 2;
+                for (int i0 = 0; i0 < n4; i0 += 64 * 8) {
+                    float4 v[8];
 #pragma unroll
-                for (int j = 0; j < 8; j++) v[j] = row4[min(i0 + j * 64 + lane, n4 - 1)];
+                    for (int j = 0; j < 8; j++) v[j] = row4[min(i0 + j * 64 + lane, n4 - 1)];
 #pragma unroll
-                for (int j = 0; j < 8; j++) {
-                    const int i4 = i0 + j * 64 + lane;
-                    collect(v[j].x, i4 * 4, i4 < n4);
-                    collect(v[j].y, i4 * 4 + 1, i4 < n4);
-                    collect(v[j].z, i4 * 4 + 2, i4 < n4);
-                    collect(v[j].w, i4 * 4 + 3, i4 < n4);
+                    for (int j = 0; j < 8; j++) {
+                        const int i4 = i0 + j * 64 + lane;
+                        collect(v[j].x, i4 * 4, i4 < n4);
+                        collect(v[j].y, i4 * 4 + 1, i4 < n4);
+                        collect(v[j].z, i4 * 4 + 2, i4 < n4);
+                        collect(v[j].w, i4 * 4 + 3, i4 < n4);
+                    }
+                }
+            } else {
+                for (int i0 = 0; i0 < a.n; i0 += 64 * 8) {
+                    float v[8];
+#pragma unroll
+                    for (int j = 0; j < 8; j++) { const int i = i0 + j * 64 + lane; v[j] = row[min(i, a.n - 1)]; }
+#pragma unroll
+                    for (int j = 0; j < 8; j++) collect(v[j], i0 + j * 64 + lane, i0 + j * 64 + lane < a.n);
                 }
             }
-        } else {
-            for (int i0 = 0; i0 < a.n; i0 += 64 * 8) {
-                float v[8];
-#pragma unroll
-                for (int j = 0; j < 8; j++) { const int i = i0 + j * 64 + lane; v[j] = row[min(i, a.n - 1)]; }
-#pragma unroll
-                for (int j = 0; j < 8; j++) collect(v[j], i0 + j * 64 + lane, i0 + j * 64 + lane < a.n);
+            wave_sync();
+            if (cnt < k) {                              // (of the sampled keys as well: nothing lower to try)
+                if (!look || want == sm.size) break;
+                want = min(sm.size, 2 * want + 8);
+                continue;
             }
-        }
-        wave_sync();
-        if (cnt >= k && cnt <= kCollect) {
             // (equal keys: lower index first; the select walks as many 64-entry chunks as were collected, not
             // as many as the buffer holds)
-            if (cnt > k) {
-                if (cnt <= 256) wave_select<4>(ent, cnt, k, nullptr);
-                else if (cnt <= 512) wave_select<8>(ent, cnt, k, nullptr);
-                else wave_select<kCollect / 64>(ent, cnt, k, nullptr);
+            const int held = min(cnt, kCollect);
+            uint32_t kth = t0;
+            if (held > k) {
+                if (held <= 256) kth = wave_select<4>(ent, held, k, nullptr);
+                else if (held <= 512) kth = wave_select<8>(ent, held, k, nullptr);
+                else kth = wave_select<kCollect / 64>(ent, held, k, nullptr);
             }
-            done = true;
+            done = cnt <= kCollect;
+            if (!done && kth == t0) break;              // (too many equal keys)
+            t0 = kth;
+            look = false;
         }
     }
 
@@ -1103,7 +1118,8 @@ __global__ __launch_bounds__(256) void k_topk_rows(TopkArgs a)
         for (int m = 0; m < PER; m++) { e[m] = lane + 64 * m < k ? ent[lane + 64 * m] : Cand{0u, 0u}; pos[m] = 0; }
         // (what is in flight at a time: 16 comparisons with as few LDS reads as that needs.  8 entries per step whatever
         // PER is, or one, took the 512 best of 4096 keys 141 us a call of 40 rows, 16 / PER 100)
-#pragma unroll (PER <= 2 ? 8 : 16 / PER)
+        constexpr int STEP = PER <= 2 ? 8 : 16 / PER;
+#pragma unroll STEP
         for (int i = 0; i < k; i++) {
             const Cand o = ent[i];
 #pragma unroll
@@ -1134,7 +1150,7 @@ hipError_t launch_topk_rows(const float* keys, const float* qnorm, int32_t* out_
                             int64_t nq, int n, int k, int l2, hipStream_t s)
 {
     if (nq <= 0) return hipSuccess;
-    TopkArgs a{keys, qnorm, out_ids, out_scores, (int)nq, n, k, l2};
+    TopkArgs a{keys, qnorm, out_ids, out_scores, (int)nq, n, k, l2, topk_sample(n, k < n ? k : n)};
     hipLaunchKernelGGL(k_topk_rows, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, s, a);
     return hipGetLastError();
 }

@@ -75,6 +75,27 @@ __host__ __device__ constexpr int sel_cap(int k)
     return c;
 }
 
+// How k_topk_rows bounds the k best of n keys from below: the want-th largest of size keys spread over the row (size 0: no
+// bound, the row is collected whole).  How many sampled keys belong to the k best is close to Poisson with mean lambda =
+// k size / n, so want lies 5.5 deviations above it: fewer than k keys are at or above the bound for one row in 10^5.  Nor
+// may more than kTopkCollect be, so for large k want is at most midway between the two: one row in 10^5 at
+// most on either side up to k 200 of 16384 keys, and then more: one in 450 too many for 128 of 32768, one in 500 too few and
+// one in 60 too many for 512 of 16384 (a second pass each).
+// Rows that fit the buffer are sampled only where that spares the select half of them; a bound that nearly all keys reach
+// would leave out some of the best (512 of 512 keys: every second row).
+constexpr int kTopkCollect = 1024;
+struct TopkSample { int size, want; };
+inline TopkSample topk_sample(int n, int k)
+{
+    const int size = n > 4 * kTopkCollect ? 1024 : (n > kTopkCollect ? 512 : 256);
+    const float lambda = (float)k * (float)size / (float)n;
+    int want = (int)(lambda + 5.5f * sqrtf(lambda) + 3.0f);
+    if (n <= kTopkCollect) return n > 256 && want * 2 <= size ? TopkSample{size, want} : TopkSample{0, 0};
+    const int most = (int)((float)size * (float)(k + kTopkCollect) * 0.5f / (float)n) + 1;
+    want = want < most ? want : most;
+    return TopkSample{size, want < 2 ? 2 : (want < size ? want : size)};
+}
+
 // order-preserving map float -> uint32 (larger float = larger unsigned), and back
 __host__ __device__ inline uint32_t enc_key(float f)
 {

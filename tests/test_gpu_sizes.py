@@ -130,3 +130,39 @@ def test_grouping_keeps_every_pair_whatever_the_batch(nlist, nq, nprobe, N):
         assert float((got[ok] - best[ok]).abs().max() if ok.any() else 0.0) < 1e-4
         assert float((score[i:i + 256][ok].double() - best[ok]).abs().max() if ok.any() else 0.0) < 1e-4
     ix.close()
+
+
+@pytest.mark.parametrize("order", ["random", "sampled high", "sampled low", "rising", "falling", "equal", "two values"])
+@pytest.mark.parametrize("nlist,nprobe", [(300, 100), (300, 300), (512, 512), (777, 300), (1024, 300), (1024, 512), (1025, 512), (2048, 512), (4099, 300),
+                                          (16384, 128), (16384, 512), (65536, 16)])
+def test_coarse_is_exact_in_whatever_order_the_scores_come(nlist, nprobe, order):
+    """Scores that are whole numbers, so every key is exact: in random order, and in orders in which the keys that the
+    selection samples (evenly spread places) are all the best or all the worst, or in which many are equal.  The probe
+    list is the oracle's, ties included: lower index first."""
+    rng = np.random.default_rng(nlist + nprobe)
+    value = rng.permutation(nlist)
+    size = 1024 if nlist > 4096 else (512 if nlist > 1024 else 256)
+    if order.startswith("sampled"):
+        at = np.unique(np.arange(size) * nlist // size)
+        rest = rng.permutation(np.setdiff1d(np.arange(nlist), at))
+        value = np.empty(nlist, dtype=np.int64)
+        value[np.concatenate([rest, at] if order.endswith("high") else [at, rest])] = np.arange(nlist)
+    elif order in ("rising", "falling"):
+        value = np.arange(nlist) if order == "rising" else np.arange(nlist)[::-1]
+    elif order == "equal":
+        value = np.zeros(nlist, dtype=np.int64)
+    elif order == "two values":
+        value = (rng.random(nlist) < 0.3).astype(np.int64)
+    # (whole numbers below 2^16: a binary16 part and a scaled rest hold 22 bits of a value)
+    cent = torch.zeros(nlist, 64, device="cuda")
+    cent[:, 0] = torch.from_numpy(np.ascontiguousarray(value)).float().cuda() / 16
+    vec = torch.zeros(nlist, 64, dtype=torch.float16, device="cuda")
+    ix = _hr().IvfIndex(cent, torch.arange(nlist + 1), vec, torch.arange(nlist, device="cuda"))
+    q = torch.zeros(3, 64, device="cuda")
+    q[:, 0] = torch.tensor([1.0, -1.0, 2.0])
+    probe, score = ix.coarse(q, nprobe, "ip")
+    for i, sign in enumerate((1, -1, 2)):
+        best = np.lexsort((np.arange(nlist), -sign * value))[:nprobe]
+        assert np.array_equal(probe[i].cpu().numpy(), best)
+        assert np.array_equal(score[i].cpu().numpy(), (sign * value[best] / 16).astype(np.float32))
+    ix.close()
