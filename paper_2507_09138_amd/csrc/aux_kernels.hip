@@ -1112,25 +1112,29 @@ __global__ __launch_bounds__(256, 4) void k_topk_rows(TopkArgs a)
     const float qn = (a.l2 && a.qnorm) ? a.qnorm[q] : 0.f;
     auto emit = [&](auto per) __attribute__((always_inline)) {
         constexpr int PER = decltype(per)::value;       // entries per lane
-        Cand e[PER];
+        uint64_t e[PER];                                // key, then the complement of the row: the larger is ahead
         int pos[PER];
 #pragma unroll
-        for (int m = 0; m < PER; m++) { e[m] = lane + 64 * m < k ? ent[lane + 64 * m] : Cand{0u, 0u}; pos[m] = 0; }
-        // (what is in flight at a time: 16 comparisons with as few LDS reads as that needs.  8 entries per step whatever
-        // PER is, or one, took the 512 best of 4096 keys 141 us a call of 40 rows, 16 / PER 100)
-        constexpr int STEP = PER <= 2 ? 8 : 16 / PER;
-#pragma unroll STEP
+        for (int m = 0; m < PER; m++) {
+            const Cand c = lane + 64 * m < k ? ent[lane + 64 * m] : Cand{0u, 0u};
+            e[m] = (uint64_t)c.key << 32 | (uint32_t)~c.row;
+            pos[m] = 0;
+        }
+        // (bound by the comparisons: one of 64 bits and one addition per pair.  Comparing key and row by themselves, three
+        // comparisons and the logic between them, the 512 best of 512 keys took 91 us a call, now 32)
+#pragma unroll 8
         for (int i = 0; i < k; i++) {
-            const Cand o = ent[i];
+            const Cand c = ent[i];
+            const uint64_t o = (uint64_t)c.key << 32 | (uint32_t)~c.row;
 #pragma unroll
-            for (int m = 0; m < PER; m++) pos[m] += (o.key > e[m].key || (o.key == e[m].key && o.row < e[m].row)) ? 1 : 0;
+            for (int m = 0; m < PER; m++) pos[m] += o > e[m] ? 1 : 0;
         }
 #pragma unroll
         for (int m = 0; m < PER; m++) {
             if (lane + 64 * m < k) {
-                const float key = dec_key(e[m].key);
+                const float key = dec_key((uint32_t)(e[m] >> 32));
                 const size_t o = (size_t)q * a.k + pos[m];
-                a.out_ids[o] = (int32_t)e[m].row;
+                a.out_ids[o] = (int32_t)~(uint32_t)e[m];
                 if (a.out_scores) a.out_scores[o] = a.l2 ? fmaxf(qn - key, 0.f) : key;
             }
         }
