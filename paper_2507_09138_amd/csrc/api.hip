@@ -232,13 +232,26 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     if (p.cchunk < 64) p.cchunk = 64;
     if (p.cchunk > nq) p.cchunk = nq > 0 ? nq : 1;
     p.nqt_c = (int)((p.cchunk + p.cw_c - 1) / p.cw_c);
-    // rows of the centroid table per work item: as many items as two whole rounds over 256 compute units (eight where
-    // the tiles are too many to split that evenly), never a few more
-    const int64_t want = p.nqt_c <= 64 ? 512 : 2048;
-    int64_t seg = want / p.nqt_c;
-    seg = (nlist + (seg < 1 ? 1 : seg) - 1) / (seg < 1 ? 1 : seg);
-    seg = (seg + 15) & ~15LL;
-    if (p.nqt_c > 1 && seg < 32) seg = 32;          // (a tile of queries is loaded per item: two blocks at least for it)
+    // Rows of the centroid table per work item.  The items are alike, so what counts is how many whole rounds over the
+    // compute units they make and how long an item is: its blocks, about four more that loading a tile of queries costs,
+    // and, for long items, a few percent by which the last ones end apart.  Mostly that is one round (8192 queries, d = 1024,
+    // two rounds with at least 32 rows per item or eight beyond 64 tiles: 512 centroids 144 us, one round 82; 4096 381 and
+    // 320; 3001 queries, d = 768, 4096 centroids 121 and 108).
+    const int64_t nblk = (nlist + kBlockRows - 1) / kBlockRows, cus = ix->num_cus;
+    int64_t per_item = nblk;                        // blocks
+    double least = 0.0;
+    for (int r = 1; r <= 8; r++) {
+        const int64_t nseg = r * cus / p.nqt_c;
+        if (nseg < 1) continue;
+        const int64_t blocks = (nblk + nseg - 1) / nseg, items = (nblk + blocks - 1) / blocks * p.nqt_c;
+        const double cost = (double)((items + cus - 1) / cus) * (double)(4 + blocks) + (double)blocks / 16.0;
+        if (least == 0.0 || cost < least) { least = cost; per_item = blocks; }
+    }
+    // (not as short as one block where two leave enough of the device busy: half the loads of queries.  One tile of 8 queries,
+    // d = 64: 4096 centroids 24.3 -> 22.8 us, 1024 of d = 768 19.1 -> 20.0; 16 tiles, d = 768, 64 centroids 38.6 -> 36.8,
+    // two tiles, 256 centroids 29.4 -> 31.2)
+    if (per_item == 1 && nblk * p.nqt_c >= (p.nqt_c > 1 ? cus / 4 : cus / 2)) per_item = 2;
+    const int64_t seg = per_item * kBlockRows;
     p.seg_c = (int)seg;
     p.nseg_c = (int)((nlist + seg - 1) / seg);
     p.items_c = p.nseg_c * p.nqt_c;

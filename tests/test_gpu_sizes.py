@@ -56,6 +56,40 @@ def test_coarse_takes_the_closest_centroids(nlist, nprobe, nq, metric):
     p = probe.cpu().numpy()
     twin = (np.abs(p[:, 1:] - p[:, :-1]) == nlist // 2) & (np.minimum(p[:, 1:], p[:, :-1]) < nlist // 8)
     assert np.all(p[:, 1:][twin] > p[:, :-1][twin])
+    _lower_twins_are_there(p, nlist)
+    ix.close()
+
+
+def _lower_twins_are_there(p, nlist):
+    """Of two equal centroids (index i and i + nlist/2) the lower one is taken first, at the last place as well."""
+    taken = np.zeros((len(p), nlist), dtype=bool)
+    np.put_along_axis(taken, p.astype(np.int64), True, axis=1)
+    low = np.arange(nlist // 8)
+    assert not np.any(taken[:, low + nlist // 2] & ~taken[:, low])
+
+
+@pytest.mark.parametrize("d", [128, 512, 768, 1024])
+@pytest.mark.parametrize("nlist,nprobe,nq", [(64, 17, 300), (100, 33, 1000), (300, 300, 129), (777, 100, 200), (1500, 16, 65), (4099, 128, 700), (2048, 32, 8200)])
+def test_coarse_at_the_edges_of_tiles_and_segments(nlist, nprobe, nq, d):
+    """Longer vectors: their fragments are addressed and grouped differently, and the work items of the scoring differ in
+    rows and queries; odd numbers of lists and queries leave the last of both unfilled."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(nlist + nq + d)
+    cent = torch.randn(nlist, d, generator=g, device="cuda")
+    cent[nlist // 2:nlist // 2 + nlist // 8] = cent[:nlist // 8]
+    vec = torch.zeros(nlist, d, dtype=torch.float16, device="cuda")
+    ix = _hr().IvfIndex(cent, torch.arange(nlist + 1), vec, torch.arange(nlist, device="cuda"))
+    q = torch.randn(nq, d, generator=g, device="cuda")
+    probe, score = ix.coarse(q, nprobe, "ip")
+    key = _keys(q.double(), cent.double(), "ip")
+    best = torch.topk(key, nprobe, dim=1).values
+    # float32 sums of d products, |q||x| below 1.5 d: 2^-24 of that for each of a few roundings
+    tol = 1.5 * d * 2.0 ** -24 * 8
+    assert float((key.gather(1, probe.long()) - best).abs().max()) <= 2 * tol
+    assert float((score.double() - key.gather(1, probe.long())).abs().max()) <= tol
+    p = probe.cpu().numpy()
+    assert all(len(set(r)) == nprobe for r in p.tolist())
+    _lower_twins_are_there(p, nlist)
     ix.close()
 
 
