@@ -392,7 +392,7 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketArgs a)
     __shared__ int s_round[WHOLE ? 8 * kRounds : 1], s_cur[WHOLE ? 8 * kRounds : 1];
     int pl[NP], pe[NP];                                // list (-1: none) of this thread's pairs, place inside its bucket
     __shared__ int s_sums1[1][16], s_sums2[3][16];
-    __shared__ long long s_cost[16], s_rows[16];
+    __shared__ long long s_cost[16], s_fine[16], s_rows[16];
     __shared__ int s_maxseg;
     const int t = threadIdx.x;
     if (t == 0) s_maxseg = 0;
@@ -455,9 +455,9 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketArgs a)
         }
     };
 
-    // pass 1: bucket offsets, cost = sum rows * query tiles, rows streamed, pairs
+    // pass 1: bucket offsets, cost = sum rows * query tiles (fine: tiles of cost_cw queries), rows streamed, pairs
     int w_sum = 0;
-    long long cost = 0, rows = 0;
+    long long cost = 0, fine = 0, rows = 0;
 #pragma unroll UN
     for (int i = 0; i < (PER > 0 ? PER : per); i++) {
         const int l = l0 + i;
@@ -467,11 +467,13 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketArgs a)
         if (a.hits != nullptr && w > 0) atomicAdd(&a.hits[l], (unsigned long long)w);     // access frequency of the list
         w_sum += w;
         cost += len * ((w + a.cw - 1) / a.cw);
+        fine += len * ((w + a.cost_cw - 1) / a.cost_cw);
         if (w > 0) rows += len;
     }
     cost = wave_sum_ll(cost);
+    fine = wave_sum_ll(fine);
     rows = wave_sum_ll(rows);
-    if ((t & 63) == 0) { s_cost[t >> 6] = cost; s_rows[t >> 6] = rows; }
+    if ((t & 63) == 0) { s_cost[t >> 6] = cost; s_fine[t >> 6] = fine; s_rows[t >> 6] = rows; }
     {
         int v[1] = {w_sum}, before[1], total[1];
         block_scan_1024(v, before, total, s_sums1);
@@ -486,14 +488,17 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketArgs a)
         }
         if (t == 0) { a.bucket_off[a.nlist] = total[0]; a.dyn[DYN_PAIRS] = total[0]; }
     }
-    long long c = 0, r = 0;
+    long long c = 0, cf = 0, r = 0;
 #pragma unroll
-    for (int i = 0; i < 16; i++) { c += s_cost[i]; r += s_rows[i]; }
+    for (int i = 0; i < 16; i++) { c += s_cost[i]; cf += s_fine[i]; r += s_rows[i]; }
     // rows per segment: about item_target items at most; and, since every item costs some ten
     // microseconds whatever its size, segments of up to 1024 rows as long as that leaves 1024 items
-    // (one million rows in 1024 lists: 1024 items of 1024 rows, 0.60 ms; 4096 items of 256 rows, 0.65 ms)
+    // (one million rows in 1024 lists: 1024 items of 1024 rows, 0.60 ms; 4096 items of 256 rows, 0.65 ms).  Counted in tiles
+    // of 64 queries where a tile holds two operands per query: its items take twice as long, and the merge walks every
+    // segment of every query (128 queries over all of 512 lists of 1024 bfloat16 rows, d = 768: with segments of 512 rows
+    // 513 us, of 1024 rows 478; 1500 queries over 32 of them 426 and 400)
     long long segll = (c + a.item_target - 1) / a.item_target;
-    const long long fewer = c / 1024 < 1024 ? c / 1024 : 1024;
+    const long long fewer = cf / 1024 < 1024 ? cf / 1024 : 1024;
     if (segll < fewer) segll = fewer;
     segll = (segll + 15) & ~15LL;
     if (segll < kMinSegRows) segll = kMinSegRows;

@@ -213,6 +213,7 @@ hipError_t launch_check_labels(const int64_t* ids, int64_t n, int* negative, hip
 struct BucketArgs {
     const int* probe;           // [nq*nprobe]
     int nq, nprobe, nlist, cw;
+    int cost_cw;                // queries per tile by which the shortest segments are counted (see k_bucket_scan)
     const int* list_off;        // [nlist+1]
     int* list_w;                // [nlist]   (zeroed by the first kernel's launch sequence)
     int* pair_entry;            // [nq*nprobe]

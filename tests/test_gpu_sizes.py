@@ -200,3 +200,19 @@ def test_coarse_is_exact_in_whatever_order_the_scores_come(nlist, nprobe, order)
         assert np.array_equal(probe[i].cpu().numpy(), best)
         assert np.array_equal(score[i].cpu().numpy(), (sign * value[best] / 16).astype(np.float32))
     ix.close()
+
+
+@pytest.mark.parametrize("storage,tables,d,nq,want", [("bf16", False, 64, 128, 512), ("f32", True, 64, 128, 512), ("bf16", False, 64, 64, 256), ("f16", False, 64, 128, 256),
+                                                      ("bf16", True, 64, 128, 256), ("bf16", False, 1024, 128, 512), ("bf16", False, 64, 512, 1024)])
+def test_segments_are_as_long_as_what_an_item_costs(storage, tables, d, nq, want):
+    """Rows per work item where the batch makes about a thousand of them: rows x tiles / 1024, tiles of 64 queries where an
+    item multiplies two operands per query, of 128 otherwise."""
+    dtype = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[storage]
+    N = 1 << 18
+    ix, cent, off, vec, ids, g = _index(N, d, 4, dtype, nq + d, tables=tables)
+    q = torch.randn(nq, d, generator=g, device="cuda")
+    ix.search(q, 4, 10, "ip")
+    torch.cuda.synchronize()
+    ws = ix.workspace(nq, 4, 10)
+    assert _hr().hr_ivf_stats(ix.handle, ws, ws.numel(), nq, 4, 10)["seg_rows"] == want
+    ix.close()
