@@ -1020,16 +1020,16 @@ __global__ __launch_bounds__(256, 4) void k_topk_rows(TopkArgs a)
             wave_sync();
             if (cnt < k) {                              // (of the sampled keys as well: nothing lower to try)
                 if (!look || want == sm.size) break;
-                want = min(sm.size, 2 * want + 8);
+                want = min(sm.size, want + want / 2 + 4);
                 continue;
             }
             // (equal keys: lower index first; the select walks as many 64-entry chunks as were collected, not
             // as many as the buffer holds)
             const int held = min(cnt, kCollect);
-            uint32_t kth = t0;
+            uint32_t kth = t0;                      // (asked for where the buffer is full alone)
             if (held > k) {
-                if (held <= 256) kth = wave_select<4>(ent, held, k, nullptr);
-                else if (held <= 512) kth = wave_select<8>(ent, held, k, nullptr);
+                if (held <= 256) wave_select<4>(ent, held, k, nullptr);
+                else if (held <= 512) wave_select<8>(ent, held, k, nullptr);
                 else kth = wave_select<kCollect / 64>(ent, held, k, nullptr);
             }
             done = cnt <= kCollect;
