@@ -216,3 +216,19 @@ def test_segments_are_as_long_as_what_an_item_costs(storage, tables, d, nq, want
     ws = ix.workspace(nq, 4, 10)
     assert _hr().hr_ivf_stats(ix.handle, ws, ws.numel(), nq, 4, 10)["seg_rows"] == want
     ix.close()
+
+
+@pytest.mark.parametrize("storage,tables,d,nlist,nq,nprobe,k", [("bf16", False, 64, 64, 256, 48, 100), ("bf16", False, 128, 64, 300, 40, 100), ("f32", True, 64, 64, 200, 64, 128),
+                                                                ("bf16", False, 64, 256, 200, 128, 100), ("bf16", False, 64, 256, 192, 128, 128), ("f32", True, 64, 256, 192, 128, 128)])
+def test_static_search_beyond_the_first_plan(storage, tables, d, nlist, nq, nprobe, k):
+    """Batches whose 256 work items do not fit the static array with whole selection buffers: with shorter ones, and, the
+    last two, with half the items.  The same results as a search that has a workspace of its own."""
+    dtype = {"f32": torch.float32, "bf16": torch.bfloat16}[storage]
+    ix, cent, off, vec, ids, g = _index(100000, d, nlist, dtype, nq, tables=tables, zipf=0.6)
+    q = torch.randn(nq, d, generator=g, device="cuda")
+    want, ws = ix.search(q, nprobe, k, "ip")
+    got = torch.full_like(want, -7)
+    score = torch.zeros_like(ws)
+    _hr().hr_ivf_search_static(ix.handle, q, nq, nprobe, k, _hr().HR_METRIC_IP, got, score)
+    assert torch.equal(got, want) and torch.equal(score, ws)
+    ix.close()
