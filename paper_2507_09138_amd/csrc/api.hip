@@ -1,5 +1,6 @@
 // Host side of the C ABI declared in hr_ivf.h: argument checks, workspace layout, launch
 // sequence.  Nothing here synchronises the caller's stream except hr_ivf_load and hr_ivf_stats.
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -148,6 +149,7 @@ struct hr_ivf_index {
     const void* vectors;
     const int64_t* ids;
     int64_t nlist, N;
+    int64_t longest;       // rows of the longest list
     int d, dtype;
     int* d_list_off;       // [nlist+1] int32
     float* d_row_norm;     // [N]
@@ -211,9 +213,10 @@ struct Plan {
 // What bounds the size of a plan: the aimed number of work items of the list scan (segments are sized so that
 // about that many items result: fewer, larger items need fewer result slots) and the bytes of the coarse key table
 // (queries are scored in chunks that fit it).
-// cap: entries of a selection buffer where those lie in the result slots (0: as many as k asks for). 
-struct PlanLimits { int item_target; size_t ckeys_bytes; int cap; };
-static constexpr PlanLimits kDefaultLimits = {kItemTarget, (size_t)512 << 20, 0};
+// cap: entries of a selection buffer where those lie in the result slots (0: as many as k asks for).  by_length: bound the
+// slots by the longest list too.
+struct PlanLimits { int item_target; size_t ckeys_bytes; bool by_length; int cap; };
+static constexpr PlanLimits kDefaultLimits = {kItemTarget, (size_t)512 << 20, true, 0};
 
 static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, const PlanLimits& lim = kDefaultLimits)
 {
@@ -263,7 +266,12 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     // Result slots: sum of segments x bucket width <= cw x item_target, plus one per pair for the ragged ends.
     p.item_target = lim.item_target;
     p.item_cap = (int)(lim.item_target + pairs / p.cw_s + (pairs < nlist ? pairs : nlist) + 8);
-    p.slot_cap = (int)((int64_t)p.cw_s * lim.item_target + pairs);
+    int64_t slots_most = (int64_t)p.cw_s * lim.item_target + pairs;
+    // (nor has a pair more slots than the longest list has segments, whatever the batch: one query over 16 of 256 lists of
+    // 65536 rows in all, k 10: 268 MB of slots without this bound, 0.3 with it)
+    const int64_t by_length = pairs * ((ix->longest + kMinSegRows - 1) / kMinSegRows);
+    if (lim.by_length && by_length < slots_most) slots_most = by_length;
+    p.slot_cap = (int)slots_most;
 
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -357,6 +365,7 @@ int hr_ivf_load(const float* centroids, const int64_t* list_offsets, const void*
     int* h_off = new (std::nothrow) int[nlist + 1];
     if (!h_off) { delete ix; return fail(HR_ERR_HIP, "out of host memory"); }
     for (int64_t l = 0; l <= nlist; l++) h_off[l] = (int)list_offsets[l];
+    for (int64_t l = 0; l < nlist; l++) ix->longest = std::max(ix->longest, list_offsets[l + 1] - list_offsets[l]);
     ix->device = dev;
     hipError_t e = hipDeviceGetAttribute(&ix->num_cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess) e = hr::static_scratch_address(dev, &ix->scratch);
@@ -697,8 +706,8 @@ int hr_ivf_search(const hr_ivf_index* ix, const float* queries, int64_t nq, int3
 
 // Limits of a plan that has to fit the static scratch array: few, large work items (result slots are
 // what takes the room) and a small coarse key table.
-static constexpr PlanLimits kStaticLimits = {256, (size_t)4 << 20, 0};
-static constexpr PlanLimits kStaticFewer = {128, (size_t)4 << 20, 0};
+static constexpr PlanLimits kStaticLimits = {256, (size_t)4 << 20, false, 0};
+static constexpr PlanLimits kStaticFewer = {128, (size_t)4 << 20, false, 0};
 
 // The plan of a call on the static array; p.total is beyond it if there is none.  Result slots are item_target x queries of
 // a tile.  Storage whose tiles have 128 queries since they hold both operand parts in registers had 64 before, and what

@@ -232,3 +232,12 @@ def test_static_search_beyond_the_first_plan(storage, tables, d, nlist, nq, npro
     _hr().hr_ivf_search_static(ix.handle, q, nq, nprobe, k, _hr().HR_METRIC_IP, got, score)
     assert torch.equal(got, want) and torch.equal(score, ws)
     ix.close()
+
+
+def test_workspace_of_a_small_batch_is_small():
+    """Result slots are bounded by the segments that the longest list has, not by the largest batch's alone."""
+    ix, *_ = _index(65536, 64, 256, torch.bfloat16, 1)
+    assert _hr().hr_ivf_workspace_bytes(ix.handle, 1, 16, 10) < 8 << 20
+    sizes = [_hr().hr_ivf_workspace_bytes(ix.handle, n, 16, 10) for n in (1, 2, 63, 64, 65, 128, 1000, 5000)]
+    assert sizes == sorted(sizes)                       # (what is enough for a batch is enough for a smaller one)
+    ix.close()
