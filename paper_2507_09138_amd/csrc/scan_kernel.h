@@ -311,11 +311,14 @@ struct ScanShape {
     static constexpr int pf = scan_prefetch(DT, KSTEPS, NCS, NW);
     static constexpr int wcols = nc * NCS;                         // query columns per wave
     // a wave whose operand fills the register file: what the rare paths need is computed there (see lane_now), and
-    // the fragment addresses come from one register.  (Binary16 lists have registers to spare and lose by it: 4096
-    // queries x 4096 lists 2.46 -> 2.74 ms.)
-    static constexpr bool lean = qp * KSTEPS >= 32;
+    // the fragment addresses come from one register.  That is both parts of a long operand, and float32 rows of 32 k-steps
+    // passing through the registers (11.00 ms without, 4 registers spilled, 10.92 with: 1024 queries, 524288 rows).  The
+    // others have registers to spare and lose by it: binary16, 4096 queries x 4096 lists, d = 768, 2.46 -> 2.74 ms; 1024
+    // queries, 524288 rows of d = 1024: binary16 1.45 -> 1.46, bfloat16 2.27 -> 2.33, row tables 4.52 -> 4.69.
+    static constexpr bool lean = (qp == 2 && KSTEPS >= 16) || (DT == HR_F32 && KSTEPS >= 32);
     // two blocks of a pair as one MFMA chain (see mfma_pair): twice the accumulators, which a wave that holds both
-    // parts of a long operand has no registers for
+    // parts of 24 k-steps has no registers for.  (Row tables of 16 k-steps would have them, 227 with the chain and 205
+    // without, and gain nothing: 1024 queries, 524288 rows 1.96 ms either way, 128 queries 0.73 without and 0.74 with.)
     static constexpr bool chain = NCS == 1 && (KSTEPS / grp) % 2 == 0 && grp * 2 <= KSTEPS && qp * planes * KSTEPS < 48;
     static constexpr int cw = wcols * NW;                          // query columns per item
 };
