@@ -189,7 +189,7 @@ static size_t align_up(size_t v) { return (v + HR_WORKSPACE_ALIGN - 1) & ~(size_
 // Layout of the caller's workspace for one batch shape.  Offsets in bytes.
 struct Plan {
     // coarse step: centroid table scanned with all queries as one dense bucket
-    int shape_c /* workgroup shape, -1 = no fit */, nbuf_c, cap_c, cw_c, nqt_c, seg_c, nseg_c, items_c;
+    int shape_c /* workgroup shape, -1 = no fit */, nbuf_c, cap_c, cw_c, nqt_c, seg_c, nseg_c;
     // list scan
     int shape_s, nbuf_s, cap_s, gsel_s, cw_s, item_cap, item_target;
     int slot_stride;                // entries per result slot of the list scan
@@ -258,7 +258,6 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     const int64_t seg = per_item * kBlockRows;
     p.seg_c = (int)seg;
     p.nseg_c = (int)((nlist + seg - 1) / seg);
-    p.items_c = p.nseg_c * p.nqt_c;
     p.cw_s = cols_per_set(scan_dtype(ix), ix->d) * shape_sets(p.shape_s < 0 ? 0 : p.shape_s);
     const int64_t pairs = nq * nprobe;
     // Work items: sum over probed lists of segments x query tiles.  Segments have at least C / item_target rows, C =
@@ -572,7 +571,6 @@ static int enqueue_coarse(const hr_ivf_index* ix, const Plan& p, char* ws, int64
         a.qop = ws + p.o_qop_c + (size_t)q0 * 2 * ix->d * 2;
         a.thr = (uint32_t*)(ws + p.o_thr);
         a.work_counter = zero + ix->nlist + DYN_COUNT;
-        a.dense = 1;
         a.dense_items = p.nseg_c * nqt;
         a.dense_nqt = nqt;
         a.dense_seg_rows = p.seg_c;
@@ -655,7 +653,6 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, int64_t
     a.xq_count = b.xq_count;
     a.xq_head = zero + ix->nlist + DYN_COUNT + 16;
     a.xq_stride = p.item_cap;
-    a.dense = 0;
     a.nq = (int)nq; a.k = k; a.cap = p.cap_s; a.l2 = metric == HR_METRIC_L2;
     a.nbuf = p.nbuf_s;
     a.gsel = p.gsel_s;

@@ -326,9 +326,9 @@ __device__ __forceinline__ long long wave_sum_ll(long long v)
 }
 
 // Largest batch that one workgroup groups by itself: four pairs and four lists per thread stay in its registers and the
-// tables of the lists (64 KB) in LDS.  Beyond that its serial share grows while the five kernels spread over the device:
-// with the counting of rounds in one workgroup 16384 pairs over 4096 lists took 1.42 ms a call against 1.34.  On this side
-// of the line (measured at 10 .. 1088 pairs) the one launch was 4 .. 9 % of the call faster.
+// tables of the lists (64 KB) in LDS, which is where the line lies: up to it the one launch is never slower.  Searches of
+// given lists, five launches against one: 64 pairs of 64 lists 77.7 and 70.0 us, 1024 of 1024 120.4 and 114.1, 4096 of 64
+// 98.3 and 85.3, 4096 of 4096 235.9 and 226.2; with 4.2 M rows in the lists, 4096 of 4096, 506.7 and 506.0.
 constexpr int kWholePairs = 4096, kWholeLists = 4096;
 
 // Work items and their order of execution.  Items are numbered list-major (segment-major,
@@ -424,7 +424,6 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketArgs a)
             if (j * 1024 + t < pairs) a.pair_entry[j * 1024 + t] = pe[j];
         }
         __syncthreads();
-        for (int l = t; l < a.nlist; l += 1024) a.list_w[l] = s_w[l];
     }
     if constexpr (PER > 0) {
 #pragma unroll

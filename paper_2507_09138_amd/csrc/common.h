@@ -34,7 +34,7 @@ __host__ __device__ constexpr int operand_parts(int dtype, int d)
 __host__ __device__ constexpr int cols_per_set(int dtype, int d) { return dtype == HR_F16 || operand_parts(dtype, d) == 2 ? 16 : 8; }
 
 // Workgroup shapes of the scan kernel: waves x column sets per wave.  A work item covers
-// shape_sets(shape) * cols_per_set(dtype) queries of a bucket.
+// shape_sets(shape) * cols_per_set(dtype, d) queries of a bucket.
 enum { SCAN_NARROW = 0 /* 4 waves, one per SIMD */, SCAN_WIDE = 1 /* 8 waves, two per SIMD */ };
 __host__ __device__ constexpr int shape_waves(int shape) { return shape == SCAN_WIDE ? 8 : 4; }
 __host__ __device__ constexpr int shape_ncs(int) { return 1; }                         // column sets per wave
@@ -136,8 +136,8 @@ struct ScanArgs {
     const int* xq_count;        // [8] queue lengths
     int* xq_head;               // [8] next position to pop (zeroed before launch)
     int xq_stride;
-    // dense mode (dense != 0): one list = all rows, bucket = all queries
-    int dense, dense_items, dense_nqt, dense_seg_rows, dense_nrows;
+    // dense mode (HR_F16X2 with gsel 0, and then key_out is not null): one list = all rows, bucket = all queries
+    int dense_items, dense_nqt, dense_seg_rows, dense_nrows;
     int nq, k, cap, l2;
     int nbuf;                   // staging buffers in LDS (16-bit storage; float32 always uses 2)
     int gsel;                   // selection buffers = the item's slots in global memory (slot_stride = cap), none in LDS
@@ -215,7 +215,7 @@ struct BucketArgs {
     int nq, nprobe, nlist, cw;
     int cost_cw;                // queries per tile by which the shortest segments are counted (see k_bucket_scan)
     const int* list_off;        // [nlist+1]
-    int* list_w;                // [nlist]   (zeroed by the first kernel's launch sequence)
+    int* list_w;                // [nlist]   (zeroed by the first kernel's launch sequence; a batch grouped in one launch has no use for it)
     int* pair_entry;            // [nq*nprobe]
     int* bucket_off;            // [nlist+1]
     int* bucket_q;              // [nq*nprobe]
