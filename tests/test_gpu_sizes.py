@@ -166,6 +166,38 @@ def test_grouping_keeps_every_pair_whatever_the_batch(nlist, nq, nprobe, N):
     ix.close()
 
 
+@pytest.mark.parametrize("sizes,nq,nprobe", [([0, 0, 700, 0, 5, 0, 1, 300, 0], 9, 9), ([0] * 5 + [2000] + [0] * 4000, 30, 130), ([3, 0] * 2048, 8, 512),
+                                             ([0, 1, 0, 600] * 1100, 8, 512), ([1000] + [0] * 99, 1, 100), ([0] * 64, 5, 64)])
+@pytest.mark.parametrize("metric", ["ip", "l2"])
+def test_grouping_with_lists_without_rows(sizes, nq, nprobe, metric):
+    """Empty lists, at the ends and in rows of them, in batches that one launch groups and (the fourth) that five do: they
+    have no work items and share the place of the next list that has."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(len(sizes) + nq)
+    nlist, N, d, k = len(sizes), sum(sizes), 64, 6
+    off = torch.zeros(nlist + 1, dtype=torch.int64)
+    off[1:] = torch.cumsum(torch.tensor(sizes), 0)
+    cent = torch.randn(nlist, d, generator=g, device="cuda")
+    vec = torch.randn(N, d, generator=g, device="cuda").half()
+    ix = _hr().IvfIndex(cent, off, vec, torch.arange(N, device="cuda"))
+    q = torch.randn(nq, d, generator=g, device="cuda")
+    probe = torch.rand(nq, nlist, generator=g, device="cuda").topk(nprobe, dim=1).indices.int()
+    found, score = ix.scan(q, probe, k, metric)
+    allowed = torch.zeros(nq, nlist, dtype=torch.bool, device="cuda")
+    allowed.scatter_(1, probe.long(), True)
+    op = q.half().double()
+    of_row = torch.repeat_interleave(torch.arange(nlist), off[1:] - off[:-1]).cuda()
+    key = torch.cat([torch.where(allowed[:, of_row], _keys(op, vec.double(), metric), -float("inf")),
+                     torch.full((nq, k), -float("inf"), device="cuda", dtype=torch.float64)], 1)
+    best = torch.topk(key, k, dim=1).values
+    assert torch.equal(found >= 0, best > -float("inf"))
+    ok = found >= 0
+    got = key.gather(1, found.clamp(min=0))
+    # float32 sums of 64 products (and norms) of values near 1, |q||x| + |x|^2 below 300: a few 2^-24 of that
+    assert float((got - best)[ok].abs().max() if ok.any() else 0.0) < 2e-4
+    ix.close()
+
+
 @pytest.mark.parametrize("order", ["random", "sampled high", "sampled low", "rising", "falling", "equal", "two values"])
 @pytest.mark.parametrize("nlist,nprobe", [(300, 100), (300, 300), (512, 512), (777, 300), (1024, 300), (1024, 512), (1025, 512), (2048, 512), (4099, 300),
                                           (16384, 128), (16384, 512), (65536, 16)])
@@ -219,11 +251,12 @@ def test_segments_are_as_long_as_what_an_item_costs(storage, tables, d, nq, want
 
 
 @pytest.mark.parametrize("storage,tables,d,nlist,nq,nprobe,k", [("bf16", False, 64, 64, 256, 48, 100), ("bf16", False, 128, 64, 300, 40, 100), ("f32", True, 64, 64, 200, 64, 128),
-                                                                ("bf16", False, 64, 256, 200, 128, 100), ("bf16", False, 64, 256, 192, 128, 128), ("f32", True, 64, 256, 192, 128, 128)])
+                                                                ("bf16", False, 64, 256, 200, 128, 100), ("bf16", False, 64, 256, 192, 128, 128), ("f32", True, 64, 256, 192, 128, 128), ("f16", False, 64, 5000, 700, 20, 5)])
 def test_static_search_beyond_the_first_plan(storage, tables, d, nlist, nq, nprobe, k):
     """Batches whose 256 work items do not fit the static array with whole selection buffers: with shorter ones, and, the
-    last two, with half the items.  The same results as a search that has a workspace of its own."""
-    dtype = {"f32": torch.float32, "bf16": torch.bfloat16}[storage]
+    next two, with half the items; then one whose coarse step goes in chunks of an odd number of half tiles.  The same
+    results as a search that has a workspace of its own."""
+    dtype = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[storage]
     ix, cent, off, vec, ids, g = _index(100000, d, nlist, dtype, nq, tables=tables, zipf=0.6)
     q = torch.randn(nq, d, generator=g, device="cuda")
     want, ws = ix.search(q, nprobe, k, "ip")
