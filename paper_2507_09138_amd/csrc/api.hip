@@ -600,7 +600,8 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, int64_t
     int* zero = (int*)(ws + p.o_zero);
     BucketArgs b{};
     b.probe = probe; b.nq = (int)nq; b.nprobe = nprobe; b.nlist = (int)ix->nlist; b.cw = p.cw_s;
-    b.cost_cw = p.cw_s / operand_parts(scan_dtype(ix), ix->d);
+    b.cw_log2 = __builtin_ctz((unsigned)p.cw_s);
+    b.half_tiles = operand_parts(scan_dtype(ix), ix->d) == 2;
     b.list_off = ix->d_list_off;
     b.list_w = zero;
     b.hits = ix->d_hits;

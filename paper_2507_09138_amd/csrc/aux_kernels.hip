@@ -454,8 +454,9 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketArgs a)
         }
     };
 
-    // pass 1: bucket offsets, cost = sum rows * query tiles (fine: tiles of cost_cw queries), rows streamed, pairs
+    // pass 1: bucket offsets, cost = sum rows * query tiles (fine: half as wide tiles, where those are counted), rows streamed, pairs
     int w_sum = 0;
+    const bool finer = a.half_tiles != 0;
     long long cost = 0, fine = 0, rows = 0;
 #pragma unroll UN
     for (int i = 0; i < (PER > 0 ? PER : per); i++) {
@@ -465,12 +466,12 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketArgs a)
         long long len = length(l);
         if (a.hits != nullptr && w > 0) atomicAdd(&a.hits[l], (unsigned long long)w);     // access frequency of the list
         w_sum += w;
-        cost += len * ((w + a.cw - 1) / a.cw);
-        fine += len * ((w + a.cost_cw - 1) / a.cost_cw);
+        cost += len * ((w + a.cw - 1) >> a.cw_log2);
+        if (finer) fine += len * ((w + (a.cw >> 1) - 1) >> (a.cw_log2 - 1));
         if (w > 0) rows += len;
     }
     cost = wave_sum_ll(cost);
-    fine = wave_sum_ll(fine);
+    fine = finer ? wave_sum_ll(fine) : cost;
     rows = wave_sum_ll(rows);
     if ((t & 63) == 0) { s_cost[t >> 6] = cost; s_fine[t >> 6] = fine; s_rows[t >> 6] = rows; }
     {
@@ -515,7 +516,7 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketArgs a)
         const int w = width(l);
         const int len = length(l);
         nseg = (w > 0 && len > 0) ? (len + seg - 1) / seg : 0;
-        nqt = (w + a.cw - 1) / a.cw;
+        nqt = (w + a.cw - 1) >> a.cw_log2;
     };
     int items = 0, slots = 0, maxseg = 0, units = 0;
 #pragma unroll UN
@@ -575,7 +576,7 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketArgs a)
             }
             l = lo; s = u - s_unit[lo];
             slot = queue_of(l, s) * kRounds + round_of(l, s, s_unit[lo + 1] - s_unit[lo], R);
-            nqt = (s_w[l] + a.cw - 1) / a.cw;
+            nqt = (s_w[l] + a.cw - 1) >> a.cw_log2;
         };
         for (int u = t; u < total[2]; u += 1024) {
             int l, s, slot, nqt; unit(u, l, s, slot, nqt);
@@ -619,7 +620,7 @@ __global__ __launch_bounds__(256) void k_round_count(BucketArgs a)
     int len = a.list_off[l + 1] - a.list_off[l];
     if (w <= 0 || len <= 0) return;
     int seg = a.dyn[DYN_SEG_ROWS];
-    int nqt = (w + a.cw - 1) / a.cw;
+    int nqt = (w + a.cw - 1) >> a.cw_log2;
     int nseg = (len + seg - 1) / seg;
     const int R = a.dyn[DYN_ROUNDS];
     for (int s = lane; s < nseg; s += 64) atomicAdd(&a.round_cnt[queue_of(l, s) * kRounds + round_of(l, s, nseg, R)], nqt);
@@ -645,7 +646,7 @@ __global__ __launch_bounds__(256) void k_item_expand(BucketArgs a)
     int len = a.list_off[l + 1] - a.list_off[l];
     if (w <= 0 || len <= 0) return;
     int seg = a.dyn[DYN_SEG_ROWS];
-    int nqt = (w + a.cw - 1) / a.cw;
+    int nqt = (w + a.cw - 1) >> a.cw_log2;
     int nseg = (len + seg - 1) / seg;
     const long long sbase = a.slot_base[l];
     const int R = a.dyn[DYN_ROUNDS];

@@ -213,7 +213,8 @@ hipError_t launch_check_labels(const int64_t* ids, int64_t n, int* negative, hip
 struct BucketArgs {
     const int* probe;           // [nq*nprobe]
     int nq, nprobe, nlist, cw;
-    int cost_cw;                // queries per tile by which the shortest segments are counted (see k_bucket_scan)
+    int cw_log2;                // (the queries of a tile are a power of two)
+    int half_tiles;             // the shortest segments are counted in tiles of cw / 2 queries (see k_bucket_scan)
     const int* list_off;        // [nlist+1]
     int* list_w;                // [nlist]   (zeroed by the first kernel's launch sequence; a batch grouped in one launch has no use for it)
     int* pair_entry;            // [nq*nprobe]
