@@ -23,8 +23,8 @@ constexpr int kHistBins = 64;              // per-query histogram of candidate k
 // (8 queries per wave) or, where two operands of d elements leave room for the rest in 256 registers, two operands of one
 // column (16 queries per wave): a tile then has twice the queries, so every row is moved into LDS half as often, and
 // every row fragment read from LDS feeds two MFMAs per plane instead of one.  Both were what the narrow form waited for:
-// 8192 queries x 16.8 M bfloat16 rows 17.9 -> 16.0 ms, 3001 queries x 16384 centroids 445 -> 355 us, float32 lists with
-// row tables (1024 queries) 705 -> 680 us; the same bits.  d = 1024 (256 registers of operand) keeps the two columns,
+// 8192 queries x 16.8 M bfloat16 rows 17.9 -> 16.0 ms, 3001 queries x 16384 centroids 445 -> 355 us, 1024 queries over all of
+// 524288 rows with row tables, d = 768, 3.90 -> 2.91 ms; the same bits.  d = 1024 (256 registers of operand) keeps the two columns,
 // as do float32 rows split on the fly, whose rows pass through the registers.
 __host__ __device__ constexpr int operand_parts(int dtype, int d)
 {
