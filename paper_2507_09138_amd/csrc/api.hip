@@ -189,7 +189,7 @@ static size_t align_up(size_t v) { return (v + HR_WORKSPACE_ALIGN - 1) & ~(size_
 // Layout of the caller's workspace for one batch shape.  Offsets in bytes.
 struct Plan {
     // coarse step: centroid table scanned with all queries as one dense bucket
-    int shape_c /* workgroup shape, -1 = no fit */, nbuf_c, cap_c, cw_c, nqt_c, seg_c, nseg_c;
+    int shape_c /* workgroup shape, -1 = no fit */, nbuf_c, cap_c, cw_c, cols_c, nqt_c, seg_c, nseg_c;
     // list scan
     int shape_s, nbuf_s, cap_s, gsel_s, cw_s, item_cap, item_target;
     int slot_stride;                // entries per result slot of the list scan
@@ -228,29 +228,40 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     for (int nbuf = 3; nbuf >= 2 && p.shape_c < 0; nbuf--)
         if (scan_lds_bytes(HR_F16X2, ix->d, 0, SCAN_WIDE, nbuf) <= (size_t)kLdsLimit) { p.shape_c = SCAN_WIDE; p.nbuf_c = nbuf; }
     p.shape_s = ps.shape; p.nbuf_s = ps.nbuf; p.cap_s = ps.gsel && lim.cap > 0 ? lim.cap : ps.cap; p.gsel_s = ps.gsel;
-    p.cw_c = cols_per_set(HR_F16X2, ix->d) * shape_sets(p.shape_c < 0 ? 0 : p.shape_c);
     // queries per coarse chunk: the [chunk, nlist] key table stays within its limit, 512 MiB by default (the more
     // queries per launch the better both kernels fill the device: 16384 lists, four chunks of 2048 queries 1.88 ms,
     // one of 8192 1.45 ms)
     p.cchunk = (int64_t)lim.ckeys_bytes / (nlist * 4) / 64 * 64;
     if (p.cchunk < 64) p.cchunk = 64;
     if (p.cchunk > nq) p.cchunk = nq > 0 ? nq : 1;
-    p.nqt_c = (int)((p.cchunk + p.cw_c - 1) / p.cw_c);
-    // Rows of the centroid table per work item.  The items are alike, so what counts is how many whole rounds over the
-    // compute units they make and how long an item is: its blocks, about four more that loading a tile of queries costs,
-    // and, for long items, a few percent by which the last ones end apart.  Mostly that is one round (8192 queries, d = 1024,
-    // two rounds with at least 32 rows per item or eight beyond 64 tiles: 512 centroids 144 us, one round 82; 4096 381 and
-    // 320; 3001 queries, d = 768, 4096 centroids 121 and 108).
+    // Work items of the coarse step: tiles of queries x rows of the centroid table.  The items are alike, so what counts is
+    // how many whole rounds over the compute units they make and how long an item is: its blocks, about four more that loading
+    // a tile of 128 queries costs (two for 64, with half the columns of every wave empty: a block takes as long), and, for
+    // long items, a few percent by which the last ones end apart.  Mostly that is one round (8192 queries, d = 1024, two
+    // rounds with at least 32 rows per item or eight beyond 64 tiles: 512 centroids 144 us, one round 82; 4096 381 and 320;
+    // 3001 queries, d = 768, 4096 centroids 121 and 108), and tiles of 64 where those fit it as well, if the vectors are long
+    // enough for the loading to count and the table so short that reading it twice as often does not (d = 768, 64 centroids:
+    // 100 queries 26.3 -> 24.3 us, 300 28.6 -> 24.5, 3001 40.7 -> 37.3; 2048 centroids, 200 queries 36.1 -> 34.3, but 4096,
+    // 100 queries 36.1 -> 37.3; d = 128, 512 centroids, 1000 queries 20.0 -> 21.5).
     const int64_t nblk = (nlist + kBlockRows - 1) / kBlockRows, cus = ix->num_cus;
+    const int full = cols_per_set(HR_F16X2, ix->d) * shape_sets(p.shape_c < 0 ? 0 : p.shape_c), waves = shape_waves(p.shape_c < 0 ? 0 : p.shape_c);
     int64_t per_item = nblk;                        // blocks
     double least = 0.0;
-    for (int r = 1; r <= 8; r++) {
-        const int64_t nseg = r * cus / p.nqt_c;
-        if (nseg < 1) continue;
-        const int64_t blocks = (nblk + nseg - 1) / nseg, items = (nblk + blocks - 1) / blocks * p.nqt_c;
-        const double cost = (double)((items + cus - 1) / cus) * (double)(4 + blocks) + (double)blocks / 16.0;
-        if (least == 0.0 || cost < least) { least = cost; per_item = blocks; }
+    p.cw_c = full;
+    for (int cw = full; cw >= full / operand_parts(HR_F16X2, ix->d); cw /= 2) {
+        const int64_t nqt = (p.cchunk + cw - 1) / cw;
+        // (a single half tile would only have twice the waves multiply: 64 queries, 64 centroids 22.0 -> 23.5)
+        if (cw < full && (nqt == 1 || ix->d < 512 || nblk > 128)) break;
+        for (int r = 1; r <= 8; r++) {
+            const int64_t nseg = r * cus / nqt;
+            if (nseg < 1) continue;
+            const int64_t blocks = (nblk + nseg - 1) / nseg, items = (nblk + blocks - 1) / blocks * nqt;
+            const double cost = (double)((items + cus - 1) / cus) * (4.0 * cw / full + (double)blocks) + (double)blocks / 16.0;
+            if (least == 0.0 || cost < least) { least = cost; per_item = blocks; p.cw_c = cw; }
+        }
     }
+    p.cols_c = p.cw_c / waves;
+    p.nqt_c = (int)((p.cchunk + p.cw_c - 1) / p.cw_c);
     // (not as short as one block where two leave enough of the device busy: half the loads of queries.  One tile of 8 queries,
     // d = 64: 4096 centroids 24.3 -> 22.8 us, 1024 of d = 768 19.1 -> 20.0; 16 tiles, d = 768, 64 centroids 38.6 -> 36.8,
     // two tiles, 256 centroids 29.4 -> 31.2)
@@ -573,6 +584,7 @@ static int enqueue_coarse(const hr_ivf_index* ix, const Plan& p, char* ws, int64
         a.work_counter = zero + ix->nlist + DYN_COUNT;
         a.dense_items = p.nseg_c * nqt;
         a.dense_nqt = nqt;
+        a.dense_cols = p.cols_c;
         a.dense_seg_rows = p.seg_c;
         a.dense_nrows = (int)ix->nlist;
         a.key_out = ckeys;

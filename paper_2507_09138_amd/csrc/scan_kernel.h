@@ -704,7 +704,10 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
         }
 
         // ---- query operands of this lane's columns into registers (B fragments)
-        const int ecol0 = qt * S::cw + wave * WC + jcol;     // entry inside the bucket, set 0
+        // entry inside the bucket, set 0 (dense: a wave may hold fewer queries than it has columns for, see make_plan)
+        constexpr bool SOME = DENSE && QP == 2 && KSTEPS >= 16;
+        const int cpw = SOME ? a.dense_cols : WC;
+        const int ecol0 = (qt * NW + wave) * cpw + jcol;
         bool col_ok[NCS];
         int q[NCS];
         float thr[NCS];
@@ -712,7 +715,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
 #pragma unroll
         for (int s = 0; s < NCS; s++) {
             const int ecol = ecol0 + s * NC;
-            col_ok[s] = ecol < w;
+            col_ok[s] = ecol < w && (!SOME || jcol < cpw);
             q[s] = 0;
             if (col_ok[s]) q[s] = DENSE ? ecol : a.bucket_q[boff + ecol];
         }
