@@ -124,7 +124,7 @@ struct ScanArgs {
     int* slot_cnt;              // [slots]: one slot per (list segment, query of the list's bucket)
     Cand* slot_ent;             // [slots * slot_stride]
     int slot_stride;            // entries per slot: k, or cap where that is small (no cut at the end of an item)
-    int* work_counter;          // zeroed before launch
+    int* work_counter;          // dense mode: items popped beyond the first of every workgroup (zeroed before launch)
     // bucket mode
     const int* list_off;        // [nlist+1] row offsets
     const int* bucket_off;      // [nlist+1]
@@ -134,7 +134,7 @@ struct ScanArgs {
                                 // (first row, rows, first entry of the list's bucket, width of the bucket),
                                 // (query tile, first result slot of the item, list, segment)
     const int* xq_count;        // [8] queue lengths
-    int* xq_head;               // [8] next position to pop (zeroed before launch)
+    int* xq_head;               // [8] items popped beyond those that the workgroups start with (zeroed before launch)
     int xq_stride;
     // dense mode (HR_F16X2 with gsel 0, and then key_out is not null): one list = all rows, bucket = all queries
     int dense_items, dense_nqt, dense_seg_rows, dense_nrows;
