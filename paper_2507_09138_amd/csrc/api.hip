@@ -76,18 +76,19 @@ hipError_t launch_scan(int dtype, int d, const ScanArgs& a, int shape, int grid,
 size_t scan_lds_bytes(int dtype, int d, int cap, int shape, int nbuf)
 {
     const int nw = shape_waves(shape);
+    const size_t rows = block_rows(dtype, d);
     size_t buf;
     if (dtype == HR_F32) {
-        buf = (size_t)kBlockRows * (d * 2 + kRowPad) * 2;
+        buf = rows * (d * 2 + kRowPad) * 2;
     } else if (dtype == HR_F16X2) {
-        const int chunks = kBlockRows * d * 2 / 16, threads = nw * 64;
+        const int chunks = (int)rows * d * 2 / 16, threads = nw * 64;
         buf = (size_t)((chunks + threads - 1) / threads) * threads * 16 * 2;
     } else {
-        const int chunks = kBlockRows * d * 2 / 16, threads = nw * 64;
+        const int chunks = (int)rows * d * 2 / 16, threads = nw * 64;
         buf = (size_t)((chunks + threads - 1) / threads) * threads * 16;
     }
     const size_t cw = (size_t)cols_per_set(dtype, d) * shape_sets(shape);
-    return nbuf * buf + cw * cap * sizeof(Cand) + (size_t)nbuf * kBlockRows * sizeof(float) + 32;
+    return nbuf * buf + cw * cap * sizeof(Cand) + nbuf * rows * sizeof(float) + 32;
 }
 }  // namespace hr
 
@@ -243,7 +244,7 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     // enough for the loading to count and the table so short that reading it twice as often does not (d = 768, 64 centroids:
     // 100 queries 26.3 -> 24.3 us, 300 28.6 -> 24.5, 3001 40.7 -> 37.3; 2048 centroids, 200 queries 36.1 -> 34.3, but 4096,
     // 100 queries 36.1 -> 37.3; d = 128, 512 centroids, 1000 queries 20.0 -> 21.5).
-    const int64_t nblk = (nlist + kBlockRows - 1) / kBlockRows, cus = ix->num_cus;
+    const int64_t nblk = (nlist + kMfmaRows - 1) / kMfmaRows, cus = ix->num_cus;
     const int full = cols_per_set(HR_F16X2, ix->d) * shape_sets(p.shape_c < 0 ? 0 : p.shape_c), waves = shape_waves(p.shape_c < 0 ? 0 : p.shape_c);
     int64_t per_item = nblk;                        // blocks
     double least = 0.0;
@@ -266,7 +267,7 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     // d = 64: 4096 centroids 24.3 -> 22.8 us, 1024 of d = 768 19.1 -> 20.0; 16 tiles, d = 768, 64 centroids 38.6 -> 36.8,
     // two tiles, 256 centroids 29.4 -> 31.2)
     if (per_item == 1 && nblk * p.nqt_c >= (p.nqt_c > 1 ? cus / 4 : cus / 2)) per_item = 2;
-    const int64_t seg = per_item * kBlockRows;
+    const int64_t seg = per_item * kMfmaRows;
     p.seg_c = (int)seg;
     p.nseg_c = (int)((nlist + seg - 1) / seg);
     p.cw_s = cols_per_set(scan_dtype(ix), ix->d) * shape_sets(p.shape_s < 0 ? 0 : p.shape_s);

@@ -11,7 +11,7 @@ constexpr int kWave = 64;
 // internal storage code next to HR_F32 / HR_F16 / HR_BF16: float32 rows already split into a
 // binary16 hi table and a 2^11-scaled binary16 lo table (the centroid table, split at load)
 constexpr int HR_F16X2 = 3;
-constexpr int kBlockRows = 16;             // rows per MFMA block (M of 16x16x32)
+constexpr int kMfmaRows = 16;              // rows per MFMA (M of 16x16x32)
 constexpr int kRowPad = 32;                // bytes of LDS padding per staged row: measured conflict-free
                                            // for the 16-rows x 16-byte MFMA fragment reads (16 is 2-way)
 constexpr int kAppendMax = 16;             // most candidates one column can gain per block
@@ -40,10 +40,25 @@ __host__ __device__ constexpr int shape_waves(int shape) { return shape == SCAN_
 __host__ __device__ constexpr int shape_ncs(int) { return 1; }                         // column sets per wave
 __host__ __device__ constexpr int shape_sets(int shape) { return shape_waves(shape) * shape_ncs(shape); }
 
+// Groups of 16 rows that are staged, waited for and filtered together: a block of the scan has 16 * block_groups rows, about
+// 16 KB.  16 rows of a short vector are a few KB and a few MFMAs, and a barrier, requests that no wave fills and a filter
+// with its compare and branch cost more than they do.  Blocks of 64 rows instead of 16, d = 64: 4000 queries over 60 of 200
+// binary16 lists of 3000 rows 880 -> 627 us, 500 over 40 of 2000 lists 426 -> 372, 500 over 40 of 1000 lists of 40 rows 113
+// -> 106 (128 rows: 626, 380, 109: a list ends in the middle of a longer block); float32 split on the fly, d = 64, the first two
+// 1578 -> 1304 and 528 -> 454.  Two planes of 16 rows of d = 256 are 16 KB already: 32 rows of row tables were 10 % faster for
+// 4000 queries and 2 .. 4 % slower for fewer.
+__host__ __device__ constexpr int block_groups(int dtype, int d)
+{
+    const int most = 4, long_enough = dtype == HR_F32 || dtype == HR_F16X2 ? 256 : 512;
+    return d >= long_enough ? 1 : (long_enough / d < most ? long_enough / d : most);
+}
+__host__ __device__ constexpr int block_rows(int dtype, int d) { return kMfmaRows * block_groups(dtype, d); }
+
 // k-steps (of 32 elements) whose row fragments a wave fetches from LDS together
 __host__ __device__ constexpr int scan_group(int dtype, int ksteps, int nw)
 {
-    if (ksteps < 8) return ksteps < 4 ? ksteps : 4;
+    if (ksteps < 16 && nw == 8) return 4;                           // (of a block of several groups of rows: 8 or 16 k-steps in all)
+    if (ksteps < 8) return 4;
     if (nw == 8 && dtype == HR_F32 && ksteps >= 24) return 2;       // (leaves registers for a second row block in flight)
     // (what a long operand in two parts leaves: 253 of 256 registers at 24 k-steps, none spilled)
     if (nw == 8 && ksteps >= 16 && operand_parts(dtype, ksteps * 32) == 2)
@@ -58,11 +73,12 @@ __host__ __device__ constexpr int scan_prefetch(int dtype, int ksteps, int ncs, 
 {
     const int planes = dtype == HR_F32 ? 2 : 1;
     const int rowb = ksteps * 32 * (dtype == HR_F32 ? 4 : 2);
-    const int chunks = kBlockRows * rowb / 16;
+    const int chunks = block_rows(dtype, ksteps * 32) * rowb / 16;
     const int nld = (chunks + nw * 64 - 1) / (nw * 64);
     const int left = (nw == 8 ? 256 : 512) - ncs * ksteps * 4 - 2 * planes * scan_group(dtype, ksteps, nw) * 4 - (nw == 8 ? 67 : 96);
     const int fit = left / (nld * 4 + 1);
-    return fit < 1 ? 1 : (fit > 4 ? 4 : fit);
+    const int most = block_groups(dtype, ksteps * 32) > 1 ? 2 : 4;  // (a list shorter than them all still loads them all)
+    return fit < 1 ? 1 : (fit > most ? most : fit);
 }
 
 // selection buffer capacity per column for a given k: room for k kept entries plus a batch of

@@ -292,19 +292,22 @@ struct ScanShape {
     static constexpr int qp = operand_parts(DT, d);                // parts of the query operand in registers of their own
     static constexpr int na = 2 * qp;                              // accumulators per column set (independent MFMA chains)
     static constexpr int planes = StoreTraits<DT>::planes;
+    static constexpr int rb = block_groups(DT, d);                 // groups of 16 rows per block
+    static constexpr int br = kMfmaRows * rb;                      // rows per block
     static constexpr bool direct = DT != HR_F32;                   // (HR_F16X2: two planes, both moved directly)
     static constexpr int rowb = d * StoreTraits<DT>::esize;        // bytes of one stored row
     static constexpr int cpr = rowb / 16;                          // 16-byte chunks per stored row
     static constexpr int swz = (cpr < 16 ? cpr : 16) - 1;          // row bits xor-ed into the chunk position
     static constexpr int rowp = direct ? rowb : d * 2 + kRowPad;   // bytes of one staged row (one plane)
-    static constexpr int plane_bytes_padded = kBlockRows * rowp;
-    static constexpr int chunks = kBlockRows * cpr;                // 16-byte chunks per block
+    static constexpr int plane_bytes_padded = br * rowp;
+    static constexpr int chunks = br * cpr;                        // 16-byte chunks per block
     static constexpr int nfw = NW;                                 // waves that move rows: all
     static constexpr int nld = (chunks + nfw * 64 - 1) / (nfw * 64);   // chunks per thread per block
     // (direct: every wave always issues nld loads, so a buffer is a whole number of them)
     static constexpr int plane_bytes = direct ? nld * nfw * 1024 : plane_bytes_padded;
     static constexpr int buf_bytes = plane_bytes * planes;
-    static constexpr int lpf = planes * nld + 1;                   // direct: loads per wave per block (chunks + norms)
+    static constexpr int nnl = (br + 63) / 64;                     // direct: loads of the norms of a block's rows
+    static constexpr int lpf = planes * nld + nnl;                 // direct: loads per wave per block (chunks + norms)
     // k-steps whose row fragments are fetched from LDS together, ahead of their MFMAs
     static constexpr int grp = scan_group(DT, KSTEPS, NW);
     // register path: row blocks kept in flight in registers ahead of the one being staged
@@ -319,7 +322,7 @@ struct ScanShape {
     // two blocks of a pair as one MFMA chain (see mfma_pair): twice the accumulators, which a wave that holds both
     // parts of 24 k-steps has no registers for.  (Row tables of 16 k-steps would have them, 227 with the chain and 205
     // without, and gain nothing: 1024 queries, 524288 rows 1.96 ms either way, 128 queries 0.73 without and 0.74 with.)
-    static constexpr bool chain = NCS == 1 && (KSTEPS / grp) % 2 == 0 && grp * 2 <= KSTEPS && qp * planes * KSTEPS < 48;
+    static constexpr bool chain = NCS == 1 && rb == 1 && (KSTEPS / grp) % 2 == 0 && grp * 2 <= KSTEPS && qp * planes * KSTEPS < 48;
     static constexpr int cw = wcols * NW;                          // query columns per item
 };
 
@@ -386,34 +389,40 @@ __device__ __forceinline__ void stage_block(char* buf, const u32x4 (&regs)[S::nl
 // with padded rows the four bases are 64 bytes apart, with the xor-ed chunk positions of the
 // direct staging they are permuted per lane.
 template <int DT, int KSTEPS, int NCS, int NA, typename S>
-__device__ __forceinline__ void mfma_block(const char* const (&ap)[4], const u32x4 (&bfrag)[NCS * S::qp][KSTEPS], floatx4 (&acc)[NCS][S::na])
+__device__ __forceinline__ void mfma_block(const char* const (&ap)[4], const u32x4 (&bfrag)[NCS * S::qp][KSTEPS], floatx4 (&acc)[NCS][S::rb][S::na])
 {
     constexpr int G = S::grp;                        // k-steps per group
-    constexpr int NG = KSTEPS / G;
+    constexpr int NT = S::rb * KSTEPS;               // k-steps of the groups of 16 rows, one after the other
+    constexpr int NG = NT / G;
     constexpr int P = StoreTraits<DT>::planes;
-    static_assert(KSTEPS % G == 0, "k-steps must split into whole groups");
+    static_assert(NT % G == 0, "k-steps must split into whole groups");
 #pragma unroll
     for (int s = 0; s < NA; s++)
 #pragma unroll
-        for (int i = 0; i < S::na; i++) acc[s][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < S::rb; j++)
+#pragma unroll
+            for (int i = 0; i < S::na; i++) acc[s][j][i] = floatx4{0.f, 0.f, 0.f, 0.f};
     u32x4 af[2][P][G];
+    auto fetch = [&](int gi, int i, int pl) __attribute__((always_inline)) {
+        const int u = gi * G + i, t = u % KSTEPS, j = u / KSTEPS;
+        af[gi & 1][pl][i] = *(const u32x4*)(ap[t & 3] + pl * S::plane_bytes + (t >> 2) * 256 + j * kMfmaRows * S::rowp);
+    };
 #pragma unroll
     for (int i = 0; i < G; i++)
 #pragma unroll
-        for (int pl = 0; pl < P; pl++) af[0][pl][i] = *(const u32x4*)(ap[i & 3] + pl * S::plane_bytes + (i >> 2) * 256);
+        for (int pl = 0; pl < P; pl++) fetch(0, i, pl);
 #pragma unroll
     for (int gi = 0; gi < NG; gi++) {
         if (gi + 1 < NG) {
 #pragma unroll
             for (int i = 0; i < G; i++)
 #pragma unroll
-                for (int pl = 0; pl < P; pl++)
-                    af[(gi + 1) & 1][pl][i] = *(const u32x4*)(ap[((gi + 1) * G + i) & 3] + pl * S::plane_bytes + (((gi + 1) * G + i) >> 2) * 256);
+                for (int pl = 0; pl < P; pl++) fetch(gi + 1, i, pl);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < G; i++) {
-            const int t = gi * G + i;
+            const int t = (gi * G + i) % KSTEPS, j = (gi * G + i) / KSTEPS;
 #pragma unroll
             for (int s = 0; s < NA; s++) {
 #pragma unroll
@@ -421,14 +430,14 @@ __device__ __forceinline__ void mfma_block(const char* const (&ap)[4], const u32
                     const u32x4 bq = bfrag[s * S::qp + qp][t];
                     if constexpr (StoreTraits<DT>::planes == 2) {
                         half8 b = __builtin_bit_cast(half8, bq);
-                        acc[s][qp * 2] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gi & 1][0][i]), b, acc[s][qp * 2], 0, 0, 0);
-                        acc[s][qp * 2 + 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gi & 1][1][i]), b, acc[s][qp * 2 + 1], 0, 0, 0);
+                        acc[s][j][qp * 2] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gi & 1][0][i]), b, acc[s][j][qp * 2], 0, 0, 0);
+                        acc[s][j][qp * 2 + 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gi & 1][1][i]), b, acc[s][j][qp * 2 + 1], 0, 0, 0);
                     } else if constexpr (DT == HR_F16) {
                         half8 b = __builtin_bit_cast(half8, bq);
-                        acc[s][t & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gi & 1][0][i]), b, acc[s][t & 1], 0, 0, 0);
+                        acc[s][j][t & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gi & 1][0][i]), b, acc[s][j][t & 1], 0, 0, 0);
                     } else {
                         bf16x8 b = __builtin_bit_cast(bf16x8, bq);
-                        acc[s][qp * 2 + (t & 1)] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[gi & 1][0][i]), b, acc[s][qp * 2 + (t & 1)], 0, 0, 0);
+                        acc[s][j][qp * 2 + (t & 1)] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[gi & 1][0][i]), b, acc[s][j][qp * 2 + (t & 1)], 0, 0, 0);
                     }
                 }
             }
@@ -443,7 +452,7 @@ __device__ __forceinline__ void mfma_block(const char* const (&ap)[4], const u32
 // filter of the first block) runs after the first MFMAs of the second block have been handed to the matrix pipe.
 template <int DT, int KSTEPS, int NCS, int NA, typename S, typename F>
 __device__ __forceinline__ void mfma_pair(const char* const (&ap0)[4], const char* const (&ap1)[4], const u32x4 (&bfrag)[NCS * S::qp][KSTEPS],
-                                          floatx4 (&acc0)[NCS][S::na], floatx4 (&acc1)[NCS][S::na], F&& between)
+                                          floatx4 (&acc0)[NCS][S::rb][S::na], floatx4 (&acc1)[NCS][S::rb][S::na], F&& between)
 {
     constexpr int G = S::grp;
     constexpr int NG = KSTEPS / G;
@@ -453,7 +462,7 @@ __device__ __forceinline__ void mfma_pair(const char* const (&ap0)[4], const cha
 #pragma unroll
     for (int s = 0; s < NA; s++)
 #pragma unroll
-        for (int i = 0; i < S::na; i++) { acc0[s][i] = floatx4{0.f, 0.f, 0.f, 0.f}; acc1[s][i] = floatx4{0.f, 0.f, 0.f, 0.f}; }
+        for (int i = 0; i < S::na; i++) { acc0[s][0][i] = floatx4{0.f, 0.f, 0.f, 0.f}; acc1[s][0][i] = floatx4{0.f, 0.f, 0.f, 0.f}; }
     u32x4 af[2][P][G];
     // (every index below is a compile-time constant: the loop over the groups is unrolled by the type system,
     // so that the operand and accumulator arrays stay in registers)
@@ -468,7 +477,7 @@ __device__ __forceinline__ void mfma_pair(const char* const (&ap0)[4], const cha
                 else                   af[gg & 1][pl][i] = *(const u32x4*)(ap1[(g0 + i) & 3] + pl * S::plane_bytes + ((g0 + i) >> 2) * 256);
             }
     };
-    auto group = [&](auto gc, floatx4 (&acc)[NCS][S::na]) __attribute__((always_inline)) {
+    auto group = [&](auto gc, floatx4 (&acc)[NCS][S::rb][S::na]) __attribute__((always_inline)) {
         constexpr int gg = decltype(gc)::value;
 #pragma unroll
         for (int i = 0; i < G; i++) {
@@ -480,14 +489,14 @@ __device__ __forceinline__ void mfma_pair(const char* const (&ap0)[4], const cha
                     const u32x4 bq = bfrag[s * S::qp + qp][t];
                     if constexpr (StoreTraits<DT>::planes == 2) {
                         half8 b = __builtin_bit_cast(half8, bq);
-                        acc[s][qp * 2] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gg & 1][0][i]), b, acc[s][qp * 2], 0, 0, 0);
-                        acc[s][qp * 2 + 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gg & 1][1][i]), b, acc[s][qp * 2 + 1], 0, 0, 0);
+                        acc[s][0][qp * 2] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gg & 1][0][i]), b, acc[s][0][qp * 2], 0, 0, 0);
+                        acc[s][0][qp * 2 + 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gg & 1][1][i]), b, acc[s][0][qp * 2 + 1], 0, 0, 0);
                     } else if constexpr (DT == HR_F16) {
                         half8 b = __builtin_bit_cast(half8, bq);
-                        acc[s][t & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gg & 1][0][i]), b, acc[s][t & 1], 0, 0, 0);
+                        acc[s][0][t & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gg & 1][0][i]), b, acc[s][0][t & 1], 0, 0, 0);
                     } else {
                         bf16x8 b = __builtin_bit_cast(bf16x8, bq);
-                        acc[s][qp * 2 + (t & 1)] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[gg & 1][0][i]), b, acc[s][qp * 2 + (t & 1)], 0, 0, 0);
+                        acc[s][0][qp * 2 + (t & 1)] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[gg & 1][0][i]), b, acc[s][0][qp * 2 + (t & 1)], 0, 0, 0);
                     }
                 }
             }
@@ -528,6 +537,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
     constexpr bool DENSE = DT == HR_F16X2 && !GS;
     constexpr int PF = S::pf;
     constexpr int NLD = S::nld;
+    constexpr int RB = S::rb, BR = S::br;
     extern __shared__ __align__(16) char smem[];
     // staging buffers in LDS: a.nbuf of them (direct) or 2 (through registers); block blk of an
     // item uses buffer blk % NB, and the blocks up to blk + NB - 1 are on their way meanwhile
@@ -538,14 +548,14 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
     const int NB = S::direct ? a.nbuf : 2;
     const bool pairs = S::direct && (NB == 4 || NB == 6);
     const int D = pairs ? NB - 2 : NB - 1;         // blocks requested ahead of the one in use
-    // LDS: [NB staging buffers][selection buffers cw*cap][row norms NB x 16][item]
+    // LDS: [NB staging buffers][selection buffers cw*cap][row norms NB x BR][item]
     // (GS: the selection buffers are the item's result slots in global memory instead: a
     // wave alone writes and reads the buffers of its columns, candidates are few, and LDS is
     // left to the row buffers)
     char* stage = smem;
     Cand* sel = (Cand*)(smem + NB * S::buf_bytes);
     float* nstage = (float*)(sel + (GS ? 0 : S::cw * a.cap));
-    int* s_item = (int*)(nstage + NB * kBlockRows);
+    int* s_item = (int*)(nstage + NB * BR);
 
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -585,7 +595,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
             for (int m = 0; m < NLD; m++) {
                 const int L = (m * S::nfw + wave) * 64 + lane;  // chunk position inside the buffer
                 const int r = L / S::cpr, pos = L % S::cpr;
-                goff[m] = (uint32_t)(min(r, kBlockRows - 1) * S::cpr + (pos ^ (r & S::swz))) * 16u;
+                goff[m] = (uint32_t)(min(r, BR - 1) * S::cpr + (pos ^ (r & S::swz))) * 16u;
             }
         } else {
 #pragma unroll
@@ -662,7 +672,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
             slot0 = __builtin_amdgcn_readfirstlane(s_item[6]);
         }
         const int nrows = row_end - row0;
-        const int nblk = (nrows + kBlockRows - 1) / kBlockRows;
+        const int nblk = (nrows + BR - 1) / BR;
         Cand* const gsel = a.slot_ent + ((size_t)slot0 + wave * WC) * (size_t)a.slot_stride;   // (GS: slot_stride = cap)
         const char* src = (const char*)a.rows + (size_t)row0 * S::rowb;
         const char* src_lo = S::planes == 2 ? (const char*)a.rows_lo + (size_t)row0 * S::rowb : src;
@@ -674,14 +684,26 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
         // direct: block blk -> buffer buf, straight from HBM; the squared norms of its rows go
         // to a place of this wave's own (each wave fetches its own copy: 64 bytes)
         const bool stream_once = !DENSE && w <= S::cw;   // the only work item that reads these rows
+        // (blocks of several groups of rows: with one 16-byte chunk for all lanes, as a short list is past its end from the start)
         auto fill_direct = [&](int blk, int buf) __attribute__((always_inline)) {
+            if (RB > 1 && blk >= nblk) {
+#pragma unroll
+                for (int m = 0; m < NLD * S::planes; m++)
+                    lds_dma16(src, 0u, lds_addr(stage) + buf * S::buf_bytes + (m / NLD) * S::plane_bytes + wave * 1024 + (m % NLD) * S::nfw * 1024);
+                if (a.l2) {
+#pragma unroll
+                    for (int j = 0; j < S::nnl; j++)
+                        if (lane_here() + 64 * j < BR) lds_dma4(a.row_norm + row0, 0u, lds_addr(nstage) + buf * (BR * 4) + 256 * j);
+                }
+                return;
+            }
             const int bl = min(blk, nblk - 1);
-            const int valid = min(nrows - bl * kBlockRows, kBlockRows);
+            const int valid = min(nrows - bl * BR, BR);
 #pragma unroll
             for (int pl = 0; pl < S::planes; pl++) {
-                const char* bsrc = (pl == 0 ? src : src_lo) + (size_t)bl * kBlockRows * S::rowb;
+                const char* bsrc = (pl == 0 ? src : src_lo) + (size_t)bl * BR * S::rowb;
                 const uint32_t dst = lds_addr(stage) + buf * S::buf_bytes + pl * S::plane_bytes + wave * 1024;
-                if (valid == kBlockRows) {
+                if (valid == BR) {
                     if (stream_once) {
 #pragma unroll
                         for (int m = 0; m < NLD; m++) lds_dma16_nt(bsrc, goff[m], dst + m * S::nfw * 1024);
@@ -701,22 +723,23 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
                     }
                 }
             }
-            // (every wave writes the same 16 norms: the same number of loads per wave; the inner
+            // (every wave writes the same norms: the same number of loads per wave; the inner
             // product needs none)
             if (a.l2) {
-                const int ln = lane_here();
-                if (ln < kBlockRows)
-                    lds_dma4(a.row_norm + row0 + bl * kBlockRows, (uint32_t)min(ln, valid - 1) * 4u,
-                             lds_addr(nstage) + buf * (kBlockRows * 4));
+#pragma unroll
+                for (int j = 0; j < S::nnl; j++) {
+                    const int ln = lane_here() + 64 * j;
+                    if (ln < BR) lds_dma4(a.row_norm + row0 + bl * BR, (uint32_t)min(ln, valid - 1) * 4u, lds_addr(nstage) + buf * (BR * 4) + 256 * j);
+                }
             }
         };
         // through registers: a ring of PF blocks in flight
         u32x4 ring[S::direct ? 1 : PF][NLD];
         float nring[S::direct ? 1 : PF];
-        auto block_chunks = [&](int blk) __attribute__((always_inline)) { return min(nrows - min(blk, nblk - 1) * kBlockRows, kBlockRows) * S::cpr; };
-        auto block_src = [&](int blk) __attribute__((always_inline)) { return src + (size_t)min(blk, nblk - 1) * kBlockRows * S::rowb; };
+        auto block_chunks = [&](int blk) __attribute__((always_inline)) { return min(nrows - min(blk, nblk - 1) * BR, BR) * S::cpr; };
+        auto block_src = [&](int blk) __attribute__((always_inline)) { return src + (size_t)min(blk, nblk - 1) * BR * S::rowb; };
         auto load_norm = [&](int blk) __attribute__((always_inline)) {
-            const int r = min(row0 + min(blk, nblk - 1) * kBlockRows + (int)(threadIdx.x & (kBlockRows - 1)), row_end - 1);
+            const int r = min(row0 + min(blk, nblk - 1) * BR + (int)(threadIdx.x & (BR - 1)), row_end - 1);
             return a.row_norm[r];
         };
 
@@ -776,7 +799,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
             // blocks still in flight, instead of draining the ring.
             __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
             stage_block<DT, S>(stage, ring[0]);
-            nstage[threadIdx.x & (kBlockRows - 1)] = nring[0];      // (same value from several threads)
+            nstage[threadIdx.x & (BR - 1)] = nring[0];      // (same value from several threads)
             static_for<PF>([&](auto pc) __attribute__((always_inline)) {
                 constexpr int slot = (decltype(pc)::value + 1) % PF;
                 load_block<S>(block_src(decltype(pc)::value + 1), block_chunks(decltype(pc)::value + 1), ring[slot], stream_once);
@@ -799,20 +822,24 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
         // step, right after the barrier.  Stores count in vmcnt like the requests for blocks,
         // and may complete in any order relative to them, so the wait at the top of a step has
         // to assume they are still outstanding; issued here they have a whole step to complete.
-        floatx4 held[NCS];
+        floatx4 held[NCS][RB];
         int held_rbase = -1;
         auto flush_keys = [&]() __attribute__((always_inline)) {
             if (held_rbase < 0) return;
 #pragma unroll
             for (int s = 0; s < NCS; s++) {
                 if (s < nact && owner && col_ok[s]) {
-                    float* out = a.key_out + (size_t)q[s] * a.dense_nrows + held_rbase;
-                    if (held_rbase + 3 < row_end && (a.dense_nrows & 3) == 0) {
-                        *(floatx4*)out = held[s];
-                    } else {
 #pragma unroll
-                        for (int r = 0; r < 4; r++)
-                            if (held_rbase + r < row_end) out[r] = held[s][r];
+                    for (int j = 0; j < RB; j++) {
+                        const int first = held_rbase + j * kMfmaRows;
+                        float* out = a.key_out + (size_t)q[s] * a.dense_nrows + first;
+                        if (first + 3 < row_end && (a.dense_nrows & 3) == 0) {
+                            *(floatx4*)out = held[s][j];
+                        } else {
+#pragma unroll
+                            for (int r = 0; r < 4; r++)
+                                if (first + r < row_end) out[r] = held[s][j][r];
+                        }
                     }
                 }
             }
@@ -820,51 +847,67 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
         };
 
         // ---- selection over the scores of one block: acc = accumulators of the block, nrm =
-        // squared norms of this lane's 4 rows, brow = first row of the block
-        auto select_block = [&](const floatx4 (&acc)[NCS][S::na], const floatx4 nrm, const int brow) __attribute__((always_inline)) {
+        // squared norms of this lane's 4 rows of every group, brow = first row of the block
+        auto select_block = [&](const floatx4 (&acc)[NCS][RB][S::na], const floatx4 (&nrm)[RB], const int brow) __attribute__((always_inline)) {
 #pragma unroll
             for (int s = 0; s < NCS; s++) {
                 if (s >= nact) break;
-                // ---- keys of this lane's 4 (row, column) pairs of set s.  The common case is
+                // ---- keys of this lane's 4 (row, column) pairs of set s in every group.  The common case is
                 // that none reaches the column's threshold: that is decided with one compare
-                // of the largest of the four (thr is +inf in lanes that own no query column).
-                float key[4];
+                // of the largest of them (thr is +inf in lanes that own no query column).
+                float keys[RB][4];
 #pragma unroll
-                for (int r = 0; r < 4; r++) {
-                    float dot;
-                    if constexpr (T::planes == 2 && QP == 2) {
-                        dot = acc[s][0][r] + (acc[s][2][r] + acc[s][1][r]) * (1.0f / 2048.0f) + acc[s][3][r] * (1.0f / 4194304.0f);
-                    } else if constexpr (QP == 2) {
-                        dot = (acc[s][0][r] + acc[s][1][r]) + (acc[s][2][r] + acc[s][3][r]);
-                    } else if constexpr (T::planes == 2) {
-                        float t0 = lane_xor8(acc[s][0][r]);      // hi rows x lo query
-                        float t1 = lane_xor8(acc[s][1][r]);      // lo rows x lo query
-                        dot = acc[s][0][r] + (t0 + acc[s][1][r]) * (1.0f / 2048.0f) + t1 * (1.0f / 4194304.0f);
-                    } else if constexpr (DT == HR_BF16) {
-                        float v = acc[s][0][r] + acc[s][1][r];
-                        dot = v + lane_xor8(v);
-                    } else {
-                        dot = acc[s][0][r] + acc[s][1][r];
+                for (int j = 0; j < RB; j++) {
+#pragma unroll
+                    for (int r = 0; r < 4; r++) {
+                        float dot;
+                        if constexpr (T::planes == 2 && QP == 2) {
+                            dot = acc[s][j][0][r] + (acc[s][j][2][r] + acc[s][j][1][r]) * (1.0f / 2048.0f) + acc[s][j][3][r] * (1.0f / 4194304.0f);
+                        } else if constexpr (QP == 2) {
+                            dot = (acc[s][j][0][r] + acc[s][j][1][r]) + (acc[s][j][2][r] + acc[s][j][3][r]);
+                        } else if constexpr (T::planes == 2) {
+                            float t0 = lane_xor8(acc[s][j][0][r]);      // hi rows x lo query
+                            float t1 = lane_xor8(acc[s][j][1][r]);      // lo rows x lo query
+                            dot = acc[s][j][0][r] + (t0 + acc[s][j][1][r]) * (1.0f / 2048.0f) + t1 * (1.0f / 4194304.0f);
+                        } else if constexpr (DT == HR_BF16) {
+                            float v = acc[s][j][0][r] + acc[s][j][1][r];
+                            dot = v + lane_xor8(v);
+                        } else {
+                            dot = acc[s][j][0][r] + acc[s][j][1][r];
+                        }
+                        keys[j][r] = dot;
                     }
-                    key[r] = dot;
-                }
-                if (a.l2) {
+                    if (a.l2) {
 #pragma unroll
-                    for (int r = 0; r < 4; r++) key[r] = 2.0f * key[r] - nrm[r];
+                        for (int r = 0; r < 4; r++) keys[j][r] = 2.0f * keys[j][r] - nrm[j][r];
+                    }
                 }
                 if (DENSE) {
                     // dense scoring only: every key goes to its place in the [query, row] table,
                     // one block late (see flush_keys)
-                    held[s] = floatx4{key[0], key[1], key[2], key[3]};
+#pragma unroll
+                    for (int j = 0; j < RB; j++) held[s][j] = floatx4{keys[j][0], keys[j][1], keys[j][2], keys[j][3]};
                     held_rbase = brow + g * 4;
                     continue;
                 }
-                const float best = fmaxf(fmaxf(key[0], key[1]), fmaxf(key[2], key[3]));
-                // ---- append what reaches the column's threshold
-                if (__builtin_amdgcn_ballot_w64(best >= thr[s]) != 0) {
+                float best = fmaxf(fmaxf(keys[0][0], keys[0][1]), fmaxf(keys[0][2], keys[0][3]));
+#pragma unroll
+                for (int j = 1; j < RB; j++) best = fmaxf(best, fmaxf(fmaxf(keys[j][0], keys[j][1]), fmaxf(keys[j][2], keys[j][3])));
+                if (__builtin_amdgcn_ballot_w64(best >= thr[s]) == 0) continue;
+                // ---- append what reaches the column's threshold, one group of 16 rows after the other
+#pragma unroll 1
+                for (int j = 0; j < RB; j++) {
+                    float key[4];
+#pragma unroll
+                    for (int r = 0; r < 4; r++) {
+                        key[r] = keys[0][r];
+#pragma unroll
+                        for (int i = 1; i < RB; i++) key[r] = j == i ? keys[i][r] : key[r];
+                    }
+                    if (RB > 1 && __builtin_amdgcn_ballot_w64(fmaxf(fmaxf(key[0], key[1]), fmaxf(key[2], key[3])) >= thr[s]) == 0) continue;
                     const int lane = lane_here();
                     const int jcol = lane & (NC - 1);
-                    const int rbase = brow + (lane >> 4) * 4;                           // first of this lane's rows
+                    const int rbase = brow + j * kMfmaRows + (lane >> 4) * 4;           // first of this lane's rows
                     const unsigned long long colmask = 0x0001000100010001ULL << jcol;   // owner lanes of my column
                     bool pass[4];
 #pragma unroll
@@ -919,8 +962,12 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
             }
         };
         int bi = 0;                                              // blk % NB
-        floatx4 accs[2][NCS][S::na];
-        floatx4 nrms[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
+        floatx4 accs[2][NCS][RB][S::na];
+        floatx4 nrms[2][RB] = {};
+        auto get_norms = [&](floatx4 (&nrm)[RB], int buf) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < RB; j++) nrm[j] = *(const floatx4*)(nstage + buf * BR + j * kMfmaRows + (lane_here() >> 4) * 4);
+        };
         // direct staging: (1) this wave's part of block blk has landed, (2) barrier: so has
         // everybody's, and nobody reads block blk-1 any more, (3) request block blk+D into the
         // buffer that one leaves, (4) multiply, (5) select
@@ -936,9 +983,9 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
             } else {
                 switch (D) {
                 case 1: wait_vmcnt<0>(); break;
-                case 2: wait_vmcnt<S::lpf - 1>(); break;
-                case 3: wait_vmcnt<2 * (S::lpf - 1)>(); break;
-                default: wait_vmcnt<3 * (S::lpf - 1)>(); break;
+                case 2: wait_vmcnt<S::lpf - S::nnl>(); break;
+                case 3: wait_vmcnt<2 * (S::lpf - S::nnl)>(); break;
+                default: wait_vmcnt<3 * (S::lpf - S::nnl)>(); break;
                 }
             }
             __builtin_amdgcn_s_barrier();
@@ -946,12 +993,12 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
             fill_direct(blk + D, bi == 0 ? NB - 1 : bi - 1);
             if (nact > 0) {
                 const char* cur = stage + bi * S::buf_bytes;
-                if (a.l2) nrms[0] = *(const floatx4*)(nstage + bi * kBlockRows + (lane_here() >> 4) * 4);
+                if (a.l2) get_norms(nrms[0], bi);
                 const char* ap[4];
                 frag_bases(ap, cur);
                 if (NCS == 2 && nact == 2) mfma_block<DT, KSTEPS, NCS, NCS, S>(ap, bfrag, accs[0]);
                 else                       mfma_block<DT, KSTEPS, NCS, 1, S>(ap, bfrag, accs[0]);
-                select_block(accs[0], nrms[0], row0 + blk * kBlockRows);
+                select_block(accs[0], nrms[0], row0 + blk * BR);
             }
             bi = bi + 1 == NB ? 0 : bi + 1;
         };
@@ -961,7 +1008,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
             // (6 buffers: the requests of the pair after the next one may still be on their way)
             if (NB != 6) wait_vmcnt<0>();
             else if (a.l2) wait_vmcnt<2 * S::lpf>();
-            else wait_vmcnt<2 * (S::lpf - 1)>();
+            else wait_vmcnt<2 * (S::lpf - S::nnl)>();
             __builtin_amdgcn_s_barrier();
             // (the requests of all waves at once keep the address unit busy for a while, and a
             // wave cannot go on before its own are accepted: half of the waves send theirs
@@ -979,8 +1026,8 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
                 const char* c0 = stage + bi * S::buf_bytes;
                 const char* c1 = c0 + S::buf_bytes;
                 if (a.l2) {
-                    nrms[0] = *(const floatx4*)(nstage + bi * kBlockRows + (lane_here() >> 4) * 4);
-                    nrms[1] = *(const floatx4*)(nstage + (bi + 1) * kBlockRows + (lane_here() >> 4) * 4);
+                    get_norms(nrms[0], bi);
+                    get_norms(nrms[1], bi + 1);
                 }
                 const char* ap0[4];
                 frag_bases(ap0, c0);
@@ -989,21 +1036,21 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
                 if constexpr (S::chain) {
                     mfma_pair<DT, KSTEPS, NCS, 1, S>(ap0, ap1, bfrag, accs[0], accs[1], [&]() __attribute__((always_inline)) {
                         if (!early) requests();
-                        select_block(accs[0], nrms[0], row0 + blk * kBlockRows);
+                        select_block(accs[0], nrms[0], row0 + blk * BR);
                     });
                 }
-                select_block(accs[1], nrms[1], row0 + (blk + 1) * kBlockRows);
+                select_block(accs[1], nrms[1], row0 + (blk + 1) * BR);
             } else {
 #pragma unroll
                 for (int h = 0; h < 2; h++) {
                     if (nact > 0 && blk + h < nblk) {
                         const char* cur = stage + (bi + h) * S::buf_bytes;
-                        if (a.l2) nrms[0] = *(const floatx4*)(nstage + (bi + h) * kBlockRows + (lane_here() >> 4) * 4);
+                        if (a.l2) get_norms(nrms[0], bi + h);
                         const char* ap[4];
                         frag_bases(ap, cur);
                         if (NCS == 2 && nact == 2) mfma_block<DT, KSTEPS, NCS, NCS, S>(ap, bfrag, accs[0]);
                         else                       mfma_block<DT, KSTEPS, NCS, 1, S>(ap, bfrag, accs[0]);
-                        select_block(accs[0], nrms[0], row0 + (blk + h) * kBlockRows);
+                        select_block(accs[0], nrms[0], row0 + (blk + h) * BR);
                     }
                     if (h == 0 && !early) requests();
                 }
@@ -1019,17 +1066,17 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
             __syncthreads();
             constexpr int pn = (p + 1) % PF;
             stage_block<DT, S>(stage + (bi ^ 1) * S::buf_bytes, ring[pn]);
-            nstage[(bi ^ 1) * kBlockRows + (threadIdx.x & (kBlockRows - 1))] = nring[pn];
+            nstage[(bi ^ 1) * BR + (threadIdx.x & (BR - 1))] = nring[pn];
             load_block<S>(block_src(blk + 1 + PF), block_chunks(blk + 1 + PF), ring[pn], stream_once);
             nring[pn] = load_norm(blk + 1 + PF);
             if (live && nact > 0) {
                 const char* cur = stage + bi * S::buf_bytes;
-                nrms[0] = *(const floatx4*)(nstage + bi * kBlockRows + (lane_here() >> 4) * 4);
+                get_norms(nrms[0], bi);
                 const char* ap[4];
                 frag_bases(ap, cur);
                 if (NCS == 2 && nact == 2) mfma_block<DT, KSTEPS, NCS, NCS, S>(ap, bfrag, accs[0]);
                 else                       mfma_block<DT, KSTEPS, NCS, 1, S>(ap, bfrag, accs[0]);
-                select_block(accs[0], nrms[0], row0 + blk * kBlockRows);
+                select_block(accs[0], nrms[0], row0 + blk * BR);
             }
             bi ^= 1;
         };

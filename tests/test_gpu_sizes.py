@@ -128,6 +128,38 @@ def test_scan_finds_the_best_rows_at_the_edges_of_query_tiles(storage, tables, d
     ix.close()
 
 
+@pytest.mark.parametrize("storage,tables", [("bf16", False), ("f32", True), ("f32", False), ("f16", False)])
+@pytest.mark.parametrize("d", [64, 128, 256])
+@pytest.mark.parametrize("nq,k,metric", [(3, 5, "l2"), (40, 20, "ip"), (150, 100, "l2")])
+def test_scan_of_lists_that_end_around_the_edges_of_blocks(storage, tables, d, nq, k, metric):
+    """Short vectors go in blocks of 16 .. 64 rows: lists of one row, and on both sides of every such block and of a few
+    of them, the last ones right at the end of the tables."""
+    dtype = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[storage]
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + nq)
+    sizes = torch.tensor([1, 15, 16, 17, 31, 32, 33, 47, 63, 64, 65, 95, 96, 97, 127, 128, 129, 255, 256, 257, 300, 1])
+    nlist, N = len(sizes), int(sizes.sum())
+    off = torch.zeros(nlist + 1, dtype=torch.int64)
+    off[1:] = torch.cumsum(sizes, 0)
+    cent = torch.randn(nlist, d, generator=g, device="cuda")
+    vec = torch.randn(N, d, generator=g, device="cuda").to(dtype)
+    ix = _hr().IvfIndex(cent, off, vec, torch.arange(N, device="cuda"), row_tables=tables)
+    q = torch.randn(nq, d, generator=g, device="cuda")
+    op = q.half().double() if storage == "bf16" and tables else _operand(q, storage)
+    key = _keys(op, vec.double(), metric)
+    for probe in (torch.arange(nlist), torch.tensor([0, 21, 9])):
+        rows = torch.cat([torch.arange(int(off[x]), int(off[x + 1])) for x in probe.tolist()]).cuda()
+        kk = min(k, len(rows))
+        found, score = ix.scan(q, probe.int().cuda().repeat(nq, 1), kk, metric)
+        best = torch.topk(key[:, rows], kk, dim=1).values
+        got = key.gather(1, found)
+        # (as above: sums of d products and norms of values near 1, in chains of at most d / 32 steps)
+        tol = 3 * d * 2.0 ** -24 * 8
+        assert float((got - best).abs().max()) <= 2 * tol
+        assert all(len(set(r)) == kk for r in found.cpu().tolist())
+    ix.close()
+
+
 @pytest.mark.parametrize("nlist,nq,nprobe,N", [(1, 1, 1, 5000), (3, 1, 3, 2000000), (3, 1365, 3, 60000), (256, 64, 16, 65536), (1000, 241, 17, 100000),
                                                (1024, 4096, 1, 40000), (1025, 1, 512, 60000), (4096, 128, 32, 100000), (4097, 128, 32, 100000),
                                                (4095, 9, 455, 50000)])
