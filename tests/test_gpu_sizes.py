@@ -306,3 +306,16 @@ def test_workspace_of_a_small_batch_is_small():
     sizes = [_hr().hr_ivf_workspace_bytes(ix.handle, n, 16, 10) for n in (1, 2, 63, 64, 65, 128, 1000, 5000)]
     assert sizes == sorted(sizes)                       # (what is enough for a batch is enough for a smaller one)
     ix.close()
+
+
+@pytest.mark.parametrize("nlist", [1, 15, 16, 17, 1023, 1024, 1025, 2049, 3000])
+def test_hot_lists_at_the_edges_of_tiles(nlist):
+    """Equal counts on both sides of every tile of counters, and lists that nobody probed."""
+    ix, *_ = _index(nlist * 2, 64, nlist, torch.float16, nlist)
+    rng = np.random.default_rng(nlist)
+    probe = torch.from_numpy(rng.integers(0, max(1, nlist - nlist // 5), (40, min(nlist, 60)))).int().cuda()
+    ix.scan(torch.zeros(40, 64, device="cuda"), probe, 1)
+    hits = torch.bincount(probe.reshape(-1).long(), minlength=nlist).cpu()
+    for gc in {1, (nlist + 1) // 2, nlist}:
+        assert torch.equal(ix.hot_lists(gc).cpu(), torch.sort(hits, descending=True, stable=True).indices[:gc].int())
+    ix.close()
