@@ -312,6 +312,50 @@ __global__ void k_bucket_count(BucketArgs a)
     a.pair_entry[i] = here ? atomicAdd(&a.list_w[l], 1) : -1;
 }
 
+// The same where a list is probed by many: a workgroup counts its pairs (2048, of large batches 8192) per list in LDS
+// first and asks for the places of all of a list's pairs at once.  Additions to one address go one after the other, 25 ns
+// each, so the most popular list decides how long the plain kernel takes.  Searches of given lists (lists of 16 rows, k 1), plain
+// and shared: 10^6 pairs of 64 lists 1820 and 682 us, of 4097 lists 792 and 737, probed as 1 / rank 1472 and 797.  The line, 16
+// pairs per list, is where evenly spread probes begin to gain: 16384 pairs of 1000 lists 95 and 97, 40000 103 and 97; 40000 of
+// 4097 251 and 254, 131072 298 and 293 (1 / rank: 249 and 224, 380 and 293).  kCountLists: the counters fit 64 KB of LDS.
+constexpr int kCountShare = 16, kCountLists = 16384;
+template <int PER>                                      // pairs per thread
+__global__ __launch_bounds__(1024) void k_bucket_count_shared(BucketArgs a)
+{
+    extern __shared__ int s_count[];                    // [nlist] pairs of the list, then the first of their places
+    const int64_t pairs = (int64_t)a.nq * a.nprobe, first = (int64_t)blockIdx.x * (PER * 1024) + threadIdx.x;
+    for (int l = threadIdx.x; l < a.nlist; l += 1024) s_count[l] = 0;
+    int pl[PER], pe[PER];                               // list of the pair (-1: none), place among the workgroup's pairs of it
+#pragma unroll
+    for (int j = 0; j < PER; j++) pl[j] = first + j * 1024 < pairs ? a.probe[first + j * 1024] : -1;
+#pragma unroll
+    for (int j = 0; j < PER; j++) {
+        const bool valid = pl[j] >= 0 && pl[j] < a.nlist;
+        const bool here = valid && a.resident[pl[j]] != 0;
+        if (valid && !here && a.hits != nullptr) atomicAdd(&a.hits[pl[j]], 1ull);       // (as in k_bucket_count)
+        if (!here) pl[j] = -1;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PER; j++) pe[j] = pl[j] >= 0 ? atomicAdd(&s_count[pl[j]], 1) : -1;
+    __syncthreads();
+    for (int l0 = threadIdx.x; l0 < a.nlist; l0 += 4096) {
+        int c[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) c[j] = l0 + j * 1024 < a.nlist ? s_count[l0 + j * 1024] : 0;
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+            if (c[j] > 0) c[j] = atomicAdd(&a.list_w[l0 + j * 1024], c[j]);
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+            if (l0 + j * 1024 < a.nlist) s_count[l0 + j * 1024] = c[j];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < PER; j++)
+        if (first + j * 1024 < pairs) a.pair_entry[first + j * 1024] = pl[j] >= 0 ? s_count[pl[j]] + pe[j] : -1;
+}
+
 // Exclusive prefix sums of N values over the 1024 threads of a workgroup (16 waves); totals returned to all.  One
 // barrier: every wave adds up the waves' sums for itself; s_wave is written by this call alone.
 template <int N>
@@ -681,7 +725,11 @@ hipError_t launch_bucketing(const BucketArgs& a, hipStream_t s)
         hipLaunchKernelGGL((k_bucket_scan<kWholeLists / 1024, true>), dim3(1), dim3(1024), 0, s, a);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_bucket_count, dim3(gp), dim3(256), 0, s, a);
+    if (pairs >= (int64_t)kCountShare * a.nlist && a.nlist <= kCountLists) {
+        if (pairs <= 131072) hipLaunchKernelGGL(k_bucket_count_shared<2>, dim3((unsigned)((pairs + 2047) / 2048)), dim3(1024), (size_t)a.nlist * 4, s, a);
+        else hipLaunchKernelGGL(k_bucket_count_shared<8>, dim3((unsigned)((pairs + 8191) / 8192)), dim3(1024), (size_t)a.nlist * 4, s, a);
+    } else
+        hipLaunchKernelGGL(k_bucket_count, dim3(gp), dim3(256), 0, s, a);
     const int per = (a.nlist + 1023) / 1024;
     if (per <= 4) hipLaunchKernelGGL((k_bucket_scan<4, false>), dim3(1), dim3(1024), 0, s, a);
     else if (per <= 16) hipLaunchKernelGGL((k_bucket_scan<16, false>), dim3(1), dim3(1024), 0, s, a);

@@ -162,10 +162,11 @@ def test_scan_of_lists_that_end_around_the_edges_of_blocks(storage, tables, d, n
 
 @pytest.mark.parametrize("nlist,nq,nprobe,N", [(1, 1, 1, 5000), (3, 1, 3, 2000000), (3, 1365, 3, 60000), (256, 64, 16, 65536), (1000, 241, 17, 100000),
                                                (1024, 4096, 1, 40000), (1025, 1, 512, 60000), (4096, 128, 32, 100000), (4097, 128, 32, 100000),
-                                               (4095, 9, 455, 50000)])
+                                               (4095, 9, 455, 50000), (64, 129, 32, 30000), (64, 3000, 48, 30000), (300, 1000, 24, 30000), (16384, 520, 510, 40000)])
 def test_grouping_keeps_every_pair_whatever_the_batch(nlist, nq, nprobe, N):
-    """Around the largest batch that one workgroup groups alone (4096 pairs, 4096 lists), with lists that are not in
-    place, probes of nothing, and one list of most of the rows; then the counters of the probes."""
+    """Around the largest batch that one workgroup groups alone (4096 pairs, 4096 lists), then with many pairs per list, up to
+    the most lists that are counted in LDS; lists that are not in place, probes of nothing, and one list of most of the
+    rows; then the counters of the probes."""
     ix, cent, off, vec, ids, g = _index(N, 64, nlist, torch.float16, nlist + nq, zipf=1.3)
     q = torch.randn(nq, 64, generator=g, device="cuda")
     probe = torch.rand(nq, nlist, generator=g, device="cuda").topk(nprobe, dim=1).indices.int()
