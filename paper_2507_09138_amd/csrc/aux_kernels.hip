@@ -773,36 +773,49 @@ hipError_t launch_state_thr(const int64_t* ids, const float* scores, const float
     return hipGetLastError();
 }
 
-constexpr int kMergeCap = 256;     // candidates buffered per query (k <= 128, up to 64 appended per step)
+constexpr int kMergeCap = 256;     // candidates buffered per wave (k <= 128, up to 64 appended per step)
 
+// W waves share the slots of a query, 64 slots at a time in turn, each with a buffer of its own; the first takes in what
+// the others kept.  Bound by a wave's chain of loads and cuts, so one wave per query is enough only where the queries
+// fill the device.  Searches with one and with four (d = 64): 40 queries over 6 of 208 lists, 624000 rows, k 83, 418 and 345 us;
+// 256 over 30 of 60 lists, 2 M rows, k 100, 782 and 674; 512 over 32 of 1024, k 10, 239 and 239.  The line: 1024 queries 705 and
+// 584, 126 and 126, 2048 999 and 886, 142 and 150, 8192 256 and 272 (sixteen waves are slower than four).
+constexpr int kMergeShare = 1024;  // most queries that get four waves each
+template <int W>
 __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
 {
-    __shared__ Cand s_buf[4][kMergeCap];
-    __shared__ int64_t s_tie[4][HR_K_MAX];
-    __shared__ int s_pref[4][HR_NPROBE_MAX + 1];
-    __shared__ int s_cnt[4];
-    __shared__ int s_first[4][64];
-    __shared__ size_t s_slot[4][64];
-    __shared__ int64_t s_ext_id[4][HR_K_MAX];
-    __shared__ float s_ext_score[4][HR_K_MAX];
-    __shared__ int s_ext_row[4][HR_K_MAX];
+    constexpr int NW = 4, Q = NW / W;                  // waves and queries of a workgroup
+    __shared__ Cand s_buf[NW][kMergeCap];
+    __shared__ int64_t s_tie[Q][HR_K_MAX];
+    __shared__ int s_pref[Q][HR_NPROBE_MAX + 1];
+    __shared__ int s_cnt[NW];
+    __shared__ uint32_t s_thr[Q];
+    __shared__ int s_total[Q];
+    __shared__ int s_first[NW][64];
+    __shared__ size_t s_slot[NW][64];
+    __shared__ int64_t s_ext_id[Q][HR_K_MAX];
+    __shared__ float s_ext_score[Q][HR_K_MAX];
+    __shared__ int s_ext_row[Q][HR_K_MAX];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t q = (int64_t)blockIdx.x * 4 + wave;
-    if (q >= a.nq) return;                       // whole wave leaves; no block barrier below
-    int64_t* ext_id = s_ext_id[wave];
-    int* ext_row = s_ext_row[wave];              // rows of the carried entries (-1: empty place or rows not carried)
-    float* ext_score = s_ext_score[wave];
+    const int own = wave / W, part = wave % W;         // query of the workgroup, place among its waves
+    const int64_t q = (int64_t)blockIdx.x * Q + own;
+    const bool live = q < a.nq;
+    if (W == 1 && !live) return;                       // (no barrier below)
+    auto together = [&]() __attribute__((always_inline)) { if (W == 1) wave_sync(); else __syncthreads(); };
+    int64_t* ext_id = s_ext_id[own];
+    int* ext_row = s_ext_row[own];               // rows of the carried entries (-1: empty place or rows not carried)
+    float* ext_score = s_ext_score[own];
     Cand* buf = s_buf[wave];
-    int64_t* tie = s_tie[wave];
-    int* pref = s_pref[wave];
+    int64_t* tie = s_tie[own];
+    int* pref = s_pref[own];
     int* first = s_first[wave];
     size_t* slot_of = s_slot[wave];
     const int k = a.k;
     const int seg_rows = a.dyn[DYN_SEG_ROWS];
 
     // ---- how many segments (= slots) does each probed list contribute
-    int total;
-    {
+    if (lane == 0) s_cnt[wave] = 0;
+    if (part == 0 && live) {
         int run = 0;
         for (int p0 = 0; p0 < a.nprobe; p0 += 64) {
             int p = p0 + lane;
@@ -814,24 +827,17 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
                     ns = (len + seg_rows - 1) / seg_rows;
                 }
             }
-            int inc = ns;                         // inclusive scan over the wave
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                int v = __shfl_up(inc, o);
-                if (lane >= o) inc += v;
-            }
+            const int inc = wave_prefix_sum(ns);
             if (p < a.nprobe) pref[p + 1] = run + inc;
-            run += __shfl(inc, 63);
+            run += __builtin_amdgcn_readlane(inc, 63);
         }
-        if (lane == 0) pref[0] = 0;
-        total = run;
+        if (lane == 0) { pref[0] = 0; s_thr[own] = 0; s_total[own] = run; }
     }
-    if (lane == 0) s_cnt[wave] = 0;
     wave_sync();
     // ---- a carried result joins as one more partial result (read whole before anything of
     // this query is written: the same arrays take the merged result)
-    const float qn0 = (a.l2 && a.qnorm) ? a.qnorm[q] : 0.f;
-    if (a.carried) {
+    const float qn0 = (live && a.l2 && a.qnorm) ? a.qnorm[q] : 0.f;
+    if (a.carried && part == 0 && live) {
         for (int j0 = 0; j0 < k; j0 += 64) {
             const int j = j0 + lane;
             const int64_t id = j < k ? a.out_ids[(size_t)q * k + j] : -1;
@@ -849,9 +855,17 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
             wave_sync();
         }
     }
+    together();
 
     uint32_t thr = 0;                              // below every encoded key
-    for (int f0 = 0; f0 < total; f0 += 64) {
+    const int total = live ? s_total[own] : 0;
+    // a full buffer is cut to the k best; the k-th of any k candidates is a bound for all waves of the query
+    auto cut = [&](Cand* b, int n) __attribute__((always_inline)) {
+        const uint32_t kth = wave_select<4>(b, n, k, a.row_ids, ext_id);
+        thr = kth > thr ? kth : thr;
+        if (W > 1 && lane == 0) atomicMax(&s_thr[own], kth);
+    };
+    for (int f0 = part * 64; f0 < total; f0 += W * 64) {
         const int f = f0 + lane;
         int c = 0;
         size_t slot = 0;
@@ -873,18 +887,14 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
         }
         // the entries of these 64 slots, 64 at a time whichever slot they sit in (a loop over the fullest slot's
         // entries would be one round trip to memory per entry: the slot of a query's own cluster holds up to k)
-        int inc = c;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            int v = __shfl_up(inc, o);
-            if (lane >= o) inc += v;
-        }
-        const int tot = __shfl(inc, 63);
+        const int inc = wave_prefix_sum(c);
+        const int tot = __builtin_amdgcn_readlane(inc, 63);
         first[lane] = inc - c;
         slot_of[lane] = slot;
         wave_sync();
         for (int e0 = 0; e0 < tot; e0 += 64) {
             const int e = e0 + lane;
+            if (W > 1) thr = max(thr, __hip_atomic_load(&s_thr[own], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
             if (e < tot) {
                 int lo = 0, hi = 64;                  // largest lane o with first[o] <= e: the slot that holds entry e
                 while (hi - lo > 1) {
@@ -905,8 +915,7 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
             wave_sync();
             int n = __builtin_amdgcn_readfirstlane(s_cnt[wave]);
             if (n > kMergeCap - 64) {
-                uint32_t kth = wave_select<4>(buf, n, k, a.row_ids, ext_id);
-                thr = kth > thr ? kth : thr;
+                cut(buf, n);
                 if (lane == 0) s_cnt[wave] = k;
                 wave_sync();
             }
@@ -916,8 +925,27 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
     wave_sync();
     int n = __builtin_amdgcn_readfirstlane(s_cnt[wave]);
     if (n > k) {
-        wave_select<4>(buf, n, k, a.row_ids, ext_id);
+        cut(buf, n);
         n = k;
+    }
+    if (W > 1) {
+        if (lane == 0) s_cnt[wave] = n;
+        __syncthreads();
+        if (part != 0 || !live) return;                // (no barrier of the workgroup below)
+        thr = max(thr, s_thr[own]);
+        for (int o = 1; o < W; o++) {
+            const int m = s_cnt[wave + o];
+            for (int e0 = 0; e0 < m; e0 += 64) {
+                const Cand cd = e0 + lane < m ? s_buf[wave + o][e0 + lane] : Cand{0u, 0u};
+                const bool take = e0 + lane < m && cd.key >= thr;
+                const unsigned long long mask = __builtin_amdgcn_ballot_w64(take);
+                if (take) buf[n + lanes_below(mask)] = cd;
+                n += __builtin_popcountll(mask);
+                wave_sync();
+                if (n > kMergeCap - 64) { cut(buf, n); n = k; }
+            }
+        }
+        if (n > k) { cut(buf, n); n = k; }
     }
     wave_sync();
 
@@ -1460,7 +1488,8 @@ hipError_t launch_rescore(const float* q, int64_t nq, int d, int dtype, const vo
 hipError_t launch_merge(const MergeArgs& a, hipStream_t s)
 {
     if (a.nq <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_merge, dim3((unsigned)((a.nq + 3) / 4)), dim3(256), 0, s, a);
+    if (a.nq <= kMergeShare) hipLaunchKernelGGL(k_merge<4>, dim3((unsigned)a.nq), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(k_merge<1>, dim3((unsigned)((a.nq + 3) / 4)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

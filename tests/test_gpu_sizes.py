@@ -320,3 +320,32 @@ def test_hot_lists_at_the_edges_of_tiles(nlist):
     for gc in {1, (nlist + 1) // 2, nlist}:
         assert torch.equal(ix.hot_lists(gc).cpu(), torch.sort(hits, descending=True, stable=True).indices[:gc].int())
     ix.close()
+
+
+@pytest.mark.parametrize("k", [1, 20, 64, 65, 128])
+@pytest.mark.parametrize("metric", ["ip", "l2"])
+def test_merge_by_one_wave_and_by_four(k, metric):
+    """1025 queries are merged by a wave each, 1024 by four: the same results, with rows that occur twice (equal keys,
+    lower label first), many segments per list, and a carried result with rows that are found again."""
+    ix, cent, off, vec, ids, g = _index(60000, 64, 7, torch.float16, k, zipf=0.8)
+    vec[30000:] = vec[:30000]
+    ix.refresh_rows(0, 60000)
+    q = torch.randn(1025, 64, generator=g, device="cuda")
+    a, sa = ix.search(q, 7, k, metric)
+    b, sb = ix.search(q[:1024], 7, k, metric)
+    assert torch.equal(a[:1024], b) and torch.equal(sa[:1024], sb)
+    op = q.half().double()
+    for i in range(0, 1025, 205):
+        best = torch.topk(_keys(op[i:i + 205], vec.double(), metric), k, dim=1).values
+        want = best if metric == "ip" else (op[i:i + 205] ** 2).sum(1, keepdim=True) - best
+        # float32 sums of 64 products (and norms) of values near 1, |q||x| + |x|^2 below 300: a few 2^-24 of that
+        assert float((sa[i:i + 205].double() - want).abs().max()) < 2e-4
+    probe = torch.rand(1025, 7, generator=g, device="cuda").topk(6, dim=1).indices.int()
+    out = []
+    for n in (1025, 1024):
+        state = ix.new_state_rows(n, k)
+        for part in (probe[:n, :3], probe[:n, 2:]):
+            ix.scan_step_rows(q[:n], part.contiguous(), state, metric)
+        out.append(state)
+    assert all(torch.equal(x[:1024], y) for x, y in zip(*out))
+    ix.close()
