@@ -349,3 +349,36 @@ def test_merge_by_one_wave_and_by_four(k, metric):
         out.append(state)
     assert all(torch.equal(x[:1024], y) for x, y in zip(*out))
     ix.close()
+
+
+@pytest.mark.parametrize("m", [1, 3, 4, 5, 16, 17, 64, 65, 128])
+@pytest.mark.parametrize("nq,d", [(5, 64), (5, 768), (1024, 128), (1025, 1024)])
+@pytest.mark.parametrize("storage,metric", [("f16", "ip"), ("bf16", "l2"), ("f32", "l2")])
+def test_rescore_whatever_the_number_of_rows(m, nq, d, storage, metric):
+    """Up to four waves per query and one, rows that are listed twice or do not exist, fewer and more places than rows."""
+    dtype = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[storage]
+    N, k = 3000, 20
+    ix, cent, off, vec, ids, g = _index(N, d, 5, dtype, m + d)
+    q = torch.randn(nq, d, generator=g, device="cuda")
+    rows = torch.randint(-1, N + 2, (nq, m), generator=g, device="cuda").int()
+    if m > 2:
+        rows[:, m // 2] = rows[:, 0]
+    found, score, at = ix.rescore(q, rows, k, metric)
+    op = _operand(q, storage)
+    r = rows.long()
+    ok = (r >= 0) & (r < N)
+    first = torch.tril((r[:, :, None] == r[:, None, :]), -1).any(2)
+    ok &= ~first
+    x = vec[r.clamp(0, N - 1)].double()
+    key = (x * op[:, None, :]).sum(2)
+    if metric == "l2":
+        key = 2 * key - (x * x).sum(2)
+    key = torch.cat([torch.where(ok, key, -float("inf")), torch.full((nq, k), -float("inf"), device="cuda", dtype=torch.float64)], 1)
+    best = torch.topk(key, k, dim=1).values
+    assert torch.equal(found >= 0, best > -float("inf")) and torch.equal(found >= 0, at >= 0)
+    assert torch.equal(torch.where(at >= 0, ids[at.clamp(min=0).long()], -1), found)
+    want = best if metric == "ip" else (op * op).sum(1, keepdim=True) - best
+    # sums of d products (and norms) of values near 1 in float32, d / 16 of them in a chain: |q||x| + |x|^2 below 3 d
+    have = found >= 0
+    assert float((score.double() - want)[have].abs().max() if have.any() else 0.0) <= 3 * d * 2.0 ** -24 * 16
+    ix.close()
