@@ -1164,7 +1164,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
                     now = __hip_atomic_load(&a.thr[qcol], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
                 int added = 0;
-                if (GS) {
+                {
                     // the entries of all columns of this wave side by side over the lanes (entry e of the
                     // wave = entry e - start[c] of column c): one load and one addition per entry, all
                     // of a pass in flight together
@@ -1185,7 +1185,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
                         const int qc = __shfl(qcol, c);
                         bool did = false;
                         if (live) {
-                            const uint32_t ek = gsel[c * a.cap + (e - start)].key;
+                            const uint32_t ek = GS ? gsel[c * a.cap + (e - start)].key : mysel[c * a.cap + (e - start)].key;
                             if (ek >= cnow) {
                                 const float key = dec_key(ek);
                                 int b = (int)fminf(fmaxf((key - cbase) * (1.0f / cwd), 0.f), (float)(kHistBins - 1));
@@ -1201,19 +1201,6 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
                             if (__builtin_amdgcn_ballot_w64(did && c == cl) != 0) gained |= 1ull << cl;
                     }
                     if (lane < WC && ((gained >> lane) & 1)) added = 1;
-                } else if (have && wd > 0.f) {
-                    const Cand* cb = mysel + lane * a.cap;
-                    const float inv = 1.0f / wd;
-                    for (int i = 0; i < n; i++) {
-                        if (cb[i].key < now) continue;
-                        const float key = dec_key(cb[i].key);
-                        int b = (int)fminf(fmaxf((key - base) * inv, 0.f), (float)(kHistBins - 1));
-                        if (hist_edge(base, wd, b) > key) b--;
-                        else if (b < kHistBins - 1 && hist_edge(base, wd, b + 1) <= key) b++;
-                        // (the returned value is used so that the additions have been performed
-                        // before the counts are read back below)
-                        if (b >= 0) added += atomicAdd(&a.hist[(size_t)qcol * kHistBins + b], 1) >= 0 ? 1 : 0;
-                    }
                 }
                 const unsigned long long todo = __builtin_amdgcn_ballot_w64(added > 0);
                 // lane i looks at bin 63 - i: the prefix sum over lanes then counts the keys
