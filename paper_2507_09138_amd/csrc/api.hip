@@ -192,7 +192,7 @@ struct Plan {
     // coarse step: centroid table scanned with all queries as one dense bucket
     int shape_c /* workgroup shape, -1 = no fit */, nbuf_c, cap_c, cw_c, cols_c, nqt_c, seg_c, nseg_c;
     // list scan
-    int shape_s, nbuf_s, cap_s, gsel_s, cw_s, item_cap, item_target;
+    int shape_s, nbuf_s, cap_s, gsel_s, cw_s, item_cap, item_target, few_items, min_rows;
     int slot_stride;                // entries per result slot of the list scan
     int slot_cap;                   // result slots: one per (list segment, query of the list's bucket)
     size_t o_zero, n_zero;          // ints cleared per call: list_w[nlist], dyn[DYN_COUNT], counters[8], ..., then
@@ -278,9 +278,19 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     p.item_target = lim.item_target;
     p.item_cap = (int)(lim.item_target + pairs / p.cw_s + (pairs < nlist ? pairs : nlist) + 8);
     int64_t slots_most = (int64_t)p.cw_s * lim.item_target + pairs;
-    // (nor has a pair more slots than the longest list has segments, whatever the batch: one query over 16 of 256 lists of
-    // 65536 rows in all, k 10: 268 MB of slots without this bound, 0.3 with it)
-    const int64_t by_length = pairs * ((ix->longest + kMinSegRows - 1) / kMinSegRows);
+    // Nor has a pair more slots than the longest list has segments, whatever the batch (one query over 16 of 256 lists of
+    // 65536 rows in all, k 10: 268 MB of slots without this bound, 1.3 with it).  Segments shorter than kMinSegRows are of
+    // min_rows rows at least, and there are at most few_items of those, and one per pair for the ragged ends.
+    // Shorter ones pay where an item takes longer to read than to start and to merge: blocks of 128 KB, vectors of 512 and more,
+    // few candidates per segment.  One request, nprobe 16, k 10: 256 lists of 256 float32 rows of d = 768 92 -> 74 us, bfloat16 of
+    // d = 1024 63 -> 55, over 2000 lists of 300 rows 67 -> 59; but 256 binary16 rows of d = 256, four requests, 54 -> 61, and k 100,
+    // 50 lists, d = 1024, 112 -> 132; and with a second round of items (segments of rows x tiles / 256 without regard to the
+    // ragged ends) 16 requests over 16 of 256 lists, d = 64, 68 -> 97.
+    p.few_items = std::min(ix->num_cus, lim.item_target);
+    p.min_rows = k <= 24 && ix->d >= 512 ? std::min(((128 << 10) / (ix->d * (ix->dtype == HR_F32 ? 4 : 2)) + 15) & ~15, kMinSegRows) : kMinSegRows;
+    if (p.min_rows < 64) p.min_rows = 64;
+    const int64_t in_short = std::min((int64_t)p.cw_s * p.few_items + pairs, pairs * ((ix->longest + p.min_rows - 1) / p.min_rows));
+    const int64_t by_length = std::max(pairs * ((ix->longest + kMinSegRows - 1) / kMinSegRows), in_short);
     if (lim.by_length && by_length < slots_most) slots_most = by_length;
     p.slot_cap = (int)slots_most;
 
@@ -625,6 +635,8 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, int64_t
     b.slot_base = (int*)(ws + p.o_slot_base);
     b.slot_cap = p.slot_cap;
     b.item_target = p.item_target;
+    b.few_items = p.few_items;
+    b.min_rows = p.min_rows;
     b.dyn = zero + ix->nlist;
     b.xq_rec = (int4*)(ws + p.o_xq);
     b.xq_count = zero + ix->nlist + DYN_COUNT + 8;

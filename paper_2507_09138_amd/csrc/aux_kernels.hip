@@ -528,6 +528,7 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketArgs a)
         cost += len * ((w + a.cw - 1) >> a.cw_log2);
         if (finer) fine += len * ((w + (a.cw >> 1) - 1) >> (a.cw_log2 - 1));
         if (w > 0) rows += len;
+        if (w > 0 && len > 0) rows += (long long)((w + a.cw - 1) >> a.cw_log2) << 32;      // (fewer than 2^31 rows: the tiles above them)
     }
     cost = wave_sum_ll(cost);
     fine = finer ? wave_sum_ll(fine) : cost;
@@ -560,7 +561,13 @@ __global__ __launch_bounds__(1024) void k_bucket_scan(BucketArgs a)
     const long long fewer = cf / 1024 < 1024 ? cf / 1024 : 1024;
     if (segll < fewer) segll = fewer;
     segll = (segll + 15) & ~15LL;
-    if (segll < kMinSegRows) segll = kMinSegRows;
+    // small batches of long vectors: shorter segments, as long as every workgroup still has one item at most (min_rows says
+    // for which, and with which figures)
+    const int tiles = (int)(r >> 32), room = a.few_items - tiles;
+    r &= 0xffffffffLL;
+    int least = kMinSegRows;
+    if (room > 0 && c < (long long)room * kMinSegRows) least = max(a.min_rows, (int)(((unsigned)c + room - 1) / (unsigned)room + 15) & ~15);
+    if (segll < least) segll = least;
     if (segll > 0x7ffffff0LL) segll = 0x7ffffff0LL;          // (a list has fewer than 2^31 rows: one segment then)
     const int seg = (int)segll;
     if (t == 0) {

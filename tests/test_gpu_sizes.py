@@ -382,3 +382,30 @@ def test_rescore_whatever_the_number_of_rows(m, nq, d, storage, metric):
     have = found >= 0
     assert float((score.double() - want)[have].abs().max() if have.any() else 0.0) <= 3 * d * 2.0 ** -24 * 16
     ix.close()
+
+
+@pytest.mark.parametrize("storage", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("d,nq,nprobe,k", [(512, 1, 7, 10), (768, 1, 40, 24), (768, 1, 3, 25), (1024, 3, 40, 1), (768, 2, 1, 10), (1024, 1, 40, 10)])
+def test_small_batches_go_in_shorter_segments(storage, d, nq, nprobe, k):
+    """Segments of a few requests: down to 128 KB of rows where every workgroup has one item at most, 256 rows beyond, for
+    short vectors and many neighbours; the best rows against float64."""
+    dtype = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[storage]
+    ix, cent, off, vec, ids, g = _index(30000, d, 40, dtype, nq + d, zipf=1.0)
+    q = torch.randn(nq, d, generator=g, device="cuda")
+    probe = torch.rand(nq, 40, generator=g, device="cuda").topk(nprobe, dim=1).indices.int()
+    found, score = ix.scan(q, probe, k, "ip")
+    torch.cuda.synchronize()
+    ws = ix.workspace(nq, nprobe, k)
+    seg = _hr().hr_ivf_stats(ix.handle, ws, ws.numel(), nq, nprobe, k)["seg_rows"]
+    least = max(64, ((128 << 10) // (d * (4 if storage == "f32" else 2)) + 15) // 16 * 16)
+    assert seg >= (least if k <= 24 else 256) and seg % 16 == 0 and (nq * nprobe > 7 or k > 24 or seg < 256)
+    of_row = torch.repeat_interleave(torch.arange(40), off[1:] - off[:-1]).cuda()
+    allowed = torch.zeros(nq, 40, dtype=torch.bool, device="cuda").scatter_(1, probe.long(), True)
+    key = torch.where(allowed[:, of_row], _keys(_operand(q, storage), vec.double(), "ip"), -float("inf"))
+    row = torch.empty_like(ids)
+    row[ids] = torch.arange(len(ids), device="cuda")
+    best = torch.topk(key, k, dim=1).values
+    # float32 sums of d products of values near 1 in chains of at most d / 32 steps: |q||x| below 1.5 d
+    assert float((key.gather(1, row[found]) - best).abs().max()) <= 1.5 * d * 2.0 ** -24 * 16
+    assert float((score.double() - best).abs().max()) <= 1.5 * d * 2.0 ** -24 * 16
+    ix.close()
