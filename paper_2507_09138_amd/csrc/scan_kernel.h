@@ -605,52 +605,57 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
         }
     }
 
-    for (;;) {
-        // ---- the next item.  The first one is the workgroup's place in the order: 256 workgroups asking eight counters
-        // at once are served one after the other, 25 ns each and eight counters per workgroup that finds none.  Later ones
-        // are asked for: in the own XCD's queue first (its items share list segments through this XCD's L2), then, once
-        // that is empty, wherever a look at all eight heads together finds some left (heads only grow, so an empty queue
-        // stays empty).  A queue entry is the whole record of the item.  (Every workgroup asking every counter, one after the
-        // other: one request over 16 of 256 lists 111.3 us, now 70.3; 64 requests 200.5, 140.8; 512 requests, 32 of 4096
-        // lists, 1162, 1091; the end of the largest batches is no shorter.)
-        if (wave == 0) {
-            const int lane = lane_now();
-            int item = -1;
-            if (DENSE) {
-                if (!started) item = blockIdx.x;
-                else if (lane == 0 && (int)gridDim.x < a.dense_items) item = gridDim.x + atomicAdd(a.work_counter, 1);
-                if (item >= a.dense_items) item = -1;
-            } else {
-                const int lx = lane & 7;
-                int x = myx, pos = started ? 0x7fffffff : (int)(blockIdx.x >> 3), count = 0;
-                if (!started || own) {
-                    if (started) {
-                        if (lane == 0) pos = given_items(x) + atomicAdd(&a.xq_head[x], 1);
-                        pos = __builtin_amdgcn_readfirstlane(pos);
-                    }
-                    count = a.xq_count[x];
-                }
-                while (pos >= count) {
-                    own = false;
-                    const int head = __hip_atomic_load(&a.xq_head[lx], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    const int all = a.xq_count[lx];
-                    const uint32_t left = (uint32_t)__builtin_amdgcn_ballot_w64(given_items(lx) + head < all) & 255u;
-                    if (left == 0) { x = -1; break; }
-                    x = (myx + __builtin_ctz(left >> myx | left << (8 - myx))) & 7;
+    // ---- the next item.  The first one is the workgroup's place in the order: 256 workgroups asking eight counters
+    // at once are served one after the other, 25 ns each and eight counters per workgroup that finds none.  Later ones
+    // are asked for: in the own XCD's queue first (its items share list segments through this XCD's L2), then, once
+    // that is empty, wherever a look at all eight heads together finds some left (heads only grow, so an empty queue
+    // stays empty).  A queue entry is the whole record of the item.  (Every workgroup asking every counter, one after the
+    // other: one request over 16 of 256 lists 111.3 us, now 70.3; 64 requests 200.5, 140.8; 512 requests, 32 of 4096
+    // lists, 1162, 1091; the end of the largest batches is no shorter.)
+    // The last wave asks, as soon as the blocks are done: its columns are the first to be empty, so that the two round
+    // trips run while other waves hand over their results (the first wave after the barrier, waiting for its own stores
+    // as well: searches of 55 .. 230 us 1 .. 2 % longer).  With many neighbours the handing over takes so long that an item
+    // taken before it is missed elsewhere at the end (k 100, 500 queries, 200 lists, 308 -> 328 us): there after the barrier.
+    auto next_item = [&]() __attribute__((always_inline)) {
+        const int lane = lane_now();
+        int item = -1;
+        if (DENSE) {
+            if (!started) item = blockIdx.x;
+            else if (lane == 0 && (int)gridDim.x < a.dense_items) item = gridDim.x + atomicAdd(a.work_counter, 1);
+            if (item >= a.dense_items) item = -1;
+        } else {
+            const int lx = lane & 7;
+            int x = myx, pos = started ? 0x7fffffff : (int)(blockIdx.x >> 3), count = 0;
+            if (!started || own) {
+                if (started) {
                     if (lane == 0) pos = given_items(x) + atomicAdd(&a.xq_head[x], 1);
                     pos = __builtin_amdgcn_readfirstlane(pos);
-                    count = __builtin_amdgcn_readlane(all, x);
                 }
-                if (x >= 0) {
-                    const int* rec = (const int*)(a.xq_rec + ((size_t)x * a.xq_stride + pos) * 2);
-                    if (lane < 6) s_item[1 + lane] = rec[lane];
-                    item = 0;
-                }
+                count = a.xq_count[x];
             }
-            if (lane == 0) s_item[0] = item;
+            while (pos >= count) {
+                own = false;
+                const int head = __hip_atomic_load(&a.xq_head[lx], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const int all = a.xq_count[lx];
+                const uint32_t left = (uint32_t)__builtin_amdgcn_ballot_w64(given_items(lx) + head < all) & 255u;
+                if (left == 0) { x = -1; break; }
+                x = (myx + __builtin_ctz(left >> myx | left << (8 - myx))) & 7;
+                if (lane == 0) pos = given_items(x) + atomicAdd(&a.xq_head[x], 1);
+                pos = __builtin_amdgcn_readfirstlane(pos);
+                count = __builtin_amdgcn_readlane(all, x);
+            }
+            if (x >= 0) {
+                const int* rec = (const int*)(a.xq_rec + ((size_t)x * a.xq_stride + pos) * 2);
+                if (lane < 6) s_item[1 + lane] = rec[lane];
+                item = 0;
+            }
         }
+        if (lane == 0) s_item[0] = item;
         started = true;
-        __syncthreads();
+    };
+    if (wave == NW - 1) next_item();
+    __syncthreads();
+    for (;;) {
         const int item = __builtin_amdgcn_readfirstlane(s_item[0]);
         if (item < 0) break;
 
@@ -1094,6 +1099,9 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
                 static_for<PF>([&](auto pc) __attribute__((always_inline)) { step_regs(b0 + decltype(pc)::value, pc); });
         }
 
+        // (everybody has read this item's record: that was before the barrier of the first block)
+        const bool early_next = DENSE || a.k <= 24;
+        if (early_next && wave == NW - 1) next_item();
         if (DENSE) flush_keys();
         // ---- hand what is left to the item's slots: columns with more entries than a slot holds
         // (slot_stride: k, or the whole buffer for small k, when nothing has to be cut) are cut
@@ -1229,6 +1237,10 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
             }
         }
         __syncthreads();
+        if (!early_next) {
+            if (wave == NW - 1) next_item();
+            __syncthreads();
+        }
     }
 }
 
