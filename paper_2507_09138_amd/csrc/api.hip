@@ -561,26 +561,37 @@ static int scan_grid(const hr_ivf_index* ix, size_t lds, int shape)
 
 // query operands for the coarse step (coarse) and / or the list scan (scan), and, in the same launch, what the
 // call needs cleared in its workspace
-static int enqueue_prep(const hr_ivf_index* ix, const Plan& p, char* ws, const float* queries, int64_t nq, bool coarse,
-                        bool scan, hipStream_t s)
+static PrepArgs prep_args(const hr_ivf_index* ix, const Plan& p, char* ws, const float* queries, int64_t nq, bool coarse, bool scan)
 {
     const int od = operand_dtype(ix);
     const bool f32 = od == HR_F32;             // the scan multiplies the operand of the coarse step
-    HR_HIP(launch_prep_queries(queries, nq, ix->d, scan ? od : (int)HR_F32, (coarse || (scan && f32)) ? ws + p.o_qop_c : nullptr,
-                               coarse ? (float*)(ws + p.o_qnorm_c) : nullptr, (scan && !f32) ? ws + p.o_qop_s : nullptr,
-                               scan ? (float*)(ws + p.o_qnorm_s) : nullptr, (int*)(ws + p.o_zero), (int64_t)p.n_zero,
-                               (int*)(ws + p.o_thr), nq * 2, (int)kKeyNegInf, s));
-    return HR_OK;
+    PrepArgs a{};
+    a.q = queries; a.nq = nq; a.d = ix->d; a.dtype = scan ? od : (int)HR_F32;
+    a.qop_coarse = (coarse || (scan && f32)) ? (_Float16*)(ws + p.o_qop_c) : nullptr;
+    a.qnorm_coarse = coarse ? (float*)(ws + p.o_qnorm_c) : nullptr;
+    a.qop_scan = (scan && !f32) ? ws + p.o_qop_s : nullptr;
+    a.qnorm_scan = scan ? (float*)(ws + p.o_qnorm_s) : nullptr;
+    a.zero = (int*)(ws + p.o_zero); a.n_zero = (int64_t)p.n_zero;
+    a.neg = (int*)(ws + p.o_thr); a.n_neg = nq * 2; a.neg_value = (int)kKeyNegInf;
+    return a;
 }
 
 // coarse scoring + top-nprobe: the scan kernel over the centroid table writes every key of a
-// chunk of queries, then one wave per query picks the nprobe best
-static int enqueue_coarse(const hr_ivf_index* ix, const Plan& p, char* ws, int64_t nq, int nprobe,
-                          int metric, int32_t* out_probe, float* out_scores, hipStream_t s)
+// chunk of queries, then one wave per query picks the nprobe best.  The queries are prepared here too, for the list scan as
+// well if one follows (scan): in a launch of their own before the scoring, or, where the scoring splits them while it
+// loads them, with the selection.  One launch less: 64 lists, d = 64, 300 queries 1.09 times as fast in the mean of list and probe
+// counts, d = 768 1.12; longer vectors have no registers to split in (d = 1024, 64 queries, 22.4 -> 25.7 us) and a few
+// queries of d = 768 wait longer for their rows than the launch takes (0.94 .. 1.2).  The scoring must not need the cleared work
+// counter (one item per workgroup), and its loads want 16-byte addresses.
+static int enqueue_coarse(const hr_ivf_index* ix, const Plan& p, char* ws, const float* queries, int64_t nq, int nprobe,
+                          int metric, bool scan, int32_t* out_probe, float* out_scores, hipStream_t s)
 {
     if (p.shape_c < 0)
         return fail(HR_ERR_UNSUPPORTED, "coarse step does not fit in LDS (d=%d)", ix->d);
     const size_t lds = scan_lds_bytes(HR_F16X2, ix->d, 0, p.shape_c, p.nbuf_c);
+    const bool ride = (ix->d <= 512 || (ix->d <= 768 && nq > 16)) && nq <= p.cchunk && (int64_t)p.nseg_c * p.nqt_c <= scan_grid(ix, lds, p.shape_c) && (uintptr_t)queries % 16 == 0;
+    const PrepArgs prep = prep_args(ix, p, ws, queries, nq, !ride, scan);
+    if (!ride) HR_HIP(launch_prep_queries(prep, s));
     int* zero = (int*)(ws + p.o_zero);
     float* ckeys = (float*)(ws + p.o_ckeys);
     for (int64_t q0 = 0; q0 < nq; q0 += p.cchunk) {
@@ -591,6 +602,7 @@ static int enqueue_coarse(const hr_ivf_index* ix, const Plan& p, char* ws, int64
         a.rows_lo = ix->d_cent_lo;
         a.row_norm = ix->d_cent_norm;
         a.qop = ws + p.o_qop_c + (size_t)q0 * 2 * ix->d * 2;
+        a.queries = ride ? queries : nullptr;
         a.thr = (uint32_t*)(ws + p.o_thr);
         a.work_counter = zero + ix->nlist + DYN_COUNT;
         a.dense_items = p.nseg_c * nqt;
@@ -607,7 +619,7 @@ static int enqueue_coarse(const hr_ivf_index* ix, const Plan& p, char* ws, int64
         HR_HIP(launch_scan(HR_F16X2, ix->d, a, p.shape_c, grid, lds, s));
         HR_HIP(launch_topk_rows(ckeys, (const float*)(ws + p.o_qnorm_c) + q0, out_probe + q0 * nprobe,
                                 out_scores ? out_scores + q0 * nprobe : nullptr, n, (int)ix->nlist, nprobe,
-                                a.l2, s));
+                                a.l2, ride ? &prep : nullptr, s));
     }
     return HR_OK;
 }
@@ -721,9 +733,8 @@ int hr_ivf_search(const hr_ivf_index* ix, const float* queries, int64_t nq, int3
     if (int rc = check_ws(p, workspace, workspace_bytes)) return rc;
     char* ws = (char*)workspace;
     hipStream_t s = (hipStream_t)stream;
-    if (int rc = enqueue_prep(ix, p, ws, queries, nq, true, true, s)) return rc;
     int32_t* probe = (int32_t*)(ws + p.o_probe);
-    if (int rc = enqueue_coarse(ix, p, ws, nq, nprobe, metric, probe, nullptr, s)) return rc;
+    if (int rc = enqueue_coarse(ix, p, ws, queries, nq, nprobe, metric, true, probe, nullptr, s)) return rc;
     return enqueue_scan(ix, p, ws, nq, probe, nprobe, k, metric, out_ids, out_scores, s);
 }
 
@@ -769,9 +780,8 @@ int hr_ivf_search_static(const hr_ivf_index* ix, const float* queries, int64_t n
                                       "use hr_ivf_search with a workspace", (long long)nq, nprobe, k, p.total, (size_t)HR_STATIC_SCRATCH_BYTES);
     char* ws = (char*)ix->scratch;
     hipStream_t s = (hipStream_t)stream;
-    if (int rc = enqueue_prep(ix, p, ws, queries, nq, true, true, s)) return rc;
     int32_t* probe = (int32_t*)(ws + p.o_probe);
-    if (int rc = enqueue_coarse(ix, p, ws, nq, nprobe, metric, probe, nullptr, s)) return rc;
+    if (int rc = enqueue_coarse(ix, p, ws, queries, nq, nprobe, metric, true, probe, nullptr, s)) return rc;
     return enqueue_scan(ix, p, ws, nq, probe, nprobe, k, metric, out_ids, out_scores, s);
 }
 
@@ -787,8 +797,7 @@ int hr_ivf_coarse(const hr_ivf_index* ix, const float* queries, int64_t nq, int3
     if (int rc = check_ws(p, workspace, workspace_bytes)) return rc;
     char* ws = (char*)workspace;
     hipStream_t s = (hipStream_t)stream;
-    if (int rc = enqueue_prep(ix, p, ws, queries, nq, true, false, s)) return rc;
-    return enqueue_coarse(ix, p, ws, nq, nprobe, metric, out_probe_ids, out_probe_scores, s);
+    return enqueue_coarse(ix, p, ws, queries, nq, nprobe, metric, false, out_probe_ids, out_probe_scores, s);
 }
 
 int hr_ivf_scan(const hr_ivf_index* ix, const float* queries, int64_t nq, const int32_t* probe_ids,
@@ -805,7 +814,7 @@ int hr_ivf_scan(const hr_ivf_index* ix, const float* queries, int64_t nq, const 
     if (int rc = check_ws(p, workspace, workspace_bytes)) return rc;
     char* ws = (char*)workspace;
     hipStream_t s = (hipStream_t)stream;
-    if (int rc = enqueue_prep(ix, p, ws, queries, nq, false, true, s)) return rc;
+    HR_HIP(launch_prep_queries(prep_args(ix, p, ws, queries, nq, false, true), s));
     return enqueue_scan(ix, p, ws, nq, probe_ids, nprobe, k, metric, out_ids, out_scores, s);
 }
 
@@ -823,7 +832,7 @@ static int scan_step(const hr_ivf_index* ix, const float* queries, int64_t nq, c
     if (int rc = check_ws(p, workspace, workspace_bytes)) return rc;
     char* ws = (char*)workspace;
     hipStream_t s = (hipStream_t)stream;
-    if (int rc = enqueue_prep(ix, p, ws, queries, nq, false, true, s)) return rc;
+    HR_HIP(launch_prep_queries(prep_args(ix, p, ws, queries, nq, false, true), s));
     return enqueue_scan(ix, p, ws, nq, probe_ids, nprobe, k, metric, io_ids, io_scores, s, true, io_rows);
 }
 

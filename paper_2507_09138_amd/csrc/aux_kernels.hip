@@ -243,55 +243,70 @@ hipError_t launch_row_norms(const void* rows, int dtype, int64_t nrows, int d, f
 // so that the expanded L2 form cancels consistently.  One wave per query.
 // The same launch clears what a call needs cleared in its workspace (counters, histograms: zero; the per-query
 // lower bounds: the key of -inf): one small launch less in front of every search.
-__global__ __launch_bounds__(256) void k_prep_queries(const float* q, int64_t nq, int d, int dtype,
-                                                      _Float16* qc, float* qnorm_c, void* qs, float* qnorm_s,
-                                                      int* zero, int64_t n_zero, int* neg, int64_t n_neg, int neg_value)
+__device__ __forceinline__ float prep_query(const PrepArgs& a, int64_t row, int lane)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_zero; i += (int64_t)gridDim.x * blockDim.x) zero[i] = 0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_neg; i += (int64_t)gridDim.x * blockDim.x) neg[i] = neg_value;
-    int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= nq) return;
-    int lane = threadIdx.x & 63;
-    const float* p = q + row * d;
+    const int d = a.d;
+    const float* p = a.q + row * d;
     float n32 = 0.f, ns = 0.f;
-    for (int i = lane; i < d; i += 64) {
-        float x = p[i];
-        n32 += x * x;
-        if (qc) {
-            _Float16 h = (_Float16)x;
-            qc[(row * 2) * d + i] = h;
-            qc[(row * 2 + 1) * d + i] = (_Float16)((x - (float)h) * 2048.0f);
-        }
-        if (qs) {
-            if (dtype == HR_F16) {
+    // (four loads in flight: waiting for each would be twelve round trips at d = 768)
+    for (int i0 = lane; i0 < d; i0 += 256) {
+        float v[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) v[j] = i0 + j * 64 < d ? p[i0 + j * 64] : 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const int i = i0 + j * 64;
+            if (i >= d) break;
+            const float x = v[j];
+            n32 += x * x;
+            if (a.qop_coarse) {
                 _Float16 h = (_Float16)x;
-                ((_Float16*)qs)[row * d + i] = h;
-                ns += (float)h * (float)h;
-            } else if (dtype == HR_BF16) {
-                uint16_t hi = bf16_rne(x);
-                uint16_t lo = bf16_rne(x - bf16_to_f32(hi));
-                ((uint16_t*)qs)[(row * 2) * d + i] = hi;
-                ((uint16_t*)qs)[(row * 2 + 1) * d + i] = lo;
-                float e = bf16_to_f32(hi) + bf16_to_f32(lo);
-                ns += e * e;
+                a.qop_coarse[(row * 2) * d + i] = h;
+                a.qop_coarse[(row * 2 + 1) * d + i] = (_Float16)((x - (float)h) * 2048.0f);
+            }
+            if (a.qop_scan) {
+                if (a.dtype == HR_F16) {
+                    _Float16 h = (_Float16)x;
+                    ((_Float16*)a.qop_scan)[row * d + i] = h;
+                    ns += (float)h * (float)h;
+                } else if (a.dtype == HR_BF16) {
+                    uint16_t hi = bf16_rne(x);
+                    uint16_t lo = bf16_rne(x - bf16_to_f32(hi));
+                    ((uint16_t*)a.qop_scan)[(row * 2) * d + i] = hi;
+                    ((uint16_t*)a.qop_scan)[(row * 2 + 1) * d + i] = lo;
+                    float e = bf16_to_f32(hi) + bf16_to_f32(lo);
+                    ns += e * e;
+                }
             }
         }
     }
     n32 = wave_sum(n32);
     ns = wave_sum(ns);
     if (lane == 0) {
-        if (qnorm_c) qnorm_c[row] = n32;
-        if (qnorm_s) qnorm_s[row] = (dtype == HR_F32) ? n32 : ns;
+        if (a.qnorm_coarse) a.qnorm_coarse[row] = n32;
+        if (a.qnorm_scan) a.qnorm_scan[row] = (a.dtype == HR_F32) ? n32 : ns;
     }
+    return n32;
 }
 
-hipError_t launch_prep_queries(const float* q, int64_t nq, int d, int dtype, void* qop_coarse,
-                               float* qnorm_coarse, void* qop_scan, float* qnorm_scan,
-                               int* zero, int64_t n_zero, int* neg, int64_t n_neg, int neg_value, hipStream_t s)
+// what a call needs cleared, shared out over the threads of a launch
+__device__ __forceinline__ void prep_clear(const PrepArgs& a)
 {
-    if (nq <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_prep_queries, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, s, q, nq, d, dtype,
-                       (_Float16*)qop_coarse, qnorm_coarse, qop_scan, qnorm_scan, zero, n_zero, neg, n_neg, neg_value);
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n_zero; i += (int64_t)gridDim.x * blockDim.x) a.zero[i] = 0;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.n_neg; i += (int64_t)gridDim.x * blockDim.x) a.neg[i] = a.neg_value;
+}
+
+__global__ __launch_bounds__(256) void k_prep_queries(PrepArgs a)
+{
+    prep_clear(a);
+    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (row < a.nq) prep_query(a, row, threadIdx.x & 63);
+}
+
+hipError_t launch_prep_queries(const PrepArgs& a, hipStream_t s)
+{
+    if (a.nq <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_prep_queries, dim3((unsigned)((a.nq + 3) / 4)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
@@ -1010,8 +1025,11 @@ struct TopkArgs {
     float* out_scores;          // [nq, k] or nullptr
     int nq, n, k, l2;
     TopkSample sample;          // (computed on the host: its square root and divisions cost each wave a microsecond)
+    PrepArgs prep;              // PREP: what k_prep_queries would have done
 };
 
+// PREP: the preparation of the queries rides on this launch (the dense scoring before it took the queries as they are)
+template <bool PREP>
 __global__ __launch_bounds__(256, 4) void k_topk_rows(TopkArgs a)
 {
     constexpr int kCollect = kTopkCollect;          // entries one wave can collect in LDS
@@ -1020,7 +1038,10 @@ __global__ __launch_bounds__(256, 4) void k_topk_rows(TopkArgs a)
     __shared__ Cand s_ent[4][kCollect];
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     const int64_t q = (int64_t)blockIdx.x * 4 + wave;
+    if (PREP) prep_clear(a.prep);
     if (q >= a.nq) return;
+    float norm = 0.f;
+    if (PREP) norm = prep_query(a.prep, q, lane);
     const float* row = a.keys + (size_t)q * a.n;
     int* hist = s_hist[wave];
     Cand* ent = s_ent[wave];
@@ -1212,7 +1233,7 @@ __global__ __launch_bounds__(256, 4) void k_topk_rows(TopkArgs a)
     }
     wave_sync();
     // order: key descending, index ascending (rank of every entry = entries ahead of it)
-    const float qn = (a.l2 && a.qnorm) ? a.qnorm[q] : 0.f;
+    const float qn = !a.l2 ? 0.f : (PREP ? norm : a.qnorm ? a.qnorm[q] : 0.f);
     auto emit = [&](auto per) __attribute__((always_inline)) {
         constexpr int PER = decltype(per)::value;       // entries per lane
         uint64_t e[PER];                                // key, then the complement of the row: the larger is ahead
@@ -1254,11 +1275,12 @@ __global__ __launch_bounds__(256, 4) void k_topk_rows(TopkArgs a)
 }
 
 hipError_t launch_topk_rows(const float* keys, const float* qnorm, int32_t* out_ids, float* out_scores,
-                            int64_t nq, int n, int k, int l2, hipStream_t s)
+                            int64_t nq, int n, int k, int l2, const PrepArgs* prep, hipStream_t s)
 {
     if (nq <= 0) return hipSuccess;
-    TopkArgs a{keys, qnorm, out_ids, out_scores, (int)nq, n, k, l2, topk_sample(n, k < n ? k : n)};
-    hipLaunchKernelGGL(k_topk_rows, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, s, a);
+    TopkArgs a{keys, qnorm, out_ids, out_scores, (int)nq, n, k, l2, topk_sample(n, k < n ? k : n), prep ? *prep : PrepArgs{}};
+    if (prep) hipLaunchKernelGGL(k_topk_rows<true>, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(k_topk_rows<false>, dim3((unsigned)((nq + 3) / 4)), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

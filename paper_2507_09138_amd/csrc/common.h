@@ -136,6 +136,7 @@ struct ScanArgs {
     const float* row_norm;      // [nrows] squared norms (used when l2 != 0)
     const int64_t* row_ids;     // [nrows] labels, or nullptr: label = row number
     const void* qop;            // query operand rows (layout depends on dtype)
+    const float* queries;       // dense mode: the queries as they are, split while they are loaded (or nullptr: qop)
     uint32_t* thr;              // [nq] running per-query lower bound of the k-th key (enc_key)
     int* slot_cnt;              // [slots]: one slot per (list segment, query of the list's bucket)
     Cand* slot_ent;             // [slots * slot_stride]
@@ -202,13 +203,22 @@ struct MergeArgs {
 hipError_t launch_scan(int dtype, int d, const ScanArgs& a, int shape, int grid, size_t lds_bytes, hipStream_t s);
 size_t scan_lds_bytes(int dtype, int d, int cap, int shape, int nbuf);
 hipError_t launch_merge(const MergeArgs& a, hipStream_t s);
+struct PrepArgs {
+    const float* q;             // [nq, d]
+    _Float16* qop_coarse;       // hi and scaled lo rows, or nullptr
+    float* qnorm_coarse;        // or nullptr
+    void* qop_scan;             // operand of the list scan, where that is not the coarse step's, or nullptr
+    float* qnorm_scan;          // or nullptr
+    int* zero;                  // [n_zero] set to 0
+    int* neg;                   // [n_neg] set to neg_value
+    int64_t nq, n_zero, n_neg;
+    int d, dtype, neg_value;    // dtype: form of the list scan's operand
+};
 hipError_t launch_topk_rows(const float* keys, const float* qnorm, int32_t* out_ids, float* out_scores,
-                            int64_t nq, int n, int k, int l2, hipStream_t s);
+                            int64_t nq, int n, int k, int l2, const PrepArgs* prep, hipStream_t s);
 hipError_t launch_seed(int dtype, int d, const SeedArgs& a, hipStream_t s);
 hipError_t launch_row_norms(const void* rows, int dtype, int64_t nrows, int d, float* out, hipStream_t s);
-hipError_t launch_prep_queries(const float* q, int64_t nq, int d, int dtype, void* qop_coarse,
-                               float* qnorm_coarse, void* qop_scan, float* qnorm_scan,
-                               int* zero, int64_t n_zero, int* neg, int64_t n_neg, int neg_value, hipStream_t s);
+hipError_t launch_prep_queries(const PrepArgs& a, hipStream_t s);
 hipError_t launch_fill_i32(int* p, int64_t n, int v, hipStream_t s);
 hipError_t launch_hot_lists(const unsigned long long* hits, int nlist, int gc, int32_t* out, hipStream_t s);
 hipError_t launch_read_hits(unsigned long long* hits, int64_t n, int64_t* out, int reset, hipStream_t s);

@@ -774,15 +774,38 @@ __global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
         }
 #pragma unroll
         for (int s = 0; s < NCS; s++) {
-            const size_t qrow = (NC == 8) ? ((size_t)q[s] * 2 + part) : (size_t)q[s] * QP;
+            if (DENSE && a.queries != nullptr) {
+                // (the same split as k_prep_queries makes; DENSE is HR_F16X2: hi and lo, in two operands or two columns)
+                const float* qp = a.queries + (size_t)q[s] * S::d + g * 8;
 #pragma unroll
-            for (int h = 0; h < QP; h++) {
-                const char* qp = (const char*)a.qop + (qrow + h) * (size_t)(S::d * 2) + g * 16;
+                for (int t = 0; t < KSTEPS; t++) {
+                    const floatx4 x0 = *(const floatx4*)(qp + t * 32), x1 = *(const floatx4*)(qp + t * 32 + 4);
+                    half8 hi, lo;
 #pragma unroll
-                for (int t = 0; t < KSTEPS; t++)
-                    bfrag[s * QP + h][t] = col_ok[s] ? *(const u32x4*)(qp + t * 64) : u32x4{0, 0, 0, 0};
+                    for (int i = 0; i < 8; i++) {
+                        const float x = i < 4 ? x0[i & 3] : x1[i & 3];
+                        hi[i] = (_Float16)x;
+                        lo[i] = (_Float16)((x - (float)hi[i]) * 2048.0f);
+                    }
+                    const u32x4 none = {0, 0, 0, 0};
+                    if constexpr (QP == 2) {
+                        bfrag[s * QP][t] = col_ok[s] ? __builtin_bit_cast(u32x4, hi) : none;
+                        bfrag[s * QP + QP - 1][t] = col_ok[s] ? __builtin_bit_cast(u32x4, lo) : none;
+                    } else {
+                        bfrag[s * QP][t] = col_ok[s] ? (part == 0 ? __builtin_bit_cast(u32x4, hi) : __builtin_bit_cast(u32x4, lo)) : none;
+                    }
+                }
+            } else {
+                const size_t qrow = (NC == 8) ? ((size_t)q[s] * 2 + part) : (size_t)q[s] * QP;
+#pragma unroll
+                for (int h = 0; h < QP; h++) {
+                    const char* qp = (const char*)a.qop + (qrow + h) * (size_t)(S::d * 2) + g * 16;
+#pragma unroll
+                    for (int t = 0; t < KSTEPS; t++)
+                        bfrag[s * QP + h][t] = col_ok[s] ? *(const u32x4*)(qp + t * 64) : u32x4{0, 0, 0, 0};
+                }
             }
-            thr[s] = (owner && col_ok[s]) ? dec_key(a.thr[q[s]]) : __builtin_inff();
+            thr[s] = (!DENSE && owner && col_ok[s]) ? dec_key(a.thr[q[s]]) : __builtin_inff();
         }
         // candidates buffered per column: kept in a register by every lane of the column (the
         // lanes of a column see the same ballots, so they stay in step without LDS traffic)

@@ -409,3 +409,29 @@ def test_small_batches_go_in_shorter_segments(storage, d, nq, nprobe, k):
     assert float((key.gather(1, row[found]) - best).abs().max()) <= 1.5 * d * 2.0 ** -24 * 16
     assert float((score.double() - best).abs().max()) <= 1.5 * d * 2.0 ** -24 * 16
     ix.close()
+
+
+@pytest.mark.parametrize("storage", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("d,nq", [(64, 1), (512, 3), (768, 16), (768, 17), (768, 300), (1024, 20), (128, 3000)])
+@pytest.mark.parametrize("metric", ["ip", "l2"])
+def test_queries_prepared_with_the_selection_or_before_the_scoring(storage, d, nq, metric):
+    """Queries at a 16-byte address and behind one (which the scoring does not load by itself): the same bits, from the
+    coarse step alone and from the whole search."""
+    dtype = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[storage]
+    ix, cent, off, vec, ids, g = _index(4000, d, 70, dtype, nq + d)
+    flat = torch.zeros(nq * d + 8, device="cuda")
+    flat[:nq * d] = torch.randn(nq * d, generator=g, device="cuda")
+    q = flat[:nq * d].view(nq, d).clone()
+    flat[1:nq * d + 1] = q.reshape(-1)
+    behind = flat[1:nq * d + 1].view(nq, d)
+    assert q.data_ptr() % 16 == 0 and behind.data_ptr() % 16 == 4 and behind.is_contiguous()
+    for run in (lambda x: ix.coarse(x, 9, metric), lambda x: ix.search(x, 9, 12, metric)):
+        for a, b in zip(run(q), run(behind)):
+            assert torch.equal(a, b)
+    probe, score = ix.coarse(q, 9, metric)
+    key = _keys(q.double(), cent.double(), metric)
+    best = torch.topk(key, 9, dim=1).values
+    want = best if metric == "ip" else (q.double() ** 2).sum(1, keepdim=True) - best
+    # float32 sums of d products and norms of values near 1: |q||x| + |x|^2 + |q|^2 below 4.5 d, a few 2^-24 of that
+    assert float((score.double() - want).abs().max()) <= 4.5 * d * 2.0 ** -24 * 8
+    ix.close()
