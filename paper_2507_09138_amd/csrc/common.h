@@ -231,6 +231,7 @@ hipError_t launch_rescore(const float* q, int64_t nq, int d, int dtype, const vo
                           const int64_t* row_ids, int64_t nrows, const int32_t* cand, int m, int k, int l2,
                           int64_t* out_ids, float* out_scores, int32_t* out_rows, hipStream_t s);
 hipError_t launch_bf16_to_f16(const void* x, int64_t n, void* out, int* overflow, hipStream_t s);
+hipError_t launch_refresh_bf16(const void* rows, int64_t nrows, int d, float* norm, void* table, int* overflow, hipStream_t s);
 hipError_t launch_split_f32(const float* x, int64_t n, void* hi, void* lo, hipStream_t s);
 hipError_t launch_set_resident(int* resident, int nlist, const int32_t* lists, int64_t n, int value, hipStream_t s);
 hipError_t launch_split_probes(const int32_t* probe, int64_t nq, int np, const int* resident, int nlist, unsigned long long* hits,
