@@ -230,6 +230,40 @@ __global__ __launch_bounds__(256) void k_row_norms(const void* rows, int dtype, 
     if (lane == 0) out[row] = acc;
 }
 
+// Replaced bfloat16 rows: their norms and their copy in the binary16 table in one pass (k_row_norms and k_bf16_to_f16 on the
+// same rows).  A value that does not fit is reported in host memory, which the caller reads once the stream is empty.
+__global__ __launch_bounds__(256) void k_refresh_bf16(const uint16_t* rows, int64_t nrows, int d, float* norm, _Float16* table, volatile int* overflow)
+{
+    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (row >= nrows) return;
+    const int lane = threadIdx.x & 63;
+    const uint16_t* p = rows + row * d;
+    float acc = 0.f;
+    bool over = false;
+    for (int i0 = lane; i0 < d; i0 += 256) {
+        float v[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) v[j] = i0 + j * 64 < d ? bf16_to_f32(p[i0 + j * 64]) : 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            if (i0 + j * 64 >= d) break;
+            acc += v[j] * v[j];
+            over |= !(fabsf(v[j]) <= 65504.0f);                       // (also for NaN)
+            table[row * d + i0 + j * 64] = (_Float16)v[j];
+        }
+    }
+    acc = wave_sum(acc);
+    if (lane == 0) norm[row] = acc;
+    if (over) *overflow = 1;
+}
+
+hipError_t launch_refresh_bf16(const void* rows, int64_t nrows, int d, float* norm, void* table, int* overflow, hipStream_t s)
+{
+    if (nrows <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_refresh_bf16, dim3((unsigned)((nrows + 3) / 4)), dim3(256), 0, s, (const uint16_t*)rows, nrows, d, norm, (_Float16*)table, overflow);
+    return hipGetLastError();
+}
+
 hipError_t launch_row_norms(const void* rows, int dtype, int64_t nrows, int d, float* out, hipStream_t s)
 {
     if (nrows <= 0) return hipSuccess;
