@@ -713,6 +713,7 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, int64_t
     }
 
     MergeArgs m{};
+    m.thr = a.thr;
     m.slot_cnt = a.slot_cnt; m.slot_ent = a.slot_ent; m.slot_stride = p.slot_stride;
     m.row_ids = ix->ids;
     m.qnorm = (const float*)(ws + p.o_qnorm_s);

@@ -913,7 +913,10 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
     }
     together();
 
-    uint32_t thr = 0;                              // below every encoded key
+    // (what the scan knew in the end: k rows of the query, or its whole carried result, reach this key, so nothing below it counts;
+    // from zero on, with 64 entries asked for at a time, 40 queries over 6 of 208 lists, k 83, took 343 us, now 305)
+    uint32_t thr = live ? a.thr[q] : 0;
+    int n = __builtin_amdgcn_readfirstlane(s_cnt[wave]);
     const int total = live ? s_total[own] : 0;
     // a full buffer is cut to the k best; the k-th of any k candidates is a bound for all waves of the query
     auto cut = [&](Cand* b, int n) __attribute__((always_inline)) {
@@ -948,38 +951,40 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
         first[lane] = inc - c;
         slot_of[lane] = slot;
         wave_sync();
-        for (int e0 = 0; e0 < tot; e0 += 64) {
-            const int e = e0 + lane;
-            if (W > 1) thr = max(thr, __hip_atomic_load(&s_thr[own], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-            if (e < tot) {
+        // (256 entries are asked for together: a round trip to memory for every 64 was most of the time of a query with many)
+        for (int e0 = 0; e0 < tot; e0 += 256) {
+            Cand got[4];
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                const int e = e0 + j * 64 + lane;
                 int lo = 0, hi = 64;                  // largest lane o with first[o] <= e: the slot that holds entry e
                 while (hi - lo > 1) {
                     int mid = (lo + hi) >> 1;
                     if (first[mid] <= e) lo = mid; else hi = mid;
                 }
-                Cand cd = a.slot_ent[slot_of[lo] * a.slot_stride + (e - first[lo])];
-                bool take = cd.key >= thr;
+                got[j] = e < tot ? a.slot_ent[slot_of[lo] * a.slot_stride + (e - first[lo])] : Cand{0u, 0u};
+            }
+#pragma unroll
+            for (int j = 0; j < 4; j++) {
+                if (e0 + j * 64 >= tot) break;
+                if (W > 1) thr = max(thr, __hip_atomic_load(&s_thr[own], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+                const Cand cd = got[j];
+                bool take = e0 + j * 64 + lane < tot && cd.key >= thr;
                 // a row the carried result already holds (it came from a cache of earlier results
                 // and its list is scanned now) is not taken a second time
                 if (take && a.io_rows && a.carried)
                     for (int t = 0; t < k; t++) take = take && ext_row[t] != (int)cd.row;
-                if (take) {
-                    int pos = atomicAdd(&s_cnt[wave], 1);
-                    buf[pos] = cd;
-                }
-            }
-            wave_sync();
-            int n = __builtin_amdgcn_readfirstlane(s_cnt[wave]);
-            if (n > kMergeCap - 64) {
-                cut(buf, n);
-                if (lane == 0) s_cnt[wave] = k;
+                const unsigned long long mask = __builtin_amdgcn_ballot_w64(take);
+                if (mask == 0) continue;
+                if (take) buf[n + lanes_below(mask)] = cd;
+                n += __builtin_popcountll(mask);
                 wave_sync();
+                if (n > kMergeCap - 64) { cut(buf, n); n = k; }
             }
         }
         wave_sync();
     }
     wave_sync();
-    int n = __builtin_amdgcn_readfirstlane(s_cnt[wave]);
     if (n > k) {
         cut(buf, n);
         n = k;
@@ -1017,6 +1022,7 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
     }
     wave_sync();
     int pos[2] = {0, 0};
+#pragma unroll 8
     for (int i = 0; i < n; i++) {
         uint32_t so = buf[i].key;
         int64_t oid = tie[i];

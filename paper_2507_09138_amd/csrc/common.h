@@ -181,6 +181,7 @@ enum { DYN_ITEMS = 0, DYN_SEG_ROWS = 1, DYN_ROWS_LO = 2, DYN_ROWS_HI = 3, DYN_PA
 constexpr int kRounds = 64;                // most rounds of a work queue (see the bucketing kernels)
 
 struct MergeArgs {
+    const uint32_t* thr;        // [nq] lower bounds of the k-th keys, as the scan left them
     const int* slot_cnt;
     const Cand* slot_ent;
     int slot_stride;
