@@ -106,12 +106,12 @@ static constexpr int kLdsLimit = 160 * 1024;      // LDS per workgroup on gfx950
 // buffers in LDS for small k when they fit (8 waves, else 4 with half the columns), in global
 // memory for large k.  shape -1 = no fit.
 struct ScanPick { int shape, nbuf, cap, gsel; };
-static ScanPick pick_shape(int dtype, int d, int k)
+static ScanPick pick_shape(int dtype, int d, int k, int groups)
 {
     const int cap = hr::sel_cap(k);
     if (dtype != HR_F32) {
         for (int nbuf : {6, 4, 3, 2})
-            if (hr::scan_lds_bytes(dtype, d, 0, hr::SCAN_WIDE, nbuf) <= (size_t)kLdsLimit) return {hr::SCAN_WIDE, nbuf, cap, 1};
+            if (hr::scan_lds_bytes(dtype, d, 0, hr::SCAN_WIDE, nbuf) <= (size_t)kLdsLimit / groups) return {hr::SCAN_WIDE, nbuf, cap, 1};
         return {-1, 0, 0, 0};
     }
     if (cap > 64) {
@@ -193,7 +193,7 @@ struct Plan {
     // coarse step: centroid table scanned with all queries as one dense bucket
     int shape_c /* workgroup shape, -1 = no fit */, nbuf_c, cap_c, cw_c, cols_c, nqt_c, seg_c, nseg_c;
     // list scan
-    int shape_s, nbuf_s, cap_s, gsel_s, cw_s, item_cap, item_target, few_items, min_rows;
+    int shape_s, groups_s, nbuf_s, cap_s, gsel_s, cw_s, item_cap, item_target, few_items, min_rows;
     int slot_stride;                // entries per result slot of the list scan
     int slot_cap;                   // result slots: one per (list segment, query of the list's bucket)
     size_t o_zero, n_zero;          // ints cleared per call: list_w[nlist], dyn[DYN_COUNT], counters[8], ..., then
@@ -225,7 +225,15 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     Plan p{};
     const int64_t nlist = ix->nlist;
     // coarse step: dense scoring (no selection buffers in LDS) in the widest shape that fits
-    const ScanPick ps = pick_shape(scan_dtype(ix), ix->d, k);
+    // Two workgroups per compute unit where the batch is bound by multiplying and filtering: full tiles (a list is probed by 128
+    // queries in the mean) and about 1024 work items of 256 rows or a list each.  4000 queries over 60 of 200 lists of 3000 rows, k
+    // 24: d = 64 686 -> 466 us, 128 733 -> 502, 256 938 -> 649; 1000 over 30, k 1, 188 -> 161, 205 -> 174, 238 -> 201.  With fewer
+    // items, or many neighbours, more of them start from the seeds alone: 500 over 30 of 64 lists, 100000 rows, k 10, 131 -> 139; 500
+    // over 40 of 200 lists, k 100, 343 -> 399; and 30 queries over 20 of 200 lists 112 -> 121.
+    const int64_t pairs = nq * nprobe;
+    const bool full_tiles = k <= 24 && pairs >= 128 * nlist && (double)(ix->N / kMinSegRows + nlist) * (double)pairs >= 1024.0 * 128.0 * (double)nlist;
+    p.groups_s = full_tiles ? groups_per_cu(scan_dtype(ix), ix->d) : 1;
+    const ScanPick ps = pick_shape(scan_dtype(ix), ix->d, k, p.groups_s);
     p.shape_c = -1; p.nbuf_c = 0; p.cap_c = 0;
     for (int nbuf = 3; nbuf >= 2 && p.shape_c < 0; nbuf--)
         if (scan_lds_bytes(HR_F16X2, ix->d, 0, SCAN_WIDE, nbuf) <= (size_t)kLdsLimit) { p.shape_c = SCAN_WIDE; p.nbuf_c = nbuf; }
@@ -272,7 +280,6 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     p.seg_c = (int)seg;
     p.nseg_c = (int)((nlist + seg - 1) / seg);
     p.cw_s = cols_per_set(scan_dtype(ix), ix->d) * shape_sets(p.shape_s < 0 ? 0 : p.shape_s);
-    const int64_t pairs = nq * nprobe;
     // Work items: sum over probed lists of segments x query tiles.  Segments have at least C / item_target rows, C =
     // sum of rows x tiles, so there are at most item_target items plus one per (list, tile) for the ragged ends.
     // Result slots: sum of segments x bucket width <= cw x item_target, plus one per pair for the ragged ends.
@@ -557,11 +564,11 @@ size_t hr_ivf_workspace_bytes(const hr_ivf_index* ix, int64_t nq, int32_t nprobe
 
 // ---------------------------------------------------------------------------------------
 // persistent workgroups: one per CU (8-wave shape), or two where LDS lets two 4-wave ones share a CU
-static int scan_grid(const hr_ivf_index* ix, size_t lds, int shape)
+static int scan_grid(const hr_ivf_index* ix, size_t lds, int shape, int groups = 1)
 {
     int occ = (int)((size_t)kLdsLimit / lds);
     if (occ < 1) occ = 1;
-    const int most = shape == SCAN_WIDE ? 1 : 2;
+    const int most = shape == SCAN_WIDE ? groups : 2;
     if (occ > most) occ = most;
     return ix->num_cus * occ;
 }
@@ -706,7 +713,7 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, int64_t
     hr_ivf_index* mix = const_cast<hr_ivf_index*>(ix);
     const bool timed = mix->prof_ev && mix->prof_n < mix->prof_cap;
     if (timed) HR_HIP(hipEventRecord(mix->prof_ev[2 * mix->prof_n], s));
-    HR_HIP(launch_scan(scan_dtype(ix), ix->d, a, p.shape_s, scan_grid(ix, lds, p.shape_s), lds, s));
+    HR_HIP(launch_scan(scan_dtype(ix), ix->d, a, p.shape_s, scan_grid(ix, lds, p.shape_s, p.groups_s), lds, s));
     if (timed) {
         HR_HIP(hipEventRecord(mix->prof_ev[2 * mix->prof_n + 1], s));
         mix->prof_n++;

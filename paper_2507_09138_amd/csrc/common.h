@@ -54,6 +54,11 @@ __host__ __device__ constexpr int block_groups(int dtype, int d)
 }
 __host__ __device__ constexpr int block_rows(int dtype, int d) { return kMfmaRows * block_groups(dtype, d); }
 
+// Most workgroups of eight waves on a compute unit: two where a wave gets by with 128 registers (binary16 rows of up to 256
+// elements).  The waves of one wait for each other at every pair of blocks; the other's fill the pipes meanwhile.  Where
+// that pays is in make_plan.
+__host__ __device__ constexpr int groups_per_cu(int dtype, int d) { return dtype == HR_F16 && d <= 256 ? 2 : 1; }
+
 // k-steps (of 32 elements) whose row fragments a wave fetches from LDS together
 __host__ __device__ constexpr int scan_group(int dtype, int ksteps, int nw)
 {

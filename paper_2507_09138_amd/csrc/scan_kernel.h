@@ -525,7 +525,7 @@ __device__ __forceinline__ uint32_t select_k(Cand* buf, int n, int k, int cap, c
 }
 
 template <int DT, int KSTEPS, int NCS, int NW, bool GS>   // GS = a.gsel
-__global__ __launch_bounds__(NW * 64, 1) void k_scan(ScanArgs a)
+__global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) == 2 ? 4 : 1) void k_scan(ScanArgs a)
 {
     using S = ScanShape<DT, KSTEPS, NCS, NW>;
     using T = StoreTraits<DT>;

@@ -435,3 +435,28 @@ def test_queries_prepared_with_the_selection_or_before_the_scoring(storage, d, n
     # float32 sums of d products and norms of values near 1: |q||x| + |x|^2 + |q|^2 below 4.5 d, a few 2^-24 of that
     assert float((score.double() - want).abs().max()) <= 4.5 * d * 2.0 ** -24 * 8
     ix.close()
+
+
+@pytest.mark.parametrize("storage,tables", [("f16", False), ("bf16", True)])
+@pytest.mark.parametrize("d,nq,nprobe,k,metric", [(64, 300, 4, 10, "l2"), (128, 257, 3, 24, "ip"), (256, 300, 4, 1, "l2"), (64, 300, 4, 25, "ip")])
+def test_full_tiles_of_short_vectors(storage, tables, d, nq, nprobe, k, metric):
+    """Batches that put two workgroups on a compute unit (all but the last), lists that end inside a block and a segment."""
+    dtype = {"f16": torch.float16, "bf16": torch.bfloat16}[storage]
+    N, nlist = 180011, 4
+    ix, cent, off, vec, ids, g = _index(N, d, nlist, dtype, nq + d, tables=tables, zipf=0.4)
+    q = torch.randn(nq, d, generator=g, device="cuda")
+    probe = torch.rand(nq, nlist, generator=g, device="cuda").topk(nprobe, dim=1).indices.int()
+    found, score = ix.scan(q, probe, k, metric)
+    allowed = torch.zeros(nq, nlist, dtype=torch.bool, device="cuda").scatter_(1, probe.long(), True)
+    of_row = torch.repeat_interleave(torch.arange(nlist), off[1:] - off[:-1]).cuda()
+    op, row = q.half().double(), torch.empty_like(ids)
+    row[ids] = torch.arange(N, device="cuda")
+    for i in range(0, nq, 100):
+        key = torch.where(allowed[i:i + 100][:, of_row], _keys(op[i:i + 100], vec.double(), metric), -float("inf"))
+        best = torch.topk(key, k, dim=1).values
+        # float32 sums of d products (and norms) of values near 1: |q||x| + |x|^2 below 3 d, a few 2^-24 of that
+        tol = 3 * d * 2.0 ** -24 * 8
+        assert float((key.gather(1, row[found[i:i + 100]]) - best).abs().max()) <= 2 * tol
+        want = best if metric == "ip" else (op[i:i + 100] ** 2).sum(1, keepdim=True) - best
+        assert float((score[i:i + 100].double() - want).abs().max()) <= 2 * tol
+    ix.close()
