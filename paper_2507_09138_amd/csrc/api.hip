@@ -227,7 +227,7 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     // coarse step: dense scoring (no selection buffers in LDS) in the widest shape that fits
     // Two workgroups per compute unit where the batch is bound by multiplying and filtering: full tiles (a list is probed by 128
     // queries in the mean) and about 1024 work items of 256 rows or a list each.  4000 queries over 60 of 200 lists of 3000 rows, k
-    // 24: d = 64 686 -> 466 us, 128 733 -> 502, 256 938 -> 649; 1000 over 30, k 1, 188 -> 161, 205 -> 174, 238 -> 201.  With fewer
+    // 24: d = 64 686 -> 466 us, 128 733 -> 502, 256 938 -> 649, float32 of d = 128 1688 -> 1198; 1000 over 30, k 1, 188 -> 161, 205 -> 174, 238 -> 201.  With fewer
     // items, or many neighbours, more of them start from the seeds alone: 500 over 30 of 64 lists, 100000 rows, k 10, 131 -> 139; 500
     // over 40 of 200 lists, k 100, 343 -> 399; and 30 queries over 20 of 200 lists 112 -> 121.
     const int64_t pairs = nq * nprobe;

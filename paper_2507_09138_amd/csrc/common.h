@@ -55,14 +55,15 @@ __host__ __device__ constexpr int block_groups(int dtype, int d)
 __host__ __device__ constexpr int block_rows(int dtype, int d) { return kMfmaRows * block_groups(dtype, d); }
 
 // Most workgroups of eight waves on a compute unit: two where a wave gets by with 128 registers (binary16 rows of up to 256
-// elements).  The waves of one wait for each other at every pair of blocks; the other's fill the pipes meanwhile.  Where
+// elements, float32 rows of 128 with fragments fetched two steps at a time; the other short ones would, with blocks of 32 rows
+// instead of 64, which cost them 3 .. 7 % where two workgroups do not pay).  The waves of one wait for each other at every pair of blocks; the other's fill the pipes meanwhile.  Where
 // that pays is in make_plan.
-__host__ __device__ constexpr int groups_per_cu(int dtype, int d) { return dtype == HR_F16 && d <= 256 ? 2 : 1; }
+__host__ __device__ constexpr int groups_per_cu(int dtype, int d) { return (dtype == HR_F16 && d <= 256) || (dtype == HR_F32 && d == 128) ? 2 : 1; }
 
 // k-steps (of 32 elements) whose row fragments a wave fetches from LDS together
 __host__ __device__ constexpr int scan_group(int dtype, int ksteps, int nw)
 {
-    if (ksteps < 16 && nw == 8) return 4;                           // (of a block of several groups of rows: 8 or 16 k-steps in all)
+    if (ksteps < 16 && nw == 8) return dtype == HR_F32 && ksteps == 4 ? 2 : 4;                           // (of a block of several groups of rows: 8 or 16 k-steps in all)
     if (ksteps < 8) return 4;
     if (nw == 8 && dtype == HR_F32 && ksteps >= 24) return 2;       // (leaves registers for a second row block in flight)
     // (what a long operand in two parts leaves: 253 of 256 registers at 24 k-steps, none spilled)

@@ -437,11 +437,12 @@ def test_queries_prepared_with_the_selection_or_before_the_scoring(storage, d, n
     ix.close()
 
 
-@pytest.mark.parametrize("storage,tables", [("f16", False), ("bf16", True)])
+@pytest.mark.parametrize("storage,tables", [("f16", False), ("bf16", True), ("f32", False)])
 @pytest.mark.parametrize("d,nq,nprobe,k,metric", [(64, 300, 4, 10, "l2"), (128, 257, 3, 24, "ip"), (256, 300, 4, 1, "l2"), (64, 300, 4, 25, "ip")])
 def test_full_tiles_of_short_vectors(storage, tables, d, nq, nprobe, k, metric):
-    """Batches that put two workgroups on a compute unit (all but the last), lists that end inside a block and a segment."""
-    dtype = {"f16": torch.float16, "bf16": torch.bfloat16}[storage]
+    """Batches that put two workgroups on a compute unit (binary16 all but the last, float32 of d = 128), lists that end
+    inside a block and a segment."""
+    dtype = {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[storage]
     N, nlist = 180011, 4
     ix, cent, off, vec, ids, g = _index(N, d, nlist, dtype, nq + d, tables=tables, zipf=0.4)
     q = torch.randn(nq, d, generator=g, device="cuda")
@@ -449,7 +450,7 @@ def test_full_tiles_of_short_vectors(storage, tables, d, nq, nprobe, k, metric):
     found, score = ix.scan(q, probe, k, metric)
     allowed = torch.zeros(nq, nlist, dtype=torch.bool, device="cuda").scatter_(1, probe.long(), True)
     of_row = torch.repeat_interleave(torch.arange(nlist), off[1:] - off[:-1]).cuda()
-    op, row = q.half().double(), torch.empty_like(ids)
+    op, row = (q if storage == "f32" else q.half()).double(), torch.empty_like(ids)
     row[ids] = torch.arange(N, device="cuda")
     for i in range(0, nq, 100):
         key = torch.where(allowed[i:i + 100][:, of_row], _keys(op[i:i + 100], vec.double(), metric), -float("inf"))
