@@ -672,9 +672,6 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, int64_t
     HR_HIP(launch_bucketing(b, s));
 
     // starting lower bounds: from a carried result, and from the first rows of every query's best-ranked list
-    if (carried)
-        HR_HIP(launch_state_thr(out_ids, out_scores, (const float*)(ws + p.o_qnorm_s), nq, k, metric == HR_METRIC_L2,
-                                (uint32_t*)(ws + p.o_thr) + nq, s));
     SeedArgs sd{};
     sd.rows = row_table(ix); sd.row_norm = ix->d_row_norm; sd.qop = ws + p.o_qop_s;
     sd.probe = probe; sd.list_off = ix->d_list_off; sd.resident = ix->d_resident;
@@ -684,6 +681,7 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, int64_t
     sd.seed_rows = k + 28 < 64 ? 64 : ((k + 28 + 15) & ~15);
     if (sd.seed_rows > 192) sd.seed_rows = 192;
     sd.l2 = metric == HR_METRIC_L2;
+    if (carried) { sd.state_ids = out_ids; sd.state_scores = out_scores; sd.qnorm = (const float*)(ws + p.o_qnorm_s); }
     HR_HIP(launch_seed(row_dtype(ix), ix->d, sd, s));
 
     ScanArgs a{};

@@ -801,34 +801,6 @@ hipError_t launch_bucketing(const BucketArgs& a, hipStream_t s)
 // Section 5 and the per-request merge of Section 4.4): one wave per query walks the slots that hold its
 // candidates, keeps the k best in an LDS buffer pruned as in the scan, then orders the
 // survivors by (key, label) and writes the output row.
-// Key (larger is better) of an entry of a carried result, from its reported score: the score
-// itself for the inner product; |q|^2 - distance for squared L2 (the inverse of what the merge
-// reports, up to rounding).
-__device__ __forceinline__ float key_of_score(float score, float qn, int l2) { return l2 ? qn - score : score; }
-
-// Carried results as starting lower bounds: a query whose carried result is full starts the
-// scan at the key of its worst entry (minus a margin for the rounding of the line above).
-__global__ void k_state_thr(const int64_t* ids, const float* scores, const float* qnorm, int64_t nq, int k, int l2,
-                            uint32_t* thr)
-{
-    int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= nq) return;
-    if (ids[q * k + k - 1] < 0) return;                      // (best first, empty places last)
-    const float sc = scores[q * k + k - 1];
-    const float qn = l2 ? qnorm[q] : 0.f;
-    const float key = key_of_score(sc, qn, l2);
-    const float margin = l2 ? 4.0e-7f * fmaxf(fabsf(qn), fabsf(sc)) : 0.f;
-    atomicMax(&thr[q], enc_key(key - margin));
-}
-
-hipError_t launch_state_thr(const int64_t* ids, const float* scores, const float* qnorm, int64_t nq, int k, int l2,
-                            uint32_t* thr, hipStream_t s)
-{
-    if (nq <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_state_thr, dim3((unsigned)((nq + 255) / 256)), dim3(256), 0, s, ids, scores, qnorm, nq, k, l2, thr);
-    return hipGetLastError();
-}
-
 constexpr int kMergeCap = 256;     // candidates buffered per wave (k <= 128, up to 64 appended per step)
 
 // W waves share the slots of a query, 64 slots at a time in turn, each with a buffer of its own; the first takes in what

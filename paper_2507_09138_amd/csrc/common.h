@@ -179,6 +179,9 @@ struct SeedArgs {
     const int* resident;        // [nlist] 1 = the list's vectors are in place
     uint32_t* thr;              // [nq]
     float* hpar;                // [nq][2] histogram parameters of the scan (see ScanArgs)
+    const int64_t* state_ids;   // [nq, k] labels and scores of a carried result, or nullptr
+    const float* state_scores;
+    const float* qnorm;         // [nq] squared norms of the query operands (with a carried result, L2 only)
     int nq, nprobe, nlist, k, seed_rows, l2;
 };
 
@@ -229,8 +232,6 @@ hipError_t launch_prep_queries(const PrepArgs& a, hipStream_t s);
 hipError_t launch_fill_i32(int* p, int64_t n, int v, hipStream_t s);
 hipError_t launch_hot_lists(const unsigned long long* hits, int nlist, int gc, int32_t* out, hipStream_t s);
 hipError_t launch_read_hits(unsigned long long* hits, int64_t n, int64_t* out, int reset, hipStream_t s);
-hipError_t launch_state_thr(const int64_t* ids, const float* scores, const float* qnorm, int64_t nq, int k, int l2,
-                            uint32_t* thr, hipStream_t s);
 hipError_t launch_lists_of_rows(const int32_t* rows, int64_t n, const int* list_off, int nlist, int32_t* out, hipStream_t s);
 hipError_t launch_reorder_probes(const int32_t* probe, int np, const int32_t* prev, int pp, const int32_t* hot, int nh,
                                  int64_t nq, int32_t* out, hipStream_t s);

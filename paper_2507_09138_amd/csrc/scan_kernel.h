@@ -1308,6 +1308,11 @@ inline hipError_t launch_scan_dtype(int d, const ScanArgs& a, int shape, int gri
     }
 }
 
+// Key (larger is better) of an entry of a carried result, from its reported score: the score
+// itself for the inner product; |q|^2 - distance for squared L2 (the inverse of what the merge
+// reports, up to rounding).
+__device__ __forceinline__ float key_of_score(float score, float qn, int l2) { return l2 ? qn - score : score; }
+
 // ------------------------------------------------------------------------------------------
 // Threshold seeding.  One workgroup per query scores the first rows of the query's best-ranked
 // list (with the very MFMA sequence of k_scan, so the keys are the ones the scan will compute
@@ -1333,6 +1338,14 @@ __global__ __launch_bounds__(256) void k_seed(SeedArgs a)
     __shared__ u32x4 s_q[QP * KSTEPS * 4];
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     const int64_t q = blockIdx.x;
+    // Carried results as starting lower bounds: a query whose carried result is full starts the scan at the key of its
+    // worst entry (minus a margin for the rounding of key_of_score).  (A launch of its own before: 4.6 us of every sub-stage.)
+    if (a.state_ids != nullptr && threadIdx.x == 0 && a.state_ids[q * a.k + a.k - 1] >= 0) {       // (best first, empty places last)
+        const float sc = a.state_scores[q * a.k + a.k - 1];
+        const float qn = a.l2 ? a.qnorm[q] : 0.f;
+        const float margin = a.l2 ? 4.0e-7f * fmaxf(fabsf(qn), fabsf(sc)) : 0.f;
+        atomicMax(&a.thr[q], enc_key(key_of_score(sc, qn, a.l2) - margin));
+    }
     // the best-ranked list of the query whose vectors are in place (among the first 64 places of its row);
     // every wave finds it for itself (same loads, same answer: what follows is uniform over the workgroup)
     int l = -1;
