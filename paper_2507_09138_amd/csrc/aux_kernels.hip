@@ -798,8 +798,8 @@ hipError_t launch_bucketing(const BucketArgs& a, hipStream_t s)
 
 // ------------------------------------------------------------------------------------------
 // Per-query merge of the scan's partial results (the reduction step of the cluster search of
-// Section 5 and the per-request merge of Section 4.4): one wave per query walks the slots that hold its
-// candidates, keeps the k best in an LDS buffer pruned as in the scan, then orders the
+// Section 5 and the per-request merge of Section 4.4): a wave, or four, walk the slots that hold a query's
+// candidates, keep the k best in LDS buffers pruned as in the scan; the first then orders the
 // survivors by (key, label) and writes the output row.
 constexpr int kMergeCap = 256;     // candidates buffered per wave (k <= 128, up to 64 appended per step)
 

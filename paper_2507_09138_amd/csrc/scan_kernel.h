@@ -1,7 +1,7 @@
 // Cluster-major list scan with in-kernel top-k selection (gfx950, wave64, MFMA 16x16x32).
 //
 // One work item = (a segment of consecutive rows of one inverted list) x (a tile of the
-// queries bucketed to that list).  The rows are streamed once through LDS in blocks of 16
+// queries bucketed to that list).  The rows are streamed once through LDS in blocks of 16 (short vectors: up to 64)
 // and every wave multiplies each block with the query operand it keeps in registers, so a
 // staged block is reused by all queries of the tile (the cross-request sharing of one pass
 // over a probed cluster: Sections 4.4 and 5 of the paper; the per-pair similarity is the
