@@ -221,7 +221,8 @@ int hr_ivf_split_probes(const hr_ivf_index* index, const int32_t* probe_ids, int
  * `stream`: put it behind the copy, and the next search behind it.  list_ids is read at search time
  * and needs no refresh; list_offsets cannot change.  Only with a binary16 table of bfloat16 rows the
  * call also waits for the stream, to learn whether a new value exceeds 65504: HR_ERR_UNSUPPORTED
- * then (the table holds an infinity there until the rows are replaced again).
+ * then (the table holds an infinity there until the rows are replaced again).  Refreshes of different rows may run at
+ * the same time on different streams and threads; each reports its own rows.
  */
 int hr_ivf_refresh_rows(hr_ivf_index* index, int64_t row_begin, int64_t row_end, void* stream);
 

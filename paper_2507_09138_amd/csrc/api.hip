@@ -1,11 +1,13 @@
 // Host side of the C ABI declared in hr_ivf.h: argument checks, workspace layout, launch
 // sequence.  Nothing here synchronises the caller's stream except hr_ivf_load and hr_ivf_stats.
 #include <algorithm>
+#include <atomic>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <thread>
 
 #include "common.h"
 
@@ -161,7 +163,10 @@ struct hr_ivf_index {
     void* d_vec_lo;        // rows (the split the scan would otherwise redo for every block it stages); else null
     void* d_vec16;         // bfloat16 lists only, when memory and the value range allow: [N, d] the rows as binary16
     int* d_flag;           // two device ints: [0] a bfloat16 value did not fit binary16, [1] a negative label
-    int* h_over;           // with d_vec16: a refreshed value did not fit binary16 (host memory that kernels write), else null
+    // with d_vec16: report words of hr_ivf_refresh_rows, one for each call under way (host memory that kernels write; bit i of
+    // over_used: word i belongs to a call), else null
+    int *h_over, *d_over;  // their address on the host and on the device
+    std::atomic<uint64_t> over_used;
     unsigned long long* d_hits;   // [nlist] probes per list since load / last reset
     int* d_resident;       // [nlist] 1 = the list's vectors are in place (all lists, until the caller says otherwise)
     int num_cus;
@@ -459,8 +464,8 @@ int hr_ivf_load(const float* centroids, const int64_t* list_offsets, const void*
         ix->d_vec16 = nullptr;
     }
     if (e == hipSuccess && ix->d_vec16) {
-        e = hipHostMalloc((void**)&ix->h_over, sizeof(int), hipHostMallocMapped | hipHostMallocCoherent);
-        if (e == hipSuccess) *ix->h_over = 0;
+        e = hipHostMalloc((void**)&ix->h_over, 64 * sizeof(int), hipHostMallocMapped | hipHostMallocCoherent);
+        if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&ix->d_over, ix->h_over, 0);
     }
     delete[] h_off;
     if (e != hipSuccess || flags[1]) {
@@ -947,6 +952,34 @@ int hr_ivf_split_probes(const hr_ivf_index* ix, const int32_t* probe_ids, int64_
     return HR_OK;
 }
 
+}  // extern "C"
+
+// The report word of one refresh, cleared, its own until the call returns: calls on other threads and streams report in other
+// words.  (With one word per index the call that reads it first takes another's report and clears it, and that other call
+// finds none.)  A sixty-fifth call waits for one of the others.
+class OverflowWord {
+public:
+    explicit OverflowWord(hr_ivf_index* ix) : ix_(ix)
+    {
+        uint64_t used = ix->over_used.load();
+        for (;;) {
+            if (used == ~0ull) { std::this_thread::yield(); used = ix->over_used.load(); continue; }
+            at_ = __builtin_ctzll(~used);
+            if (ix->over_used.compare_exchange_weak(used, used | 1ull << at_)) break;
+        }
+        ((volatile int*)ix->h_over)[at_] = 0;
+    }
+    ~OverflowWord() { ix_->over_used.fetch_and(~(1ull << at_)); }
+    OverflowWord(const OverflowWord&) = delete;
+    int* on_device() const { return ix_->d_over + at_; }
+    int value() const { return ((volatile int*)ix_->h_over)[at_]; }
+private:
+    hr_ivf_index* ix_;
+    int at_;
+};
+
+extern "C" {
+
 int hr_ivf_refresh_rows(hr_ivf_index* ix, int64_t row_begin, int64_t row_end, void* stream)
 {
     if (int rc = check_index(ix)) return rc;
@@ -961,16 +994,13 @@ int hr_ivf_refresh_rows(hr_ivf_index* ix, int64_t row_begin, int64_t row_end, vo
         // (the only case in which this call waits for the stream: a new value beyond binary16 cannot go into the
         // table, and a later search must not read an infinity there.  The kernel reports it in host memory, so the wait is all
         // there is: with two launches and a copy of the flag as well, a batch that swaps eight ranges in took 753 us, now 643)
-        volatile int* over = ix->h_over;
-        int* over_dev = nullptr;
-        HR_HIP(hipHostGetDevicePointer((void**)&over_dev, ix->h_over, 0));
-        HR_HIP(launch_refresh_bf16(rows, n, ix->d, ix->d_row_norm + row_begin, (char*)ix->d_vec16 + (size_t)row_begin * ix->d * 2, over_dev, s));
+        const OverflowWord word(ix);
+        HR_HIP(launch_refresh_bf16(rows, n, ix->d, ix->d_row_norm + row_begin, (char*)ix->d_vec16 + (size_t)row_begin * ix->d * 2,
+                                   word.on_device(), s));
         HR_HIP(hipStreamSynchronize(s));
-        if (*over) {
-            *over = 0;
+        if (word.value())
             return fail(HR_ERR_UNSUPPORTED, "a refreshed bfloat16 value exceeds 65504 and does not fit the binary16 row table: "
                                             "replace the rows again, or load the index without HR_LOAD_ROW_TABLES");
-        }
         return HR_OK;
     }
     HR_HIP(launch_row_norms(rows, ix->dtype, n, ix->d, ix->d_row_norm + row_begin, s));

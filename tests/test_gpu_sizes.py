@@ -1,5 +1,7 @@
 """Sizes at which the kernels around the list scan change their way: edges of samples, buffers and tiles, the smallest
 and the largest of each range, against float64 arithmetic of the same operands."""
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -460,4 +462,37 @@ def test_full_tiles_of_short_vectors(storage, tables, d, nq, nprobe, k, metric):
         assert float((key.gather(1, row[found[i:i + 100]]) - best).abs().max()) <= 2 * tol
         want = best if metric == "ip" else (op[i:i + 100] ** 2).sum(1, keepdim=True) - best
         assert float((score[i:i + 100].double() - want).abs().max()) <= 2 * tol
+    ix.close()
+
+
+@pytest.mark.parametrize("threads", [2, 8, 80])
+def test_refreshes_at_the_same_time_report_their_own_rows(threads):
+    """bfloat16 rows with a binary16 table, every thread with rows of its own, on several streams: a value beyond binary16 is
+    reported by the call that refreshed its row, every time, and by no other (more threads than there are report words, too)."""
+    N, each = 16000, 200
+    ix, cent, off, vec, ids, g = _index(N, 64, 8, torch.bfloat16, threads, tables=True)
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    for t in range(1, threads, 2):
+        vec[t * each + 7 * t % each, t % 64] = 1.0e6
+    torch.cuda.synchronize()
+    start, wrong = threading.Barrier(threads), []
+
+    def work(t):
+        with torch.cuda.stream(streams[t % len(streams)]):
+            start.wait()
+            for i in range(40):
+                try:
+                    ix.refresh_rows(t * each, (t + 1) * each)
+                    code = 0
+                except _hr().HrError as e:
+                    code = e.code
+                if code != (-5 if t % 2 else 0):
+                    wrong.append((t, i, code))
+
+    pool = [threading.Thread(target=work, args=(t,)) for t in range(threads)]
+    for p in pool:
+        p.start()
+    for p in pool:
+        p.join()
+    assert not wrong
     ix.close()
