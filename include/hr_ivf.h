@@ -92,7 +92,7 @@ int hr_ivf_free(hr_ivf_index* index);
  * Bytes of DEV scratch that hr_ivf_search / hr_ivf_coarse / hr_ivf_scan and the step-wise calls
  * need for this batch shape; 0 on invalid arguments (nprobe 1 .. HR_NPROBE_MAX: hr_ivf_scan takes
  * rows of that many places whatever the number of lists).  Depends only on (index, nq, nprobe, k),
- * never on the data.
+ * never on the data, and is enough for fewer queries, probes and neighbours as well.
  */
 size_t hr_ivf_workspace_bytes(const hr_ivf_index* index, int64_t nq, int32_t nprobe, int32_t k);
 

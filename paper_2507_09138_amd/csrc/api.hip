@@ -225,6 +225,8 @@ struct Plan {
 struct PlanLimits { int item_target; size_t ckeys_bytes; bool by_length; int cap; };
 static constexpr PlanLimits kDefaultLimits = {kItemTarget, (size_t)512 << 20, true, 0};
 
+static constexpr int kShortSegK = 24;          // most neighbours of a search that may go in segments shorter than kMinSegRows
+
 static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, const PlanLimits& lim = kDefaultLimits)
 {
     Plan p{};
@@ -300,7 +302,7 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     // 50 lists, d = 1024, 112 -> 132; and with a second round of items (segments of rows x tiles / 256 without regard to the
     // ragged ends) 16 requests over 16 of 256 lists, d = 64, 68 -> 97.
     p.few_items = std::min(ix->num_cus, lim.item_target);
-    p.min_rows = k <= 24 && ix->d >= 512 ? std::min(((128 << 10) / (ix->d * (ix->dtype == HR_F32 ? 4 : 2)) + 15) & ~15, kMinSegRows) : kMinSegRows;
+    p.min_rows = k <= kShortSegK && ix->d >= 512 ? std::min(((128 << 10) / (ix->d * (ix->dtype == HR_F32 ? 4 : 2)) + 15) & ~15, kMinSegRows) : kMinSegRows;
     if (p.min_rows < 64) p.min_rows = 64;
     const int64_t in_short = std::min((int64_t)p.cw_s * p.few_items + pairs, pairs * ((ix->longest + p.min_rows - 1) / p.min_rows));
     const int64_t by_length = std::max(pairs * ((ix->longest + kMinSegRows - 1) / kMinSegRows), in_short);
@@ -562,7 +564,10 @@ size_t hr_ivf_workspace_bytes(const hr_ivf_index* ix, int64_t nq, int32_t nprobe
     // (hr_ivf_scan and its step-wise forms take rows of up to HR_NPROBE_MAX places whatever the number of lists)
     if (nprobe < 1 || nprobe > HR_NPROBE_MAX) { fail(HR_ERR_ARG, "nprobe=%d must be in 1..%d", nprobe, HR_NPROBE_MAX); return 0; }
     if (check_batch(ix, nq, nprobe > ix->nlist ? (int)ix->nlist : nprobe, k, HR_METRIC_IP, true)) return 0;
-    return make_plan(ix, nq, nprobe, k).total;
+    // what is enough for k is enough for fewer: searches of few neighbours may take more, shorter segments, so more result slots
+    // (one request over 16 of 256 lists, the longest of 11000 rows, k 10 1386 KB of slots, k 100 1034)
+    const size_t need = make_plan(ix, nq, nprobe, k).total;
+    return k > kShortSegK ? std::max(need, make_plan(ix, nq, nprobe, kShortSegK).total) : need;
 }
 
 }  // extern "C"

@@ -311,6 +311,27 @@ def test_workspace_of_a_small_batch_is_small():
     ix.close()
 
 
+@pytest.mark.parametrize("dtype,d,N", [(torch.float16, 768, 65536), (torch.float32, 512, 20000), (torch.bfloat16, 64, 65536)])
+def test_workspace_for_many_neighbours_is_enough_for_few(dtype, d, N):
+    """Also where few neighbours go in shorter segments: sizes along k, and calls with the workspace of the largest k."""
+    hr = _hr()
+    ix, cent, off, vec, ids, g = _index(N, d, 64, dtype, d, zipf=1.0)
+    for nq, nprobe in ((1, 16), (3, 8), (40, 60)):
+        sizes = [hr.hr_ivf_workspace_bytes(ix.handle, nq, nprobe, k) for k in range(1, hr.HR_K_MAX + 1)]
+        assert sizes == sorted(sizes)
+        q = torch.randn(nq, d, generator=g, device="cuda")
+        ws = torch.empty(sizes[24], dtype=torch.uint8, device="cuda")            # (of k = 25)
+        for k in (1, 10, 24):
+            want = ix.search(q, nprobe, k, "ip")
+            got = torch.empty_like(want[0]), torch.empty_like(want[1])
+            hr.hr_ivf_search(ix.handle, q, nq, nprobe, k, hr.HR_METRIC_IP, got[0], got[1], ws, ws.numel())
+            assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+        probe = torch.empty(nq, nprobe, dtype=torch.int32, device="cuda")
+        hr.hr_ivf_coarse(ix.handle, q, nq, nprobe, hr.HR_METRIC_IP, probe, None, ws, ws.numel())
+        assert torch.equal(probe, ix.coarse(q, nprobe, "ip")[0])
+    ix.close()
+
+
 @pytest.mark.parametrize("nlist", [1, 15, 16, 17, 1023, 1024, 1025, 2049, 3000])
 def test_hot_lists_at_the_edges_of_tiles(nlist):
     """Equal counts on both sides of every tile of counters, and lists that nobody probed."""
