@@ -631,6 +631,12 @@ static int enqueue_coarse(const hr_ivf_index* ix, const Plan& p, char* ws, const
         a.work_counter = zero + ix->nlist + DYN_COUNT;
         a.dense_items = p.nseg_c * nqt;
         a.dense_nqt = nqt;
+        // Long items: up to eight tiles that read the same rows go to one XCD, whose L2 then serves all but the first of them.  In
+        // plain order the first items, which are the workgroups' places, put neighbouring tiles into different XCDs: 500 queries,
+        // d = 1024, 65536 centroids 456 us, 368 in groups (379 with items as the workgroups came for them), 4096 49 .. 59, 46 (53);
+        // 1000 queries, d = 512, 16384 centroids 105 .. 125, 104 (110).  Short items load more queries than rows: 500 queries,
+        // d = 64, 16384 centroids, 64 KB of rows an item, 49, 53; 1500, d = 1024, 1024 centroids, 12 tiles, 256 KB, 39.6, 41.6.
+        if ((int64_t)p.seg_c * ix->d * 4 >= (nqt <= 8 ? 256 << 10 : 512 << 10)) a.dense_groups = (nqt + 7) / 8;
         a.dense_cols = p.cols_c;
         a.dense_seg_rows = p.seg_c;
         a.dense_nrows = (int)ix->nlist;

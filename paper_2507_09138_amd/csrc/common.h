@@ -161,6 +161,7 @@ struct ScanArgs {
     int xq_stride;
     // dense mode (HR_F16X2 with gsel 0, and then key_out is not null): one list = all rows, bucket = all queries
     int dense_items, dense_nqt, dense_seg_rows, dense_nrows;
+    int dense_groups;           // groups that the tiles are taken in, so that the items of a segment meet in one XCD (0: plain order)
     int dense_cols;             // queries per wave (d < 512: as many as it has columns for)
     int nq, k, cap, l2;
     int nbuf;                   // staging buffers in LDS (16-bit storage; float32 always uses 2)

@@ -620,7 +620,8 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
         const int lane = lane_now();
         int item = -1;
         if (DENSE) {
-            if (!started) item = blockIdx.x;
+            // (in groups: the workgroups of an XCD start with items that lie one behind the other)
+            if (!started) item = a.dense_groups == 0 ? (int)blockIdx.x : myx * ((int)gridDim.x >> 3) + min(myx, (int)gridDim.x & 7) + ((int)blockIdx.x >> 3);
             else if (lane == 0 && (int)gridDim.x < a.dense_items) item = gridDim.x + atomicAdd(a.work_counter, 1);
             if (item >= a.dense_items) item = -1;
         } else {
@@ -662,8 +663,20 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
         // ---- decode the work item
         int qt, row0, row_end, w, boff, slot0 = 0;
         if (DENSE) {
-            const int seg = item / a.dense_nqt;
-            qt = item - seg * a.dense_nqt;
+            // plain order: all tiles of a segment, then those of the next.  In groups: tiles g, g + groups, g + 2 groups, .. of all
+            // segments, then those of the next group; the first `more` groups have one tile more than the others.
+            int seg;
+            if (a.dense_groups == 0) {
+                seg = item / a.dense_nqt;
+                qt = item - seg * a.dense_nqt;
+            } else {
+                const int nseg = a.dense_items / a.dense_nqt, fewer = a.dense_nqt / a.dense_groups, more = a.dense_nqt - fewer * a.dense_groups;
+                const int wide = more * (fewer + 1) * nseg;             // items of those groups
+                const int tiles = item < wide ? fewer + 1 : fewer, at = item < wide ? item : item - wide;
+                const int grp = at / (tiles * nseg), rest = at - grp * tiles * nseg;
+                seg = rest / tiles;
+                qt = (item < wide ? grp : more + grp) + (rest - seg * tiles) * a.dense_groups;
+            }
             row0 = seg * seg_rows;
             row_end = min(a.dense_nrows, row0 + seg_rows);
             w = a.nq;

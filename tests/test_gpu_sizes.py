@@ -302,6 +302,28 @@ def test_static_search_beyond_the_first_plan(storage, tables, d, nlist, nq, npro
     ix.close()
 
 
+@pytest.mark.parametrize("nq", [100, 500, 1024, 1025, 1100, 2100])
+@pytest.mark.parametrize("nlist", [4100, 16385])
+def test_tiles_of_the_coarse_step_in_groups(nlist, nq):
+    """Long items of the scoring, one to eight tiles of queries in a group, groups of unequal size, and, with the static
+    array, chunks of queries; every query against float64."""
+    d, nprobe = 1024, 24
+    ix, cent, off, vec, ids, g = _index(nlist, d, nlist, torch.float16, nq)
+    q = torch.randn(nq, d, generator=g, device="cuda")
+    probe, score = ix.coarse(q, nprobe, "ip")
+    key = q.double() @ cent.double().T
+    # float32 sums of d products of values near 1: |q||x| below 1.5 d, a few 2^-24 of that
+    tol = 1.5 * d * 2.0 ** -24 * 8
+    best = torch.topk(key, nprobe, dim=1).values
+    assert float((key.gather(1, probe.long()) - best).abs().max()) <= 2 * tol
+    assert float((score.double() - best).abs().max()) <= tol
+    want = ix.search(q, nprobe, 4, "ip")
+    got = torch.empty_like(want[0]), torch.empty_like(want[1])
+    _hr().hr_ivf_search_static(ix.handle, q, nq, nprobe, 4, _hr().HR_METRIC_IP, got[0], got[1])
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    ix.close()
+
+
 def test_workspace_of_a_small_batch_is_small():
     """Result slots are bounded by the segments that the longest list has, not by the largest batch's alone."""
     ix, *_ = _index(65536, 64, 256, torch.bfloat16, 1)
