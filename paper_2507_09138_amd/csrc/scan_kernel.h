@@ -524,7 +524,9 @@ __device__ __forceinline__ uint32_t select_k(Cand* buf, int n, int k, int cap, c
     return wave_select<3>(buf, n, k, ids, nullptr, lane);
 }
 
-template <int DT, int KSTEPS, int NCS, int NW, bool GS>   // GS = a.gsel
+// GS = a.gsel, GROUPS = a.dense_groups > 0 (an instance of its own: both orders in one made the shortest coarse calls up to 0.5 us
+// longer, 200 queries, 1024 centroids, d = 64, 15.6 and 16.1)
+template <int DT, int KSTEPS, int NCS, int NW, bool GS, bool GROUPS = false>
 __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) == 2 ? 4 : 1) void k_scan(ScanArgs a)
 {
     using S = ScanShape<DT, KSTEPS, NCS, NW>;
@@ -621,7 +623,8 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
         int item = -1;
         if (DENSE) {
             // (in groups: the workgroups of an XCD start with items that lie one behind the other)
-            if (!started) item = a.dense_groups == 0 ? (int)blockIdx.x : myx * ((int)gridDim.x >> 3) + min(myx, (int)gridDim.x & 7) + ((int)blockIdx.x >> 3);
+            const int each = (int)gridDim.x >> 3, odd = (int)gridDim.x & 7;
+            if (!started) item = !GROUPS ? (int)blockIdx.x : myx * each + min(myx, odd) + ((int)blockIdx.x >> 3);
             else if (lane == 0 && (int)gridDim.x < a.dense_items) item = gridDim.x + atomicAdd(a.work_counter, 1);
             if (item >= a.dense_items) item = -1;
         } else {
@@ -666,7 +669,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
             // plain order: all tiles of a segment, then those of the next.  In groups: tiles g, g + groups, g + 2 groups, .. of all
             // segments, then those of the next group; the first `more` groups have one tile more than the others.
             int seg;
-            if (a.dense_groups == 0) {
+            if (!GROUPS) {
                 seg = item / a.dense_nqt;
                 qt = item - seg * a.dense_nqt;
             } else {
@@ -1280,12 +1283,12 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
     }
 }
 
-template <int DT, int NCS, int NW, bool GS>
+template <int DT, int NCS, int NW, bool GS, bool GROUPS = false>
 inline hipError_t launch_scan_shape(int d, const ScanArgs& a, int grid, size_t lds, hipStream_t s)
 {
 #define HR_SCAN_CASE(KS)                                                                           \
     case KS * 32: {                                                                                \
-        auto kern = k_scan<DT, KS, NCS, NW, GS>;                                                      \
+        auto kern = k_scan<DT, KS, NCS, NW, GS, GROUPS>;                                           \
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
         if (e != hipSuccess) return e;                                                             \
         hipLaunchKernelGGL(kern, dim3(grid), dim3(NW * 64), lds, s, a);                            \
@@ -1309,7 +1312,9 @@ inline hipError_t launch_scan_dtype(int d, const ScanArgs& a, int shape, int gri
     if constexpr (DT == HR_F16X2) {
         // (the centroid table in the coarse step, gsel 0 and every key written out, and float32 lists split at load)
         if ((a.key_out != nullptr) == (a.gsel != 0)) return hipErrorInvalidValue;
-        return a.gsel ? launch_scan_shape<DT, 1, 8, true>(d, a, grid, lds, s) : launch_scan_shape<DT, 1, 8, false>(d, a, grid, lds, s);
+        if (a.gsel) return launch_scan_shape<DT, 1, 8, true>(d, a, grid, lds, s);
+        return a.dense_groups > 0 ? launch_scan_shape<DT, 1, 8, false, true>(d, a, grid, lds, s)
+                                  : launch_scan_shape<DT, 1, 8, false>(d, a, grid, lds, s);
     } else {
         if (a.gsel) return shape == SCAN_WIDE ? launch_scan_shape<DT, 1, 8, true>(d, a, grid, lds, s) : hipErrorInvalidValue;
         if constexpr (DT == HR_F32) {
