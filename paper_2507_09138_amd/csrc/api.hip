@@ -259,7 +259,10 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     // 3001 queries, d = 768, 4096 centroids 121 and 108), and tiles of 64 where those fit it as well, if the vectors are long
     // enough for the loading to count and the table so short that reading it twice as often does not (d = 768, 64 centroids:
     // 100 queries 26.3 -> 24.3 us, 300 28.6 -> 24.5, 3001 40.7 -> 37.3; 2048 centroids, 200 queries 36.1 -> 34.3, but 4096,
-    // 100 queries 36.1 -> 37.3; d = 128, 512 centroids, 1000 queries 20.0 -> 21.5).
+    // 100 queries 36.1 -> 37.3; then still with a launch of the preparation).  Rows count in sixteens for short vectors too, whose
+    // blocks are of 64 (d = 64) or 32 (d = 128): an item of 16 or 48 rows multiplies copies of its last one, but rounding items
+    // up to whole blocks takes as many from the device (1 .. 8192 queries, 64 .. 65536 centroids, 172 cases: as fast in the
+    // mean, 0.94 .. 1.04; 777 centroids, d = 64, 300 queries 15.3 -> 16.3, 16384, 3001 122.1 -> 117.0).
     const int64_t nblk = (nlist + kMfmaRows - 1) / kMfmaRows, cus = ix->num_cus;
     const int full = cols_per_set(HR_F16X2, ix->d) * shape_sets(p.shape_c < 0 ? 0 : p.shape_c), waves = shape_waves(p.shape_c < 0 ? 0 : p.shape_c);
     int64_t per_item = nblk;                        // blocks
@@ -279,10 +282,6 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     }
     p.cols_c = p.cw_c / waves;
     p.nqt_c = (int)((p.cchunk + p.cw_c - 1) / p.cw_c);
-    // (not as short as one block where two leave enough of the device busy: half the loads of queries.  One tile of 8 queries,
-    // d = 64: 4096 centroids 24.3 -> 22.8 us, 1024 of d = 768 19.1 -> 20.0; 16 tiles, d = 768, 64 centroids 38.6 -> 36.8,
-    // two tiles, 256 centroids 29.4 -> 31.2)
-    if (per_item == 1 && nblk * p.nqt_c >= (p.nqt_c > 1 ? cus / 4 : cus / 2)) per_item = 2;
     const int64_t seg = per_item * kMfmaRows;
     p.seg_c = (int)seg;
     p.nseg_c = (int)((nlist + seg - 1) / seg);
