@@ -508,6 +508,25 @@ def test_full_tiles_of_short_vectors(storage, tables, d, nq, nprobe, k, metric):
     ix.close()
 
 
+@pytest.mark.parametrize("storage,tables", [("bf16", True), ("bf16", False), ("f32", True), ("f16", False)])
+@pytest.mark.parametrize("d,rows", [(64, 777), (256, 1), (512, 64), (768, 1001), (1024, 3)])
+def test_refreshed_rows_are_as_freshly_loaded(storage, tables, d, rows):
+    """Squared L2, which reads the norms that the refresh derives again (and the tables): the same bits as from an index
+    that is loaded with the new rows, for rows of one to four steps of a wave."""
+    dtype = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[storage]
+    ix, cent, off, vec, ids, g = _index(5000, d, 9, dtype, d + rows, tables=tables)
+    q = torch.randn(33, d, generator=g, device="cuda")
+    before = ix.search(q, 9, 20, "l2")
+    vec[1500:1500 + rows] = (0.5 * torch.randn(rows, d, generator=g, device="cuda")).to(dtype)        # (nearer than the others)
+    ix.refresh_rows(1500, 1500 + rows)
+    got = ix.search(q, 9, 20, "l2")
+    fresh = _hr().IvfIndex(cent, off, vec, ids, row_tables=tables)
+    want = fresh.search(q, 9, 20, "l2")
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]) and not torch.equal(got[0], before[0])
+    ix.close()
+    fresh.close()
+
+
 @pytest.mark.parametrize("threads", [2, 8, 80])
 def test_refreshes_at_the_same_time_report_their_own_rows(threads):
     """bfloat16 rows with a binary16 table, every thread with rows of its own, on several streams: a value beyond binary16 is
@@ -538,4 +557,26 @@ def test_refreshes_at_the_same_time_report_their_own_rows(threads):
     for p in pool:
         p.join()
     assert not wrong
+    ix.close()
+
+
+@pytest.mark.parametrize("storage", ["f16", "f32"])
+@pytest.mark.parametrize("rows,nlist,nq,nprobe", [(4, 300, 2400, 60), (33, 200, 2700, 60), (80, 50, 4000, 30)])
+def test_full_tiles_of_short_lists(storage, rows, nlist, nq, nprobe):
+    """Two workgroups on a compute unit and lists that are shorter than a block, or end in their second or third one."""
+    dtype, d, k = {"f16": torch.float16, "f32": torch.float32}[storage], 128, 9
+    ix, cent, off, vec, ids, g = _index(rows * nlist, d, nlist, dtype, nq + rows, zipf=0.3)
+    q = torch.randn(nq, d, generator=g, device="cuda")
+    probe = torch.rand(nq, nlist, generator=g, device="cuda").topk(nprobe, dim=1).indices.int()
+    found, score = ix.scan(q, probe, k, "l2")
+    allowed = torch.zeros(nq, nlist, dtype=torch.bool, device="cuda").scatter_(1, probe.long(), True)
+    of_row = torch.repeat_interleave(torch.arange(nlist), off[1:] - off[:-1]).cuda()
+    op, row = (q if storage == "f32" else q.half()).double(), torch.empty_like(ids)
+    row[ids] = torch.arange(len(ids), device="cuda")
+    key = torch.where(allowed[:, of_row], _keys(op, vec.double(), "l2"), -float("inf"))
+    best = torch.topk(key, k, dim=1).values
+    # float32 sums of d products and norms of values near 1: |q||x| + |x|^2 below 3 d, a few 2^-24 of that
+    tol = 3 * d * 2.0 ** -24 * 8
+    assert float((key.gather(1, row[found]) - best).abs().max()) <= 2 * tol
+    assert float((score.double() - ((op ** 2).sum(1, keepdim=True) - best)).abs().max()) <= 2 * tol
     ix.close()
