@@ -1,5 +1,6 @@
 // Host side of the C ABI declared in hr_ivf.h: argument checks, workspace layout, launch
-// sequence.  Nothing here synchronises the caller's stream except hr_ivf_load and hr_ivf_stats.
+// sequence.  Nothing here synchronises the caller's stream except hr_ivf_load, hr_ivf_stats, hr_ivf_profile_end and, with a
+// binary16 table of bfloat16 rows, hr_ivf_refresh_rows.
 #include <algorithm>
 #include <atomic>
 #include <cstdarg>
@@ -100,8 +101,8 @@ static constexpr int kLdsLimit = 160 * 1024;      // LDS per workgroup on gfx950
 // Rows that go straight from HBM to LDS (16-bit storage, and float32 lists split into two
 // binary16 tables at load): 8 waves, the selection buffers in global memory (they are the
 // item's result slots; a wave alone uses those of its columns and candidates are few), and
-// LDS left to as many 16-row buffers as fit: 6 or 4 (blocks in pairs, one barrier per pair),
-// else 3 or 2.  More rows on their way is what counts when few queries share a list and the
+// LDS left to as many buffers of a block of rows as fit, in half of it where two workgroups share a unit: 6 or 4 (blocks in
+// pairs, one barrier per pair), else 3 or 2.  More rows on their way is what counts when few queries share a list and the
 // scan is bound by HBM (measured with the buffers in LDS and 4 row buffers instead: C4 +2 %,
 // the 38 M x 1024 index +2.5 %, C3 +1 %).
 // float32 rows split on the fly are staged through registers into 2 padded buffers: selection
@@ -231,16 +232,22 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
 {
     Plan p{};
     const int64_t nlist = ix->nlist;
-    // coarse step: dense scoring (no selection buffers in LDS) in the widest shape that fits
     // Two workgroups per compute unit where the batch is bound by multiplying and filtering: full tiles (a list is probed by 128
     // queries in the mean) and about 1024 work items of 256 rows or a list each.  4000 queries over 60 of 200 lists of 3000 rows, k
-    // 24: d = 64 686 -> 466 us, 128 733 -> 502, 256 938 -> 649, float32 of d = 128 1688 -> 1198; 1000 over 30, k 1, 188 -> 161, 205 -> 174, 238 -> 201.  With fewer
-    // items, or many neighbours, more of them start from the seeds alone: 500 over 30 of 64 lists, 100000 rows, k 10, 131 -> 139; 500
-    // over 40 of 200 lists, k 100, 343 -> 399; and 30 queries over 20 of 200 lists 112 -> 121.
+    // 24: d = 64 686 -> 466 us, 128 733 -> 502, 256 938 -> 649, float32 of d = 128 1688 -> 1198; 1000 over 30, k 1, 188 -> 161,
+    // 205 -> 174, 238 -> 201.  With fewer items, or many neighbours, more of them start from the seeds alone: 500 over 30 of 64
+    // lists, 100000 rows, k 10, 131 -> 139; 500 over 40 of 200 lists, k 100, 343 -> 399; and 30 queries over 20 of 200 lists
+    // 112 -> 121.  The rule takes lists and probes to be alike, and is off by up to a fifth where they are far from it.  Probes
+    // that are empty, half of them: 4000 over 60 of 200 lists of 3000 rows, d = 128, 490 -> 343, nine in ten: 500 over 60, 147 ->
+    // 147, 97 in 100: 8000 over 32 of 64 lists, 146 -> 161.  Nine lists in ten out of place: 500 over 60 of 200, float32, 141 ->
+    // 151.  Short lists, d = 128, one and two: 4000 over 100 of 200 lists of 50 rows, sizes as 1 / rank^0.8, 280 and 252, 1000 over
+    // 100 of 500 of 80 rows 176 and 203, 4000 over 100 of 2000 of 4 float32 rows 482 and 597.
     const int64_t pairs = nq * nprobe;
-    const bool full_tiles = k <= 24 && pairs >= 128 * nlist && (double)(ix->N / kMinSegRows + nlist) * (double)pairs >= 1024.0 * 128.0 * (double)nlist;
+    const bool full_tiles = k <= 24 && pairs >= 128 * nlist &&
+                            (double)(ix->N / kMinSegRows + nlist) * (double)pairs >= 1024.0 * 128.0 * (double)nlist;
     p.groups_s = full_tiles ? groups_per_cu(scan_dtype(ix), ix->d) : 1;
     const ScanPick ps = pick_shape(scan_dtype(ix), ix->d, k, p.groups_s);
+    // coarse step: dense scoring (no selection buffers in LDS) in the widest shape that fits
     p.shape_c = -1; p.nbuf_c = 0; p.cap_c = 0;
     for (int nbuf = 3; nbuf >= 2 && p.shape_c < 0; nbuf--)
         if (scan_lds_bytes(HR_F16X2, ix->d, 0, SCAN_WIDE, nbuf) <= (size_t)kLdsLimit) { p.shape_c = SCAN_WIDE; p.nbuf_c = nbuf; }
@@ -572,7 +579,7 @@ size_t hr_ivf_workspace_bytes(const hr_ivf_index* ix, int64_t nq, int32_t nprobe
 }  // extern "C"
 
 // ---------------------------------------------------------------------------------------
-// persistent workgroups: one per CU (8-wave shape), or two where LDS lets two 4-wave ones share a CU
+// persistent workgroups: one of eight waves per CU, or `groups` of them, or two of four waves, where LDS has room for them
 static int scan_grid(const hr_ivf_index* ix, size_t lds, int shape, int groups = 1)
 {
     int occ = (int)((size_t)kLdsLimit / lds);
@@ -612,7 +619,8 @@ static int enqueue_coarse(const hr_ivf_index* ix, const Plan& p, char* ws, const
     if (p.shape_c < 0)
         return fail(HR_ERR_UNSUPPORTED, "coarse step does not fit in LDS (d=%d)", ix->d);
     const size_t lds = scan_lds_bytes(HR_F16X2, ix->d, 0, p.shape_c, p.nbuf_c);
-    const bool ride = (ix->d <= 512 || (ix->d <= 768 && nq > 16)) && nq <= p.cchunk && (int64_t)p.nseg_c * p.nqt_c <= scan_grid(ix, lds, p.shape_c) && (uintptr_t)queries % 16 == 0;
+    const bool one_item_each = nq <= p.cchunk && (int64_t)p.nseg_c * p.nqt_c <= scan_grid(ix, lds, p.shape_c);
+    const bool ride = (ix->d <= 512 || (ix->d <= 768 && nq > 16)) && one_item_each && (uintptr_t)queries % 16 == 0;
     const PrepArgs prep = prep_args(ix, p, ws, queries, nq, !ride, scan);
     if (!ride) HR_HIP(launch_prep_queries(prep, s));
     int* zero = (int*)(ws + p.o_zero);
@@ -709,9 +717,6 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, int64_t
     a.slot_cnt = (int*)(ws + p.o_slot_cnt);
     a.slot_ent = (Cand*)(ws + p.o_slot_ent);
     a.slot_stride = p.slot_stride;
-    a.work_counter = zero + ix->nlist + DYN_COUNT + 1;
-    a.list_off = ix->d_list_off;
-    a.bucket_off = b.bucket_off;
     a.bucket_q = b.bucket_q;
     a.dyn = b.dyn;
     a.xq_rec = b.xq_rec;

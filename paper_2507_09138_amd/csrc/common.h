@@ -14,7 +14,7 @@ constexpr int HR_F16X2 = 3;
 constexpr int kMfmaRows = 16;              // rows per MFMA (M of 16x16x32)
 constexpr int kRowPad = 32;                // bytes of LDS padding per staged row: measured conflict-free
                                            // for the 16-rows x 16-byte MFMA fragment reads (16 is 2-way)
-constexpr int kAppendMax = 16;             // most candidates one column can gain per block
+constexpr int kAppendMax = 16;             // most candidates one column can gain per group of kMfmaRows rows
 constexpr int kMinSegRows = 256;           // smallest rows-per-work-item
 constexpr int kItemTarget = 4096;          // aimed number of scan work items per batch
 constexpr int kHistBins = 64;              // per-query histogram of candidate keys (one bin per lane)
@@ -54,16 +54,22 @@ __host__ __device__ constexpr int block_groups(int dtype, int d)
 }
 __host__ __device__ constexpr int block_rows(int dtype, int d) { return kMfmaRows * block_groups(dtype, d); }
 
-// Most workgroups of eight waves on a compute unit: two where a wave gets by with 128 registers (binary16 rows of up to 256
-// elements, float32 rows of 128 with fragments fetched two steps at a time; the other short ones would, with blocks of 32 rows
-// instead of 64, which cost them 3 .. 7 % where two workgroups do not pay).  The waves of one wait for each other at every pair of blocks; the other's fill the pipes meanwhile.  Where
-// that pays is in make_plan.
-__host__ __device__ constexpr int groups_per_cu(int dtype, int d) { return (dtype == HR_F16 && d <= 256) || (dtype == HR_F32 && d == 128) ? 2 : 1; }
+// Most workgroups of eight waves on a compute unit: two where a wave can do with 128 registers (binary16 rows of up to 256
+// elements, of which d = 128 spills two registers, 12 bytes a lane; float32 rows of 128 with fragments fetched two steps at a
+// time; the other short ones could, with blocks of 32 rows instead of 64, which cost them 3 .. 7 % where two workgroups do not
+// pay).  The waves of one wait for each other at every pair of blocks; the other's fill the pipes meanwhile.  Where that pays is
+// in make_plan.  The bound on registers holds for all launches of the kernel: without it binary16 searches of d = 128 that put
+// one workgroup on a unit took 0.97 .. 1.03 of the time, 1.00 in the mean of 45 (1 .. 500 queries, 46 .. 526 us).
+__host__ __device__ constexpr int groups_per_cu(int dtype, int d)
+{
+    return (dtype == HR_F16 && d <= 256) || (dtype == HR_F32 && d == 128) ? 2 : 1;
+}
 
 // k-steps (of 32 elements) whose row fragments a wave fetches from LDS together
 __host__ __device__ constexpr int scan_group(int dtype, int ksteps, int nw)
 {
-    if (ksteps < 16 && nw == 8) return dtype == HR_F32 && ksteps == 4 ? 2 : 4;                           // (of a block of several groups of rows: 8 or 16 k-steps in all)
+    // (blocks of several groups of rows: 8 or 16 k-steps in all)
+    if (ksteps < 16 && nw == 8) return dtype == HR_F32 && ksteps == 4 ? 2 : 4;
     if (ksteps < 8) return 4;
     if (nw == 8 && dtype == HR_F32 && ksteps >= 24) return 2;       // (leaves registers for a second row block in flight)
     // (what a long operand in two parts leaves: 253 of 256 registers at 24 k-steps, none spilled)
@@ -149,8 +155,6 @@ struct ScanArgs {
     int slot_stride;            // entries per slot: k, or cap where that is small (no cut at the end of an item)
     int* work_counter;          // dense mode: items popped beyond the first of every workgroup (zeroed before launch)
     // bucket mode
-    const int* list_off;        // [nlist+1] row offsets
-    const int* bucket_off;      // [nlist+1]
     const int* bucket_q;        // [pairs] query index per bucket entry
     const int* dyn;             // device scalars: [0] = items, [1] = rows per segment
     const int4* xq_rec;         // [8][xq_stride][2] the items queued per XCD, each a record of two int4:

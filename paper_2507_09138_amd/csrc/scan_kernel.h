@@ -269,15 +269,16 @@ template <> struct StoreTraits<HR_BF16> { static constexpr int esize = 2, planes
 template <> struct StoreTraits<HR_F16X2> { static constexpr int esize = 2, planes = 2; };
 
 // NW = waves per workgroup (4: one per SIMD, each may use all 512 registers; 8: two per SIMD
-// with 256 registers each, so that one wave's MFMAs run while the other selects or waits).
+// with 256 registers each, so that one wave's MFMAs run while the other selects or waits, or, two
+// workgroups on a unit, four with 128: see groups_per_cu).
 // NCS = 16-column MFMA sets per wave (1 or 2).  Every wave owns NCS * nc query columns, so a
 // work item covers NW * NCS * nc queries of a bucket; all waves share the staged rows.
 //
-// Two ways of staging a block of 16 rows in LDS:
+// Two ways of staging a block of rows (16, or up to 64 short ones: see block_groups) in LDS:
 //   direct (16-bit storage): global_load_lds moves 16-byte chunks from HBM straight into LDS,
 //     no registers and no LDS store instructions in between.  Such a load writes the 64 chunks
 //     of a wave next to each other, so rows cannot be padded; instead chunk c of row r sits at
-//     position c ^ (r & 15) of its row, which spreads the 16 rows of an MFMA fragment read over
+//     position c ^ (r & 15) of its row (d = 64: r & 7), which spreads the 16 rows of an MFMA fragment read over
 //     all banks.  Up to four blocks are in flight or waiting in LDS ahead of the one in use.
 //   through registers (float32 storage): rows are split into binary16 hi and lo planes on the
 //     way, from a ring of prefetch registers into two padded buffers.
@@ -381,11 +382,11 @@ __device__ __forceinline__ void stage_block(char* buf, const u32x4 (&regs)[S::nl
     }
 }
 
-// 16 staged rows x NA column sets x d: the MFMA chain of one block.  acc[s][*] are the partial
-// accumulators of set s (for HR_F32: [0] hi-row and [1] lo-row products; else summed at the end).  The row fragments
+// The staged rows x NA column sets x d: the MFMA chains of one block.  acc[s][j][*] are the partial
+// accumulators of set s and the j-th 16 rows (for HR_F32: [0] hi-row and [1] lo-row products; else summed at the end).  The row fragments
 // are fetched from LDS a group of k-steps ahead of the MFMAs that use them (the scheduling
 // barriers keep the compiler from sinking each read next to its use, which would expose the
-// LDS latency 24 times per block).  The fragment of k-step t is at ap[t & 3] + (t >> 2) * 256:
+// LDS latency 24 times per block).  The fragment of k-step t of the first 16 rows is at ap[t & 3] + (t >> 2) * 256:
 // with padded rows the four bases are 64 bytes apart, with the xor-ed chunk positions of the
 // direct staging they are permuted per lane.
 template <int DT, int KSTEPS, int NCS, int NA, typename S>
@@ -673,7 +674,8 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
                 seg = item / a.dense_nqt;
                 qt = item - seg * a.dense_nqt;
             } else {
-                const int nseg = a.dense_items / a.dense_nqt, fewer = a.dense_nqt / a.dense_groups, more = a.dense_nqt - fewer * a.dense_groups;
+                const int nseg = a.dense_items / a.dense_nqt;
+                const int fewer = a.dense_nqt / a.dense_groups, more = a.dense_nqt - fewer * a.dense_groups;
                 const int wide = more * (fewer + 1) * nseg;             // items of those groups
                 const int tiles = item < wide ? fewer + 1 : fewer, at = item < wide ? item : item - wide;
                 const int grp = at / (tiles * nseg), rest = at - grp * tiles * nseg;
@@ -698,14 +700,13 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
         const char* src = (const char*)a.rows + (size_t)row0 * S::rowb;
         const char* src_lo = S::planes == 2 ? (const char*)a.rows_lo + (size_t)row0 * S::rowb : src;
 
-        // ---- staging.  Requests for a block past the end of the segment fetch its last block
-        // again (nobody reads the copy): every wave then has the same, fixed number of loads
-        // in flight at every point of the loop, which is what the wait counts below rely on.
+        // ---- staging.  Requests for a block past the end of the segment fetch its last block again, or, where
+        // blocks have several groups of rows, one chunk for all lanes, as a short list is past its end from the
+        // start (nobody reads the copy): every wave then has the same, fixed number of loads in flight at every
+        // point of the loop, which is what the wait counts below rely on.
         //
-        // direct: block blk -> buffer buf, straight from HBM; the squared norms of its rows go
-        // to a place of this wave's own (each wave fetches its own copy: 64 bytes)
+        // direct: block blk -> buffer buf, straight from HBM, and the squared norms of its rows (64 .. 256 bytes) beside it
         const bool stream_once = !DENSE && w <= S::cw;   // the only work item that reads these rows
-        // (blocks of several groups of rows: with one 16-byte chunk for all lanes, as a short list is past its end from the start)
         auto fill_direct = [&](int blk, int buf) __attribute__((always_inline)) {
             if (RB > 1 && blk >= nblk) {
 #pragma unroll
@@ -972,6 +973,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
                         }
                         add += __builtin_popcountll(mine);
                     }
+                    static_assert(kAppendMax >= kMfmaRows, "a column has room for what one group of rows appends");
                     ccnt[s] += add;
                     unsigned long long full = __builtin_amdgcn_ballot_w64(lane < NC && ccnt[s] > a.cap - kAppendMax);
                     if (full) wave_sync();
