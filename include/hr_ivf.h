@@ -68,10 +68,10 @@ enum {
  * centroids, list_vectors and list_ids are BORROWED: they must stay valid and unchanged until
  * hr_ivf_free.  The library allocates (hipMalloc) derived tables: device copies of the offsets,
  * 4 bytes per row / per centroid of squared norms, the centroids as two binary16 tables, 8 bytes
- * per list of access counters.  Nothing the size of list_vectors, unless the caller asks for it:
- * with dtype = HR_F32 | HR_LOAD_ROW_TABLES the rows are also kept as two binary16 tables (hi and
- * scaled lo part: N*d*4 bytes, as much as list_vectors itself) which the scan then reads instead of
- * splitting every row block on the fly: same products in the same order, the same bits, faster.
+ * per list of access counters (HR_F32: 8 more of bounds).  Nothing the size of list_vectors, unless the caller asks for it:
+ * with dtype = HR_F32 | HR_LOAD_ROW_TABLES the rows are also kept rounded to binary16 (N*d*2 bytes, half of
+ * list_vectors) for the scan to read, which looks for candidates with the rounded rows either way and scores those that
+ * may be among the best from the float32 rows: the same results, faster.
  * With HR_BF16 | HR_LOAD_ROW_TABLES the rows are also kept as one binary16 table (N*d*2 bytes; every
  * bfloat16 value of magnitude 2^-14 .. 65504 is a binary16 value, smaller ones are rounded to a
  * multiple of 2^-24): the lists are then multiplied with the query rounded to binary16 (as HR_F16
@@ -217,7 +217,8 @@ int hr_ivf_split_probes(const hr_ivf_index* index, const int32_t* probe_ids, int
  * hr_ivf_refresh_rows — after the caller has replaced the vectors of rows row_begin ..
  * row_end-1 in list_vectors (a cluster loaded asynchronously into the place of another one of
  * the same length: the index loading interface of Section 5), recompute what the library
- * derives from them (squared norms; the binary16 row tables of HR_LOAD_ROW_TABLES).  Enqueued on
+ * derives from them (squared norms; with HR_F32 what bounds the scores of a list's rows, which searches with either
+ * metric rely on; the binary16 row tables of HR_LOAD_ROW_TABLES).  Enqueued on
  * `stream`: put it behind the copy, and the next search behind it.  list_ids is read at search time
  * and needs no refresh; list_offsets cannot change.  Only with a binary16 table of bfloat16 rows the
  * call also waits for the stream, to learn whether a new value exceeds 65504: HR_ERR_UNSUPPORTED

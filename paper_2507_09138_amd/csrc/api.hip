@@ -43,10 +43,11 @@ hipError_t hr::static_scratch_address(int dev, void** out)
 }
 
 namespace hr {
-hipError_t launch_scan_f32(int d, const ScanArgs& a, int shape, int grid, size_t lds, hipStream_t s);
-hipError_t launch_scan_f16(int d, const ScanArgs& a, int shape, int grid, size_t lds, hipStream_t s);
-hipError_t launch_scan_bf16(int d, const ScanArgs& a, int shape, int grid, size_t lds, hipStream_t s);
-hipError_t launch_scan_f16x2(int d, const ScanArgs& a, int shape, int grid, size_t lds, hipStream_t s);
+hipError_t launch_scan_f32(int d, const ScanArgs& a, int grid, size_t lds, hipStream_t s);
+hipError_t launch_scan_f16(int d, const ScanArgs& a, int grid, size_t lds, hipStream_t s);
+hipError_t launch_scan_bf16(int d, const ScanArgs& a, int grid, size_t lds, hipStream_t s);
+hipError_t launch_scan_f16x2(int d, const ScanArgs& a, int grid, size_t lds, hipStream_t s);
+hipError_t launch_scan_f16hi(int d, const ScanArgs& a, int grid, size_t lds, hipStream_t s);
 
 hipError_t launch_seed_f32(int d, const SeedArgs& a, hipStream_t s);
 hipError_t launch_seed_f16(int d, const SeedArgs& a, hipStream_t s);
@@ -62,68 +63,40 @@ hipError_t launch_seed(int dtype, int d, const SeedArgs& a, hipStream_t s)
     }
 }
 
-hipError_t launch_scan(int dtype, int d, const ScanArgs& a, int shape, int grid, size_t lds, hipStream_t s)
+hipError_t launch_scan(int dtype, int d, const ScanArgs& a, int grid, size_t lds, hipStream_t s)
 {
     switch (dtype) {
-    case HR_F32: return launch_scan_f32(d, a, shape, grid, lds, s);
-    case HR_F16: return launch_scan_f16(d, a, shape, grid, lds, s);
-    case HR_BF16: return launch_scan_bf16(d, a, shape, grid, lds, s);
-    case HR_F16X2: return launch_scan_f16x2(d, a, shape, grid, lds, s);
+    case HR_F32: return launch_scan_f32(d, a, grid, lds, s);
+    case HR_F16: return launch_scan_f16(d, a, grid, lds, s);
+    case HR_BF16: return launch_scan_bf16(d, a, grid, lds, s);
+    case HR_F16X2: return launch_scan_f16x2(d, a, grid, lds, s);
+    case HR_F16HI: return launch_scan_f16hi(d, a, grid, lds, s);
     default: return hipErrorInvalidValue;
     }
 }
 
-// LDS bytes of one workgroup of the given shape with nbuf staging buffers and selection
-// buffers of cap entries per query column (must match the carve-up at the top of k_scan and
+// LDS bytes of one workgroup with nbuf staging buffers (must match the carve-up at the top of k_scan and
 // ScanShape::buf_bytes)
-size_t scan_lds_bytes(int dtype, int d, int cap, int shape, int nbuf)
+size_t scan_lds_bytes(int dtype, int d, int nbuf)
 {
-    const int nw = shape_waves(shape);
-    const size_t rows = block_rows(dtype, d);
-    size_t buf;
-    if (dtype == HR_F32) {
-        buf = rows * (d * 2 + kRowPad) * 2;
-    } else if (dtype == HR_F16X2) {
-        const int chunks = (int)rows * d * 2 / 16, threads = nw * 64;
-        buf = (size_t)((chunks + threads - 1) / threads) * threads * 16 * 2;
-    } else {
-        const int chunks = (int)rows * d * 2 / 16, threads = nw * 64;
-        buf = (size_t)((chunks + threads - 1) / threads) * threads * 16;
-    }
-    const size_t cw = (size_t)cols_per_set(dtype, d) * shape_sets(shape);
-    return nbuf * buf + cw * cap * sizeof(Cand) + nbuf * rows * sizeof(float) + 32;
+    const size_t rows = block_rows(dtype, d), threads = kScanWaves * 64;
+    const size_t chunks = rows * d * (dtype == HR_F32 ? 4 : 2) / 16;
+    const size_t buf = (chunks + threads - 1) / threads * threads * 16 * (dtype == HR_F16X2 ? 2 : 1);
+    return nbuf * (buf + rows * sizeof(float)) + 32;
 }
 }  // namespace hr
 
 static constexpr int kLdsLimit = 160 * 1024;      // LDS per workgroup on gfx950
 
-// Workgroup shape, number of staging buffers and selection buffers of a list scan.
-// Rows that go straight from HBM to LDS (16-bit storage, and float32 lists split into two
-// binary16 tables at load): 8 waves, the selection buffers in global memory (they are the
-// item's result slots; a wave alone uses those of its columns and candidates are few), and
-// LDS left to as many buffers of a block of rows as fit, in half of it where two workgroups share a unit: 6 or 4 (blocks in
-// pairs, one barrier per pair), else 3 or 2.  More rows on their way is what counts when few queries share a list and the
-// scan is bound by HBM (measured with the buffers in LDS and 4 row buffers instead: C4 +2 %,
-// the 38 M x 1024 index +2.5 %, C3 +1 %).
-// float32 rows split on the fly are staged through registers into 2 padded buffers: selection
-// buffers in LDS for small k when they fit (8 waves, else 4 with half the columns), in global
-// memory for large k.  shape -1 = no fit.
-struct ScanPick { int shape, nbuf, cap, gsel; };
-static ScanPick pick_shape(int dtype, int d, int k, int groups)
+// Staging buffers of a list scan: as many as fit in LDS, or in half of it where two workgroups share a unit: 6 or 4 (blocks in
+// pairs, one barrier per pair), else 3 or 2 (those of 16 float32 rows of d = 1024 are 64 KB).  More rows on their way is what
+// counts when few queries share a list and the scan is bound by HBM (measured with the selection buffers in LDS and 4 row
+// buffers instead of 6: C4 +2 %, the 38 M x 1024 index +2.5 %, C3 +1 %).
+static int pick_buffers(int dtype, int d, int groups)
 {
-    const int cap = hr::sel_cap(k);
-    if (dtype != HR_F32) {
-        for (int nbuf : {6, 4, 3, 2})
-            if (hr::scan_lds_bytes(dtype, d, 0, hr::SCAN_WIDE, nbuf) <= (size_t)kLdsLimit / groups) return {hr::SCAN_WIDE, nbuf, cap, 1};
-        return {-1, 0, 0, 0};
-    }
-    if (cap > 64) {
-        if (hr::scan_lds_bytes(dtype, d, 0, hr::SCAN_WIDE, 2) <= (size_t)kLdsLimit) return {hr::SCAN_WIDE, 2, cap, 1};
-        return {-1, 0, 0, 0};
-    }
-    for (int shape : {hr::SCAN_WIDE, hr::SCAN_NARROW})
-        if (hr::scan_lds_bytes(dtype, d, cap, shape, 2) <= (size_t)kLdsLimit) return {shape, 2, cap, 0};
-    return {-1, 0, 0, 0};
+    for (int nbuf : {6, 4, 3})
+        if (hr::scan_lds_bytes(dtype, d, nbuf) <= (size_t)kLdsLimit / groups) return nbuf;
+    return 2;
 }
 
 using namespace hr;
@@ -160,14 +133,14 @@ struct hr_ivf_index {
     float* d_cent_norm;    // [nlist]
     void* d_cent_hi;       // [nlist, d] binary16: centroids rounded
     void* d_cent_lo;       // [nlist, d] binary16: (centroid - hi) * 2^11
-    void* d_vec_hi;        // float32 lists only, when memory allows: [N, d] binary16 hi and scaled lo tables of the
-    void* d_vec_lo;        // rows (the split the scan would otherwise redo for every block it stages); else null
+    void* d_vec_hi;        // float32 lists only, when asked for and memory allows: [N, d] the rows rounded to binary16; else null
     void* d_vec16;         // bfloat16 lists only, when memory and the value range allow: [N, d] the rows as binary16
     int* d_flag;           // two device ints: [0] a bfloat16 value did not fit binary16, [1] a negative label
     // with d_vec16: report words of hr_ivf_refresh_rows, one for each call under way (host memory that kernels write; bit i of
     // over_used: word i belongs to a call), else null
     int *h_over, *d_over;  // their address on the host and on the device
     std::atomic<uint64_t> over_used;
+    float2* d_list_bound;  // float32 lists: [nlist] what scan_slack needs to know of the list's rows, else null
     unsigned long long* d_hits;   // [nlist] probes per list since load / last reset
     int* d_resident;       // [nlist] 1 = the list's vectors are in place (all lists, until the caller says otherwise)
     int num_cus;
@@ -180,9 +153,9 @@ struct hr_ivf_index {
 };
 
 // storage type the list scan runs on
-static int scan_dtype(const hr_ivf_index* ix) { return ix->d_vec_hi ? (int)HR_F16X2 : (ix->d_vec16 ? (int)HR_F16 : ix->dtype); }
+static int scan_dtype(const hr_ivf_index* ix) { return ix->d_vec_hi ? (int)HR_F16HI : (ix->d_vec16 ? (int)HR_F16 : ix->dtype); }
 // form of the query operand the list scan multiplies (what k_prep_queries is asked for)
-static int operand_dtype(const hr_ivf_index* ix) { const int s = scan_dtype(ix); return s == HR_F16X2 ? (int)HR_F32 : s; }
+static int operand_dtype(const hr_ivf_index* ix) { const int s = scan_dtype(ix); return s == HR_F16HI ? (int)HR_F32 : s; }
 // rows and their type for the kernels that read single rows (threshold seeding, rescoring)
 static int row_dtype(const hr_ivf_index* ix) { return ix->d_vec16 ? (int)HR_F16 : ix->dtype; }
 static const void* row_table(const hr_ivf_index* ix) { return ix->d_vec16 ? ix->d_vec16 : ix->vectors; }
@@ -197,14 +170,13 @@ static size_t align_up(size_t v) { return (v + HR_WORKSPACE_ALIGN - 1) & ~(size_
 // Layout of the caller's workspace for one batch shape.  Offsets in bytes.
 struct Plan {
     // coarse step: centroid table scanned with all queries as one dense bucket
-    int shape_c /* workgroup shape, -1 = no fit */, nbuf_c, cap_c, cw_c, cols_c, nqt_c, seg_c, nseg_c;
+    int nbuf_c, cw_c, cols_c, nqt_c, seg_c, nseg_c;
     // list scan
-    int shape_s, groups_s, nbuf_s, cap_s, gsel_s, cw_s, item_cap, item_target, few_items, min_rows;
-    int slot_stride;                // entries per result slot of the list scan
+    int groups_s, nbuf_s, cap_s, cw_s, item_cap, item_target, few_items, min_rows;
     int slot_cap;                   // result slots: one per (list segment, query of the list's bucket)
     size_t o_zero, n_zero;          // ints cleared per call: list_w[nlist], dyn[DYN_COUNT], counters[8], ..., then
     size_t zoff_round, zoff_hist, zoff_hpar;   // (in ints from o_zero) round counters of the queues, per-query key histograms and their parameters
-    size_t o_thr;                   // 2*nq ints set to "-inf"
+    size_t o_thr;                   // nq floats (qlo), then nq ints set to "-inf"
     size_t o_qop_c, o_qnorm_c, o_qop_s, o_qnorm_s;
     size_t o_probe;
     size_t o_pair_entry, o_bucket_off, o_bucket_q, o_slot_base, o_xq;
@@ -246,12 +218,9 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     const bool full_tiles = k <= 24 && pairs >= 128 * nlist &&
                             (double)(ix->N / kMinSegRows + nlist) * (double)pairs >= 1024.0 * 128.0 * (double)nlist;
     p.groups_s = full_tiles ? groups_per_cu(scan_dtype(ix), ix->d) : 1;
-    const ScanPick ps = pick_shape(scan_dtype(ix), ix->d, k, p.groups_s);
-    // coarse step: dense scoring (no selection buffers in LDS) in the widest shape that fits
-    p.shape_c = -1; p.nbuf_c = 0; p.cap_c = 0;
-    for (int nbuf = 3; nbuf >= 2 && p.shape_c < 0; nbuf--)
-        if (scan_lds_bytes(HR_F16X2, ix->d, 0, SCAN_WIDE, nbuf) <= (size_t)kLdsLimit) { p.shape_c = SCAN_WIDE; p.nbuf_c = nbuf; }
-    p.shape_s = ps.shape; p.nbuf_s = ps.nbuf; p.cap_s = ps.gsel && lim.cap > 0 ? lim.cap : ps.cap; p.gsel_s = ps.gsel;
+    p.nbuf_s = pick_buffers(scan_dtype(ix), ix->d, p.groups_s);
+    p.cap_s = lim.cap > 0 ? lim.cap : sel_cap(scan_dtype(ix), k);
+    p.nbuf_c = scan_lds_bytes(HR_F16X2, ix->d, 3) <= (size_t)kLdsLimit ? 3 : 2;
     // queries per coarse chunk: the [chunk, nlist] key table stays within its limit, 512 MiB by default (the more
     // queries per launch the better both kernels fill the device: 16384 lists, four chunks of 2048 queries 1.88 ms,
     // one of 8192 1.45 ms)
@@ -271,7 +240,7 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     // up to whole blocks takes as many from the device (1 .. 8192 queries, 64 .. 65536 centroids, 172 cases: as fast in the
     // mean, 0.94 .. 1.04; 777 centroids, d = 64, 300 queries 15.3 -> 16.3, 16384, 3001 122.1 -> 117.0).
     const int64_t nblk = (nlist + kMfmaRows - 1) / kMfmaRows, cus = ix->num_cus;
-    const int full = cols_per_set(HR_F16X2, ix->d) * shape_sets(p.shape_c < 0 ? 0 : p.shape_c), waves = shape_waves(p.shape_c < 0 ? 0 : p.shape_c);
+    const int full = tile_cols(HR_F16X2, ix->d);
     int64_t per_item = nblk;                        // blocks
     double least = 0.0;
     p.cw_c = full;
@@ -287,12 +256,12 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
             if (least == 0.0 || cost < least) { least = cost; per_item = blocks; p.cw_c = cw; }
         }
     }
-    p.cols_c = p.cw_c / waves;
+    p.cols_c = p.cw_c / kScanWaves;
     p.nqt_c = (int)((p.cchunk + p.cw_c - 1) / p.cw_c);
     const int64_t seg = per_item * kMfmaRows;
     p.seg_c = (int)seg;
     p.nseg_c = (int)((nlist + seg - 1) / seg);
-    p.cw_s = cols_per_set(scan_dtype(ix), ix->d) * shape_sets(p.shape_s < 0 ? 0 : p.shape_s);
+    p.cw_s = tile_cols(scan_dtype(ix), ix->d);
     // Work items: sum over probed lists of segments x query tiles.  Segments have at least C / item_target rows, C =
     // sum of rows x tiles, so there are at most item_target items plus one per (list, tile) for the ragged ends.
     // Result slots: sum of segments x bucket width <= cw x item_target, plus one per pair for the ragged ends.
@@ -342,8 +311,7 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     p.o_ckeys = take((size_t)p.cchunk * nlist * 4);
     const size_t slots = (size_t)p.slot_cap;
     p.o_slot_cnt = take(slots * 4);
-    p.slot_stride = p.gsel_s || (p.cap_s <= 64 && p.cap_s > k) ? p.cap_s : k;   // whole selection buffers, nothing to cut (else: k)
-    p.o_slot_ent = take(slots * (size_t)p.slot_stride * sizeof(Cand));
+    p.o_slot_ent = take(slots * (size_t)p.cap_s * sizeof(Cand));
     p.total = o;
     return p;
 }
@@ -423,6 +391,7 @@ int hr_ivf_load(const float* centroids, const int64_t* list_offsets, const void*
     }
     if (e == hipSuccess) e = hipMalloc(&ix->d_list_off, (size_t)(nlist + 1) * 4);
     if (e == hipSuccess) e = hipMalloc(&ix->d_row_norm, (size_t)(N > 0 ? N : 1) * 4);
+    if (e == hipSuccess && dtype == HR_F32) e = hipMalloc(&ix->d_list_bound, (size_t)nlist * sizeof(float2));
     if (e == hipSuccess) e = hipMalloc(&ix->d_cent_norm, (size_t)nlist * 4);
     if (e == hipSuccess) e = hipMalloc(&ix->d_cent_hi, (size_t)nlist * d * 2);
     if (e == hipSuccess) e = hipMalloc(&ix->d_cent_lo, (size_t)nlist * d * 2);
@@ -434,23 +403,23 @@ int hr_ivf_load(const float* centroids, const int64_t* list_offsets, const void*
     if (e == hipSuccess) e = hipMemsetAsync(ix->d_flag, 0, 2 * sizeof(int), s);
     if (e == hipSuccess) e = launch_check_labels(list_ids, N, ix->d_flag + 1, s);
     if (e == hipSuccess) e = hipMemcpyAsync(ix->d_list_off, h_off, (size_t)(nlist + 1) * 4, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = launch_row_norms(list_vectors, dtype, N, d, ix->d_row_norm, s);
-    if (e == hipSuccess) e = launch_row_norms(centroids, HR_F32, nlist, d, ix->d_cent_norm, s);
-    if (e == hipSuccess) e = launch_split_f32(centroids, nlist * d, ix->d_cent_hi, ix->d_cent_lo, s);
-    if (e == hipSuccess && dtype == HR_F32 && N > 0 && row_tables) {
-        // float32 lists, when the caller asks for row tables: the scan multiplies binary16 hi and lo parts
-        // of the rows.  Made once here (same bytes again: 2 + 2 per element) they go straight from HBM to
-        // LDS like 16-bit lists; made on the fly they pass through registers for every block.  Only when
-        // that leaves at least half of the free device memory; otherwise the scan splits on the fly.
+    if (e == hipSuccess && dtype == HR_F32) {
+        // float32 lists, when the caller asks for row tables: the scan multiplies the rows rounded to binary16.  Rounded once
+        // here (half the bytes again) they go straight from HBM to LDS like 16-bit lists; else the scan moves
+        // float32 rows.  Only when that leaves at least half of the free device memory.
         const size_t bytes = (size_t)N * d * 2;
         size_t free_b = 0, total_b = 0;
-        if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && 2 * bytes <= free_b / 2) {
+        if (row_tables && N > 0 && hipMemGetInfo(&free_b, &total_b) == hipSuccess && bytes <= free_b / 2) {
             if (hipMalloc(&ix->d_vec_hi, bytes) != hipSuccess) ix->d_vec_hi = nullptr;
-            if (ix->d_vec_hi && hipMalloc(&ix->d_vec_lo, bytes) != hipSuccess) { (void)hipFree(ix->d_vec_hi); ix->d_vec_hi = nullptr; ix->d_vec_lo = nullptr; }
             if (!ix->d_vec_hi) (void)hipGetLastError();          // (not an error of the load: the other path is taken)
-            else e = launch_split_f32((const float*)list_vectors, N * d, ix->d_vec_hi, ix->d_vec_lo, s);
         }
+        e = hipMemsetAsync(ix->d_list_bound, 0, (size_t)nlist * sizeof(float2), s);
+        if (e == hipSuccess) e = launch_list_bounds((const float*)list_vectors, d, 0, N, ix->d_list_off, (int)nlist, ix->d_row_norm, (uint2*)ix->d_list_bound, ix->d_vec_hi, s);
+    } else if (e == hipSuccess) {
+        e = launch_row_norms(list_vectors, dtype, N, d, ix->d_row_norm, s);
     }
+    if (e == hipSuccess) e = launch_row_norms(centroids, HR_F32, nlist, d, ix->d_cent_norm, s);
+    if (e == hipSuccess) e = launch_split_f32(centroids, nlist * d, ix->d_cent_hi, ix->d_cent_lo, s);
     if (e == hipSuccess && dtype == HR_BF16 && N > 0 && row_tables) {
         // bfloat16 lists, when the caller asks for row tables: as binary16 (same bytes again) every value
         // keeps its 8 significant bits, and the scan can multiply them with the query rounded to binary16
@@ -479,13 +448,13 @@ int hr_ivf_load(const float* centroids, const int64_t* list_offsets, const void*
     if (e != hipSuccess || flags[1]) {
         if (ix->d_list_off) (void)hipFree(ix->d_list_off);
         if (ix->d_row_norm) (void)hipFree(ix->d_row_norm);
+        if (ix->d_list_bound) (void)hipFree(ix->d_list_bound);
         if (ix->d_cent_norm) (void)hipFree(ix->d_cent_norm);
         if (ix->d_cent_hi) (void)hipFree(ix->d_cent_hi);
         if (ix->d_cent_lo) (void)hipFree(ix->d_cent_lo);
         if (ix->d_hits) (void)hipFree(ix->d_hits);
         if (ix->d_resident) (void)hipFree(ix->d_resident);
         if (ix->d_vec_hi) (void)hipFree(ix->d_vec_hi);
-        if (ix->d_vec_lo) (void)hipFree(ix->d_vec_lo);
         if (ix->d_vec16) (void)hipFree(ix->d_vec16);
         if (ix->d_flag) (void)hipFree(ix->d_flag);
         if (ix->h_over) (void)hipHostFree(ix->h_over);
@@ -550,13 +519,13 @@ int hr_ivf_free(hr_ivf_index* ix)
     ix->magic = 0;
     (void)hipFree(ix->d_list_off);
     (void)hipFree(ix->d_row_norm);
+    if (ix->d_list_bound) (void)hipFree(ix->d_list_bound);
     (void)hipFree(ix->d_cent_norm);
     (void)hipFree(ix->d_cent_hi);
     (void)hipFree(ix->d_cent_lo);
     (void)hipFree(ix->d_hits);
     (void)hipFree(ix->d_resident);
     if (ix->d_vec_hi) (void)hipFree(ix->d_vec_hi);
-    if (ix->d_vec_lo) (void)hipFree(ix->d_vec_lo);
     if (ix->d_vec16) (void)hipFree(ix->d_vec16);
     if (ix->d_flag) (void)hipFree(ix->d_flag);
     if (ix->h_over) (void)hipHostFree(ix->h_over);
@@ -579,14 +548,11 @@ size_t hr_ivf_workspace_bytes(const hr_ivf_index* ix, int64_t nq, int32_t nprobe
 }  // extern "C"
 
 // ---------------------------------------------------------------------------------------
-// persistent workgroups: one of eight waves per CU, or `groups` of them, or two of four waves, where LDS has room for them
-static int scan_grid(const hr_ivf_index* ix, size_t lds, int shape, int groups = 1)
+// persistent workgroups: one per CU, or `groups` of them where LDS has room for them
+static int scan_grid(const hr_ivf_index* ix, size_t lds, int groups = 1)
 {
-    int occ = (int)((size_t)kLdsLimit / lds);
-    if (occ < 1) occ = 1;
-    const int most = shape == SCAN_WIDE ? groups : 2;
-    if (occ > most) occ = most;
-    return ix->num_cus * occ;
+    const int occ = (int)((size_t)kLdsLimit / lds);
+    return ix->num_cus * (occ < 1 ? 1 : (occ < groups ? occ : groups));
 }
 
 // query operands for the coarse step (coarse) and / or the list scan (scan), and, in the same launch, what the
@@ -602,7 +568,8 @@ static PrepArgs prep_args(const hr_ivf_index* ix, const Plan& p, char* ws, const
     a.qop_scan = (scan && !f32) ? ws + p.o_qop_s : nullptr;
     a.qnorm_scan = scan ? (float*)(ws + p.o_qnorm_s) : nullptr;
     a.zero = (int*)(ws + p.o_zero); a.n_zero = (int64_t)p.n_zero;
-    a.neg = (int*)(ws + p.o_thr); a.n_neg = nq * 2; a.neg_value = (int)kKeyNegInf;
+    a.qlo = scan && scan_bounded(scan_dtype(ix)) ? (float*)(ws + p.o_thr) : nullptr;
+    a.neg = (int*)(ws + p.o_thr) + nq; a.n_neg = nq; a.neg_value = (int)kKeyNegInf;
     return a;
 }
 
@@ -616,10 +583,8 @@ static PrepArgs prep_args(const hr_ivf_index* ix, const Plan& p, char* ws, const
 static int enqueue_coarse(const hr_ivf_index* ix, const Plan& p, char* ws, const float* queries, int64_t nq, int nprobe,
                           int metric, bool scan, int32_t* out_probe, float* out_scores, hipStream_t s)
 {
-    if (p.shape_c < 0)
-        return fail(HR_ERR_UNSUPPORTED, "coarse step does not fit in LDS (d=%d)", ix->d);
-    const size_t lds = scan_lds_bytes(HR_F16X2, ix->d, 0, p.shape_c, p.nbuf_c);
-    const bool one_item_each = nq <= p.cchunk && (int64_t)p.nseg_c * p.nqt_c <= scan_grid(ix, lds, p.shape_c);
+    const size_t lds = scan_lds_bytes(HR_F16X2, ix->d, p.nbuf_c);
+    const bool one_item_each = nq <= p.cchunk && (int64_t)p.nseg_c * p.nqt_c <= scan_grid(ix, lds);
     const bool ride = (ix->d <= 512 || (ix->d <= 768 && nq > 16)) && one_item_each && (uintptr_t)queries % 16 == 0;
     const PrepArgs prep = prep_args(ix, p, ws, queries, nq, !ride, scan);
     if (!ride) HR_HIP(launch_prep_queries(prep, s));
@@ -634,7 +599,6 @@ static int enqueue_coarse(const hr_ivf_index* ix, const Plan& p, char* ws, const
         a.row_norm = ix->d_cent_norm;
         a.qop = ws + p.o_qop_c + (size_t)q0 * 2 * ix->d * 2;
         a.queries = ride ? queries : nullptr;
-        a.thr = (uint32_t*)(ws + p.o_thr);
         a.work_counter = zero + ix->nlist + DYN_COUNT;
         a.dense_items = p.nseg_c * nqt;
         a.dense_nqt = nqt;
@@ -651,9 +615,9 @@ static int enqueue_coarse(const hr_ivf_index* ix, const Plan& p, char* ws, const
         a.nq = (int)n; a.k = nprobe; a.cap = 0; a.l2 = metric == HR_METRIC_L2;
         a.nbuf = p.nbuf_c;
         if (q0 > 0) HR_HIP(launch_fill_i32(a.work_counter, 1, 0, s));
-        int grid = scan_grid(ix, lds, p.shape_c);
+        int grid = scan_grid(ix, lds);
         if (grid > a.dense_items) grid = a.dense_items;
-        HR_HIP(launch_scan(HR_F16X2, ix->d, a, p.shape_c, grid, lds, s));
+        HR_HIP(launch_scan(HR_F16X2, ix->d, a, grid, lds, s));
         HR_HIP(launch_topk_rows(ckeys, (const float*)(ws + p.o_qnorm_c) + q0, out_probe + q0 * nprobe,
                                 out_scores ? out_scores + q0 * nprobe : nullptr, n, (int)ix->nlist, nprobe,
                                 a.l2, ride ? &prep : nullptr, s));
@@ -662,18 +626,16 @@ static int enqueue_coarse(const hr_ivf_index* ix, const Plan& p, char* ws, const
 }
 
 // grouping by list + cluster-major scan + per-query merge
-static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, int64_t nq, const int32_t* probe,
+static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, const float* queries, int64_t nq, const int32_t* probe,
                         int nprobe, int k, int metric, int64_t* out_ids, float* out_scores, hipStream_t s,
                         bool carried = false, int32_t* io_rows = nullptr)
 {
-    if (p.shape_s < 0)
-        return fail(HR_ERR_UNSUPPORTED, "list scan does not fit in LDS (d=%d, k=%d)", ix->d, k);
-    const size_t lds = scan_lds_bytes(scan_dtype(ix), ix->d, p.gsel_s ? 0 : p.cap_s, p.shape_s, p.nbuf_s);
+    const size_t lds = scan_lds_bytes(scan_dtype(ix), ix->d, p.nbuf_s);
     int* zero = (int*)(ws + p.o_zero);
     BucketArgs b{};
     b.probe = probe; b.nq = (int)nq; b.nprobe = nprobe; b.nlist = (int)ix->nlist; b.cw = p.cw_s;
     b.cw_log2 = __builtin_ctz((unsigned)p.cw_s);
-    b.half_tiles = operand_parts(scan_dtype(ix), ix->d) == 2;
+    b.half_tiles = ix->d_vec_hi != nullptr || scan_dtype(ix) == HR_F32 || operand_parts(scan_dtype(ix), ix->d) == 2;
     b.list_off = ix->d_list_off;
     b.list_w = zero;
     b.hits = ix->d_hits;
@@ -704,19 +666,24 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, int64_t
     sd.seed_rows = k + 28 < 64 ? 64 : ((k + 28 + 15) & ~15);
     if (sd.seed_rows > 192) sd.seed_rows = 192;
     sd.l2 = metric == HR_METRIC_L2;
-    if (carried) { sd.state_ids = out_ids; sd.state_scores = out_scores; sd.qnorm = (const float*)(ws + p.o_qnorm_s); }
+    sd.qnorm = (const float*)(ws + p.o_qnorm_s);
+    sd.list_bound = ix->d_list_bound;
+    if (carried) { sd.state_ids = out_ids; sd.state_scores = out_scores; }
     HR_HIP(launch_seed(row_dtype(ix), ix->d, sd, s));
 
     ScanArgs a{};
     a.rows = ix->d_vec_hi ? ix->d_vec_hi : row_table(ix);
-    a.rows_lo = ix->d_vec_lo;
     a.row_norm = ix->d_row_norm;
     a.row_ids = ix->ids;
     a.qop = ws + p.o_qop_s;
     a.thr = (uint32_t*)(ws + p.o_thr) + nq;
     a.slot_cnt = (int*)(ws + p.o_slot_cnt);
     a.slot_ent = (Cand*)(ws + p.o_slot_ent);
-    a.slot_stride = p.slot_stride;
+    a.qnorm = (const float*)(ws + p.o_qnorm_s);
+    a.qlo = (const float*)(ws + p.o_thr);
+    a.list_bound = ix->d_list_bound;
+    a.rows_f32 = (const float*)ix->vectors;
+    a.queries = queries;
     a.bucket_q = b.bucket_q;
     a.dyn = b.dyn;
     a.xq_rec = b.xq_rec;
@@ -725,13 +692,12 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, int64_t
     a.xq_stride = p.item_cap;
     a.nq = (int)nq; a.k = k; a.cap = p.cap_s; a.l2 = metric == HR_METRIC_L2;
     a.nbuf = p.nbuf_s;
-    a.gsel = p.gsel_s;
     a.hist = zero + p.zoff_hist;
     a.hpar = (const float*)(zero + p.zoff_hpar);
     hr_ivf_index* mix = const_cast<hr_ivf_index*>(ix);
     const bool timed = mix->prof_ev && mix->prof_n < mix->prof_cap;
     if (timed) HR_HIP(hipEventRecord(mix->prof_ev[2 * mix->prof_n], s));
-    HR_HIP(launch_scan(scan_dtype(ix), ix->d, a, p.shape_s, scan_grid(ix, lds, p.shape_s, p.groups_s), lds, s));
+    HR_HIP(launch_scan(scan_dtype(ix), ix->d, a, scan_grid(ix, lds, p.groups_s), lds, s));
     if (timed) {
         HR_HIP(hipEventRecord(mix->prof_ev[2 * mix->prof_n + 1], s));
         mix->prof_n++;
@@ -739,7 +705,7 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, int64_t
 
     MergeArgs m{};
     m.thr = a.thr;
-    m.slot_cnt = a.slot_cnt; m.slot_ent = a.slot_ent; m.slot_stride = p.slot_stride;
+    m.slot_cnt = a.slot_cnt; m.slot_ent = a.slot_ent; m.slot_stride = p.cap_s;
     m.row_ids = ix->ids;
     m.qnorm = (const float*)(ws + p.o_qnorm_s);
     m.probe = probe; m.pair_entry = b.pair_entry;
@@ -748,6 +714,10 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, int64_t
     m.out_ids = out_ids; m.out_scores = out_scores;
     m.carried = carried ? 1 : 0;
     m.io_rows = io_rows;
+    if (scan_bounded(scan_dtype(ix))) {
+        m.rows_f32 = a.rows_f32;
+        m.queries = queries; m.row_norm = ix->d_row_norm; m.qlo = a.qlo; m.list_bound = ix->d_list_bound; m.d = ix->d;
+    }
     HR_HIP(launch_merge(m, s));
     return HR_OK;
 }
@@ -768,33 +738,36 @@ int hr_ivf_search(const hr_ivf_index* ix, const float* queries, int64_t nq, int3
     hipStream_t s = (hipStream_t)stream;
     int32_t* probe = (int32_t*)(ws + p.o_probe);
     if (int rc = enqueue_coarse(ix, p, ws, queries, nq, nprobe, metric, true, probe, nullptr, s)) return rc;
-    return enqueue_scan(ix, p, ws, nq, probe, nprobe, k, metric, out_ids, out_scores, s);
+    return enqueue_scan(ix, p, ws, queries, nq, probe, nprobe, k, metric, out_ids, out_scores, s);
 }
 
 // Limits of a plan that has to fit the static scratch array: few, large work items (result slots are
 // what takes the room) and a small coarse key table.
-static constexpr PlanLimits kStaticLimits = {256, (size_t)4 << 20, false, 0};
-static constexpr PlanLimits kStaticFewer = {128, (size_t)4 << 20, false, 0};
+static constexpr PlanLimits kStaticLimits[] = {{256, (size_t)4 << 20, false, 0}, {128, (size_t)4 << 20, false, 0}, {64, (size_t)4 << 20, false, 0}};
 
 // The plan of a call on the static array; p.total is beyond it if there is none.  Result slots are item_target x queries of
-// a tile.  Storage whose tiles have 128 queries since they hold both operand parts in registers had 64 before, and what
-// fitted then still does: with 128 items, half the slots.  But those leave half of the compute units idle, so as long as
-// they can the 256 items stay and the selection buffers, which lie in the slots, become shorter instead: 256 queries over
-// 48 of 64 lists, k 100, half a million bfloat16 rows of d = 768:
-// 1282 us a call with tiles of 64 queries, 1537 with 128 items, 1177 with 256 and buffers of 184 entries instead of 192.
+// a tile.  Storage whose tiles have 128 queries since the low parts of the operands wait for the blocks that need them had 64
+// before, float32 rows of d = 1024 32, and what fitted then still does: with 128 or 64 items, as many slots.  But those leave
+// compute units idle, so as long as they can the 256 items stay and the selection buffers, which lie in the slots,
+// become shorter instead: 256 queries over 48 of 64 lists, k 100, half a million bfloat16 rows of d = 768, tiles of 64 queries
+// 1282 us a call, of 128 with 128 items 1537, with 256 and buffers of 184 entries instead of 192 1177.
 static Plan static_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k)
 {
     const size_t most = HR_STATIC_SCRATCH_BYTES;
-    const Plan p = make_plan(ix, nq, nprobe, k, kStaticLimits);
-    if (p.total <= most || operand_parts(scan_dtype(ix), ix->d) != 2) return p;
-    const Plan fewer = make_plan(ix, nq, nprobe, k, kStaticFewer);
-    if (fewer.total > most) return fewer;
-    const size_t column = (size_t)p.slot_cap * sizeof(Cand);                     // one entry of every slot
-    PlanLimits shorter = kStaticLimits;
-    shorter.cap = (p.cap_s - (int)((p.total - most + column - 1) / column)) & ~3;
-    if (shorter.cap < k + kAppendMax + 4) return fewer;
-    const Plan s = make_plan(ix, nq, nprobe, k, shorter);
-    return s.total <= most ? s : fewer;
+    const Plan p = make_plan(ix, nq, nprobe, k, kStaticLimits[0]);
+    if (p.total <= most || (scan_dtype(ix) == HR_F16)) return p;
+    Plan s = p;
+    for (const PlanLimits& lim : kStaticLimits) {
+        s = make_plan(ix, nq, nprobe, k, lim);
+        if (s.total <= most) return s;
+        const size_t column = (size_t)s.slot_cap * sizeof(Cand);                 // one entry of every slot
+        PlanLimits shorter = lim;
+        shorter.cap = (s.cap_s - (int)((s.total - most + column - 1) / column)) & ~3;
+        if (shorter.cap < k + kAppendMax + kRoomAfterCut) continue;
+        s = make_plan(ix, nq, nprobe, k, shorter);
+        if (s.total <= most) return s;
+    }
+    return s;
 }
 
 int hr_ivf_search_static(const hr_ivf_index* ix, const float* queries, int64_t nq, int32_t nprobe, int32_t k,
@@ -815,7 +788,7 @@ int hr_ivf_search_static(const hr_ivf_index* ix, const float* queries, int64_t n
     hipStream_t s = (hipStream_t)stream;
     int32_t* probe = (int32_t*)(ws + p.o_probe);
     if (int rc = enqueue_coarse(ix, p, ws, queries, nq, nprobe, metric, true, probe, nullptr, s)) return rc;
-    return enqueue_scan(ix, p, ws, nq, probe, nprobe, k, metric, out_ids, out_scores, s);
+    return enqueue_scan(ix, p, ws, queries, nq, probe, nprobe, k, metric, out_ids, out_scores, s);
 }
 
 int hr_ivf_coarse(const hr_ivf_index* ix, const float* queries, int64_t nq, int32_t nprobe, int32_t metric,
@@ -848,7 +821,7 @@ int hr_ivf_scan(const hr_ivf_index* ix, const float* queries, int64_t nq, const 
     char* ws = (char*)workspace;
     hipStream_t s = (hipStream_t)stream;
     HR_HIP(launch_prep_queries(prep_args(ix, p, ws, queries, nq, false, true), s));
-    return enqueue_scan(ix, p, ws, nq, probe_ids, nprobe, k, metric, out_ids, out_scores, s);
+    return enqueue_scan(ix, p, ws, queries, nq, probe_ids, nprobe, k, metric, out_ids, out_scores, s);
 }
 
 static int scan_step(const hr_ivf_index* ix, const float* queries, int64_t nq, const int32_t* probe_ids,
@@ -866,7 +839,7 @@ static int scan_step(const hr_ivf_index* ix, const float* queries, int64_t nq, c
     char* ws = (char*)workspace;
     hipStream_t s = (hipStream_t)stream;
     HR_HIP(launch_prep_queries(prep_args(ix, p, ws, queries, nq, false, true), s));
-    return enqueue_scan(ix, p, ws, nq, probe_ids, nprobe, k, metric, io_ids, io_scores, s, true, io_rows);
+    return enqueue_scan(ix, p, ws, queries, nq, probe_ids, nprobe, k, metric, io_ids, io_scores, s, true, io_rows);
 }
 
 int hr_ivf_scan_step(const hr_ivf_index* ix, const float* queries, int64_t nq, const int32_t* probe_ids,
@@ -1018,10 +991,11 @@ int hr_ivf_refresh_rows(hr_ivf_index* ix, int64_t row_begin, int64_t row_end, vo
                                             "replace the rows again, or load the index without HR_LOAD_ROW_TABLES");
         return HR_OK;
     }
-    HR_HIP(launch_row_norms(rows, ix->dtype, n, ix->d, ix->d_row_norm + row_begin, s));
-    if (ix->d_vec_hi)
-        HR_HIP(launch_split_f32((const float*)rows, n * ix->d, (char*)ix->d_vec_hi + (size_t)row_begin * ix->d * 2,
-                                (char*)ix->d_vec_lo + (size_t)row_begin * ix->d * 2, s));
+    // (bounds only grow: rows that were replaced count on)
+    if (ix->d_list_bound)
+        HR_HIP(launch_list_bounds((const float*)ix->vectors, ix->d, row_begin, n, ix->d_list_off, (int)ix->nlist, ix->d_row_norm, (uint2*)ix->d_list_bound, ix->d_vec_hi, s));
+    else
+        HR_HIP(launch_row_norms(rows, ix->dtype, n, ix->d, ix->d_row_norm + row_begin, s));
     return HR_OK;
 }
 

@@ -230,6 +230,58 @@ __global__ __launch_bounds__(256) void k_row_norms(const void* rows, int dtype, 
     if (lane == 0) out[row] = acc;
 }
 
+// float32 rows: the squared norm of every row, and of every list the largest of them and the largest squared norm of what
+// rounding a row to binary16 leaves over (hi: the rounded rows, or nullptr).  Squares are not negative, so their bits are in order; NaN counts as infinite.  One
+// wave per 16 rows, which asks once per list for all of them.
+constexpr int kBoundRows = 16;
+__global__ __launch_bounds__(256) void k_list_bounds(const float* rows, int d, int64_t row0, int64_t nrows, const int* list_off, int nlist,
+                                                     float* row_norm, uint2* bound, _Float16* hi)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t first = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kBoundRows;
+    if (first >= nrows) return;
+    const int n = (int)min((int64_t)kBoundRows, nrows - first);
+    int lo = 0;                                                 // list of the row
+    for (int end = nlist; end - lo > 1;) {
+        const int mid = (lo + end) >> 1;
+        if (list_off[mid] <= row0 + first) lo = mid; else end = mid;
+    }
+    uint32_t most = 0, most_left = 0;
+    auto bits = [](float v) __attribute__((always_inline)) { return __builtin_bit_cast(uint32_t, v < __builtin_inff() ? v : __builtin_inff()); };
+    auto report = [&]() __attribute__((always_inline)) {
+        if (lane == 0) { atomicMax(&bound[lo].x, most); atomicMax(&bound[lo].y, most_left); }
+        most = most_left = 0;
+    };
+    for (int i = 0; i < n; i++) {
+        const int64_t row = row0 + first + i;
+        while (row >= list_off[lo + 1]) { if (most) report(); lo++; }
+        const float* p = rows + row * d;
+        float sum = 0.f, left = 0.f;
+        for (int j = lane; j < d; j += 64) {
+            const float x = p[j];
+            const _Float16 h = (_Float16)x;
+            const float r = x - (float)h;
+            if (hi) hi[row * d + j] = h;
+            sum += x * x;
+            left += r * r;
+        }
+        sum = wave_sum(sum);
+        left = wave_sum(left);
+        if (lane == 0) row_norm[row] = sum;
+        most = max(most, bits(sum));
+        most_left = max(most_left, bits(left));
+    }
+    report();
+}
+
+hipError_t launch_list_bounds(const float* rows, int d, int64_t row0, int64_t nrows, const int* list_off, int nlist, float* row_norm, uint2* bound, void* hi, hipStream_t s)
+{
+    if (nrows <= 0) return hipSuccess;
+    const int64_t waves = (nrows + kBoundRows - 1) / kBoundRows;
+    hipLaunchKernelGGL(k_list_bounds, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, rows, d, row0, nrows, list_off, nlist, row_norm, bound, (_Float16*)hi);
+    return hipGetLastError();
+}
+
 // Replaced bfloat16 rows: their norms and their copy in the binary16 table in one pass (k_row_norms and k_bf16_to_f16 on the
 // same rows).  A value that does not fit is reported in host memory, which the caller reads once the stream is empty.
 __global__ __launch_bounds__(256) void k_refresh_bf16(const uint16_t* rows, int64_t nrows, int d, float* norm, _Float16* table, volatile int* overflow)
@@ -281,7 +333,7 @@ __device__ __forceinline__ float prep_query(const PrepArgs& a, int64_t row, int 
 {
     const int d = a.d;
     const float* p = a.q + row * d;
-    float n32 = 0.f, ns = 0.f;
+    float n32 = 0.f, ns = 0.f, nl = 0.f;
     // (four loads in flight: waiting for each would be twelve round trips at d = 768)
     for (int i0 = lane; i0 < d; i0 += 256) {
         float v[4];
@@ -295,8 +347,10 @@ __device__ __forceinline__ float prep_query(const PrepArgs& a, int64_t row, int 
             n32 += x * x;
             if (a.qop_coarse) {
                 _Float16 h = (_Float16)x;
+                const _Float16 l = (_Float16)((x - (float)h) * 2048.0f);
                 a.qop_coarse[(row * 2) * d + i] = h;
-                a.qop_coarse[(row * 2 + 1) * d + i] = (_Float16)((x - (float)h) * 2048.0f);
+                a.qop_coarse[(row * 2 + 1) * d + i] = l;
+                nl += ((float)l * (1.0f / 2048.0f)) * ((float)l * (1.0f / 2048.0f));
             }
             if (a.qop_scan) {
                 if (a.dtype == HR_F16) {
@@ -316,7 +370,10 @@ __device__ __forceinline__ float prep_query(const PrepArgs& a, int64_t row, int 
     }
     n32 = wave_sum(n32);
     ns = wave_sum(ns);
+    if (a.qlo) nl = wave_sum(nl);
     if (lane == 0) {
+        // (a query so small that squares of parts that matter vanish has no bound; one that is beyond binary16 has no keys)
+        if (a.qlo) a.qlo[row] = !(nl < __builtin_inff()) ? __builtin_nanf("") : (n32 >= 1e-18f ? sqrtf(nl) : __builtin_inff());
         if (a.qnorm_coarse) a.qnorm_coarse[row] = n32;
         if (a.qnorm_scan) a.qnorm_scan[row] = (a.dtype == HR_F32) ? n32 : ns;
     }
@@ -801,7 +858,8 @@ hipError_t launch_bucketing(const BucketArgs& a, hipStream_t s)
 // Section 5 and the per-request merge of Section 4.4): a wave, or four, walk the slots that hold a query's
 // candidates, keep the k best in LDS buffers pruned as in the scan; the first then orders the
 // survivors by (key, label) and writes the output row.
-constexpr int kMergeCap = 256;     // candidates buffered per wave (k <= 128, up to 64 appended per step)
+// candidates buffered per wave: k <= 128 and up to 64 appended per step, with upper bounds also what is within their slack of the k-th
+__host__ __device__ constexpr int merge_cap(bool bounded) { return bounded ? 384 : 256; }
 
 // W waves share the slots of a query, 64 slots at a time in turn, each with a buffer of its own; the first takes in what
 // the others kept.  Bound by a wave's chain of loads and cuts, so one wave per query is enough only where the queries
@@ -809,16 +867,22 @@ constexpr int kMergeCap = 256;     // candidates buffered per wave (k <= 128, up
 // 256 over 30 of 60 lists, 2 M rows, k 100, 782 and 674; 512 over 32 of 1024, k 10, 239 and 239.  The line: 1024 queries 705 and
 // 584, 126 and 126, 2048 999 and 886, 142 and 150, 8192 256 and 272 (sixteen waves are slower than four).
 constexpr int kMergeShare = 1024;  // most queries that get four waves each
-template <int W>
+// BOUNDED: the slots hold upper bounds; a cut keeps what is within twice the slack of the k-th, and the exact keys of what is left in
+// the end, k rows and a few more, are computed by all W waves.
+template <int W, bool BOUNDED>
 __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
 {
     constexpr int NW = 4, Q = NW / W;                  // waves and queries of a workgroup
-    __shared__ Cand s_buf[NW][kMergeCap];
-    __shared__ int64_t s_tie[Q][HR_K_MAX];
+    constexpr int AT = W > 1 ? 8 : 4;                  // rows on their way together while exact keys are computed
+    constexpr int CAP = merge_cap(BOUNDED), CE = CAP / 64;
+    const int cap = BOUNDED && a.k <= 64 ? 256 : CAP;  // (a cut takes longer the more it looks at)
+    __shared__ Cand s_buf[NW][CAP];
+    __shared__ int64_t s_tie[Q][HR_K_MAX];         // labels of the last entries
     __shared__ int s_pref[Q][HR_NPROBE_MAX + 1];
     __shared__ int s_cnt[NW];
     __shared__ uint32_t s_thr[Q];
     __shared__ int s_total[Q];
+    __shared__ float s_slack[Q], s_norm[Q];         // largest slack and squared norm of the probed lists
     __shared__ int s_first[NW][64];
     __shared__ size_t s_slot[NW][64];
     __shared__ int64_t s_ext_id[Q][HR_K_MAX];
@@ -845,6 +909,8 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
     if (lane == 0) s_cnt[wave] = 0;
     if (part == 0 && live) {
         int run = 0;
+        float slack = 0.f, norm2 = 0.f;
+        const float qn = BOUNDED ? sqrtf(a.qnorm[q]) : 0.f, ql = BOUNDED ? a.qlo[q] : 0.f;
         for (int p0 = 0; p0 < a.nprobe; p0 += 64) {
             int p = p0 + lane;
             int ns = 0;
@@ -853,13 +919,15 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
                 if (l >= 0 && l < a.nlist && a.pair_entry[q * a.nprobe + p] >= 0) {
                     int len = a.list_off[l + 1] - a.list_off[l];
                     ns = (len + seg_rows - 1) / seg_rows;
+                    if (BOUNDED) { slack = fmaxf(slack, scan_slack(qn, ql, a.list_bound[l], a.l2)); norm2 = fmaxf(norm2, a.list_bound[l].x); }
                 }
             }
             const int inc = wave_prefix_sum(ns);
             if (p < a.nprobe) pref[p + 1] = run + inc;
             run += __builtin_amdgcn_readlane(inc, 63);
         }
-        if (lane == 0) { pref[0] = 0; s_thr[own] = 0; s_total[own] = run; }
+        if (BOUNDED) { slack = wave_max(slack); norm2 = wave_max(norm2); }
+        if (lane == 0) { pref[0] = 0; s_thr[own] = 0; s_total[own] = run; s_slack[own] = slack; s_norm[own] = norm2; }
     }
     wave_sync();
     // ---- a carried result joins as one more partial result (read whole before anything of
@@ -890,14 +958,37 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
     uint32_t thr = live ? a.thr[q] : 0;
     int n = __builtin_amdgcn_readfirstlane(s_cnt[wave]);
     const int total = live ? s_total[own] : 0;
-    // a full buffer is cut to the k best; the k-th of any k candidates is a bound for all waves of the query
+    const float slack2 = BOUNDED && live ? 2.0f * s_slack[own] : 0.f;
+    auto window = [&](Cand* b, int n, uint32_t& bound, int& best) __attribute__((always_inline)) {
+        if (n <= 64) return wave_window<1>(b, n, k, slack2, bound, best, lane);
+        if (n <= 256) return wave_window<4>(b, n, k, slack2, bound, best, lane);
+        return wave_window<CE>(b, n, k, slack2, bound, best, lane);
+    };
+    // a full buffer is cut to the k best (BOUNDED: and what is too close to them to tell, unless that is too much); the k-th of
+    // any k candidates is a bound for all waves of the query
     auto cut = [&](Cand* b, int n) __attribute__((always_inline)) {
-        const uint32_t kth = wave_select<4>(b, n, k, a.row_ids, ext_id);
+        uint32_t kth;
+        int left = k;
+        if constexpr (BOUNDED) {
+            int best;
+            left = window(b, n, kth, best);
+            if (left > cap - 64) {
+                // (a bound may stay above the exact key by what two sums of the same products differ by, see k_scan)
+                const float add = exact_add(a.qnorm[q], s_norm[own], a.l2);
+                exact_keys<8, 1>(b, left, 0, 1, a.rows_f32, a.row_norm, a.queries + (size_t)q * a.d, a.d, a.l2, add);
+                kth = key_below(wave_select<CE>(b, left, k, a.row_ids, ext_id), 2.0f * add);
+                left = k;
+            }
+        } else {
+            kth = wave_select<4>(b, n, k, a.row_ids, ext_id);
+        }
         thr = kth > thr ? kth : thr;
         if (W > 1 && lane == 0) atomicMax(&s_thr[own], kth);
+        return left;
     };
-    for (int f0 = part * 64; f0 < total; f0 += W * 64) {
-        const int f = f0 + lane;
+    // (every W-th slot: the segments of a list lie side by side, and most of a query's entries are in those of one list)
+    for (int f0 = 0; f0 < total; f0 += W * 64) {
+        const int f = f0 + lane * W + part;
         int c = 0;
         size_t slot = 0;
         if (f < total) {
@@ -951,22 +1042,19 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
                 if (take) buf[n + lanes_below(mask)] = cd;
                 n += __builtin_popcountll(mask);
                 wave_sync();
-                if (n > kMergeCap - 64) { cut(buf, n); n = k; }
+                if (n > cap - 64) n = cut(buf, n);
             }
         }
         wave_sync();
     }
     wave_sync();
-    if (n > k) {
-        cut(buf, n);
-        n = k;
-    }
+    if (W > 1 && n > max(k, 64)) n = cut(buf, n);      // (few are handed over as they are: a cut takes 0.5 .. 2 us)
     if (W > 1) {
         if (lane == 0) s_cnt[wave] = n;
         __syncthreads();
-        if (part != 0 || !live) return;                // (no barrier of the workgroup below)
+        if (!BOUNDED && (part != 0 || !live)) return;  // (no barrier of the workgroup below)
         thr = max(thr, s_thr[own]);
-        for (int o = 1; o < W; o++) {
+        for (int o = 1; o < W && part == 0; o++) {
             const int m = s_cnt[wave + o];
             for (int e0 = 0; e0 < m; e0 += 64) {
                 const Cand cd = e0 + lane < m ? s_buf[wave + o][e0 + lane] : Cand{0u, 0u};
@@ -975,14 +1063,57 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
                 if (take) buf[n + lanes_below(mask)] = cd;
                 n += __builtin_popcountll(mask);
                 wave_sync();
-                if (n > kMergeCap - 64) { cut(buf, n); n = k; }
+                if (n > cap - 64) n = cut(buf, n);
             }
         }
-        if (n > k) { cut(buf, n); n = k; }
     }
     wave_sync();
+    if constexpr (BOUNDED) {
+        // the k largest bounds are made exact first; of the others, only those that reach the least of these keys can matter
+        int best = n;
+        if (part == 0 && n > k && n > W * AT) {        // (else all in one go)
+            uint32_t bound;
+            n = window(buf, n, bound, best);
+            if (n <= W * AT) best = n;
+        }
+        if (W > 1) {
+            if (part == 0 && lane == 0) { s_cnt[0] = best; s_cnt[1] = n; }
+            __syncthreads();
+            best = s_cnt[0];
+            n = s_cnt[1];
+        }
+        for (int from = 0;;) {
+            exact_keys<AT, 4>(s_buf[wave - part] + from, best - from, part, W, a.rows_f32, a.row_norm, a.queries + (size_t)q * a.d, a.d, a.l2, 0.f);
+            together();
+            if (best == n) break;
+            if (part == 0) {
+                uint32_t least = ~0u;
+                for (int e0 = 0; e0 < best; e0 += 64) least = min(least, wave_min(e0 + lane < best ? buf[e0 + lane].key : ~0u));
+                int m = best;
+                for (int e0 = best; e0 < n; e0 += 64) {
+                    const Cand cd = e0 + lane < n ? buf[e0 + lane] : Cand{0u, 0u};
+                    const bool keep = e0 + lane < n && cd.key >= least;
+                    const unsigned long long mask = __builtin_amdgcn_ballot_w64(keep);
+                    if (keep) buf[m + lanes_below(mask)] = cd;
+                    m += __builtin_popcountll(mask);
+                    wave_sync();
+                }
+                n = m;
+            }
+            if (W > 1) {
+                if (part == 0 && lane == 0) s_cnt[1] = n;
+                __syncthreads();
+                n = s_cnt[1];
+            }
+            from = best;
+            best = n;
+        }
+        if (W > 1 && part != 0) return;
+    }
+    if (n > HR_K_MAX) { wave_select<CE>(buf, n, k, a.row_ids, ext_id); n = k; }
+    wave_sync();
 
-    // ---- final order by (key descending, label ascending); n <= k <= 128: two entries per lane
+    // ---- final order by (key descending, label ascending), the first k of it: two entries per lane
     Cand e[2];
     int64_t id[2];
 #pragma unroll
@@ -1006,7 +1137,7 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
 #pragma unroll
     for (int m = 0; m < 2; m++) {
         int idx = lane + 64 * m;
-        if (idx < n) {
+        if (idx < n && pos[m] < k) {
             float key = dec_key(e[m].key);
             float score = a.l2 ? fmaxf(qn - key, 0.f) : key;
             if (e[m].row & kCarried) score = ext_score[e[m].row & ~kCarried];     // (as it was reported)
@@ -1537,9 +1668,13 @@ hipError_t launch_rescore(const float* q, int64_t nq, int d, int dtype, const vo
 hipError_t launch_merge(const MergeArgs& a, hipStream_t s)
 {
     if (a.nq <= 0) return hipSuccess;
-    if (a.nq <= kMergeShare) hipLaunchKernelGGL(k_merge<4>, dim3((unsigned)a.nq), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(k_merge<1>, dim3((unsigned)((a.nq + 3) / 4)), dim3(256), 0, s, a);
-    return hipGetLastError();
+    auto launch = [&](auto bounded) {
+        constexpr bool B = decltype(bounded)::value;
+        if (a.nq <= kMergeShare) hipLaunchKernelGGL((k_merge<4, B>), dim3((unsigned)a.nq), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((k_merge<1, B>), dim3((unsigned)((a.nq + 3) / 4)), dim3(256), 0, s, a);
+        return hipGetLastError();
+    };
+    return a.rows_f32 != nullptr ? launch(std::true_type{}) : launch(std::false_type{});
 }
 
 }  // namespace hr

@@ -8,37 +8,32 @@
 namespace hr {
 
 constexpr int kWave = 64;
-// internal storage code next to HR_F32 / HR_F16 / HR_BF16: float32 rows already split into a
-// binary16 hi table and a 2^11-scaled binary16 lo table (the centroid table, split at load)
-constexpr int HR_F16X2 = 3;
+// internal storage codes next to HR_F32 / HR_F16 / HR_BF16: float32 rows already split into a
+// binary16 hi table and a 2^11-scaled binary16 lo table (the centroid table, split at load), and rounded to a binary16 table
+// (lists with row tables)
+constexpr int HR_F16X2 = 3, HR_F16HI = 4;
 constexpr int kMfmaRows = 16;              // rows per MFMA (M of 16x16x32)
-constexpr int kRowPad = 32;                // bytes of LDS padding per staged row: measured conflict-free
-                                           // for the 16-rows x 16-byte MFMA fragment reads (16 is 2-way)
 constexpr int kAppendMax = 16;             // most candidates one column can gain per group of kMfmaRows rows
 constexpr int kMinSegRows = 256;           // smallest rows-per-work-item
 constexpr int kItemTarget = 4096;          // aimed number of scan work items per batch
 constexpr int kHistBins = 64;              // per-query histogram of candidate keys (one bin per lane)
 
-// Parts of a query operand that a wave keeps in registers of their own.  A (hi, lo) pair either occupies two MFMA columns
-// (8 queries per wave) or, where two operands of d elements leave room for the rest in 256 registers, two operands of one
-// column (16 queries per wave): a tile then has twice the queries, so every row is moved into LDS half as often, and
-// every row fragment read from LDS feeds two MFMAs per plane instead of one.  Both were what the narrow form waited for:
-// 8192 queries x 16.8 M bfloat16 rows 17.9 -> 16.0 ms, 3001 queries x 16384 centroids 445 -> 355 us, 1024 queries over all of
-// 524288 rows with row tables, d = 768, 3.90 -> 2.91 ms; the same bits.  d = 1024 (256 registers of operand) keeps the two columns,
-// as do float32 rows split on the fly, whose rows pass through the registers.
+// Storage of which the scan multiplies the high parts alone and keeps every row that may count with what it left out; the
+// merge computes the exact scores of the few that are left (see scan_slack)
+__host__ __device__ constexpr bool scan_bounded(int dtype) { return dtype == HR_F32 || dtype == HR_F16HI; }
+
+// Parts of a query operand that a wave keeps in registers of their own.  Two operands of d elements leave room for the rest in
+// 256 registers up to d = 768.  Beyond that they take two MFMA columns per query (8 queries per wave).
 __host__ __device__ constexpr int operand_parts(int dtype, int d)
 {
     return (dtype == HR_BF16 || dtype == HR_F16X2) && d <= 768 ? 2 : 1;
 }
-// columns (queries) per 16-column MFMA set
-__host__ __device__ constexpr int cols_per_set(int dtype, int d) { return dtype == HR_F16 || operand_parts(dtype, d) == 2 ? 16 : 8; }
+// columns (queries) per wave
+__host__ __device__ constexpr int cols_per_set(int dtype, int d) { return (dtype == HR_BF16 || dtype == HR_F16X2) && operand_parts(dtype, d) == 1 ? 8 : 16; }
 
-// Workgroup shapes of the scan kernel: waves x column sets per wave.  A work item covers
-// shape_sets(shape) * cols_per_set(dtype, d) queries of a bucket.
-enum { SCAN_NARROW = 0 /* 4 waves, one per SIMD */, SCAN_WIDE = 1 /* 8 waves, two per SIMD */ };
-__host__ __device__ constexpr int shape_waves(int shape) { return shape == SCAN_WIDE ? 8 : 4; }
-__host__ __device__ constexpr int shape_ncs(int) { return 1; }                         // column sets per wave
-__host__ __device__ constexpr int shape_sets(int shape) { return shape_waves(shape) * shape_ncs(shape); }
+constexpr int kScanWaves = 8;              // waves of a workgroup of the scan, two per SIMD
+// queries of a work item
+__host__ __device__ constexpr int tile_cols(int dtype, int d) { return kScanWaves * cols_per_set(dtype, d); }
 
 // Groups of 16 rows that are staged, waited for and filtered together: a block of the scan has 16 * block_groups rows, about
 // 16 KB.  16 rows of a short vector are a few KB and a few MFMAs, and a barrier, requests that no wave fills and a filter
@@ -66,40 +61,26 @@ __host__ __device__ constexpr int groups_per_cu(int dtype, int d)
 }
 
 // k-steps (of 32 elements) whose row fragments a wave fetches from LDS together
-__host__ __device__ constexpr int scan_group(int dtype, int ksteps, int nw)
+__host__ __device__ constexpr int scan_group(int dtype, int ksteps)
 {
     // (blocks of several groups of rows: 8 or 16 k-steps in all)
-    if (ksteps < 16 && nw == 8) return dtype == HR_F32 && ksteps == 4 ? 2 : 4;
-    if (ksteps < 8) return 4;
-    if (nw == 8 && dtype == HR_F32 && ksteps >= 24) return 2;       // (leaves registers for a second row block in flight)
+    if (ksteps < 16) return dtype == HR_F32 ? 2 : 4;
     // (what a long operand in two parts leaves: 253 of 256 registers at 24 k-steps, none spilled)
-    if (nw == 8 && ksteps >= 16 && operand_parts(dtype, ksteps * 32) == 2)
+    if (operand_parts(dtype, ksteps * 32) == 2)
         return dtype == HR_F16X2 ? (ksteps >= 24 ? 1 : 2) : (ksteps >= 24 ? 2 : 4);
-    if (nw == 8) return ((dtype == HR_F32 || dtype == HR_F16X2) && ksteps >= 32) ? 2 : 4;   // (256 registers per lane)
-    return 8;
-}
-// row blocks a wave keeps in flight in registers ahead of the one being staged: what the
-// register budget (512 per lane with one wave per SIMD, 256 with two) leaves after the query
-// operand, two groups of row fragments and working registers; at most 4
-__host__ __device__ constexpr int scan_prefetch(int dtype, int ksteps, int ncs, int nw)
-{
-    const int planes = dtype == HR_F32 ? 2 : 1;
-    const int rowb = ksteps * 32 * (dtype == HR_F32 ? 4 : 2);
-    const int chunks = block_rows(dtype, ksteps * 32) * rowb / 16;
-    const int nld = (chunks + nw * 64 - 1) / (nw * 64);
-    const int left = (nw == 8 ? 256 : 512) - ncs * ksteps * 4 - 2 * planes * scan_group(dtype, ksteps, nw) * 4 - (nw == 8 ? 67 : 96);
-    const int fit = left / (nld * 4 + 1);
-    const int most = block_groups(dtype, ksteps * 32) > 1 ? 2 : 4;  // (a list shorter than them all still loads them all)
-    return fit < 1 ? 1 : (fit > most ? most : fit);
+    return (dtype == HR_F32 && ksteps >= 24) || (dtype == HR_F16X2 && ksteps >= 32) ? 2 : 4;   // (256 registers per lane)
 }
 
 // selection buffer capacity per column for a given k: room for k kept entries plus a batch of
 // new ones between two prunes (a prune costs about the same for any fill up to 64 entries per
 // lane slot, so bigger batches make each candidate cheaper), bounded by LDS
-__host__ __device__ constexpr int sel_cap(int k)
+// (bounded types keep what is within the slack of the k-th best too: half of a buffer that has just been cut, or more, is meant to be free)
+constexpr int kRoomAfterCut = 4;           // free entries beyond kAppendMax that a cut has to leave
+__host__ __device__ constexpr int sel_cap(int dtype, int k)
 {
     int c = k <= 24 ? 64 : (k <= 64 ? 128 : 192);
-    if (c < k + kAppendMax + 4) c = k + kAppendMax + 4;
+    if (scan_bounded(dtype)) c = k <= 12 ? 64 : (k <= 24 ? 96 : (k <= 36 ? 128 : (k <= 64 ? 192 : 256)));
+    if (c < k + kAppendMax + kRoomAfterCut) c = k + kAppendMax + kRoomAfterCut;
     return c;
 }
 
@@ -148,11 +129,15 @@ struct ScanArgs {
     const float* row_norm;      // [nrows] squared norms (used when l2 != 0)
     const int64_t* row_ids;     // [nrows] labels, or nullptr: label = row number
     const void* qop;            // query operand rows (layout depends on dtype)
-    const float* queries;       // dense mode: the queries as they are, split while they are loaded (or nullptr: qop)
+    const float* queries;       // the queries as they are (dense mode: split while they are loaded, or nullptr: qop)
     uint32_t* thr;              // [nq] running per-query lower bound of the k-th key (enc_key)
     int* slot_cnt;              // [slots]: one slot per (list segment, query of the list's bucket)
-    Cand* slot_ent;             // [slots * slot_stride]
-    int slot_stride;            // entries per slot: k, or cap where that is small (no cut at the end of an item)
+    Cand* slot_ent;             // [slots * cap] the selection buffers of the items
+    // bounded types (scan_slack)
+    const float* qnorm;         // [nq] squared norms of the queries
+    const float* qlo;           // [nq] norms of their low parts
+    const float2* list_bound;   // [nlist]
+    const float* rows_f32;      // [nrows, d] the rows as they are
     int* work_counter;          // dense mode: items popped beyond the first of every workgroup (zeroed before launch)
     // bucket mode
     const int* bucket_q;        // [pairs] query index per bucket entry
@@ -163,13 +148,12 @@ struct ScanArgs {
     const int* xq_count;        // [8] queue lengths
     int* xq_head;               // [8] items popped beyond those that the workgroups start with (zeroed before launch)
     int xq_stride;
-    // dense mode (HR_F16X2 with gsel 0, and then key_out is not null): one list = all rows, bucket = all queries
+    // dense mode (HR_F16X2, and then key_out is not null): one list = all rows, bucket = all queries
     int dense_items, dense_nqt, dense_seg_rows, dense_nrows;
     int dense_groups;           // groups that the tiles are taken in, so that the items of a segment meet in one XCD (0: plain order)
     int dense_cols;             // queries per wave (d < 512: as many as it has columns for)
     int nq, k, cap, l2;
-    int nbuf;                   // staging buffers in LDS (16-bit storage; float32 always uses 2)
-    int gsel;                   // selection buffers = the item's slots in global memory (slot_stride = cap), none in LDS
+    int nbuf;                   // staging buffers in LDS
     float* key_out;             // dense mode: [nq, dense_nrows] every key is written here and nothing is selected
     int* hist;                  // [nq][kHistBins] keys found so far per query, by key range (or nullptr)
     const float* hpar;          // [nq][2] lower edge of bin 0 and bin width (width 0: query has no histogram)
@@ -186,7 +170,8 @@ struct SeedArgs {
     float* hpar;                // [nq][2] histogram parameters of the scan (see ScanArgs)
     const int64_t* state_ids;   // [nq, k] labels and scores of a carried result, or nullptr
     const float* state_scores;
-    const float* qnorm;         // [nq] squared norms of the query operands (with a carried result, L2 only)
+    const float* qnorm;         // [nq] squared norms of the query operands
+    const float2* list_bound;   // [nlist] float32 rows: see scan_slack
     int nq, nprobe, nlist, k, seed_rows, l2;
 };
 
@@ -211,12 +196,19 @@ struct MergeArgs {
     int carried;                // out_ids / out_scores hold a previous result on entry: merged in (ids < 0: empty places)
     int64_t* out_ids;           // [nq, k] or nullptr
     float* out_scores;          // [nq, k] or nullptr
+    // bounded types: slots hold upper bounds (scan_slack); the exact keys of those that may count are computed here
+    const float* queries;       // [nq, d] the queries as they are
+    const float* rows_f32;      // [nrows, d] the rows, or nullptr: the slots hold exact keys
+    const float* row_norm;      // [nrows]
+    const float* qlo;           // [nq]
+    const float2* list_bound;   // [nlist]
+    int d;
     int32_t* io_rows;           // [nq, k] or nullptr: row numbers of the entries, carried along with them (-1: empty place)
 };
 
 // launchers implemented in the .hip files
-hipError_t launch_scan(int dtype, int d, const ScanArgs& a, int shape, int grid, size_t lds_bytes, hipStream_t s);
-size_t scan_lds_bytes(int dtype, int d, int cap, int shape, int nbuf);
+hipError_t launch_scan(int dtype, int d, const ScanArgs& a, int grid, size_t lds_bytes, hipStream_t s);
+size_t scan_lds_bytes(int dtype, int d, int nbuf);
 hipError_t launch_merge(const MergeArgs& a, hipStream_t s);
 struct PrepArgs {
     const float* q;             // [nq, d]
@@ -224,6 +216,7 @@ struct PrepArgs {
     float* qnorm_coarse;        // or nullptr
     void* qop_scan;             // operand of the list scan, where that is not the coarse step's, or nullptr
     float* qnorm_scan;          // or nullptr
+    float* qlo;                 // [nq] norms of the low parts (see scan_slack), or nullptr
     int* zero;                  // [n_zero] set to 0
     int* neg;                   // [n_neg] set to neg_value
     int64_t nq, n_zero, n_neg;
@@ -236,6 +229,7 @@ hipError_t launch_row_norms(const void* rows, int dtype, int64_t nrows, int d, f
 hipError_t launch_prep_queries(const PrepArgs& a, hipStream_t s);
 hipError_t launch_fill_i32(int* p, int64_t n, int v, hipStream_t s);
 hipError_t launch_hot_lists(const unsigned long long* hits, int nlist, int gc, int32_t* out, hipStream_t s);
+hipError_t launch_list_bounds(const float* rows, int d, int64_t row0, int64_t nrows, const int* list_off, int nlist, float* row_norm, uint2* bound, void* hi, hipStream_t s);
 hipError_t launch_read_hits(unsigned long long* hits, int64_t n, int64_t* out, int reset, hipStream_t s);
 hipError_t launch_lists_of_rows(const int32_t* rows, int64_t n, const int* list_off, int nlist, int32_t* out, hipStream_t s);
 hipError_t launch_reorder_probes(const int32_t* probe, int np, const int32_t* prev, int pp, const int32_t* hot, int nh,

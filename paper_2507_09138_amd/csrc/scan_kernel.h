@@ -14,11 +14,15 @@
 //   HR_BF16  rows are bfloat16; the query is split into bfloat16 hi + lo parts, each an operand in registers of its
 //            own (d <= 768), or the two in two MFMA columns (lanes j and j+8 of each 16-lane row); the same products
 //            in the same order either way, summed after the MFMA.
-//   HR_F32   rows are float32, split on the fly into binary16 hi + 2^11-scaled lo planes; the
-//            query likewise; the four partial products are recombined with their scales,
-//            which keeps about 22 bits of each factor with float32 accumulation.
-//   HR_F16X2 (internal) the same arithmetic on rows that were split into hi and lo tables
-//            beforehand (the centroid table: the coarse step of Section 2.2 runs this kernel
+//   HR_F32   rows are float32 and rounded to binary16 as they are read from LDS, the query likewise; the key is that product
+//            plus what the roundings can have taken from it (an upper bound, see scan_slack), and the merge computes the
+//            exact float32 scores of the rows that may be among the k best.  All four products of (hi + lo) parts, which this
+//            replaces, multiplied for every row what decides for a few: 1024 queries, 32 of 1024 lists of 1024 rows,
+//            d = 768, scan 601 -> 498 us (6.4 TB/s of rows), 3000 queries over 16 of 256 lists, d = 64, k 100, 1020 -> 803 a call.
+//   HR_F16HI (internal) the same with rows that were rounded beforehand: half the bytes (600 -> 290 us of the first).
+//   HR_F16X2 (internal) rows that were split into binary16 hi and 2^11-scaled lo tables beforehand, the query likewise; the
+//            four partial products are recombined with their scales, which keeps about 22 bits of each factor with
+//            float32 accumulation (the centroid table: the coarse step of Section 2.2 runs this kernel
 //            in "dense" mode, all queries against all rows, and writes every key out).
 #pragma once
 #include <utility>
@@ -125,6 +129,22 @@ __device__ __forceinline__ int wave_prefix_sum(int v)
     return v;
 }
 
+// sum over the 64 lanes of a wave, in the last lane (the lane steps of the prefix sum above)
+__device__ __forceinline__ float wave_add(float v)
+{
+    auto from = [&](auto step, auto rows) __attribute__((always_inline)) {
+        v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(step)::value, decltype(rows)::value, 0xf, false));
+    };
+    using std::integral_constant;
+    from(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});
+    from(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+    from(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+    from(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+    from(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});
+    from(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});
+    return v;
+}
+
 // bitwise or / smallest value over the 64 lanes of a wave, to all lanes (the lane steps of the prefix sum above; lanes
 // that a step does not reach combine their value with itself)
 template <typename F>
@@ -140,6 +160,12 @@ __device__ __forceinline__ uint32_t wave_fold(uint32_t v, F&& f)
 }
 __device__ __forceinline__ uint32_t wave_or(uint32_t v) { return wave_fold(v, [](uint32_t x, uint32_t y) { return x | y; }); }
 __device__ __forceinline__ uint32_t wave_min(uint32_t v) { return wave_fold(v, [](uint32_t x, uint32_t y) { return x < y ? x : y; }); }
+
+// largest of 64 numbers, none of them negative (their bits are in order)
+__device__ __forceinline__ float wave_max(float v)
+{
+    return __builtin_bit_cast(float, wave_fold(__builtin_bit_cast(uint32_t, v), [](uint32_t x, uint32_t y) { return x > y ? x : y; }));
+}
 
 // Lower edge of histogram bin b of a query whose bin 0 starts at base and whose bins are w
 // wide; one expression, used wherever a key is binned or a bound is derived, so that a key
@@ -263,185 +289,148 @@ __device__ __forceinline__ uint32_t wave_select(Cand* buf, int n, int k, const i
 }
 
 template <int DT> struct StoreTraits;
-template <> struct StoreTraits<HR_F32>  { static constexpr int esize = 4, planes = 2; };
+template <> struct StoreTraits<HR_F32>  { static constexpr int esize = 4, planes = 1; };
 template <> struct StoreTraits<HR_F16>  { static constexpr int esize = 2, planes = 1; };
 template <> struct StoreTraits<HR_BF16> { static constexpr int esize = 2, planes = 1; };
+template <> struct StoreTraits<HR_F16HI> { static constexpr int esize = 2, planes = 1; };
 template <> struct StoreTraits<HR_F16X2> { static constexpr int esize = 2, planes = 2; };
 
-// NW = waves per workgroup (4: one per SIMD, each may use all 512 registers; 8: two per SIMD
-// with 256 registers each, so that one wave's MFMAs run while the other selects or waits, or, two
-// workgroups on a unit, four with 128: see groups_per_cu).
-// NCS = 16-column MFMA sets per wave (1 or 2).  Every wave owns NCS * nc query columns, so a
-// work item covers NW * NCS * nc queries of a bucket; all waves share the staged rows.
+// Eight waves per workgroup: two per SIMD with 256 registers each, so that one wave's MFMAs run while the other selects or
+// waits, or, two workgroups on a unit, four with 128 (see groups_per_cu).  Every wave owns nc query columns, so a work item
+// covers 8 * nc queries of a bucket; all waves share the staged rows.
 //
-// Two ways of staging a block of rows (16, or up to 64 short ones: see block_groups) in LDS:
-//   direct (16-bit storage): global_load_lds moves 16-byte chunks from HBM straight into LDS,
-//     no registers and no LDS store instructions in between.  Such a load writes the 64 chunks
-//     of a wave next to each other, so rows cannot be padded; instead chunk c of row r sits at
-//     position c ^ (r & 15) of its row (d = 64: r & 7), which spreads the 16 rows of an MFMA fragment read over
-//     all banks.  Up to four blocks are in flight or waiting in LDS ahead of the one in use.
-//   through registers (float32 storage): rows are split into binary16 hi and lo planes on the
-//     way, from a ring of prefetch registers into two padded buffers.
-constexpr int kMaxAhead = 4;                  // most blocks staged ahead of the one in use (direct)
+// A block of rows (16, or up to 64 short ones: see block_groups) is staged by global_load_lds, which moves 16-byte
+// chunks from HBM straight into LDS, no registers and no LDS store instructions in between.  Such a load writes the 64 chunks
+// of a wave next to each other, so rows cannot be padded; instead chunk c of row r sits at position c ^ (r & 15) of its
+// row (rows of 8 chunks: r & 7), which spreads the 16 rows of an MFMA fragment read over all banks.  Up to four blocks
+// are in flight or waiting in LDS ahead of the one in use.
 
-template <int DT, int KSTEPS, int NCS, int NW>
+template <int DT, int KSTEPS>
 struct ScanShape {
-    static constexpr int nw = NW;
-    static constexpr int threads = NW * 64;
+    static constexpr int nw = kScanWaves;
     static constexpr int d = KSTEPS * 32;
-    static constexpr int nc = cols_per_set(DT, d);                 // query columns per 16-column MFMA set
+    static constexpr bool dense = DT == HR_F16X2;                  // the coarse step: every key written out, nothing selected
+    static constexpr bool bounded = scan_bounded(DT);              // keys are upper bounds: see k_scan
+    static constexpr int nc = cols_per_set(DT, d);                 // query columns per wave
     static constexpr int qp = operand_parts(DT, d);                // parts of the query operand in registers of their own
-    static constexpr int na = 2 * qp;                              // accumulators per column set (independent MFMA chains)
+    static constexpr int na = 2 * qp;                              // accumulators per group of rows (independent MFMA chains)
     static constexpr int planes = StoreTraits<DT>::planes;
+    static constexpr int raw = DT == HR_F32 ? 2 : planes;          // 16-byte reads from LDS per row fragment of a k-step
     static constexpr int rb = block_groups(DT, d);                 // groups of 16 rows per block
     static constexpr int br = kMfmaRows * rb;                      // rows per block
-    static constexpr bool direct = DT != HR_F32;                   // (HR_F16X2: two planes, both moved directly)
     static constexpr int rowb = d * StoreTraits<DT>::esize;        // bytes of one stored row
     static constexpr int cpr = rowb / 16;                          // 16-byte chunks per stored row
     static constexpr int swz = (cpr < 16 ? cpr : 16) - 1;          // row bits xor-ed into the chunk position
-    static constexpr int rowp = direct ? rowb : d * 2 + kRowPad;   // bytes of one staged row (one plane)
-    static constexpr int plane_bytes_padded = br * rowp;
     static constexpr int chunks = br * cpr;                        // 16-byte chunks per block
-    static constexpr int nfw = NW;                                 // waves that move rows: all
-    static constexpr int nld = (chunks + nfw * 64 - 1) / (nfw * 64);   // chunks per thread per block
-    // (direct: every wave always issues nld loads, so a buffer is a whole number of them)
-    static constexpr int plane_bytes = direct ? nld * nfw * 1024 : plane_bytes_padded;
+    static constexpr int nld = (chunks + nw * 64 - 1) / (nw * 64); // chunks per thread per block
+    // (every wave always issues nld loads, so a buffer is a whole number of them)
+    static constexpr int plane_bytes = nld * nw * 1024;
     static constexpr int buf_bytes = plane_bytes * planes;
-    static constexpr int nnl = (br + 63) / 64;                     // direct: loads of the norms of a block's rows
-    static constexpr int lpf = planes * nld + nnl;                 // direct: loads per wave per block (chunks + norms)
+    static constexpr int nnl = (br + 63) / 64;                     // loads of the norms of a block's rows
+    static constexpr int lpf = planes * nld + nnl;                 // loads per wave per block (chunks + norms)
     // k-steps whose row fragments are fetched from LDS together, ahead of their MFMAs
-    static constexpr int grp = scan_group(DT, KSTEPS, NW);
-    // register path: row blocks kept in flight in registers ahead of the one being staged
-    static constexpr int pf = scan_prefetch(DT, KSTEPS, NCS, NW);
-    static constexpr int wcols = nc * NCS;                         // query columns per wave
+    static constexpr int grp = scan_group(DT, KSTEPS);
     // a wave whose operand fills the register file: what the rare paths need is computed there (see lane_now), and
-    // the fragment addresses come from one register.  That is both parts of a long operand, and float32 rows of 32 k-steps
-    // passing through the registers (11.00 ms without, 4 registers spilled, 10.92 with: 1024 queries, 524288 rows).  The
-    // others have registers to spare and lose by it: binary16, 4096 queries x 4096 lists, d = 768, 2.46 -> 2.74 ms; 1024
-    // queries, 524288 rows of d = 1024: binary16 1.45 -> 1.46, bfloat16 2.27 -> 2.33, row tables 4.52 -> 4.69.
-    static constexpr bool lean = (qp == 2 && KSTEPS >= 16) || (DT == HR_F32 && KSTEPS >= 32);
+    // the fragment addresses come from one register.  The others have registers to spare and lose by it: binary16,
+    // 4096 queries x 4096 lists, d = 768, 2.46 -> 2.74 ms; 1024 queries, 524288 rows of d = 1024: binary16 1.45 -> 1.46.
+    static constexpr bool lean = qp == 2 && KSTEPS >= 16;
     // two blocks of a pair as one MFMA chain (see mfma_pair): twice the accumulators, which a wave that holds both
-    // parts of 24 k-steps has no registers for.  (Row tables of 16 k-steps would have them, 227 with the chain and 205
-    // without, and gain nothing: 1024 queries, 524288 rows 1.96 ms either way, 128 queries 0.73 without and 0.74 with.)
-    static constexpr bool chain = NCS == 1 && rb == 1 && (KSTEPS / grp) % 2 == 0 && grp * 2 <= KSTEPS && qp * planes * KSTEPS < 48;
-    static constexpr int cw = wcols * NW;                          // query columns per item
+    // parts of 24 k-steps has no registers for.
+    static constexpr bool chain = !dense && rb == 1 && (KSTEPS / grp) % 2 == 0 && grp * 2 <= KSTEPS && qp * KSTEPS < 48;
+    static constexpr int cw = nc * nw;                             // query columns per item
 };
 
 // s_waitcnt immediate that waits for all but n vector-memory operations (n <= 63) and for
 // nothing else
 __host__ __device__ constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
 
-
-// Every thread always loads (chunks past the end of the segment re-read its last chunk; the
-// rows they would belong to are masked out of the selection): an unconditional load keeps the
-// ring registers free of the zero-fill writes that would otherwise have to wait for the
-// loads still in flight.
-template <typename S>
-__device__ __forceinline__ void load_block(const char* src, int valid_chunks, u32x4 (&regs)[S::nld], bool once)
+// eight float32 values as binary16
+__device__ __forceinline__ half8 round8(const u32x4 (&raw)[2])
 {
-    // (once: nobody else reads these rows: non-temporal loads, so that they do not displace shared rows in the L2)
-    if (once) {
+    typedef float floatx8 __attribute__((ext_vector_type(8)));
+    const floatx4 x0 = __builtin_bit_cast(floatx4, raw[0]), x1 = __builtin_bit_cast(floatx4, raw[1]);
+    const floatx8 x = __builtin_shufflevector(x0, x1, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_convertvector(x, half8);
+}
+
+// eight float32 values as binary16, and what that rounding left over, times 2^11
+__device__ __forceinline__ void split8(const u32x4 (&raw)[2], half8& hi, half8& lo)
+{
+    const floatx4 x0 = __builtin_bit_cast(floatx4, raw[0]), x1 = __builtin_bit_cast(floatx4, raw[1]);
 #pragma unroll
-        for (int m = 0; m < S::nld; m++) {
-            int c = min((int)threadIdx.x + S::threads * m, valid_chunks - 1);
-            regs[m] = __builtin_nontemporal_load((const u32x4*)(src + (size_t)c * 16));
-        }
-    } else {
-#pragma unroll
-        for (int m = 0; m < S::nld; m++) {
-            int c = min((int)threadIdx.x + S::threads * m, valid_chunks - 1);
-            regs[m] = *(const u32x4*)(src + (size_t)c * 16);
-        }
+    for (int i = 0; i < 8; i++) {
+        const float x = i < 4 ? x0[i & 3] : x1[i & 3];
+        hi[i] = (_Float16)x;
+        lo[i] = (_Float16)((x - (float)hi[i]) * 2048.0f);
     }
 }
 
+// The products of one row fragment with the query operand of a wave (fragments of k-step t).
 template <int DT, typename S>
-__device__ __forceinline__ void stage_block(char* buf, const u32x4 (&regs)[S::nld])
+__device__ __forceinline__ void mfma_step(const u32x4 (&row)[S::raw], const u32x4 q_hi, const u32x4 q_lo, const int t, floatx4 (&acc)[S::na])
 {
-#pragma unroll
-    for (int m = 0; m < S::nld; m++) {
-        int c = threadIdx.x + S::threads * m;
-        if (S::chunks % S::threads != 0 && c >= S::chunks) continue;
-        constexpr int cpr = S::rowb / 16;              // chunks per row
-        int r = c / cpr, p = c % cpr;
-        if constexpr (DT == HR_F32) {
-            const floatx4 xv = __builtin_bit_cast(floatx4, regs[m]);
-            const float x[4] = {xv[0], xv[1], xv[2], xv[3]};
-            half4 hi, lo;
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                _Float16 h = (_Float16)x[i];
-                hi[i] = h;
-                lo[i] = (_Float16)((x[i] - (float)h) * 2048.0f);
-            }
-            *(half4*)(buf + r * S::rowp + p * 8) = hi;
-            *(half4*)(buf + S::plane_bytes + r * S::rowp + p * 8) = lo;
-        } else {
-            *(u32x4*)(buf + r * S::rowp + p * 16) = regs[m];
+    auto f16 = [](half8 x, u32x4 q, floatx4& c) __attribute__((always_inline)) { c = __builtin_amdgcn_mfma_f32_16x16x32_f16(x, __builtin_bit_cast(half8, q), c, 0, 0, 0); };
+    if constexpr (DT == HR_F16 || DT == HR_F16HI) {
+        f16(__builtin_bit_cast(half8, row[0]), q_hi, acc[t & 1]);
+    } else if constexpr (DT == HR_F32) {
+        f16(round8(row), q_hi, acc[t & 1]);
+    } else if constexpr (DT == HR_BF16) {
+        auto bf16 = [&](u32x4 q, floatx4& c) __attribute__((always_inline)) {
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, row[0]), __builtin_bit_cast(bf16x8, q), c, 0, 0, 0);
+        };
+        bf16(q_hi, acc[t & 1]);
+        if constexpr (S::qp == 2) bf16(q_lo, acc[2 + (t & 1)]);
+    } else {
+        // (in one column: hi q x hi and lo rows, lo q x hi and lo rows; in two columns each lane has its part of the query)
+        f16(__builtin_bit_cast(half8, row[0]), q_hi, acc[0]);
+        f16(__builtin_bit_cast(half8, row[1]), q_hi, acc[1]);
+        if constexpr (S::qp == 2) {
+            f16(__builtin_bit_cast(half8, row[0]), q_lo, acc[2]);
+            f16(__builtin_bit_cast(half8, row[1]), q_lo, acc[3]);
         }
     }
 }
 
-// The staged rows x NA column sets x d: the MFMA chains of one block.  acc[s][j][*] are the partial
-// accumulators of set s and the j-th 16 rows (for HR_F32: [0] hi-row and [1] lo-row products; else summed at the end).  The row fragments
-// are fetched from LDS a group of k-steps ahead of the MFMAs that use them (the scheduling
-// barriers keep the compiler from sinking each read next to its use, which would expose the
-// LDS latency 24 times per block).  The fragment of k-step t of the first 16 rows is at ap[t & 3] + (t >> 2) * 256:
-// with padded rows the four bases are 64 bytes apart, with the xor-ed chunk positions of the
-// direct staging they are permuted per lane.
-template <int DT, int KSTEPS, int NCS, int NA, typename S>
-__device__ __forceinline__ void mfma_block(const char* const (&ap)[4], const u32x4 (&bfrag)[NCS * S::qp][KSTEPS], floatx4 (&acc)[NCS][S::rb][S::na])
+// The staged rows x the wave's query columns x d: the MFMA chains of one block.  acc[j][*] are the partial
+// accumulators of the j-th 16 rows.  The row fragments are fetched from LDS a group of k-steps ahead of the MFMAs that
+// use them (the scheduling barriers keep the compiler from sinking each read next to its use, which would expose the
+// LDS latency 24 times per block).  The fragment of k-step t of the first 16 rows is at ap[t & 3] + (t >> 2) * 256
+// (float32: its halves at ap[2 (t & 1)] and ap[2 (t & 1) + 1], + (t >> 1) * 256); the four bases are permuted per lane
+// by the xor-ed chunk positions of the staging.
+template <int DT, int KSTEPS, typename S>
+__device__ __forceinline__ void mfma_block(const char* const (&ap)[4], const u32x4 (&bfrag)[S::qp][KSTEPS], floatx4 (&acc)[S::rb][S::na])
 {
     constexpr int G = S::grp;                        // k-steps per group
     constexpr int NT = S::rb * KSTEPS;               // k-steps of the groups of 16 rows, one after the other
     constexpr int NG = NT / G;
-    constexpr int P = StoreTraits<DT>::planes;
     static_assert(NT % G == 0, "k-steps must split into whole groups");
+    static_assert(KSTEPS % G == 0 || S::rb > 1, "k-steps must split into whole groups");
 #pragma unroll
-    for (int s = 0; s < NA; s++)
+    for (int j = 0; j < S::rb; j++)
 #pragma unroll
-        for (int j = 0; j < S::rb; j++)
-#pragma unroll
-            for (int i = 0; i < S::na; i++) acc[s][j][i] = floatx4{0.f, 0.f, 0.f, 0.f};
-    u32x4 af[2][P][G];
-    auto fetch = [&](int gi, int i, int pl) __attribute__((always_inline)) {
+        for (int i = 0; i < S::na; i++) acc[j][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+    u32x4 af[2][G][S::raw];
+    auto fetch = [&](int gi, int i) __attribute__((always_inline)) {
         const int u = gi * G + i, t = u % KSTEPS, j = u / KSTEPS;
-        af[gi & 1][pl][i] = *(const u32x4*)(ap[t & 3] + pl * S::plane_bytes + (t >> 2) * 256 + j * kMfmaRows * S::rowp);
+#pragma unroll
+        for (int r = 0; r < S::raw; r++) {
+            if constexpr (DT == HR_F32) af[gi & 1][i][r] = *(const u32x4*)(ap[(t & 1) * 2 + r] + (t >> 1) * 256 + j * kMfmaRows * S::rowb);
+            else                        af[gi & 1][i][r] = *(const u32x4*)(ap[t & 3] + r * S::plane_bytes + (t >> 2) * 256 + j * kMfmaRows * S::rowb);
+        }
     };
 #pragma unroll
-    for (int i = 0; i < G; i++)
-#pragma unroll
-        for (int pl = 0; pl < P; pl++) fetch(0, i, pl);
+    for (int i = 0; i < G; i++) fetch(0, i);
 #pragma unroll
     for (int gi = 0; gi < NG; gi++) {
         if (gi + 1 < NG) {
 #pragma unroll
-            for (int i = 0; i < G; i++)
-#pragma unroll
-                for (int pl = 0; pl < P; pl++) fetch(gi + 1, i, pl);
+            for (int i = 0; i < G; i++) fetch(gi + 1, i);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < G; i++) {
             const int t = (gi * G + i) % KSTEPS, j = (gi * G + i) / KSTEPS;
-#pragma unroll
-            for (int s = 0; s < NA; s++) {
-#pragma unroll
-                for (int qp = 0; qp < S::qp; qp++) {
-                    const u32x4 bq = bfrag[s * S::qp + qp][t];
-                    if constexpr (StoreTraits<DT>::planes == 2) {
-                        half8 b = __builtin_bit_cast(half8, bq);
-                        acc[s][j][qp * 2] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gi & 1][0][i]), b, acc[s][j][qp * 2], 0, 0, 0);
-                        acc[s][j][qp * 2 + 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gi & 1][1][i]), b, acc[s][j][qp * 2 + 1], 0, 0, 0);
-                    } else if constexpr (DT == HR_F16) {
-                        half8 b = __builtin_bit_cast(half8, bq);
-                        acc[s][j][t & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gi & 1][0][i]), b, acc[s][j][t & 1], 0, 0, 0);
-                    } else {
-                        bf16x8 b = __builtin_bit_cast(bf16x8, bq);
-                        acc[s][j][qp * 2 + (t & 1)] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[gi & 1][0][i]), b, acc[s][j][qp * 2 + (t & 1)], 0, 0, 0);
-                    }
-                }
-            }
+            mfma_step<DT, S>(af[gi & 1][i], bfrag[0][t], bfrag[S::qp - 1][t], t, acc[j]);
         }
         __builtin_amdgcn_sched_barrier(0);
     }
@@ -451,20 +440,17 @@ __device__ __forceinline__ void mfma_block(const char* const (&ap)[4], const u32
 // fragments of the second block are fetched while the last MFMAs of the first are issued (a block started on
 // its own begins with a round trip to LDS during which the wave has nothing to issue), and `between` (the
 // filter of the first block) runs after the first MFMAs of the second block have been handed to the matrix pipe.
-template <int DT, int KSTEPS, int NCS, int NA, typename S, typename F>
-__device__ __forceinline__ void mfma_pair(const char* const (&ap0)[4], const char* const (&ap1)[4], const u32x4 (&bfrag)[NCS * S::qp][KSTEPS],
-                                          floatx4 (&acc0)[NCS][S::rb][S::na], floatx4 (&acc1)[NCS][S::rb][S::na], F&& between)
+template <int DT, int KSTEPS, typename S, typename F>
+__device__ __forceinline__ void mfma_pair(const char* const (&ap0)[4], const char* const (&ap1)[4], const u32x4 (&bfrag)[S::qp][KSTEPS],
+                                          floatx4 (&acc0)[S::rb][S::na], floatx4 (&acc1)[S::rb][S::na], F&& between)
 {
     constexpr int G = S::grp;
     constexpr int NG = KSTEPS / G;
-    constexpr int P = StoreTraits<DT>::planes;
     static_assert(KSTEPS % G == 0, "k-steps must split into whole groups");
     static_assert(NG % 2 == 0, "the fragment buffers alternate: an even number of groups per block");
 #pragma unroll
-    for (int s = 0; s < NA; s++)
-#pragma unroll
-        for (int i = 0; i < S::na; i++) { acc0[s][0][i] = floatx4{0.f, 0.f, 0.f, 0.f}; acc1[s][0][i] = floatx4{0.f, 0.f, 0.f, 0.f}; }
-    u32x4 af[2][P][G];
+    for (int i = 0; i < S::na; i++) { acc0[0][i] = floatx4{0.f, 0.f, 0.f, 0.f}; acc1[0][i] = floatx4{0.f, 0.f, 0.f, 0.f}; }
+    u32x4 af[2][G][S::raw];
     // (every index below is a compile-time constant: the loop over the groups is unrolled by the type system,
     // so that the operand and accumulator arrays stay in registers)
     auto fetch = [&](auto gc) __attribute__((always_inline)) {       // group gg of the 2 * NG groups of the pair
@@ -473,34 +459,19 @@ __device__ __forceinline__ void mfma_pair(const char* const (&ap0)[4], const cha
 #pragma unroll
         for (int i = 0; i < G; i++)
 #pragma unroll
-            for (int pl = 0; pl < P; pl++) {
-                if constexpr (gg < NG) af[gg & 1][pl][i] = *(const u32x4*)(ap0[(g0 + i) & 3] + pl * S::plane_bytes + ((g0 + i) >> 2) * 256);
-                else                   af[gg & 1][pl][i] = *(const u32x4*)(ap1[(g0 + i) & 3] + pl * S::plane_bytes + ((g0 + i) >> 2) * 256);
+            for (int r = 0; r < S::raw; r++) {
+                const int t = g0 + i;
+                const char* b = DT == HR_F32 ? (gg < NG ? ap0[(t & 1) * 2 + r] : ap1[(t & 1) * 2 + r]) + (t >> 1) * 256
+                                             : (gg < NG ? ap0[t & 3] : ap1[t & 3]) + r * S::plane_bytes + (t >> 2) * 256;
+                af[gg & 1][i][r] = *(const u32x4*)b;
             }
     };
-    auto group = [&](auto gc, floatx4 (&acc)[NCS][S::rb][S::na]) __attribute__((always_inline)) {
+    auto group = [&](auto gc, floatx4 (&acc)[S::rb][S::na]) __attribute__((always_inline)) {
         constexpr int gg = decltype(gc)::value;
 #pragma unroll
         for (int i = 0; i < G; i++) {
             const int t = (gg < NG ? gg : gg - NG) * G + i;
-#pragma unroll
-            for (int s = 0; s < NA; s++) {
-#pragma unroll
-                for (int qp = 0; qp < S::qp; qp++) {
-                    const u32x4 bq = bfrag[s * S::qp + qp][t];
-                    if constexpr (StoreTraits<DT>::planes == 2) {
-                        half8 b = __builtin_bit_cast(half8, bq);
-                        acc[s][0][qp * 2] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gg & 1][0][i]), b, acc[s][0][qp * 2], 0, 0, 0);
-                        acc[s][0][qp * 2 + 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gg & 1][1][i]), b, acc[s][0][qp * 2 + 1], 0, 0, 0);
-                    } else if constexpr (DT == HR_F16) {
-                        half8 b = __builtin_bit_cast(half8, bq);
-                        acc[s][0][t & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8, af[gg & 1][0][i]), b, acc[s][0][t & 1], 0, 0, 0);
-                    } else {
-                        bf16x8 b = __builtin_bit_cast(bf16x8, bq);
-                        acc[s][0][qp * 2 + (t & 1)] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af[gg & 1][0][i]), b, acc[s][0][qp * 2 + (t & 1)], 0, 0, 0);
-                    }
-                }
-            }
+            mfma_step<DT, S>(af[gg & 1][i], bfrag[0][t], bfrag[S::qp - 1][t], t, acc[0]);
         }
     };
     fetch(std::integral_constant<int, 0>{});
@@ -522,42 +493,187 @@ __device__ __forceinline__ uint32_t select_k(Cand* buf, int n, int k, int cap, c
 {
     if (cap <= 64) return wave_select<1>(buf, n, k, ids, nullptr, lane);
     if (cap <= 128) return wave_select<2>(buf, n, k, ids, nullptr, lane);
-    return wave_select<3>(buf, n, k, ids, nullptr, lane);
+    if (cap <= 192) return wave_select<3>(buf, n, k, ids, nullptr, lane);
+    return wave_select<4>(buf, n, k, ids, nullptr, lane);
 }
 
-// GS = a.gsel, GROUPS = a.dense_groups > 0 (an instance of its own: both orders in one made the shortest coarse calls up to 0.5 us
-// longer, 200 queries, 1024 centroids, d = 64, 15.6 and 16.1)
-template <int DT, int KSTEPS, int NCS, int NW, bool GS, bool GROUPS = false>
-__global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) == 2 ? 4 : 1) void k_scan(ScanArgs a)
+// what is xor-ed into the address of a lane's row fragment of k-step 0 for base j of mfma_block
+template <int DT>
+__device__ __forceinline__ constexpr int frag_step(int j) { return DT == HR_F32 ? 128 * (j >> 1) + 16 * (j & 1) : 64 * j; }
+
+// Bounded types: the scan multiplies the high parts of rows and query alone, and the key of a row is that product's plus what the
+// parts left out can add at most, |x.y| <= |x| |y|: an upper bound of its exact key, and less two slacks a lower one.
+// bound: of the list's rows the largest squared norm and the largest squared norm of what rounding them to
+// binary16 left over.  q, q_lo: norms of the query and of its low part (infinite: no bound).  Two hundredths more for the
+// roundings of the norms and for the product of the low parts, 2^-19 |q| |x| for the float32 sums of key and exact
+// key; with squared L2 a key is twice the product less the squared norm, both rounded.
+__device__ __forceinline__ float scan_slack(float q, float q_lo, float2 bound, int l2)
 {
-    using S = ScanShape<DT, KSTEPS, NCS, NW>;
-    using T = StoreTraits<DT>;
+    const float n2 = fmaxf(bound.x, 1e-18f), norm = sqrtf(n2);   // (squares of smaller numbers may have vanished)
+    float s = 1.02f * (q_lo * norm + q * sqrtf(bound.y)) + 1.9073486328125e-06f * q * norm;
+    if (l2) s = 2.0f * s + n2 * 9.5367431640625e-07f;
+    return s < __builtin_inff() ? s : __builtin_inff();          // (also for NaN)
+}
+
+// What two float32 sums of the same products may differ by, with room: half of what scan_slack counts for it.
+__device__ __forceinline__ float exact_add(float qnorm2, float norm2, int l2)
+{
+    const float s = 9.5367431640625e-07f * sqrtf(qnorm2) * sqrtf(fmaxf(norm2, 1e-18f));
+    return l2 ? 2.0f * s + norm2 * 4.76837158203125e-07f : s;
+}
+
+// Order-preserving image of the key that lies w below the one with image u.
+__device__ __forceinline__ uint32_t key_below(uint32_t u, float w)
+{
+    const float f = dec_key(u) - w;
+    return f == f ? enc_key(f) : kKeyNegInf;                     // (an infinite key less an infinite slack)
+}
+
+// Of the n candidates in buf those that may be among the k best, given that a key is at most w above the exact one: all within w
+// of the k-th largest key.  bound: set to a key that the k-th best exact one reaches; best: how many keys at the head of buf are the
+// k largest (and those equal to the k-th).  Returns how many are left in buf.
+template <int CAPE>   // entries held per lane: CAPE * 64 >= n
+__device__ __forceinline__ int wave_window(Cand* buf, int n, int k, float w, uint32_t& bound, int& best, const int lane)
+{
+    Cand e[CAPE];
+    unsigned long long alive[CAPE];
+    uint32_t has1 = 0, has0 = 0;
+#pragma unroll
+    for (int m = 0; m < CAPE; m++) {
+        const bool valid = lane + 64 * m < n;
+        e[m] = valid ? buf[lane + 64 * m] : Cand{0u, 0u};
+        alive[m] = __builtin_amdgcn_ballot_w64(valid);
+        if (valid) { has1 |= e[m].key; has0 |= ~e[m].key; }
+    }
+    // the k-th largest key (or, once as many keys are left as are wanted, what is below all of them and above the others)
+    has1 = wave_or(has1);
+    const uint32_t differ = has1 & wave_or(has0);
+    int b = differ ? 31 - __builtin_clz(differ) : -1;
+    uint32_t T = b < 0 ? has1 : has1 & ~(uint32_t)((2ull << b) - 1);
+    for (int need = k, left = n; b >= 0 && left != need; b--) {
+        unsigned long long ones[CAPE];
+        int c1 = 0;
+#pragma unroll
+        for (int m = 0; m < CAPE; m++) {
+            ones[m] = alive[m] & __builtin_amdgcn_ballot_w64((e[m].key >> b) & 1u);
+            c1 += __builtin_popcountll(ones[m]);
+        }
+        const bool up = c1 >= need;
+        if (up) { T |= 1u << b; left = c1; } else { need -= c1; left -= c1; }
+#pragma unroll
+        for (int m = 0; m < CAPE; m++) alive[m] = up ? ones[m] : alive[m] & ~ones[m];
+    }
+    bound = key_below(T, w);
+    wave_sync();
+    int left = 0;
+#pragma unroll
+    for (int part = 0; part < 2; part++) {
+#pragma unroll
+        for (int m = 0; m < CAPE; m++) {
+            const bool keep = lane + 64 * m < n && (part == 0 ? e[m].key >= T : e[m].key < T && e[m].key >= bound);
+            const unsigned long long mask = __builtin_amdgcn_ballot_w64(keep);
+            if (keep) buf[left + lanes_below(mask)] = e[m];
+            left += __builtin_popcountll(mask);
+        }
+        if (part == 0) best = left;
+    }
+    wave_sync();
+    return left;
+}
+
+// The exact keys (plus add) of the entries first, first + step, .. of the n in buf, in place of their bounds: rows and query
+// in float32, one wave, CH chunks of 256 elements of AT rows on their way together (past the end of a row its first elements
+// again, times zero: a load under a condition would wait for the one before).  Entries of a carried result stay as they are.
+template <int AT, int CH>
+__device__ __forceinline__ void exact_keys(Cand* buf, int n, int first, int step, const float* rows, const float* row_norm, const float* query, int d, int l2, float add)
+{
+    const int lane = lane_now();
+    if (first >= n) return;
+    for (int c0 = 0; c0 < d; c0 += CH * 256) {                  // (once where CH chunks are a whole row: first and last)
+        floatx4 y[CH];
+        int at[CH];
+#pragma unroll
+        for (int c = 0; c < CH; c++) {
+            const int i = c0 + c * 256 + lane * 4;
+            at[c] = i < d ? i : 0;
+            y[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+            if (i < d) y[c] = floatx4{query[i], query[i + 1], query[i + 2], query[i + 3]};       // (the caller's: any alignment)
+        }
+        const bool last = c0 + CH * 256 >= d;
+#pragma unroll 1
+        for (int e0 = first; e0 < n; e0 += AT * step) {
+            uint32_t r[AT];
+            floatx4 x[AT][CH];
+            float norm[AT], dot[AT];
+#pragma unroll
+            for (int j = 0; j < AT; j++) r[j] = __builtin_amdgcn_readfirstlane(buf[min(e0 + j * step, n - 1)].row);
+#pragma unroll
+            for (int j = 0; j < AT; j++) {
+                const float* p = rows + (size_t)(r[j] & kCarried ? 0u : r[j]) * d;
+#pragma unroll
+                for (int c = 0; c < CH; c++) x[j][c] = *(const floatx4*)(p + at[c]);
+                norm[j] = l2 ? row_norm[r[j] & kCarried ? 0u : r[j]] : 0.f;
+            }
+#pragma unroll
+            for (int j = 0; j < AT; j++) {
+                dot[j] = 0.f;
+#pragma unroll
+                for (int c = 0; c < CH; c++)
+#pragma unroll
+                    for (int m = 0; m < 4; m++) dot[j] = __builtin_fmaf(x[j][c][m], y[c][m], dot[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < AT; j++) dot[j] = wave_add(dot[j]);
+#pragma unroll
+            for (int j = 0; j < AT; j++) {
+                const int e = e0 + j * step;
+                if (lane == 63 && e < n && !(r[j] & kCarried)) {
+                    float sum = dot[j];
+                    if (c0 > 0) sum += dec_key(buf[e].key);
+                    if (last) sum = (l2 ? 2.0f * sum - norm[j] : sum) + add;
+                    buf[e].key = enc_key(sum);
+                }
+            }
+        }
+        wave_sync();
+    }
+}
+
+__device__ __forceinline__ int window_k(Cand* buf, int n, int k, int cap, float w, uint32_t& bound, int lane)
+{
+    int best;
+    if (cap <= 64) return wave_window<1>(buf, n, k, w, bound, best, lane);
+    if (cap <= 128) return wave_window<2>(buf, n, k, w, bound, best, lane);
+    if (cap <= 192) return wave_window<3>(buf, n, k, w, bound, best, lane);
+    return wave_window<4>(buf, n, k, w, bound, best, lane);
+}
+
+// GROUPS = a.dense_groups > 0 (an instance of its own: both orders in one made the shortest coarse calls up to 0.5 us
+// longer, 200 queries, 1024 centroids, d = 64, 15.6 and 16.1)
+template <int DT, int KSTEPS, bool GROUPS = false>
+__global__ __launch_bounds__(kScanWaves * 64, groups_per_cu(DT, KSTEPS * 32) == 2 ? 4 : 1) void k_scan(ScanArgs a)
+{
+    using S = ScanShape<DT, KSTEPS>;
+    constexpr int NW = S::nw;
     constexpr int NC = S::nc;
     constexpr int QP = S::qp;
-    constexpr int WC = S::wcols;
-    // the coarse step: all queries against all rows, every key written out, nothing selected (lists split into two
-    // tables at load always keep their selection buffers in global memory)
-    constexpr bool DENSE = DT == HR_F16X2 && !GS;
-    constexpr int PF = S::pf;
+    constexpr bool DENSE = S::dense;
     constexpr int NLD = S::nld;
     constexpr int RB = S::rb, BR = S::br;
     extern __shared__ __align__(16) char smem[];
-    // staging buffers in LDS: a.nbuf of them (direct) or 2 (through registers); block blk of an
-    // item uses buffer blk % NB, and the blocks up to blk + NB - 1 are on their way meanwhile
-    // With 4 or 6 buffers (direct) the blocks go in pairs: one barrier per two blocks, the next pair
+    // staging buffers in LDS: a.nbuf of them; block blk of an item uses buffer blk % NB, and the blocks up to blk + NB - 1 are
+    // on their way meanwhile.
+    // With 4 or 6 buffers the blocks go in pairs: one barrier per two blocks, the next pair
     // on its way meanwhile.  A barrier per block keeps the two waves of a SIMD in step (both
     // want the matrix pipeline, then both the vector ALU); between the barriers of a pair they
     // drift apart and overlap.
-    const int NB = S::direct ? a.nbuf : 2;
-    const bool pairs = S::direct && (NB == 4 || NB == 6);
+    const int NB = a.nbuf;
+    const bool pairs = NB == 4 || NB == 6;
     const int D = pairs ? NB - 2 : NB - 1;         // blocks requested ahead of the one in use
-    // LDS: [NB staging buffers][selection buffers cw*cap][row norms NB x BR][item]
-    // (GS: the selection buffers are the item's result slots in global memory instead: a
-    // wave alone writes and reads the buffers of its columns, candidates are few, and LDS is
-    // left to the row buffers)
+    // LDS: [NB staging buffers][row norms NB x BR][item].  The selection buffers are the item's result slots in global
+    // memory: a wave alone writes and reads the buffers of its columns, candidates are few, and LDS is left to the rows.
     char* stage = smem;
-    Cand* sel = (Cand*)(smem + NB * S::buf_bytes);
-    float* nstage = (float*)(sel + (GS ? 0 : S::cw * a.cap));
+    float* nstage = (float*)(smem + NB * S::buf_bytes);
     int* s_item = (int*)(nstage + NB * BR);
 
     const int lane = lane_id();
@@ -566,7 +682,6 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
     const int jcol = lane & (NC - 1);              // column inside a set
     const int part = (NC == 8) ? ((lane >> 3) & 1) : 0;   // 0 = hi, 1 = lo operand column
     const bool owner = (NC == 16) || part == 0;    // lane whose accumulator holds the full dot
-    Cand* mysel = sel + (wave * WC) * a.cap;
     const int seg_rows = a.dense_seg_rows;                   // (dense mode only: the items of the lists carry their rows)
     const int myx = blockIdx.x & 7;                // workgroups are dealt round-robin to the 8 XCDs
     bool started = false, own = true;              // first item taken; own queue not seen empty yet
@@ -579,32 +694,24 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
     // ---- per-lane constants of the staging layout
     // row fragment of k-step t of this lane: abase[t & 3] + (t >> 2) * 256 inside a buffer
     int abase[4];
-    // direct: byte offset inside a stored block of the chunk that load m of this lane moves
+    // byte offset inside a stored block of the chunk that load m of this lane moves
     uint32_t goff[NLD];
     {
         const int i = lane & 15;
-        if constexpr (S::direct) {
-            const int hi = (i & S::swz) >> 2, lo = i & 3;
-            static_assert(!S::lean || S::rowp % 256 == 0, "the xor below stays inside a row");
-            if constexpr (S::lean) {
-                // (a row is a multiple of 256 bytes: the address of step j is that of step 0 with 64 j xor-ed in)
-                abase[0] = i * S::rowp + 64 * hi + 16 * (g ^ lo);
-                abase[1] = abase[2] = abase[3] = 0;
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; j++) abase[j] = i * S::rowp + 64 * (j ^ hi) + 16 * (g ^ lo);
-            }
-#pragma unroll
-            for (int m = 0; m < NLD; m++) {
-                const int L = (m * S::nfw + wave) * 64 + lane;  // chunk position inside the buffer
-                const int r = L / S::cpr, pos = L % S::cpr;
-                goff[m] = (uint32_t)(min(r, BR - 1) * S::cpr + (pos ^ (r & S::swz))) * 16u;
-            }
+        static_assert(!S::lean || S::rowb % 256 == 0, "the xor below stays inside a row");
+        if constexpr (S::lean) {
+            // (a row is a multiple of 256 bytes: the address of step j is that of step 0 with frag_step(j) xor-ed in)
+            abase[0] = i * S::rowb + 16 * ((DT == HR_F32 ? 2 * g : g) ^ (i & S::swz));
+            abase[1] = abase[2] = abase[3] = 0;
         } else {
 #pragma unroll
-            for (int j = 0; j < 4; j++) abase[j] = i * S::rowp + g * 16 + j * 64;
+            for (int j = 0; j < 4; j++) abase[j] = i * S::rowb + ((16 * ((DT == HR_F32 ? 2 * g : g) ^ (i & S::swz))) ^ frag_step<DT>(j));
+        }
 #pragma unroll
-            for (int m = 0; m < NLD; m++) goff[m] = 0;
+        for (int m = 0; m < NLD; m++) {
+            const int L = (m * S::nw + wave) * 64 + lane;  // chunk position inside the buffer
+            const int r = L / S::cpr, pos = L % S::cpr;
+            goff[m] = (uint32_t)(min(r, BR - 1) * S::cpr + (pos ^ (r & S::swz))) * 16u;
         }
     }
 
@@ -651,7 +758,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
             }
             if (x >= 0) {
                 const int* rec = (const int*)(a.xq_rec + ((size_t)x * a.xq_stride + pos) * 2);
-                if (lane < 6) s_item[1 + lane] = rec[lane];
+                if (lane < 7) s_item[1 + lane] = rec[lane];
                 item = 0;
             }
         }
@@ -665,7 +772,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
         if (item < 0) break;
 
         // ---- decode the work item
-        int qt, row0, row_end, w, boff, slot0 = 0;
+        int qt, row0, row_end, w, boff, slot0 = 0, list = 0;
         if (DENSE) {
             // plain order: all tiles of a segment, then those of the next.  In groups: tiles g, g + groups, g + 2 groups, .. of all
             // segments, then those of the next group; the first `more` groups have one tile more than the others.
@@ -693,10 +800,11 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
             w = __builtin_amdgcn_readfirstlane(s_item[4]);
             qt = __builtin_amdgcn_readfirstlane(s_item[5]);
             slot0 = __builtin_amdgcn_readfirstlane(s_item[6]);
+            list = __builtin_amdgcn_readfirstlane(s_item[7]);
         }
         const int nrows = row_end - row0;
         const int nblk = (nrows + BR - 1) / BR;
-        Cand* const gsel = a.slot_ent + ((size_t)slot0 + wave * WC) * (size_t)a.slot_stride;   // (GS: slot_stride = cap)
+        Cand* const sel = a.slot_ent + ((size_t)slot0 + wave * NC) * (size_t)a.cap;     // selection buffers of this wave's columns
         const char* src = (const char*)a.rows + (size_t)row0 * S::rowb;
         const char* src_lo = S::planes == 2 ? (const char*)a.rows_lo + (size_t)row0 * S::rowb : src;
 
@@ -705,13 +813,13 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
         // start (nobody reads the copy): every wave then has the same, fixed number of loads in flight at every
         // point of the loop, which is what the wait counts below rely on.
         //
-        // direct: block blk -> buffer buf, straight from HBM, and the squared norms of its rows (64 .. 256 bytes) beside it
+        // Block blk -> buffer buf, straight from HBM, and the squared norms of its rows (64 .. 256 bytes) beside it
         const bool stream_once = !DENSE && w <= S::cw;   // the only work item that reads these rows
-        auto fill_direct = [&](int blk, int buf) __attribute__((always_inline)) {
+        auto fill = [&](int blk, int buf) __attribute__((always_inline)) {
             if (RB > 1 && blk >= nblk) {
 #pragma unroll
                 for (int m = 0; m < NLD * S::planes; m++)
-                    lds_dma16(src, 0u, lds_addr(stage) + buf * S::buf_bytes + (m / NLD) * S::plane_bytes + wave * 1024 + (m % NLD) * S::nfw * 1024);
+                    lds_dma16(src, 0u, lds_addr(stage) + buf * S::buf_bytes + (m / NLD) * S::plane_bytes + wave * 1024 + (m % NLD) * S::nw * 1024);
                 if (a.l2) {
 #pragma unroll
                     for (int j = 0; j < S::nnl; j++)
@@ -728,20 +836,20 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
                 if (valid == BR) {
                     if (stream_once) {
 #pragma unroll
-                        for (int m = 0; m < NLD; m++) lds_dma16_nt(bsrc, goff[m], dst + m * S::nfw * 1024);
+                        for (int m = 0; m < NLD; m++) lds_dma16_nt(bsrc, goff[m], dst + m * S::nw * 1024);
                     } else {
 #pragma unroll
-                        for (int m = 0; m < NLD; m++) lds_dma16(bsrc, goff[m], dst + m * S::nfw * 1024);
+                        for (int m = 0; m < NLD; m++) lds_dma16(bsrc, goff[m], dst + m * S::nw * 1024);
                     }
                 } else {
                     // ragged last block: rows past the end repeat the last valid one (their scores
                     // are masked out of the selection)
 #pragma unroll
                     for (int m = 0; m < NLD; m++) {
-                        const int L = (m * S::nfw + wave) * 64 + lane_here();
+                        const int L = (m * S::nw + wave) * 64 + lane_here();
                         const int r = L / S::cpr, pos = L % S::cpr;
                         const uint32_t o = (uint32_t)(min(r, valid - 1) * S::cpr + (pos ^ (r & S::swz))) * 16u;
-                        lds_dma16(bsrc, o, dst + m * S::nfw * 1024);
+                        lds_dma16(bsrc, o, dst + m * S::nw * 1024);
                     }
                 }
             }
@@ -755,108 +863,65 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
                 }
             }
         };
-        // through registers: a ring of PF blocks in flight
-        u32x4 ring[S::direct ? 1 : PF][NLD];
-        float nring[S::direct ? 1 : PF];
-        auto block_chunks = [&](int blk) __attribute__((always_inline)) { return min(nrows - min(blk, nblk - 1) * BR, BR) * S::cpr; };
-        auto block_src = [&](int blk) __attribute__((always_inline)) { return src + (size_t)min(blk, nblk - 1) * BR * S::rowb; };
-        auto load_norm = [&](int blk) __attribute__((always_inline)) {
-            const int r = min(row0 + min(blk, nblk - 1) * BR + (int)(threadIdx.x & (BR - 1)), row_end - 1);
-            return a.row_norm[r];
-        };
-
         // ---- first row blocks on their way before anything else
-        if constexpr (S::direct) {
-            for (int i = 0; i < D; i++) fill_direct(i, i);
-        } else {
-            load_block<S>(block_src(0), block_chunks(0), ring[0], stream_once);
-            nring[0] = load_norm(0);
-        }
+        for (int i = 0; i < D; i++) fill(i, i);
 
         // ---- query operands of this lane's columns into registers (B fragments)
-        // entry inside the bucket, set 0 (dense: a wave may hold fewer queries than it has columns for, see make_plan)
+        // entry inside the bucket (dense: a wave may hold fewer queries than it has columns for, see make_plan)
         constexpr bool SOME = DENSE && QP == 2 && KSTEPS >= 16;
-        const int cpw = SOME ? a.dense_cols : WC;
-        const int ecol0 = (qt * NW + wave) * cpw + jcol;
-        bool col_ok[NCS];
-        int q[NCS];
-        float thr[NCS];
-        u32x4 bfrag[NCS * QP][KSTEPS];
+        const int cpw = SOME ? a.dense_cols : NC;
+        const int ecol = (qt * NW + wave) * cpw + jcol;
+        u32x4 bfrag[QP][KSTEPS];
+        const bool col_ok = ecol < w && (!SOME || jcol < cpw);
+        int q = 0;
+        if (col_ok) q = DENSE ? ecol : a.bucket_q[boff + ecol];
+        // operand rows of a query: both parts where they are in registers or in two columns, and of bounded types
+        constexpr int QROWS = DT == HR_F16 ? 1 : 2;
+        const char* const qrow = (const char*)a.qop + ((size_t)q * QROWS + (NC == 8 ? part : 0)) * (size_t)(S::d * 2) + g * 16;
+        if (DENSE && a.queries != nullptr) {
+            // (the same split as k_prep_queries makes; DENSE is HR_F16X2: hi and lo, in two operands or two columns)
+            const float* qp = a.queries + (size_t)q * S::d + g * 8;
 #pragma unroll
-        for (int s = 0; s < NCS; s++) {
-            const int ecol = ecol0 + s * NC;
-            col_ok[s] = ecol < w && (!SOME || jcol < cpw);
-            q[s] = 0;
-            if (col_ok[s]) q[s] = DENSE ? ecol : a.bucket_q[boff + ecol];
-        }
-#pragma unroll
-        for (int s = 0; s < NCS; s++) {
-            if (DENSE && a.queries != nullptr) {
-                // (the same split as k_prep_queries makes; DENSE is HR_F16X2: hi and lo, in two operands or two columns)
-                const float* qp = a.queries + (size_t)q[s] * S::d + g * 8;
-#pragma unroll
-                for (int t = 0; t < KSTEPS; t++) {
-                    const floatx4 x0 = *(const floatx4*)(qp + t * 32), x1 = *(const floatx4*)(qp + t * 32 + 4);
-                    half8 hi, lo;
-#pragma unroll
-                    for (int i = 0; i < 8; i++) {
-                        const float x = i < 4 ? x0[i & 3] : x1[i & 3];
-                        hi[i] = (_Float16)x;
-                        lo[i] = (_Float16)((x - (float)hi[i]) * 2048.0f);
-                    }
-                    const u32x4 none = {0, 0, 0, 0};
-                    if constexpr (QP == 2) {
-                        bfrag[s * QP][t] = col_ok[s] ? __builtin_bit_cast(u32x4, hi) : none;
-                        bfrag[s * QP + QP - 1][t] = col_ok[s] ? __builtin_bit_cast(u32x4, lo) : none;
-                    } else {
-                        bfrag[s * QP][t] = col_ok[s] ? (part == 0 ? __builtin_bit_cast(u32x4, hi) : __builtin_bit_cast(u32x4, lo)) : none;
-                    }
-                }
-            } else {
-                const size_t qrow = (NC == 8) ? ((size_t)q[s] * 2 + part) : (size_t)q[s] * QP;
-#pragma unroll
-                for (int h = 0; h < QP; h++) {
-                    const char* qp = (const char*)a.qop + (qrow + h) * (size_t)(S::d * 2) + g * 16;
-#pragma unroll
-                    for (int t = 0; t < KSTEPS; t++)
-                        bfrag[s * QP + h][t] = col_ok[s] ? *(const u32x4*)(qp + t * 64) : u32x4{0, 0, 0, 0};
+            for (int t = 0; t < KSTEPS; t++) {
+                const u32x4 x[2] = {*(const u32x4*)(qp + t * 32), *(const u32x4*)(qp + t * 32 + 4)};
+                half8 hi, lo;
+                split8(x, hi, lo);
+                const u32x4 none = {0, 0, 0, 0};
+                if constexpr (QP == 2) {
+                    bfrag[0][t] = col_ok ? __builtin_bit_cast(u32x4, hi) : none;
+                    bfrag[QP - 1][t] = col_ok ? __builtin_bit_cast(u32x4, lo) : none;
+                } else {
+                    bfrag[0][t] = col_ok ? (part == 0 ? __builtin_bit_cast(u32x4, hi) : __builtin_bit_cast(u32x4, lo)) : none;
                 }
             }
-            thr[s] = (!DENSE && owner && col_ok[s]) ? dec_key(a.thr[q[s]]) : __builtin_inff();
+        } else {
+#pragma unroll
+            for (int h = 0; h < QP; h++) {
+#pragma unroll
+                for (int t = 0; t < KSTEPS; t++)
+                    bfrag[h][t] = col_ok ? *(const u32x4*)(qrow + (size_t)h * (S::d * 2) + t * 64) : u32x4{0, 0, 0, 0};
+            }
+        }
+        float thr = (!DENSE && owner && col_ok) ? dec_key(a.thr[q]) : __builtin_inff();
+        // how far the key of a row of this list can lie above its exact key, halved (see scan_slack; infinite: every row is kept)
+        float slack = 0.f;
+        if constexpr (S::bounded) {
+            if (col_ok) {
+                const float lo = a.qlo[q];
+                slack = scan_slack(sqrtf(a.qnorm[q]), lo, a.list_bound[list], a.l2);
+                if (lo != lo) thr = __builtin_inff();            // (a query beyond binary16)
+            }
         }
         // candidates buffered per column: kept in a register by every lane of the column (the
         // lanes of a column see the same ballots, so they stay in step without LDS traffic)
-        int ccnt[NCS];
-#pragma unroll
-        for (int s = 0; s < NCS; s++) ccnt[s] = 0;
-        // column sets of this wave that hold at least one query (sets fill in order); a wave
-        // with none only helps to stage rows
-        int nact = 0;
-#pragma unroll
-        for (int s = 0; s < NCS; s++) nact += __builtin_amdgcn_ballot_w64(col_ok[s]) != 0 ? 1 : 0;
-
-        if constexpr (!S::direct) {
-            // Everything loaded so far (query operands, thresholds, first row block) is waited
-            // for here, once, and only then are the next PF blocks requested, oldest ring slot
-            // first.  The loop is thus entered with exactly the loads in flight, in exactly the
-            // order, that every later iteration sees; the compiler's wait-count analysis can
-            // then let the staging of a block wait for that block alone, with the PF-1 younger
-            // blocks still in flight, instead of draining the ring.
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-            stage_block<DT, S>(stage, ring[0]);
-            nstage[threadIdx.x & (BR - 1)] = nring[0];      // (same value from several threads)
-            static_for<PF>([&](auto pc) __attribute__((always_inline)) {
-                constexpr int slot = (decltype(pc)::value + 1) % PF;
-                load_block<S>(block_src(decltype(pc)::value + 1), block_chunks(decltype(pc)::value + 1), ring[slot], stream_once);
-                nring[slot] = load_norm(decltype(pc)::value + 1);
-            });
-        } else {
-            // The query operands and thresholds are waited for here, once (the first blocks
-            // with them): if the compiler still counted them as in flight inside the loop it
-            // would wait for "everything" at their first use in every iteration, and that
-            // includes the blocks on their way to LDS.
-            __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-        }
+        int ccnt = 0;
+        // (a wave without columns only helps to stage rows)
+        const bool active = __builtin_amdgcn_ballot_w64(col_ok) != 0;
+        // The query operands and thresholds are waited for here, once (the first blocks
+        // with them): if the compiler still counted them as in flight inside the loop it
+        // would wait for "everything" at their first use in every iteration, and that
+        // includes the blocks on their way to LDS.
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
 
         // ---- the blocks of the segment.  Per block (direct staging): (1) this wave's part of
         // the block has landed, (2) barrier: so has everybody's, and nobody reads the previous
@@ -867,157 +932,173 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
         // step, right after the barrier.  Stores count in vmcnt like the requests for blocks,
         // and may complete in any order relative to them, so the wait at the top of a step has
         // to assume they are still outstanding; issued here they have a whole step to complete.
-        floatx4 held[NCS][RB];
+        floatx4 held[RB];
         int held_rbase = -1;
         auto flush_keys = [&]() __attribute__((always_inline)) {
             if (held_rbase < 0) return;
+            if (active && owner && col_ok) {
 #pragma unroll
-            for (int s = 0; s < NCS; s++) {
-                if (s < nact && owner && col_ok[s]) {
+                for (int j = 0; j < RB; j++) {
+                    const int first = held_rbase + j * kMfmaRows;
+                    float* out = a.key_out + (size_t)q * a.dense_nrows + first;
+                    if (first + 3 < row_end && (a.dense_nrows & 3) == 0) {
+                        *(floatx4*)out = held[j];
+                    } else {
 #pragma unroll
-                    for (int j = 0; j < RB; j++) {
-                        const int first = held_rbase + j * kMfmaRows;
-                        float* out = a.key_out + (size_t)q[s] * a.dense_nrows + first;
-                        if (first + 3 < row_end && (a.dense_nrows & 3) == 0) {
-                            *(floatx4*)out = held[s][j];
-                        } else {
-#pragma unroll
-                            for (int r = 0; r < 4; r++)
-                                if (first + r < row_end) out[r] = held[s][j][r];
-                        }
+                        for (int r = 0; r < 4; r++)
+                            if (first + r < row_end) out[r] = held[j][r];
                     }
                 }
             }
             held_rbase = -1;
         };
 
-        // ---- selection over the scores of one block: acc = accumulators of the block, nrm =
-        // squared norms of this lane's 4 rows of every group, brow = first row of the block
-        auto select_block = [&](const floatx4 (&acc)[NCS][RB][S::na], const floatx4 (&nrm)[RB], const int brow) __attribute__((always_inline)) {
-#pragma unroll
-            for (int s = 0; s < NCS; s++) {
-                if (s >= nact) break;
-                // ---- keys of this lane's 4 (row, column) pairs of set s in every group.  The common case is
-                // that none reaches the column's threshold: that is decided with one compare
-                // of the largest of them (thr is +inf in lanes that own no query column).
-                float keys[RB][4];
-#pragma unroll
-                for (int j = 0; j < RB; j++) {
-#pragma unroll
-                    for (int r = 0; r < 4; r++) {
-                        float dot;
-                        if constexpr (T::planes == 2 && QP == 2) {
-                            dot = acc[s][j][0][r] + (acc[s][j][2][r] + acc[s][j][1][r]) * (1.0f / 2048.0f) + acc[s][j][3][r] * (1.0f / 4194304.0f);
-                        } else if constexpr (QP == 2) {
-                            dot = (acc[s][j][0][r] + acc[s][j][1][r]) + (acc[s][j][2][r] + acc[s][j][3][r]);
-                        } else if constexpr (T::planes == 2) {
-                            float t0 = lane_xor8(acc[s][j][0][r]);      // hi rows x lo query
-                            float t1 = lane_xor8(acc[s][j][1][r]);      // lo rows x lo query
-                            dot = acc[s][j][0][r] + (t0 + acc[s][j][1][r]) * (1.0f / 2048.0f) + t1 * (1.0f / 4194304.0f);
-                        } else if constexpr (DT == HR_BF16) {
-                            float v = acc[s][j][0][r] + acc[s][j][1][r];
-                            dot = v + lane_xor8(v);
-                        } else {
-                            dot = acc[s][j][0][r] + acc[s][j][1][r];
-                        }
-                        keys[j][r] = dot;
-                    }
-                    if (a.l2) {
-#pragma unroll
-                        for (int r = 0; r < 4; r++) keys[j][r] = 2.0f * keys[j][r] - nrm[j][r];
-                    }
-                }
-                if (DENSE) {
-                    // dense scoring only: every key goes to its place in the [query, row] table,
-                    // one block late (see flush_keys)
-#pragma unroll
-                    for (int j = 0; j < RB; j++) held[s][j] = floatx4{keys[j][0], keys[j][1], keys[j][2], keys[j][3]};
-                    held_rbase = brow + g * 4;
-                    continue;
-                }
-                float best = fmaxf(fmaxf(keys[0][0], keys[0][1]), fmaxf(keys[0][2], keys[0][3]));
-#pragma unroll
-                for (int j = 1; j < RB; j++) best = fmaxf(best, fmaxf(fmaxf(keys[j][0], keys[j][1]), fmaxf(keys[j][2], keys[j][3])));
-                if (__builtin_amdgcn_ballot_w64(best >= thr[s]) == 0) continue;
-                // ---- append what reaches the column's threshold, one group of 16 rows after the other
-#pragma unroll 1
-                for (int j = 0; j < RB; j++) {
-                    float key[4];
-#pragma unroll
-                    for (int r = 0; r < 4; r++) {
-                        key[r] = keys[0][r];
-#pragma unroll
-                        for (int i = 1; i < RB; i++) key[r] = j == i ? keys[i][r] : key[r];
-                    }
-                    if (RB > 1 && __builtin_amdgcn_ballot_w64(fmaxf(fmaxf(key[0], key[1]), fmaxf(key[2], key[3])) >= thr[s]) == 0) continue;
-                    const int lane = lane_here();
-                    const int jcol = lane & (NC - 1);
-                    const int rbase = brow + j * kMfmaRows + (lane >> 4) * 4;           // first of this lane's rows
-                    const unsigned long long colmask = 0x0001000100010001ULL << jcol;   // owner lanes of my column
-                    bool pass[4];
-#pragma unroll
-                    for (int r = 0; r < 4; r++) pass[r] = key[r] >= thr[s] && (rbase + r < row_end);
-                    Cand* ssel = mysel + (s * NC) * a.cap;
-                    Cand* gs = gsel + (s * NC) * a.cap;
-                    // slot of each new candidate = column count + candidates of the same
-                    // column in earlier row slots and in lower lanes of this row slot
-                    int add = 0;
-#pragma unroll
-                    for (int r = 0; r < 4; r++) {
-                        const unsigned long long mine = __builtin_amdgcn_ballot_w64(pass[r]) & colmask;
-                        if (pass[r]) {
-                            const int pos = ccnt[s] + add + lanes_below(mine);
-                            const Cand cd{enc_key(key[r]), (uint32_t)(rbase + r)};
-                            if (GS) gs[jcol * a.cap + pos] = cd;
-                            else ssel[jcol * a.cap + pos] = cd;
-                        }
-                        add += __builtin_popcountll(mine);
-                    }
-                    static_assert(kAppendMax >= kMfmaRows, "a column has room for what one group of rows appends");
-                    ccnt[s] += add;
-                    unsigned long long full = __builtin_amdgcn_ballot_w64(lane < NC && ccnt[s] > a.cap - kAppendMax);
-                    if (full) wave_sync();
-                    while (full) {
-                        int col = __builtin_ctzll(full);
-                        full &= full - 1;
-                        int n = __builtin_amdgcn_readlane(ccnt[s], col);
-                        uint32_t kth = GS ? select_k(gs + col * a.cap, n, a.k, a.cap, a.row_ids, lane)
-                                              : select_k(ssel + col * a.cap, n, a.k, a.cap, a.row_ids, lane);
-                        float nt = 0.f;
-                        if (lane == col) {
-                            uint32_t old = atomicMax(&a.thr[q[s]], kth);
-                            nt = dec_key(kth > old ? kth : old);
-                        }
-                        nt = __shfl(nt, col);
-                        if (jcol == col) { thr[s] = fmaxf(thr[s], nt); ccnt[s] = a.k; }
-                    }
-                }
-            }
-        };
-
         // where the row fragments of this lane start in a staged block (mfma_block's ap)
         auto frag_bases = [&](const char* (&ap)[4], const char* cur) __attribute__((always_inline)) {
-            if constexpr (S::direct && S::lean) {
+            if constexpr (S::lean) {
                 int a0 = abase[0];
                 asm volatile("" : "+v"(a0));                     // (one register across the loop instead of four)
 #pragma unroll
-                for (int j = 0; j < 4; j++) ap[j] = cur + (a0 ^ (64 * j));
+                for (int j = 0; j < 4; j++) ap[j] = cur + (a0 ^ frag_step<DT>(j));
             } else {
 #pragma unroll
                 for (int j = 0; j < 4; j++) ap[j] = cur + abase[j];
             }
         };
+
+        // ---- selection over the scores of block blk in buffer buf: acc = accumulators of the block, nrm =
+        // squared norms of this lane's 4 rows of every group
+        auto select_block = [&](floatx4 (&acc)[RB][S::na], const floatx4 (&nrm)[RB], const int blk, const int buf) __attribute__((always_inline)) {
+            const int brow = row0 + blk * BR;
+            float keys[RB][4];
+            auto make_keys = [&](auto dot) __attribute__((always_inline)) {
+#pragma unroll
+                for (int j = 0; j < RB; j++) {
+#pragma unroll
+                    for (int r = 0; r < 4; r++) keys[j][r] = dot(acc[j], r);
+                    if (a.l2) {
+#pragma unroll
+                        for (int r = 0; r < 4; r++) keys[j][r] = 2.0f * keys[j][r] - nrm[j][r];
+                    }
+                }
+            };
+            auto largest = [&]() __attribute__((always_inline)) {
+                float best = fmaxf(fmaxf(keys[0][0], keys[0][1]), fmaxf(keys[0][2], keys[0][3]));
+#pragma unroll
+                for (int j = 1; j < RB; j++) best = fmaxf(best, fmaxf(fmaxf(keys[j][0], keys[j][1]), fmaxf(keys[j][2], keys[j][3])));
+                return best;
+            };
+            make_keys([](const floatx4 (&c)[S::na], int r) __attribute__((always_inline)) {
+                if constexpr (!DENSE && QP == 1) {
+                    const float v = c[0][r] + c[1][r];
+                    return NC == 8 ? v + lane_xor8(v) : v;
+                } else if constexpr (!DENSE) {
+                    return (c[0][r] + c[1][r]) + (c[2][r] + c[3][r]);
+                } else if constexpr (QP == 2) {
+                    return c[0][r] + (c[2][r] + c[1][r]) * (1.0f / 2048.0f) + c[3][r] * (1.0f / 4194304.0f);
+                } else {
+                    const float t0 = lane_xor8(c[0][r]);      // hi rows x lo query
+                    const float t1 = lane_xor8(c[1][r]);      // lo rows x lo query
+                    return c[0][r] + (t0 + c[1][r]) * (1.0f / 2048.0f) + t1 * (1.0f / 4194304.0f);
+                }
+            });
+            if (DENSE) {
+                // dense scoring only: every key goes to its place in the [query, row] table,
+                // one block late (see flush_keys)
+#pragma unroll
+                for (int j = 0; j < RB; j++) held[j] = floatx4{keys[j][0], keys[j][1], keys[j][2], keys[j][3]};
+                held_rbase = brow + g * 4;
+                return;
+            }
+            // ---- keys of this lane's 4 (row, column) pairs in every group.  The common case is
+            // that none reaches the column's threshold: that is decided with one compare
+            // of the largest of them (thr is +inf in lanes that own no query column).
+            if (__builtin_amdgcn_ballot_w64(largest() >= (S::bounded ? thr - slack : thr)) == 0) return;
+            // ---- append what reaches the column's threshold, one group of 16 rows after the other
+#pragma unroll 1
+            for (int j = 0; j < RB; j++) {
+                float key[4];
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    key[r] = keys[0][r];
+#pragma unroll
+                    for (int i = 1; i < RB; i++) key[r] = j == i ? keys[i][r] : key[r];
+                }
+                if (RB > 1 && __builtin_amdgcn_ballot_w64(fmaxf(fmaxf(key[0], key[1]), fmaxf(key[2], key[3])) >= (S::bounded ? thr - slack : thr)) == 0) continue;
+                const int lane = lane_here();
+                const int jcol = lane & (NC - 1);
+                const int rbase = brow + j * kMfmaRows + (lane >> 4) * 4;           // first of this lane's rows
+                const unsigned long long colmask = 0x0001000100010001ULL << jcol;   // lanes of my column
+                bool pass[4];
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    // (a row beyond binary16, whose product is infinite, has no key)
+                    pass[r] = (S::bounded ? key[r] >= thr - slack && key[r] < __builtin_inff() : key[r] >= thr) && (rbase + r < row_end);
+                    if (S::bounded) key[r] += slack;
+                }
+                // slot of each new candidate = column count + candidates of the same
+                // column in earlier row slots and in lower lanes of this row slot
+                int add = 0;
+#pragma unroll
+                for (int r = 0; r < 4; r++) {
+                    const unsigned long long mine = __builtin_amdgcn_ballot_w64(pass[r]) & colmask;
+                    if (pass[r]) sel[jcol * a.cap + ccnt + add + lanes_below(mine)] = Cand{enc_key(key[r]), (uint32_t)(rbase + r)};
+                    add += __builtin_popcountll(mine);
+                }
+                static_assert(kAppendMax >= kMfmaRows, "a column has room for what one group of rows appends");
+                ccnt += add;
+                unsigned long long full = __builtin_amdgcn_ballot_w64(lane < NC && ccnt > a.cap - kAppendMax);
+                if (full) wave_sync();
+                while (full) {
+                    int col = __builtin_ctzll(full);
+                    full &= full - 1;
+                    int n = __builtin_amdgcn_readlane(ccnt, col);
+                    uint32_t kth;
+                    int left = a.k;
+                    if constexpr (S::bounded) {
+                        const float w = 2.0f * __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, slack), col));
+                        left = window_k(sel + col * a.cap, n, a.k, a.cap, w, kth, lane);
+                        if (left > a.cap - kAppendMax - kRoomAfterCut) {
+                            // more rows than that are within the slack of the k-th best: their exact keys, plus
+                            // what another sum of the same products may differ by, which is at most a slack
+                            const int qc = __builtin_amdgcn_readlane(q, col);
+                            const float add = exact_add(a.qnorm[qc], a.list_bound[list].x, a.l2);
+                            exact_keys<8, 1>(sel + col * a.cap, left, 0, 1, a.rows_f32, a.row_norm, a.queries + (size_t)qc * S::d, S::d, a.l2, add);
+                            kth = key_below(select_k(sel + col * a.cap, left, a.k, a.cap, a.row_ids, lane), 2.0f * add);
+                            left = a.k;
+                        }
+                    } else {
+                        kth = select_k(sel + col * a.cap, n, a.k, a.cap, a.row_ids, lane);
+                    }
+                    float nt = 0.f;
+                    if (lane == col) {
+                        uint32_t old = atomicMax(&a.thr[q], kth);
+                        nt = dec_key(kth > old ? kth : old);
+                    }
+                    nt = __shfl(nt, col);
+                    if (jcol == col) { thr = fmaxf(thr, nt); ccnt = left; }
+                }
+            }
+        };
+
         int bi = 0;                                              // blk % NB
-        floatx4 accs[2][NCS][RB][S::na];
+        floatx4 accs[2][RB][S::na];
         floatx4 nrms[2][RB] = {};
         auto get_norms = [&](floatx4 (&nrm)[RB], int buf) __attribute__((always_inline)) {
 #pragma unroll
             for (int j = 0; j < RB; j++) nrm[j] = *(const floatx4*)(nstage + buf * BR + j * kMfmaRows + (lane_here() >> 4) * 4);
         };
-        // direct staging: (1) this wave's part of block blk has landed, (2) barrier: so has
+        auto multiply = [&](int blk, int buf) __attribute__((always_inline)) {
+            const char* ap[4];
+            frag_bases(ap, stage + buf * S::buf_bytes);
+            if (a.l2) get_norms(nrms[0], buf);
+            mfma_block<DT, KSTEPS, S>(ap, bfrag, accs[0]);
+            select_block(accs[0], nrms[0], blk, buf);
+        };
+        // (1) this wave's part of block blk has landed, (2) barrier: so has
         // everybody's, and nobody reads block blk-1 any more, (3) request block blk+D into the
         // buffer that one leaves, (4) multiply, (5) select
-        auto step_direct = [&](int blk) __attribute__((always_inline)) {
+        auto step_one = [&](int blk) __attribute__((always_inline)) {
             // all but the D-1 youngest requests of this wave (S::lpf loads each) are done
             if (a.l2) {
                 switch (D) {
@@ -1036,21 +1117,13 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
             }
             __builtin_amdgcn_s_barrier();
             if (DENSE) flush_keys();
-            fill_direct(blk + D, bi == 0 ? NB - 1 : bi - 1);
-            if (nact > 0) {
-                const char* cur = stage + bi * S::buf_bytes;
-                if (a.l2) get_norms(nrms[0], bi);
-                const char* ap[4];
-                frag_bases(ap, cur);
-                if (NCS == 2 && nact == 2) mfma_block<DT, KSTEPS, NCS, NCS, S>(ap, bfrag, accs[0]);
-                else                       mfma_block<DT, KSTEPS, NCS, 1, S>(ap, bfrag, accs[0]);
-                select_block(accs[0], nrms[0], row0 + blk * BR);
-            }
+            fill(blk + D, bi == 0 ? NB - 1 : bi - 1);
+            if (active) multiply(blk, bi);
             bi = bi + 1 == NB ? 0 : bi + 1;
         };
-        // direct staging, 4 buffers: blocks blk and blk+1 between two barriers, blocks blk+2 and
+        // 4 or 6 buffers: blocks blk and blk+1 between two barriers, blocks blk+2 and
         // blk+3 requested into the two buffers the previous pair leaves
-        auto pair_direct = [&](int blk) __attribute__((always_inline)) {
+        auto step_pair = [&](int blk) __attribute__((always_inline)) {
             // (6 buffers: the requests of the pair after the next one may still be on their way)
             if (NB != 6) wait_vmcnt<0>();
             else if (a.l2) wait_vmcnt<2 * S::lpf>();
@@ -1059,14 +1132,14 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
             // (the requests of all waves at once keep the address unit busy for a while, and a
             // wave cannot go on before its own are accepted: half of the waves send theirs
             // now, the other half after their first block, when the first half multiplies)
-            const bool early = NW != 8 || wave < 4 || nact == 0;
+            const bool early = wave < NW / 2 || !active;
             auto requests = [&]() __attribute__((always_inline)) {
                 const int fb = bi + D >= NB ? bi + D - NB : bi + D;     // the buffers the pair before this one used
-                fill_direct(blk + D, fb);
-                fill_direct(blk + D + 1, fb + 1);
+                fill(blk + D, fb);
+                fill(blk + D + 1, fb + 1);
             };
             if (early) requests();
-            if (S::chain && nact > 0 && blk + 1 < nblk) {
+            if (S::chain && active && blk + 1 < nblk) {
                 // both blocks of the pair as one chain (see mfma_pair); the late requests go out with the
                 // filter of the first block
                 const char* c0 = stage + bi * S::buf_bytes;
@@ -1080,116 +1153,38 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
                 const char* ap1[4];
                 frag_bases(ap1, c1);
                 if constexpr (S::chain) {
-                    mfma_pair<DT, KSTEPS, NCS, 1, S>(ap0, ap1, bfrag, accs[0], accs[1], [&]() __attribute__((always_inline)) {
+                    mfma_pair<DT, KSTEPS, S>(ap0, ap1, bfrag, accs[0], accs[1], [&]() __attribute__((always_inline)) {
                         if (!early) requests();
-                        select_block(accs[0], nrms[0], row0 + blk * BR);
+                        select_block(accs[0], nrms[0], blk, bi);
                     });
                 }
-                select_block(accs[1], nrms[1], row0 + (blk + 1) * BR);
+                select_block(accs[1], nrms[1], blk + 1, bi + 1);
             } else {
 #pragma unroll
                 for (int h = 0; h < 2; h++) {
-                    if (nact > 0 && blk + h < nblk) {
-                        const char* cur = stage + (bi + h) * S::buf_bytes;
-                        if (a.l2) get_norms(nrms[0], bi + h);
-                        const char* ap[4];
-                        frag_bases(ap, cur);
-                        if (NCS == 2 && nact == 2) mfma_block<DT, KSTEPS, NCS, NCS, S>(ap, bfrag, accs[0]);
-                        else                       mfma_block<DT, KSTEPS, NCS, 1, S>(ap, bfrag, accs[0]);
-                        select_block(accs[0], nrms[0], row0 + (blk + h) * BR);
-                    }
+                    if (active && blk + h < nblk) multiply(blk + h, bi + h);
                     if (h == 0 && !early) requests();
                 }
             }
             bi = bi + 2 == NB ? 0 : bi + 2;
         };
-        // through registers: (1) barrier: block blk is complete in LDS and nobody reads block
-        // blk-1 any more, (2) block blk+1 from the ring into the buffer that one leaves, and
-        // its ring slot refilled, (3) multiply, (4) select
-        auto step_regs = [&](int blk, auto pc) __attribute__((always_inline)) {
-            constexpr int p = decltype(pc)::value;               // ring position
-            const bool live = blk < nblk;
-            __syncthreads();
-            constexpr int pn = (p + 1) % PF;
-            stage_block<DT, S>(stage + (bi ^ 1) * S::buf_bytes, ring[pn]);
-            nstage[(bi ^ 1) * BR + (threadIdx.x & (BR - 1))] = nring[pn];
-            load_block<S>(block_src(blk + 1 + PF), block_chunks(blk + 1 + PF), ring[pn], stream_once);
-            nring[pn] = load_norm(blk + 1 + PF);
-            if (live && nact > 0) {
-                const char* cur = stage + bi * S::buf_bytes;
-                get_norms(nrms[0], bi);
-                const char* ap[4];
-                frag_bases(ap, cur);
-                if (NCS == 2 && nact == 2) mfma_block<DT, KSTEPS, NCS, NCS, S>(ap, bfrag, accs[0]);
-                else                       mfma_block<DT, KSTEPS, NCS, 1, S>(ap, bfrag, accs[0]);
-                select_block(accs[0], nrms[0], row0 + blk * BR);
-            }
-            bi ^= 1;
-        };
-        if constexpr (S::direct) {
-            if (pairs) {
-                for (int blk = 0; blk < nblk; blk += 2) pair_direct(blk);
-            } else {
-                for (int blk = 0; blk < nblk; blk++) step_direct(blk);
-            }
+        if (pairs) {
+            for (int blk = 0; blk < nblk; blk += 2) step_pair(blk);
         } else {
-            // (iterations past the last block of a ragged round still stage and load: an early
-            // exit would be a path with fewer loads in flight, and the compiler would size
-            // every wait in the loop for that path)
-            for (int b0 = 0; b0 < nblk; b0 += PF)
-                static_for<PF>([&](auto pc) __attribute__((always_inline)) { step_regs(b0 + decltype(pc)::value, pc); });
+            for (int blk = 0; blk < nblk; blk++) step_one(blk);
         }
 
         // (everybody has read this item's record: that was before the barrier of the first block)
         const bool early_next = DENSE || a.k <= 24;
         if (early_next && wave == NW - 1) next_item();
         if (DENSE) flush_keys();
-        // ---- hand what is left to the item's slots: columns with more entries than a slot holds
-        // (slot_stride: k, or the whole buffer for small k, when nothing has to be cut) are cut
-        // down to the k best first (one at a time, whole wave), then every lane copies one
-        // column's entries
+        // ---- what is left in the selection buffers is in the item's slots already: every column's count
         wave_sync();
         if (!DENSE) {
             const int lane = lane_here();
-            int c = 0;
-#pragma unroll
-            for (int s = 0; s < NCS; s++) {
-                const int v = __shfl(ccnt[s], (lane - s * NC) & 63);
-                if (lane >= s * NC && lane < (s + 1) * NC) c = v;
-            }
-            unsigned long long over = __builtin_amdgcn_ballot_w64(!GS && c > a.slot_stride);
-            while (over) {
-                const int wc = __builtin_ctzll(over);
-                over &= over - 1;
-                const int n = __builtin_amdgcn_readlane(c, wc);
-                uint32_t kth = select_k(mysel + wc * a.cap, n, a.k, a.cap, a.row_ids, lane);
-                // column wc = set wc / NC, lane wc % NC of that set holds its query
-                int qq = 0;
-#pragma unroll
-                for (int s = 0; s < NCS; s++) {
-                    int v = __builtin_amdgcn_readlane(q[s], wc % NC);
-                    if (s == wc / NC) qq = v;
-                }
-                if (lane == 0) atomicMax(&a.thr[qq], kth);
-            }
-            wave_sync();
-            bool ok = false;
-#pragma unroll
-            for (int s = 0; s < NCS; s++) {
-                // is column `lane` of this wave (set s, lane - s*NC) a real query?
-                bool v = __shfl(col_ok[s] ? 1 : 0, (lane - s * NC) & 63) != 0;
-                if (lane >= s * NC && lane < (s + 1) * NC) ok = v;
-            }
-            const int n = c > a.slot_stride ? a.k : c;
-            if (lane < WC && ok) {
-                const size_t slot = (size_t)slot0 + wave * WC + lane;
-                a.slot_cnt[slot] = n;
-                if (!GS) {
-                    const Cand* cb = mysel + lane * a.cap;
-                    Cand* out = a.slot_ent + slot * a.slot_stride;
-                    for (int i = 0; i < n; i++) out[i] = cb[i];
-                }
-            }
+            const int n = ccnt;                                  // (lanes below NC: of column `lane` of this wave)
+            const bool ok = col_ok && lane < NC;
+            if (ok) a.slot_cnt[(size_t)slot0 + wave * NC + lane] = n;
             // ---- what this item found tightens the lower bounds of its queries for the items
             // still to come.  Every query has a histogram of the keys reported so far over
             // fixed key ranges above its seed; each reported key is a distinct row (an item
@@ -1197,13 +1192,8 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
             // the query is at least the lower edge of bin b.  Counts only grow, so a reader
             // that misses concurrent additions merely gets a weaker bound.
             if (keep_hist) {
-                int qcol = 0;
-#pragma unroll
-                for (int s = 0; s < NCS; s++) {
-                    const int v = __shfl(q[s], (lane - s * NC) & 63);
-                    if (lane >= s * NC && lane < (s + 1) * NC) qcol = v;
-                }
-                const bool have = lane < WC && ok && n > 0;
+                const int qcol = q;
+                const bool have = ok && n > 0;
                 float base = 0.f, wd = 0.f;
                 uint32_t now = 0;
                 if (have) {
@@ -1226,15 +1216,17 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
                         const bool live = e < total;
                         int c = 0;                                   // column of entry e: columns that end at or before e
 #pragma unroll
-                        for (int cl = 0; cl < WC; cl++) c += (__builtin_amdgcn_readlane(incl, cl) <= e) ? 1 : 0;
+                        for (int cl = 0; cl < NC; cl++) c += (__builtin_amdgcn_readlane(incl, cl) <= e) ? 1 : 0;
                         c = live ? c : 0;
                         const int start = __shfl(incl - cnt, c);
                         const float cbase = __shfl(base, c), cwd = __shfl(wd, c);
                         const uint32_t cnow = (uint32_t)__shfl((int)now, c);
+                        const float cslack = S::bounded ? __shfl(slack, c) : 0.f;
                         const int qc = __shfl(qcol, c);
                         bool did = false;
                         if (live) {
-                            const uint32_t ek = GS ? gsel[c * a.cap + (e - start)].key : mysel[c * a.cap + (e - start)].key;
+                            uint32_t ek = sel[c * a.cap + (e - start)].key;
+                            if constexpr (S::bounded) ek = key_below(ek, 2.0f * cslack);          // (what the exact key reaches)
                             if (ek >= cnow) {
                                 const float key = dec_key(ek);
                                 int b = (int)fminf(fmaxf((key - cbase) * (1.0f / cwd), 0.f), (float)(kHistBins - 1));
@@ -1246,17 +1238,17 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
                             }
                         }
 #pragma unroll
-                        for (int cl = 0; cl < WC; cl++)
+                        for (int cl = 0; cl < NC; cl++)
                             if (__builtin_amdgcn_ballot_w64(did && c == cl) != 0) gained |= 1ull << cl;
                     }
-                    if (lane < WC && ((gained >> lane) & 1)) added = 1;
+                    if (lane < NC && ((gained >> lane) & 1)) added = 1;
                 }
                 const unsigned long long todo = __builtin_amdgcn_ballot_w64(added > 0);
                 // lane i looks at bin 63 - i: the prefix sum over lanes then counts the keys
                 // from the top bin down (all columns' loads go out before the first is used)
-                int h[WC];
+                int h[NC];
 #pragma unroll
-                for (int cl = 0; cl < WC; cl++) {
+                for (int cl = 0; cl < NC; cl++) {
                     const int qc = __builtin_amdgcn_readlane(qcol, cl);
                     h[cl] = 0;
                     if ((todo >> cl) & 1)
@@ -1264,7 +1256,7 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
                                                   __HIP_MEMORY_SCOPE_AGENT);
                 }
 #pragma unroll
-                for (int cl = 0; cl < WC; cl++) {
+                for (int cl = 0; cl < NC; cl++) {
                     if (!((todo >> cl) & 1)) continue;
                     const unsigned long long reach = __builtin_amdgcn_ballot_w64(wave_prefix_sum(h[cl]) >= a.k);
                     if (reach) {
@@ -1285,15 +1277,15 @@ __global__ __launch_bounds__(NW * 64, NW == 8 && groups_per_cu(DT, KSTEPS * 32) 
     }
 }
 
-template <int DT, int NCS, int NW, bool GS, bool GROUPS = false>
+template <int DT, bool GROUPS = false>
 inline hipError_t launch_scan_shape(int d, const ScanArgs& a, int grid, size_t lds, hipStream_t s)
 {
 #define HR_SCAN_CASE(KS)                                                                           \
     case KS * 32: {                                                                                \
-        auto kern = k_scan<DT, KS, NCS, NW, GS, GROUPS>;                                           \
+        auto kern = k_scan<DT, KS, GROUPS>;                                           \
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds); \
         if (e != hipSuccess) return e;                                                             \
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(NW * 64), lds, s, a);                            \
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(kScanWaves * 64), lds, s, a);                            \
         return hipGetLastError();                                                                  \
     }
     switch (d) {
@@ -1309,23 +1301,14 @@ inline hipError_t launch_scan_shape(int d, const ScanArgs& a, int grid, size_t l
 }
 
 template <int DT>
-inline hipError_t launch_scan_dtype(int d, const ScanArgs& a, int shape, int grid, size_t lds, hipStream_t s)
+inline hipError_t launch_scan_dtype(int d, const ScanArgs& a, int grid, size_t lds, hipStream_t s)
 {
+    // (HR_F16X2 is the centroid table in the coarse step, every key written out)
+    if ((a.key_out != nullptr) != (DT == HR_F16X2)) return hipErrorInvalidValue;
     if constexpr (DT == HR_F16X2) {
-        // (the centroid table in the coarse step, gsel 0 and every key written out, and float32 lists split at load)
-        if ((a.key_out != nullptr) == (a.gsel != 0)) return hipErrorInvalidValue;
-        if (a.gsel) return launch_scan_shape<DT, 1, 8, true>(d, a, grid, lds, s);
-        return a.dense_groups > 0 ? launch_scan_shape<DT, 1, 8, false, true>(d, a, grid, lds, s)
-                                  : launch_scan_shape<DT, 1, 8, false>(d, a, grid, lds, s);
-    } else {
-        if (a.gsel) return shape == SCAN_WIDE ? launch_scan_shape<DT, 1, 8, true>(d, a, grid, lds, s) : hipErrorInvalidValue;
-        if constexpr (DT == HR_F32) {
-            return shape == SCAN_WIDE ? launch_scan_shape<DT, 1, 8, false>(d, a, grid, lds, s)
-                                      : launch_scan_shape<DT, 1, 4, false>(d, a, grid, lds, s);
-        } else {
-            return hipErrorInvalidValue;       // (16-bit lists always keep their selection buffers in global memory)
-        }
+        if (a.dense_groups > 0) return launch_scan_shape<DT, true>(d, a, grid, lds, s);
     }
+    return launch_scan_shape<DT>(d, a, grid, lds, s);
 }
 
 // Key (larger is better) of an entry of a carried result, from its reported score: the score
@@ -1492,7 +1475,13 @@ __global__ __launch_bounds__(256) void k_seed(SeedArgs a)
         }
     }
     // a few units in the last place lower, in case a later pass rounds a sum differently
-    const uint32_t pub = kth > 8u ? kth - 8u : 0u;
+    uint32_t pub = kth > 8u ? kth - 8u : 0u;
+    if constexpr (DT == HR_F32) {
+        // (the scores of the scan are exact ones; here, elements below 2^-36 or so vanish in the low parts)
+        const float qn = a.qnorm[q], xn = a.list_bound[l].x;
+        const float lost = 2.9103830456733704e-11f * sqrtf((float)d) * (sqrtf(qn) + sqrtf(xn)) * (a.l2 ? 2.0f : 1.0f);
+        pub = qn > 1e-30f && xn > 1e-30f ? key_below(pub, lost) : 0u;
+    }
     if (lane == 0) atomicMax(&a.thr[q], pub);
     // key ranges of the query's histogram in the scan: from the seed upwards, an eighth of
     // the distance between the seed and the best key of the sample per bin

@@ -580,3 +580,65 @@ def test_full_tiles_of_short_lists(storage, rows, nlist, nq, nprobe):
     assert float((key.gather(1, row[found]) - best).abs().max()) <= 2 * tol
     assert float((score.double() - ((op ** 2).sum(1, keepdim=True) - best)).abs().max()) <= 2 * tol
     ix.close()
+
+
+@pytest.mark.parametrize("tables", [False, True])
+@pytest.mark.parametrize("d,N,nlist,nq,k,metric", [(64, 900, 3, 3, 1, "ip"), (768, 4000, 4, 5, 10, "l2"), (1024, 3000, 2, 130, 24, "ip"), (512, 2500, 5, 33, 25, "l2"),
+                                                   (128, 6000, 2, 40, 64, "ip"), (256, 5000, 2, 20, 100, "l2"), (64, 1500, 4, 1100, 128, "ip"), (768, 700, 3, 1030, 37, "l2"),
+                                                   (1024, 300, 6, 1024, 12, "ip"), (768, 90, 2, 7, 128, "l2")])
+@pytest.mark.parametrize("spread,scale", [(1e-5, 1.0), (1e-2, 1.0), (1.0, 1e-6), (1e-5, 1e-12)])
+def test_float32_rows_that_binary16_cannot_tell_apart(tables, d, N, nlist, nq, k, metric, spread, scale):
+    """Rows so close to each other, or so small, that all of them, or many, lie within what rounding to binary16 may have taken:
+    selection buffers overflow with them in the scan and in the merge (one wave and four), and the best are still those of
+    float64.  The queries start at an odd address; a carried result goes on being merged exactly."""
+    hr = _hr()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + k)
+    cent = torch.randn(nlist, d, generator=g, device="cuda") * scale
+    off = torch.linspace(0, N, nlist + 1).long()
+    base = torch.randn(1, d, generator=g, device="cuda")
+    vec = ((base + spread * torch.randn(N, d, generator=g, device="cuda")) * scale).contiguous()
+    ids = torch.randperm(N, generator=g, device="cuda")
+    ix = hr.IvfIndex(cent, off, vec, ids, row_tables=tables)
+    q = (torch.randn(nq * d + 1, generator=g, device="cuda") * scale)[1:].view(nq, d)
+    probe = torch.arange(nlist, dtype=torch.int32, device="cuda").repeat(nq, 1)
+    found, score = ix.scan(q, probe, k, metric)
+    key = _keys(q.double(), vec.double(), metric)
+    n = min(k, N)
+    best = torch.topk(key, n, dim=1).values
+    row = torch.empty_like(ids)
+    row[ids] = torch.arange(N, device="cuda")
+    assert bool((found[:, :n] >= 0).all()) and bool((found[:, n:] == -1).all())
+    # float32 sums of d products in chains of at most d/64 + 6 steps: 2^-24 of |q||x| (+ |x|^2) for each
+    size = q.double().norm(dim=1, keepdim=True) * vec.double().norm(dim=1).max() * 2 + (vec.double().norm(dim=1).max() ** 2 if metric == "l2" else 0)
+    tol = size * 2.0 ** -24 * 24
+    got = key.gather(1, row[found[:, :n]])
+    assert bool(((got - best).abs() <= 2 * tol).all())
+    qq = (q.double() ** 2).sum(1, keepdim=True)
+    want = best if metric == "ip" else (qq - best).clamp(min=0)
+    assert bool(((score[:, :n].double() - want).abs() <= 2 * tol + qq * 2.0 ** -22).all())
+    assert all(len(set(r)) == n for r in found[:, :n].cpu().tolist())
+    # list by list with a carried result
+    state = ix.new_state_rows(nq, k)
+    for x in range(nlist):
+        ix.scan_step_rows(q, probe[:, x:x + 1].contiguous(), state, metric)
+    got = key.gather(1, row[state[0][:, :n]])
+    assert bool(((got - best).abs() <= 2 * tol + qq * 2.0 ** -22).all())
+    ix.close()
+
+
+@pytest.mark.parametrize("tables", [False, True])
+def test_bounds_of_replaced_float32_rows(tables):
+    """Rows ten times as long in place of others, in the middle of a list and over the edge of the next: found with the inner
+    product, which reads no norms but the bounds."""
+    d, N = 256, 4000
+    ix, cent, off, vec, ids, g = _index(N, d, 7, torch.float32, 5, tables=tables)
+    q = torch.randn(40, d, generator=g, device="cuda")
+    for a, b in ((100, 101), (int(off[2]) - 20, int(off[2]) + 3)):
+        vec[a:b] = 10 * torch.randn(b - a, d, generator=g, device="cuda")
+        ix.refresh_rows(a, b)
+        found, score = ix.search(q, 7, 30, "ip")
+        best = torch.topk(q.double() @ vec.double().T, 30, dim=1).values
+        # 2^-24 of |q||x| below 16 * 160 * 1.3, with room for the steps of the sums
+        assert float((score.double() - best).abs().max()) <= 2600 * 2.0 ** -24 * 16
+    ix.close()
