@@ -16,8 +16,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libhr_ivf.so")
 SOURCES = ["api.hip", "aux_kernels.hip", "scan_f16.hip", "scan_bf16.hip", "scan_f32.hip"]
-HEADERS = [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "scan_kernel.h"),
-           os.path.join(ROOT, "include", "hr_ivf.h")]
+HEADERS = [os.path.join(CSRC, h) for h in ("common.h", "wave.h", "group.h", "scan_kernel.h")] + [os.path.join(ROOT, "include", "hr_ivf.h")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC] + os.environ.get("HR_EXTRA_HIPCC_FLAGS", "").split()

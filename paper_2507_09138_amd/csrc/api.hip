@@ -49,16 +49,16 @@ hipError_t launch_scan_bf16(int d, const ScanArgs& a, int grid, size_t lds, hipS
 hipError_t launch_scan_f16x2(int d, const ScanArgs& a, int grid, size_t lds, hipStream_t s);
 hipError_t launch_scan_f16hi(int d, const ScanArgs& a, int grid, size_t lds, hipStream_t s);
 
-hipError_t launch_seed_f32(int d, const SeedArgs& a, hipStream_t s);
-hipError_t launch_seed_f16(int d, const SeedArgs& a, hipStream_t s);
-hipError_t launch_seed_bf16(int d, const SeedArgs& a, hipStream_t s);
+hipError_t launch_seed_f32(int d, const SeedArgs& a, const BucketArgs* group, hipStream_t s);
+hipError_t launch_seed_f16(int d, const SeedArgs& a, const BucketArgs* group, hipStream_t s);
+hipError_t launch_seed_bf16(int d, const SeedArgs& a, const BucketArgs* group, hipStream_t s);
 
-hipError_t launch_seed(int dtype, int d, const SeedArgs& a, hipStream_t s)
+hipError_t launch_seed(int dtype, int d, const SeedArgs& a, const BucketArgs* group, hipStream_t s)
 {
     switch (dtype) {
-    case HR_F32: return launch_seed_f32(d, a, s);
-    case HR_F16: return launch_seed_f16(d, a, s);
-    case HR_BF16: return launch_seed_bf16(d, a, s);
+    case HR_F32: return launch_seed_f32(d, a, group, s);
+    case HR_F16: return launch_seed_f16(d, a, group, s);
+    case HR_BF16: return launch_seed_bf16(d, a, group, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -654,7 +654,9 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, const f
     b.round_cnt = zero + p.zoff_round;
     b.round_cur = zero + p.zoff_round + 8 * 64;
     b.item_cap = p.item_cap;
-    HR_HIP(launch_bucketing(b, s));
+    // (the grouping of a small batch rides on the seeding)
+    const bool together = grouped_whole(b) && nq <= kSeedBeside;
+    if (!together) HR_HIP(launch_bucketing(b, s));
 
     // starting lower bounds: from a carried result, and from the first rows of every query's best-ranked list
     SeedArgs sd{};
@@ -669,7 +671,7 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, const f
     sd.qnorm = (const float*)(ws + p.o_qnorm_s);
     sd.list_bound = ix->d_list_bound;
     if (carried) { sd.state_ids = out_ids; sd.state_scores = out_scores; }
-    HR_HIP(launch_seed(row_dtype(ix), ix->d, sd, s));
+    HR_HIP(launch_seed(row_dtype(ix), ix->d, sd, together ? &b : nullptr, s));
 
     ScanArgs a{};
     a.rows = ix->d_vec_hi ? ix->d_vec_hi : row_table(ix);

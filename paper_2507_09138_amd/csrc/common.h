@@ -224,7 +224,6 @@ struct PrepArgs {
 };
 hipError_t launch_topk_rows(const float* keys, const float* qnorm, int32_t* out_ids, float* out_scores,
                             int64_t nq, int n, int k, int l2, const PrepArgs* prep, hipStream_t s);
-hipError_t launch_seed(int dtype, int d, const SeedArgs& a, hipStream_t s);
 hipError_t launch_row_norms(const void* rows, int dtype, int64_t nrows, int d, float* out, hipStream_t s);
 hipError_t launch_prep_queries(const PrepArgs& a, hipStream_t s);
 hipError_t launch_fill_i32(int* p, int64_t n, int v, hipStream_t s);
@@ -270,5 +269,18 @@ struct BucketArgs {
     const int* resident;        // [nlist] 1 = the list's vectors are in place; probes of the other lists are dropped
 };
 hipError_t launch_bucketing(const BucketArgs& a, hipStream_t s);
+hipError_t launch_seed(int dtype, int d, const SeedArgs& a, const BucketArgs* group, hipStream_t s);
+
+// Largest batch that one workgroup groups by itself: four pairs and four lists per thread stay in its registers and the
+// tables of the lists (64 KB) in LDS, which is where the line lies: up to it the one launch is never slower.  Searches of
+// given lists, five launches against one: 64 pairs of 64 lists 77.7 and 70.0 us, 1024 of 1024 120.4 and 114.1, 4096 of 64
+// 98.3 and 85.3, 4096 of 4096 235.9 and 226.2; with 4.2 M rows in the lists, 4096 of 4096, 506.7 and 506.0.
+constexpr int kWholePairs = 4096, kWholeLists = 4096;
+inline bool grouped_whole(const BucketArgs& a) { return (int64_t)a.nq * a.nprobe <= kWholePairs && a.nlist <= kWholeLists; }
+// Most queries whose seeding the grouping rides on (see k_group_seed): beyond that the workgroups of the seeding, twice as wide and
+// with the tables of the grouping in LDS, two on a compute unit, make more rounds than the launch takes.  Two launches and one: 300
+// queries over 12 of 512 lists 165 and 154 us (float32, d = 768), 1000 over 4 208 and 198, 2000 over 2 242 and 234; binary16,
+// d = 128, 1000 over 4 187 and 182, 2000 over 2 228 and 231, 4096 over 1 274 and 294.
+constexpr int kSeedBeside = 1024;
 
 }  // namespace hr

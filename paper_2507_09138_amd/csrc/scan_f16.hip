@@ -6,5 +6,5 @@ hipError_t launch_scan_f16(int d, const ScanArgs& a, int grid, size_t lds, hipSt
 {
     return launch_scan_dtype<HR_F16>(d, a, grid, lds, s);
 }
-hipError_t launch_seed_f16(int d, const SeedArgs& a, hipStream_t s) { return launch_seed_dtype<HR_F16>(d, a, s); }
+hipError_t launch_seed_f16(int d, const SeedArgs& a, const BucketArgs* group, hipStream_t s) { return launch_seed_dtype<HR_F16>(d, a, group, s); }
 }  // namespace hr

@@ -14,5 +14,5 @@ hipError_t launch_scan_f16hi(int d, const ScanArgs& a, int grid, size_t lds, hip
 {
     return launch_scan_dtype<HR_F16HI>(d, a, grid, lds, s);
 }
-hipError_t launch_seed_f32(int d, const SeedArgs& a, hipStream_t s) { return launch_seed_dtype<HR_F32>(d, a, s); }
+hipError_t launch_seed_f32(int d, const SeedArgs& a, const BucketArgs* group, hipStream_t s) { return launch_seed_dtype<HR_F32>(d, a, group, s); }
 }  // namespace hr

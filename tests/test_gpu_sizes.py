@@ -642,3 +642,20 @@ def test_bounds_of_replaced_float32_rows(tables):
         # 2^-24 of |q||x| below 16 * 160 * 1.3, with room for the steps of the sums
         assert float((score.double() - best).abs().max()) <= 2600 * 2.0 ** -24 * 16
     ix.close()
+
+
+@pytest.mark.parametrize("storage,d", [("f16", 64), ("bf16", 768), ("f32", 1024)])
+@pytest.mark.parametrize("nq,nprobe,nlist", [(1, 1, 7), (1024, 4, 64), (1023, 4, 4096), (8, 512, 512), (1024, 4, 4097)])
+def test_seeding_and_grouping_in_one_launch_or_in_two(storage, d, nq, nprobe, nlist):
+    """The largest batch that takes the one launch and smaller ones, some lists out of place: the results of the same queries
+    as part of a batch that is too large for it."""
+    dtype = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[storage]
+    ix, cent, off, vec, ids, g = _index(9000, d, nlist, dtype, nq + d, zipf=0.6)
+    q = torch.randn(nq + 1100, d, generator=g, device="cuda")
+    ix.set_resident(torch.arange(0, nlist, 5, dtype=torch.int32, device="cuda"), False)
+    probe = torch.rand(nq + 1100, nlist, generator=g, device="cuda").topk(nprobe, dim=1).indices.int()
+    probe[::3, 0] = -1
+    few = ix.scan(q[:nq], probe[:nq].contiguous(), 10, "l2")
+    many = ix.scan(q, probe, 10, "l2")
+    assert torch.equal(few[0], many[0][:nq]) and torch.equal(few[1], many[1][:nq])
+    ix.close()
