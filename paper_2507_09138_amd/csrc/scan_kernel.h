@@ -667,7 +667,13 @@ __global__ __launch_bounds__(kScanWaves * 64, groups_per_cu(DT, KSTEPS * 32) == 
         }
         const int nrows = row_end - row0;
         const int nblk = (nrows + BR - 1) / BR;
-        Cand* const sel = a.slot_ent + ((size_t)slot0 + wave * NC) * (size_t)a.cap;     // selection buffers of this wave's columns
+        // queries per wave (dense: see make_plan).  Bounded types with more than a few neighbours: a tile that is at most half full goes
+        // on twice the waves, which share its selections: 250 queries over 16 of 512 lists, k 128, float32 rows of d = 768 266 -> 221
+        // us, with row tables 255 -> 209, d = 64 419 -> 365, 128 queries over 32, k 24, d = 1024 183 -> 170 (k 10, 1024 queries over 32
+        // of 1024 lists of 1024 rows 620 -> 626: there more waves read the same rows from LDS).
+        constexpr bool SOME = (DENSE && QP == 2 && KSTEPS >= 16) || S::bounded;
+        const int cpw = DENSE ? (SOME ? a.dense_cols : NC) : (S::bounded && a.k > 12 && w - qt * S::cw <= S::cw / 2 ? NC / 2 : NC);
+        Cand* const sel = a.slot_ent + ((size_t)slot0 + wave * cpw) * (size_t)a.cap;    // selection buffers of this wave's columns
         const char* src = (const char*)a.rows + (size_t)row0 * S::rowb;
         const char* src_lo = S::planes == 2 ? (const char*)a.rows_lo + (size_t)row0 * S::rowb : src;
 
@@ -730,10 +736,7 @@ __global__ __launch_bounds__(kScanWaves * 64, groups_per_cu(DT, KSTEPS * 32) == 
         for (int i = 0; i < D; i++) fill(i, i);
 
         // ---- query operands of this lane's columns into registers (B fragments)
-        // entry inside the bucket (dense: a wave may hold fewer queries than it has columns for, see make_plan)
-        constexpr bool SOME = DENSE && QP == 2 && KSTEPS >= 16;
-        const int cpw = SOME ? a.dense_cols : NC;
-        const int ecol = (qt * NW + wave) * cpw + jcol;
+        const int ecol = (DENSE ? qt * NW * cpw : qt * S::cw) + wave * cpw + jcol;      // entry inside the bucket
         u32x4 bfrag[QP][KSTEPS];
         const bool col_ok = ecol < w && (!SOME || jcol < cpw);
         int q = 0;
@@ -1047,7 +1050,7 @@ __global__ __launch_bounds__(kScanWaves * 64, groups_per_cu(DT, KSTEPS * 32) == 
             const int lane = lane_here();
             const int n = ccnt;                                  // (lanes below NC: of column `lane` of this wave)
             const bool ok = col_ok && lane < NC;
-            if (ok) a.slot_cnt[(size_t)slot0 + wave * NC + lane] = n;
+            if (ok) a.slot_cnt[(size_t)slot0 + wave * cpw + lane] = n;
             // ---- what this item found tightens the lower bounds of its queries for the items
             // still to come.  Every query has a histogram of the keys reported so far over
             // fixed key ranges above its seed; each reported key is a distinct row (an item
