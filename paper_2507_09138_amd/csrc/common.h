@@ -153,6 +153,7 @@ struct ScanArgs {
     int dense_groups;           // groups that the tiles are taken in, so that the items of a segment meet in one XCD (0: plain order)
     int dense_cols;             // queries per wave (d < 512: as many as it has columns for)
     int nq, k, cap, l2;
+    int tile;                   // lists: queries of a work item
     int nbuf;                   // staging buffers in LDS
     float* key_out;             // dense mode: [nq, dense_nrows] every key is written here and nothing is selected
     int* hist;                  // [nq][kHistBins] keys found so far per query, by key range (or nullptr)

@@ -672,7 +672,8 @@ __global__ __launch_bounds__(kScanWaves * 64, groups_per_cu(DT, KSTEPS * 32) == 
         // us, with row tables 255 -> 209, d = 64 419 -> 365, 128 queries over 32, k 24, d = 1024 183 -> 170 (k 10, 1024 queries over 32
         // of 1024 lists of 1024 rows 620 -> 626: there more waves read the same rows from LDS).
         constexpr bool SOME = (DENSE && QP == 2 && KSTEPS >= 16) || S::bounded;
-        const int cpw = DENSE ? (SOME ? a.dense_cols : NC) : (S::bounded && a.k > 12 && w - qt * S::cw <= S::cw / 2 ? NC / 2 : NC);
+        const int tile = S::bounded ? a.tile : S::cw;
+        const int cpw = DENSE ? (SOME ? a.dense_cols : NC) : (S::bounded && (tile < S::cw || (a.k > 12 && w - qt * tile <= S::cw / 2)) ? NC / 2 : NC);
         Cand* const sel = a.slot_ent + ((size_t)slot0 + wave * cpw) * (size_t)a.cap;    // selection buffers of this wave's columns
         const char* src = (const char*)a.rows + (size_t)row0 * S::rowb;
         const char* src_lo = S::planes == 2 ? (const char*)a.rows_lo + (size_t)row0 * S::rowb : src;
@@ -683,7 +684,7 @@ __global__ __launch_bounds__(kScanWaves * 64, groups_per_cu(DT, KSTEPS * 32) == 
         // point of the loop, which is what the wait counts below rely on.
         //
         // Block blk -> buffer buf, straight from HBM, and the squared norms of its rows (64 .. 256 bytes) beside it
-        const bool stream_once = !DENSE && w <= S::cw;   // the only work item that reads these rows
+        const bool stream_once = !DENSE && w <= (S::bounded ? a.tile : S::cw);   // the only work item that reads these rows
         auto fill = [&](int blk, int buf) __attribute__((always_inline)) {
             if (RB > 1 && blk >= nblk) {
 #pragma unroll
@@ -736,7 +737,7 @@ __global__ __launch_bounds__(kScanWaves * 64, groups_per_cu(DT, KSTEPS * 32) == 
         for (int i = 0; i < D; i++) fill(i, i);
 
         // ---- query operands of this lane's columns into registers (B fragments)
-        const int ecol = (DENSE ? qt * NW * cpw : qt * S::cw) + wave * cpw + jcol;      // entry inside the bucket
+        const int ecol = (DENSE ? qt * NW * cpw : qt * tile) + wave * cpw + jcol;      // entry inside the bucket
         u32x4 bfrag[QP][KSTEPS];
         const bool col_ok = ecol < w && (!SOME || jcol < cpw);
         int q = 0;
