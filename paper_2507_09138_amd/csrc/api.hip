@@ -658,9 +658,10 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, const f
     b.round_cnt = zero + p.zoff_round;
     b.round_cur = zero + p.zoff_round + 8 * 64;
     b.item_cap = p.item_cap;
-    // (the grouping of a small batch rides on the seeding)
-    const bool together = grouped_whole(b) && nq <= kSeedBeside;
+    // (the one workgroup of the grouping rides on the seeding)
+    const bool whole = grouped_whole(b), together = whole ? nq <= kSeedBeside : ix->nlist <= kWholeLists;
     if (!together) HR_HIP(launch_bucketing(b, s));
+    else if (!whole) HR_HIP(launch_bucketing_before(b, s));
 
     // starting lower bounds: from a carried result, and from the first rows of every query's best-ranked list
     SeedArgs sd{};
@@ -676,6 +677,7 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, const f
     sd.list_bound = ix->d_list_bound;
     if (carried) { sd.state_ids = out_ids; sd.state_scores = out_scores; }
     HR_HIP(launch_seed(row_dtype(ix), ix->d, sd, together ? &b : nullptr, s));
+    if (together && !whole) HR_HIP(launch_bucketing_behind(b, s));
 
     ScanArgs a{};
     a.rows = ix->d_vec_hi ? ix->d_vec_hi : row_table(ix);

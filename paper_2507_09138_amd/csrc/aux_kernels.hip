@@ -466,20 +466,19 @@ __global__ __launch_bounds__(1024) void k_bucket_count_shared(BucketArgs a)
 template <int PER, bool WHOLE>
 __global__ __launch_bounds__(1024) void k_bucket_scan(BucketArgs a) { group_pairs<1024, PER, WHOLE>(a); }
 
-__global__ void k_bucket_scatter(BucketArgs a)
+// Pairs to their places in the buckets (the first `scatter` workgroups), and items per queue and round (one wave per list, its
+// segments over the lanes): neither needs the other.
+__global__ __launch_bounds__(256) void k_scatter_count(BucketArgs a, unsigned scatter)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)a.nq * a.nprobe) return;
-    int e = a.pair_entry[i];
-    if (e < 0) return;
-    int l = a.probe[i];
-    a.bucket_q[a.bucket_off[l] + e] = (int)(i / a.nprobe);
-}
-
-// items per queue and round (one wave per list, its segments over the lanes)
-__global__ __launch_bounds__(256) void k_round_count(BucketArgs a)
-{
-    int l = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (blockIdx.x < scatter) {
+        const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+        if (i >= (int64_t)a.nq * a.nprobe) return;
+        const int e = a.pair_entry[i];
+        if (e < 0) return;
+        a.bucket_q[a.bucket_off[a.probe[i]] + e] = (int)(i / a.nprobe);
+        return;
+    }
+    const int l = (blockIdx.x - scatter) * 4 + (threadIdx.x >> 6);
     if (l >= a.nlist) return;
     int lane = threadIdx.x & 63;
     int w = a.list_w[l];
@@ -524,27 +523,39 @@ __global__ __launch_bounds__(256) void k_item_expand(BucketArgs a)
     }
 }
 
-hipError_t launch_bucketing(const BucketArgs& a, hipStream_t s)
+hipError_t launch_bucketing_before(const BucketArgs& a, hipStream_t s)
 {
-    int64_t pairs = (int64_t)a.nq * a.nprobe;
-    unsigned gp = (unsigned)((pairs + 255) / 256);
-    if (grouped_whole(a)) {
-        hipLaunchKernelGGL((k_bucket_scan<kWholeLists / 1024, true>), dim3(1), dim3(1024), 0, s, a);
-        return hipGetLastError();
-    }
+    const int64_t pairs = (int64_t)a.nq * a.nprobe;
     if (pairs >= (int64_t)kCountShare * a.nlist && a.nlist <= kCountLists) {
         if (pairs <= 131072) hipLaunchKernelGGL(k_bucket_count_shared<2>, dim3((unsigned)((pairs + 2047) / 2048)), dim3(1024), (size_t)a.nlist * 4, s, a);
         else hipLaunchKernelGGL(k_bucket_count_shared<8>, dim3((unsigned)((pairs + 8191) / 8192)), dim3(1024), (size_t)a.nlist * 4, s, a);
     } else
-        hipLaunchKernelGGL(k_bucket_count, dim3(gp), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(k_bucket_count, dim3((unsigned)((pairs + 255) / 256)), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_bucketing_behind(const BucketArgs& a, hipStream_t s)
+{
+    const unsigned gp = (unsigned)(((int64_t)a.nq * a.nprobe + 255) / 256), gl = (unsigned)((a.nlist + 3) / 4);
+    hipLaunchKernelGGL(k_scatter_count, dim3(gp + gl), dim3(256), 0, s, a, gp);
+    hipLaunchKernelGGL(k_item_expand, dim3(gl), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_bucketing(const BucketArgs& a, hipStream_t s)
+{
+    if (grouped_whole(a)) {
+        hipLaunchKernelGGL((k_bucket_scan<kWholeLists / 1024, true>), dim3(1), dim3(1024), 0, s, a);
+        return hipGetLastError();
+    }
+    hipError_t e = launch_bucketing_before(a, s);
+    if (e != hipSuccess) return e;
     const int per = (a.nlist + 1023) / 1024;
     if (per <= 4) hipLaunchKernelGGL((k_bucket_scan<4, false>), dim3(1), dim3(1024), 0, s, a);
     else if (per <= 16) hipLaunchKernelGGL((k_bucket_scan<16, false>), dim3(1), dim3(1024), 0, s, a);
     else hipLaunchKernelGGL((k_bucket_scan<0, false>), dim3(1), dim3(1024), 0, s, a);
-    hipLaunchKernelGGL(k_bucket_scatter, dim3(gp), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_round_count, dim3((unsigned)((a.nlist + 3) / 4)), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_item_expand, dim3((unsigned)((a.nlist + 3) / 4)), dim3(256), 0, s, a);
-    return hipGetLastError();
+    e = hipGetLastError();
+    return e != hipSuccess ? e : launch_bucketing_behind(a, s);
 }
 
 // ------------------------------------------------------------------------------------------

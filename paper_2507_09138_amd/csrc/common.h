@@ -269,7 +269,10 @@ struct BucketArgs {
     unsigned long long* hits;   // [nlist] probes per list since load or the last reset (index-owned), or nullptr
     const int* resident;        // [nlist] 1 = the list's vectors are in place; probes of the other lists are dropped
 };
+// grouping of a batch, all of it, or what comes before and behind k_bucket_scan
 hipError_t launch_bucketing(const BucketArgs& a, hipStream_t s);
+hipError_t launch_bucketing_before(const BucketArgs& a, hipStream_t s);
+hipError_t launch_bucketing_behind(const BucketArgs& a, hipStream_t s);
 hipError_t launch_seed(int dtype, int d, const SeedArgs& a, const BucketArgs* group, hipStream_t s);
 
 // Largest batch that one workgroup groups by itself: four pairs and four lists per thread stay in its registers and the

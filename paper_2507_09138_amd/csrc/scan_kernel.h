@@ -1375,12 +1375,16 @@ __global__ __launch_bounds__(256) void k_seed(SeedArgs a) { seed_query<DT, KSTEP
 // of 512 lists, float32 of d = 768 57.4 and 48.5, binary16 of d = 128 45.7 and 39.0, bfloat16 of d = 1024 61.1 and 52.3; 250 over 16
 // 155 and 144, 155 and 150, 141 and 130.  512 threads: with 1024 a wave has 128 registers, too few for the rows that the seeding
 // asks for at once.
-constexpr int kGroupSeedThreads = 512;
-template <int DT, int KSTEPS>
-__global__ __launch_bounds__(kGroupSeedThreads) void k_group_seed(BucketArgs b, SeedArgs a)
+//
+// A larger batch: the one workgroup between the counting of the probes and the work items goes beside the seeding of 256 threads a
+// query (PER: lists of its threads, whose widths sit in registers).  777 queries over 33 of 1000 lists 192 -> 181 us a call (with
+// k_scatter_count, a launch less), 214 over 23 of 199 112 -> 102, 1024 over 32 of 1024 629 -> 614.  Up to 4096 lists: 64 lists a thread
+// take 256 registers, which the seeding misses (466 over 15 of 12754 lists 468 -> 485, 8192 over 128 of 16384 15.6 -> 15.8 ms).
+template <int DT, int KSTEPS, int T, int PER>
+__global__ __launch_bounds__(T) void k_group_seed(BucketArgs b, SeedArgs a)
 {
-    if (blockIdx.x == 0) group_pairs<kGroupSeedThreads, kWholeLists / kGroupSeedThreads, true>(b);
-    else seed_query<DT, KSTEPS, kGroupSeedThreads / 64>(a, blockIdx.x - 1);
+    if (blockIdx.x == 0) group_pairs<T, PER, T == 512>(b);
+    else seed_query<DT, KSTEPS, T / 64>(a, blockIdx.x - 1);
 }
 
 // group: the grouping of the batch rides along, or nullptr
@@ -1388,11 +1392,15 @@ template <int DT>
 inline hipError_t launch_seed_dtype(int d, const SeedArgs& a, const BucketArgs* group, hipStream_t s)
 {
     if (a.nq <= 0) return hipSuccess;
-#define HR_SEED_CASE(KS)                                                                                                          \
-    case KS * 32:                                                                                                                 \
-        if (group) hipLaunchKernelGGL((k_group_seed<DT, KS>), dim3((unsigned)a.nq + 1), dim3(kGroupSeedThreads), 0, s, *group, a); \
-        else hipLaunchKernelGGL((k_seed<DT, KS>), dim3((unsigned)a.nq), dim3(256), 0, s, a);                                      \
+    const dim3 grid((unsigned)a.nq + (group ? 1 : 0));
+    auto launch = [&](auto ks) {
+        constexpr int KS = decltype(ks)::value;
+        if (!group) hipLaunchKernelGGL((k_seed<DT, KS>), grid, dim3(256), 0, s, a);
+        else if (grouped_whole(*group)) hipLaunchKernelGGL((k_group_seed<DT, KS, 512, kWholeLists / 512>), grid, dim3(512), 0, s, *group, a);
+        else hipLaunchKernelGGL((k_group_seed<DT, KS, 256, kWholeLists / 256>), grid, dim3(256), 0, s, *group, a);
         return hipGetLastError();
+    };
+#define HR_SEED_CASE(KS) case KS * 32: return launch(std::integral_constant<int, KS>{});
     switch (d) {
         HR_SEED_CASE(2)
         HR_SEED_CASE(4)

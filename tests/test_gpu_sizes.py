@@ -645,10 +645,10 @@ def test_bounds_of_replaced_float32_rows(tables):
 
 
 @pytest.mark.parametrize("storage,d", [("f16", 64), ("bf16", 768), ("f32", 1024)])
-@pytest.mark.parametrize("nq,nprobe,nlist", [(1, 1, 7), (1024, 4, 64), (1023, 4, 4096), (8, 512, 512), (1024, 4, 4097)])
+@pytest.mark.parametrize("nq,nprobe,nlist", [(1, 1, 7), (1024, 4, 64), (1023, 4, 4096), (8, 512, 512), (1024, 4, 4097), (9, 456, 4096), (1025, 4, 16), (9, 456, 4097)])
 def test_seeding_and_grouping_in_one_launch_or_in_two(storage, d, nq, nprobe, nlist):
-    """The largest batch that takes the one launch and smaller ones, some lists out of place: the results of the same queries
-    as part of a batch that is too large for it."""
+    """The largest batch that takes the one launch and smaller ones, one more pair, query or list than that, some lists out of
+    place: the results of the same queries as part of a larger batch."""
     dtype = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[storage]
     ix, cent, off, vec, ids, g = _index(9000, d, nlist, dtype, nq + d, zipf=0.6)
     q = torch.randn(nq + 1100, d, generator=g, device="cuda")
