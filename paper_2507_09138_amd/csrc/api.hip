@@ -172,7 +172,7 @@ struct Plan {
     // coarse step: centroid table scanned with all queries as one dense bucket
     int nbuf_c, cw_c, cols_c, nqt_c, seg_c, nseg_c;
     // list scan
-    int groups_s, nbuf_s, cap_s, cw_s, item_cap, item_target, few_items, min_rows;
+    int groups_s, nbuf_s, cap_s, cw_s, item_cap, item_target, few_items, min_rows, base_rows;
     int slot_cap;                   // result slots: one per (list segment, query of the list's bucket)
     size_t o_zero, n_zero;          // ints cleared per call: list_w[nlist], dyn[DYN_COUNT], counters[8], ..., then
     size_t zoff_round, zoff_hist, zoff_hpar;   // (in ints from o_zero) round counters of the queues, per-query key histograms and their parameters
@@ -281,10 +281,14 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     // 50 lists, d = 1024, 112 -> 132; and with a second round of items (segments of rows x tiles / 256 without regard to the
     // ragged ends) 16 requests over 16 of 256 lists, d = 64, 68 -> 97.
     p.few_items = std::min(ix->num_cus, lim.item_target);
+    // Float32 rows of d = 1024 as they are (blocks of 64 KB, two in LDS, so an item moves 30 GB/s at most): half as long.  700
+    // queries over 32 of 512 lists, 48828 rows, 232 -> 204 us, 250 over 16 168 -> 152, 8 over 32 104 -> 96, 700 over 32 of 1024, 97656
+    // rows, 246 -> 238, 700 over 16 of 512, k 50, 280 -> 247; shorter rows lose by it (d = 768, 64 over 16 of 512 141 -> 161, bfloat16 of d = 1024 116 -> 127).
+    p.base_rows = scan_dtype(ix) == HR_F32 && ix->d >= 1024 ? kMinSegRows / 2 : kMinSegRows;
     p.min_rows = k <= kShortSegK && ix->d >= 512 ? std::min(((128 << 10) / (ix->d * (ix->dtype == HR_F32 ? 4 : 2)) + 15) & ~15, kMinSegRows) : kMinSegRows;
     if (p.min_rows < 64) p.min_rows = 64;
     const int64_t in_short = std::min((int64_t)p.cw_s * p.few_items + pairs, pairs * ((ix->longest + p.min_rows - 1) / p.min_rows));
-    const int64_t by_length = std::max(pairs * ((ix->longest + kMinSegRows - 1) / kMinSegRows), in_short);
+    const int64_t by_length = std::max(pairs * ((ix->longest + p.base_rows - 1) / p.base_rows), in_short);
     if (lim.by_length && by_length < slots_most) slots_most = by_length;
     p.slot_cap = (int)slots_most;
 
@@ -652,6 +656,7 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, const f
     b.item_target = p.item_target;
     b.few_items = p.few_items;
     b.min_rows = p.min_rows;
+    b.base_rows = p.base_rows;
     b.dyn = zero + ix->nlist;
     b.xq_rec = (int4*)(ws + p.o_xq);
     b.xq_count = zero + ix->nlist + DYN_COUNT + 8;

@@ -264,7 +264,8 @@ struct BucketArgs {
     int item_cap;
     int slot_cap;               // result slots the workspace holds
     int item_target;            // aimed number of work items (rows per segment follow from it)
-    int few_items;              // work items below which segments become shorter than kMinSegRows
+    int base_rows;              // shortest segments
+    int few_items;              // work items below which segments become shorter than that
     int min_rows;               // but not shorter than this
     unsigned long long* hits;   // [nlist] probes per list since load or the last reset (index-owned), or nullptr
     const int* resident;        // [nlist] 1 = the list's vectors are in place; probes of the other lists are dropped

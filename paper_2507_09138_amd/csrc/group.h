@@ -208,8 +208,8 @@ __device__ __forceinline__ void group_pairs(const BucketArgs& a)
     // for which, and with which figures)
     const int tiles = (int)(r >> 32), room = a.few_items - tiles;
     r &= 0xffffffffLL;
-    int least = kMinSegRows;
-    if (room > 0 && c < (long long)room * kMinSegRows) least = max(a.min_rows, (int)(((unsigned)c + room - 1) / (unsigned)room + 15) & ~15);
+    int least = a.base_rows;
+    if (room > 0 && c < (long long)room * a.base_rows) least = max(a.min_rows, (int)(((unsigned)c + room - 1) / (unsigned)room + 15) & ~15);
     if (segll < least) segll = least;
     if (segll > 0x7ffffff0LL) segll = 0x7ffffff0LL;          // (a list has fewer than 2^31 rows: one segment then)
     const int seg = (int)segll;
