@@ -243,7 +243,7 @@ class IvfIndex:
     """Keeps the borrowed tensors alive, owns the handle and a growable workspace tensor."""
 
     def __init__(self, centroids, list_offsets, list_vectors, list_ids, row_tables=False):
-        """row_tables: also keep float32 / bfloat16 rows as binary16 tables (as many bytes again) that the scan
+        """row_tables: also keep float32 / bfloat16 rows as a binary16 table (two bytes an element more) that the scan
         reads instead: HR_LOAD_ROW_TABLES of hr_ivf_load."""
         for t, name in ((centroids, "centroids"), (list_vectors, "list_vectors"), (list_ids, "list_ids")):
             if not isinstance(t, torch.Tensor) or not t.is_cuda:

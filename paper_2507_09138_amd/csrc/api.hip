@@ -264,8 +264,8 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     p.cw_s = tile_cols(scan_dtype(ix), ix->d);
     // Many neighbours and few queries per list, float32 rows: what a wave does is select, so it has eight queries instead of 16.  Tiles
     // of 128 and 64: 700 queries over 16 of 512 lists, k 50, d = 768 277 and 245 us, d = 64 322 and 295, 3000 queries, k 100, 594
-    // and 549, 607 and 614; over 16 of 256 lists (187 queries per list) 671 and 817, 801 and 1089.
-    if (scan_dtype(ix) == HR_F32 && k > kShortSegK && pairs <= 96 * nlist) p.cw_s /= 2;
+    // and 549, 607 and 614; 662 over 6 of 1703, k 23, 268 and 226; over 16 of 256 lists (187 queries per list) 671 and 817, 801 and 1089.
+    if (scan_dtype(ix) == HR_F32 && k > 12 && pairs <= 96 * nlist) p.cw_s /= 2;
     // Work items: sum over probed lists of segments x query tiles.  Segments have at least C / item_target rows, C =
     // sum of rows x tiles, so there are at most item_target items plus one per (list, tile) for the ragged ends.
     // Result slots: sum of segments x bucket width <= cw x item_target, plus one per pair for the ragged ends.
