@@ -25,16 +25,16 @@ ESIZE = {"f32": 4, "f16": 2, "bf16": 2}
 
 
 def mfma_peak(cfg, ix):
-    """float32 lists are a float32 contraction to the caller (that it runs as three binary16 products per element on
-    the matrix pipes is this library's choice): its 2 d flops per (query, row) pair are priced against the float32
-    peak; 16-bit lists against the dense 16-bit MFMA peak."""
+    """float32 lists are a float32 contraction to the caller (that its candidates come from a binary16 product on the matrix
+    pipes is this library's choice): its 2 d flops per (query, row) pair are priced against the float32 peak; 16-bit lists
+    against the dense 16-bit MFMA peak."""
     return F32_PEAK_TFLOPS if cfg.dtype == "f32" else F16_MFMA_PEAK_TFLOPS
 
 
 def operand_name(cfg, ix):
     """The type the list scan multiplies in (accumulation is float32 throughout)."""
     if cfg.dtype == "f32":
-        return "f16x2"                              # binary16 hi + scaled lo parts of both operands
+        return "f16"                                # rows and queries rounded to binary16; exact float32 scores of the candidates
     if cfg.dtype == "bf16":
         return "f16" if ix.row_tables else "bf16"   # binary16 row table asked for at load, else bfloat16 rows x (hi, lo) query
     return "f16"
@@ -328,7 +328,7 @@ def main():
                     help="extra mode: the list scan over the lists that fewer than this many queries probe; reports bytes / "
                          "time against the HBM peak; prints its own JSON line")
     ap.add_argument("--row-tables", action="store_true",
-                    help="load float32 / bfloat16 lists with HR_LOAD_ROW_TABLES (binary16 row tables: as many bytes again)")
+                    help="load float32 / bfloat16 lists with HR_LOAD_ROW_TABLES (binary16 row tables: two bytes an element more)")
     ap.add_argument("--flush-mb", type=int, default=0,
                     help="write this many MB of scratch between the timed calls (512 evicts the last-level cache, for batches "
                          "small enough to stay in it); each call is then timed by its own pair of events")
@@ -427,12 +427,13 @@ def main():
     pair_rows = int((w * lens).sum())
     rows_streamed = int(lens[w > 0].sum())
     assert rows_streamed == st["rows_streamed"], (rows_streamed, st)
-    scan_bytes = rows_streamed * cfg.d * ESIZE[cfg.dtype]
+    # (float32 lists with a row table: the scan reads the rows rounded to binary16)
+    scan_bytes = rows_streamed * cfg.d * (2 if cfg.dtype == "f32" and args.row_tables else ESIZE[cfg.dtype])
     scan_flops = 2.0 * cfg.d * pair_rows
-    # flops the matrix pipes execute for them: a wave's MFMA covers 16 columns = 16 queries (binary16 operands) or 8
-    # queries in hi and lo parts (bfloat16 rows as stored; float32 rows, which also come as two planes), whether or
-    # not all of them belong to the bucket (the 16-row padding of a segment's last block is not counted)
-    gran, mult = (16, 1) if operand_name(cfg, ix) == "f16" else ((8, 2) if cfg.dtype == "bf16" else (8, 4))
+    # flops the matrix pipes execute for them: a wave's MFMA covers 16 columns = 16 queries, or, bfloat16 rows as stored, 8
+    # queries in hi and lo parts, whether or not all of them belong to the bucket (the 16-row padding of a segment's last
+    # block is not counted)
+    gran, mult = (16, 1) if operand_name(cfg, ix) == "f16" else (8, 2)
     executed_rows = int((((w + gran - 1) // gran) * gran * lens).sum()) * mult
     achieved = scan_bytes / (scan_ms * 1e-3) / 1e9 if scan_ms > 0 else 0.0
 
