@@ -39,7 +39,7 @@ __host__ __device__ constexpr int tile_cols(int dtype, int d) { return kScanWave
 // 16 KB.  16 rows of a short vector are a few KB and a few MFMAs, and a barrier, requests that no wave fills and a filter
 // with its compare and branch cost more than they do.  Blocks of 64 rows instead of 16, d = 64: 4000 queries over 60 of 200
 // binary16 lists of 3000 rows 880 -> 627 us, 500 over 40 of 2000 lists 426 -> 372, 500 over 40 of 1000 lists of 40 rows 113
-// -> 106 (128 rows: 626, 380, 109: a list ends in the middle of a longer block); float32 split on the fly, d = 64, the first two
+// -> 106 (128 rows: 626, 380, 109: a list ends in the middle of a longer block); float32 (split on its way into LDS then), d = 64, the first two
 // 1578 -> 1304 and 528 -> 454.  Two planes of 16 rows of d = 256 are 16 KB already: 32 rows of row tables were 10 % faster for
 // 4000 queries and 2 .. 4 % slower for fewer.
 __host__ __device__ constexpr int block_groups(int dtype, int d)
