@@ -595,7 +595,7 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
     __shared__ int s_cnt[NW];
     __shared__ uint32_t s_thr[Q];
     __shared__ int s_total[Q];
-    __shared__ float s_slack[Q], s_norm[Q];         // largest slack and squared norm of the probed lists
+    __shared__ float s_slack[Q];                    // largest slack of the probed lists
     __shared__ int s_first[NW][64];
     __shared__ size_t s_slot[NW][64];
     __shared__ int64_t s_ext_id[Q][HR_K_MAX];
@@ -622,7 +622,7 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
     if (lane == 0) s_cnt[wave] = 0;
     if (part == 0 && live) {
         int run = 0;
-        float slack = 0.f, norm2 = 0.f;
+        float slack = 0.f;
         const float qn = BOUNDED ? sqrtf(a.qnorm[q]) : 0.f, ql = BOUNDED ? a.qlo[q] : 0.f;
         for (int p0 = 0; p0 < a.nprobe; p0 += 64) {
             int p = p0 + lane;
@@ -632,15 +632,15 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
                 if (l >= 0 && l < a.nlist && a.pair_entry[q * a.nprobe + p] >= 0) {
                     int len = a.list_off[l + 1] - a.list_off[l];
                     ns = (len + seg_rows - 1) / seg_rows;
-                    if (BOUNDED) { slack = fmaxf(slack, scan_slack(qn, ql, a.list_bound[l], a.l2)); norm2 = fmaxf(norm2, a.list_bound[l].x); }
+                    if (BOUNDED) slack = fmaxf(slack, scan_slack(qn, ql, a.list_bound[l], a.l2));
                 }
             }
             const int inc = wave_prefix_sum(ns);
             if (p < a.nprobe) pref[p + 1] = run + inc;
             run += __builtin_amdgcn_readlane(inc, 63);
         }
-        if (BOUNDED) { slack = wave_max(slack); norm2 = wave_max(norm2); }
-        if (lane == 0) { pref[0] = 0; s_thr[own] = 0; s_total[own] = run; s_slack[own] = slack; s_norm[own] = norm2; }
+        if (BOUNDED) slack = wave_max(slack);
+        if (lane == 0) { pref[0] = 0; s_thr[own] = 0; s_total[own] = run; s_slack[own] = slack; }
     }
     wave_sync();
     // ---- a carried result joins as one more partial result (read whole before anything of
@@ -686,10 +686,8 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
             int best;
             left = window(b, n, kth, best);
             if (left > cap - 64) {
-                // (a bound may stay above the exact key by what two sums of the same products differ by, see k_scan)
-                const float add = exact_add(a.qnorm[q], s_norm[own], a.l2);
-                exact_keys<8, 1>(b, left, 0, 1, a.rows_f32, a.row_norm, a.queries + (size_t)q * a.d, a.d, a.l2, add);
-                kth = key_below(wave_select<CE>(b, left, k, a.row_ids, ext_id), 2.0f * add);
+                exact_keys<8, 1>(b, left, 0, 1, a.rows_f32, a.row_norm, a.queries + (size_t)q * a.d, a.d, a.l2);
+                kth = wave_select<CE>(b, left, k, a.row_ids, ext_id);
                 left = k;
             }
         } else {
@@ -796,7 +794,7 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
             n = s_cnt[1];
         }
         for (int from = 0;;) {
-            exact_keys<AT, 4>(s_buf[wave - part] + from, best - from, part, W, a.rows_f32, a.row_norm, a.queries + (size_t)q * a.d, a.d, a.l2, 0.f);
+            exact_keys<AT, 4>(s_buf[wave - part] + from, best - from, part, W, a.rows_f32, a.row_norm, a.queries + (size_t)q * a.d, a.d, a.l2);
             together();
             if (best == n) break;
             if (part == 0) {

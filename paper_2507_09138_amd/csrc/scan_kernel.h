@@ -378,13 +378,6 @@ __device__ __forceinline__ float scan_slack(float q, float q_lo, float2 bound, i
     return s < __builtin_inff() ? s : __builtin_inff();          // (also for NaN)
 }
 
-// What two float32 sums of the same products may differ by, with room: half of what scan_slack counts for it.
-__device__ __forceinline__ float exact_add(float qnorm2, float norm2, int l2)
-{
-    const float s = 9.5367431640625e-07f * sqrtf(qnorm2) * sqrtf(fmaxf(norm2, 1e-18f));
-    return l2 ? 2.0f * s + norm2 * 4.76837158203125e-07f : s;
-}
-
 // Order-preserving image of the key that lies w below the one with image u.
 __device__ __forceinline__ uint32_t key_below(uint32_t u, float w)
 {
@@ -444,17 +437,20 @@ __device__ __forceinline__ int wave_window(Cand* buf, int n, int k, float w, uin
     return left;
 }
 
-// The exact keys (plus add) of the entries first, first + step, .. of the n in buf, in place of their bounds: rows and query
-// in float32, one wave, CH chunks of 256 elements of AT rows on their way together (past the end of a row its first elements
-// again, times zero: a load under a condition would wait for the one before).  Entries of a carried result stay as they are.
+// The exact keys of the entries first, first + step, .. of the n in buf, in place of their bounds: rows and query in float32, one
+// wave, CH chunks of 256 elements of AT rows on their way together (past the end of a row its first elements again, times zero:
+// a load under a condition would wait for the one before).  Every lane adds up its elements of the whole row in order, then the
+// lanes are added up: the same sum whatever CH and AT, so a key is the same bits wherever it is computed, and a row that is left out for
+// its exact key is behind k others in the final order too.  Entries of a carried result stay as they are.
 template <int AT, int CH>
-__device__ __forceinline__ void exact_keys(Cand* buf, int n, int first, int step, const float* rows, const float* row_norm, const float* query, int d, int l2, float add)
+__device__ __forceinline__ void exact_keys(Cand* buf, int n, int first, int step, const float* rows, const float* row_norm, const float* query, int d, int l2)
 {
+    constexpr bool whole = CH * 256 >= 1024;                    // (the longest supported row)
     const int lane = lane_now();
     if (first >= n) return;
-    for (int c0 = 0; c0 < d; c0 += CH * 256) {                  // (once where CH chunks are a whole row: first and last)
-        floatx4 y[CH];
-        int at[CH];
+    floatx4 y[CH];
+    int at[CH];
+    auto part = [&](int c0) __attribute__((always_inline)) {    // the query's elements from c0 on
 #pragma unroll
         for (int c = 0; c < CH; c++) {
             const int i = c0 + c * 256 + lane * 4;
@@ -462,44 +458,44 @@ __device__ __forceinline__ void exact_keys(Cand* buf, int n, int first, int step
             y[c] = floatx4{0.f, 0.f, 0.f, 0.f};
             if (i < d) y[c] = floatx4{query[i], query[i + 1], query[i + 2], query[i + 3]};       // (the caller's: any alignment)
         }
-        const bool last = c0 + CH * 256 >= d;
+    };
+    if (whole) part(0);
 #pragma unroll 1
-        for (int e0 = first; e0 < n; e0 += AT * step) {
-            uint32_t r[AT];
-            floatx4 x[AT][CH];
-            float norm[AT], dot[AT];
+    for (int e0 = first; e0 < n; e0 += AT * step) {
+        uint32_t r[AT];
+        float norm[AT], dot[AT];
 #pragma unroll
-            for (int j = 0; j < AT; j++) r[j] = __builtin_amdgcn_readfirstlane(buf[min(e0 + j * step, n - 1)].row);
+        for (int j = 0; j < AT; j++) {
+            r[j] = __builtin_amdgcn_readfirstlane(buf[min(e0 + j * step, n - 1)].row);
+            dot[j] = 0.f;
+        }
+#pragma unroll 1
+        for (int c0 = 0; c0 < (whole ? 1 : d); c0 += CH * 256) {
+            floatx4 x[AT][CH];
+            if (!whole) part(c0);
 #pragma unroll
             for (int j = 0; j < AT; j++) {
                 const float* p = rows + (size_t)(r[j] & kCarried ? 0u : r[j]) * d;
 #pragma unroll
                 for (int c = 0; c < CH; c++) x[j][c] = *(const floatx4*)(p + at[c]);
-                norm[j] = l2 ? row_norm[r[j] & kCarried ? 0u : r[j]] : 0.f;
+                if (c0 == 0) norm[j] = l2 ? row_norm[r[j] & kCarried ? 0u : r[j]] : 0.f;
             }
 #pragma unroll
-            for (int j = 0; j < AT; j++) {
-                dot[j] = 0.f;
+            for (int j = 0; j < AT; j++)
 #pragma unroll
                 for (int c = 0; c < CH; c++)
 #pragma unroll
                     for (int m = 0; m < 4; m++) dot[j] = __builtin_fmaf(x[j][c][m], y[c][m], dot[j]);
-            }
-#pragma unroll
-            for (int j = 0; j < AT; j++) dot[j] = wave_add(dot[j]);
-#pragma unroll
-            for (int j = 0; j < AT; j++) {
-                const int e = e0 + j * step;
-                if (lane == 63 && e < n && !(r[j] & kCarried)) {
-                    float sum = dot[j];
-                    if (c0 > 0) sum += dec_key(buf[e].key);
-                    if (last) sum = (l2 ? 2.0f * sum - norm[j] : sum) + add;
-                    buf[e].key = enc_key(sum);
-                }
-            }
         }
-        wave_sync();
+#pragma unroll
+        for (int j = 0; j < AT; j++) dot[j] = wave_add(dot[j]);
+#pragma unroll
+        for (int j = 0; j < AT; j++) {
+            const int e = e0 + j * step;
+            if (lane == 63 && e < n && !(r[j] & kCarried)) buf[e].key = enc_key(l2 ? 2.0f * dot[j] - norm[j] : dot[j]);
+        }
     }
+    wave_sync();
 }
 
 __device__ __forceinline__ int window_k(Cand* buf, int n, int k, int cap, float w, uint32_t& bound, int lane)
@@ -926,12 +922,10 @@ __global__ __launch_bounds__(kScanWaves * 64, groups_per_cu(DT, KSTEPS * 32) == 
                         const float w = 2.0f * __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, slack), col));
                         left = window_k(sel + col * a.cap, n, a.k, a.cap, w, kth, lane);
                         if (left > a.cap - kAppendMax - kRoomAfterCut) {
-                            // more rows than that are within the slack of the k-th best: their exact keys, plus
-                            // what another sum of the same products may differ by, which is at most a slack
+                            // more rows than that are within the slack of the k-th best: the best by their exact keys
                             const int qc = __builtin_amdgcn_readlane(q, col);
-                            const float add = exact_add(a.qnorm[qc], a.list_bound[list].x, a.l2);
-                            exact_keys<8, 1>(sel + col * a.cap, left, 0, 1, a.rows_f32, a.row_norm, a.queries + (size_t)qc * S::d, S::d, a.l2, add);
-                            kth = key_below(select_k(sel + col * a.cap, left, a.k, a.cap, a.row_ids, lane), 2.0f * add);
+                            exact_keys<4, 1>(sel + col * a.cap, left, 0, 1, a.rows_f32, a.row_norm, a.queries + (size_t)qc * S::d, S::d, a.l2);
+                            kth = select_k(sel + col * a.cap, left, a.k, a.cap, a.row_ids, lane);
                             left = a.k;
                         }
                     } else {

@@ -659,3 +659,47 @@ def test_seeding_and_grouping_in_one_launch_or_in_two(storage, d, nq, nprobe, nl
     many = ix.scan(q, probe, 10, "l2")
     assert torch.equal(few[0], many[0][:nq]) and torch.equal(few[1], many[1][:nq])
     ix.close()
+
+
+def _replaced(N, d, nlist, rows, seed, tables):
+    """An index of float32 lists loaded with rows that differ, all of which are replaced afterwards."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    cent = torch.randn(nlist, d, generator=g, device="cuda")
+    off = torch.linspace(0, N, nlist + 1).long()
+    vec = torch.randn(N, d, generator=g, device="cuda")
+    ids = torch.randperm(N, generator=g, device="cuda")
+    ix = _hr().IvfIndex(cent, off, vec, ids, row_tables=tables)
+    vec.copy_(rows(g))
+    ix.refresh_rows(0, N)
+    return ix, vec, ids, g
+
+
+@pytest.mark.parametrize("tables", [False, True])
+@pytest.mark.parametrize("d,k,metric", [(64, 10, "ip"), (256, 20, "l2"), (512, 10, "l2"), (768, 10, "ip"), (768, 1, "l2"), (1024, 24, "ip"), (1024, 10, "l2")])
+@pytest.mark.parametrize("spread", [1e-5, 1e-4])
+def test_close_float32_rows_are_the_same_bits_in_every_call(tables, d, k, metric, spread):
+    """Rows so close that buffers overflow with rows whose bounds say nothing: ids and scores must not depend on the batch around a
+    query, on the plan (segments and buffers of the static scratch) or on which lists are searched together."""
+    hr = _hr()
+    nlist, nq = 6, 250
+    N = nlist * 1500
+    ix, vec, ids, g = _replaced(N, d, nlist, lambda g: torch.randn(1, d, generator=g, device="cuda") + spread * torch.randn(N, d, generator=g, device="cuda"),
+                                d + k, tables)
+    q = torch.randn(1100, d, generator=g, device="cuda")
+    alone = ix.search(q[:nq], nlist, k, metric)
+    for _ in range(3):
+        again = ix.search(q[:nq], nlist, k, metric)
+        assert torch.equal(again[0], alone[0]) and torch.equal(again[1], alone[1])
+    larger = ix.search(q, nlist, k, metric)
+    assert torch.equal(larger[0][:nq], alone[0]) and torch.equal(larger[1][:nq], alone[1])
+    fixed = torch.empty_like(alone[0]), torch.empty_like(alone[1])
+    hr.hr_ivf_search_static(ix.handle, q[:nq], nq, nlist, k, hr.HR_METRIC_IP if metric == "ip" else hr.HR_METRIC_L2, *fixed)
+    assert torch.equal(fixed[0], alone[0]) and torch.equal(fixed[1], alone[1])
+    if metric == "ip":                                 # (equal scores may be different keys with the other metric)
+        found, score = zip(*(ix.scan(q[:nq], torch.full((nq, 1), x, dtype=torch.int32, device="cuda"), k, metric) for x in range(nlist)))
+        found, score = torch.cat(found, 1).cpu().numpy(), torch.cat(score, 1).cpu().numpy()
+        order = np.lexsort((found, -score), axis=1)[:, :k]
+        assert np.array_equal(np.take_along_axis(found, order, 1), alone[0].cpu().numpy())
+        assert np.array_equal(np.take_along_axis(score, order, 1), alone[1].cpu().numpy())
+    ix.close()
