@@ -1337,9 +1337,12 @@ __device__ __forceinline__ void seed_query(const SeedArgs& a, const int64_t q)
     // a few units in the last place lower, in case a later pass rounds a sum differently
     uint32_t pub = kth > 8u ? kth - 8u : 0u;
     if constexpr (DT == HR_F32) {
-        // (the scores of the scan are exact ones; here, elements below 2^-36 or so vanish in the low parts)
+        // (the scores that count are exact ones: other sums of products of about 22 bits per factor, half of the 2^-19 |q| |x| that
+        // scan_slack counts for both; and elements below 2^-36 or so vanish in the low parts.  A bound too high by that would keep
+        // rows of lists with shorter rows out)
         const float qn = a.qnorm[q], xn = a.list_bound[l].x;
-        const float lost = 2.9103830456733704e-11f * sqrtf((float)d) * (sqrtf(qn) + sqrtf(xn)) * (a.l2 ? 2.0f : 1.0f);
+        float lost = 2.9103830456733704e-11f * sqrtf((float)d) * (sqrtf(qn) + sqrtf(xn)) + 9.5367431640625e-07f * sqrtf(qn) * sqrtf(xn);
+        if (a.l2) lost = 2.0f * lost + xn * 4.76837158203125e-07f;
         pub = qn > 1e-30f && xn > 1e-30f ? key_below(pub, lost) : 0u;
     }
     if (lane == 0) atomicMax(&a.thr[q], pub);

@@ -703,3 +703,39 @@ def test_close_float32_rows_are_the_same_bits_in_every_call(tables, d, k, metric
         assert np.array_equal(np.take_along_axis(found, order, 1), alone[0].cpu().numpy())
         assert np.array_equal(np.take_along_axis(score, order, 1), alone[1].cpu().numpy())
     ix.close()
+
+
+@pytest.mark.parametrize("tables", [False, True])
+@pytest.mark.parametrize("d", [64, 768, 1024])
+@pytest.mark.parametrize("metric", ["ip", "l2"])
+def test_a_long_row_does_not_hide_a_short_one(tables, d, metric):
+    """A query's first list holds a long row that is nearly orthogonal to it, so sums of its products differ by more than all that
+    bounds the short row of the other list: of the two, searched together, the one with the better score alone is found."""
+    nq = 300
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    q = torch.randn(nq, d, generator=g, device="cuda")
+    long = torch.randn(nq, d, generator=g, device="cuda").double() * 2e4
+    long = (long - (long * q.double()).sum(1, keepdim=True) / (q.double() ** 2).sum(1, keepdim=True) * q.double()).float()
+    size = q.double().norm(dim=1) * long.double().norm(dim=1)
+    key = (long.double() * q.double()).sum(1) * (1 if metric == "ip" else 2) - (0 if metric == "ip" else 1) * (long.double() ** 2).sum(1)
+    gap = size * torch.tensor([0.0, 1e-9, 4e-9, 1.6e-8, 6.4e-8], dtype=torch.float64, device="cuda").repeat(nq // 5)
+    # short row: along the query for the inner product; for the distance as far from it as the long one
+    along = ((key + gap) / (q.double() ** 2).sum(1))[:, None] * q.double()
+    if metric == "l2":
+        far = torch.roll(long.double(), 1, 0)
+        far = far - (far * q.double()).sum(1, keepdim=True) / (q.double() ** 2).sum(1, keepdim=True) * q.double()
+        along = far / far.norm(dim=1, keepdim=True) * (-key - gap).clamp(min=0).sqrt()[:, None]
+    vec = torch.stack([long, along.float()], 1).reshape(2 * nq, d).contiguous()
+    ids = torch.randperm(2 * nq, generator=g, device="cuda")
+    ix = _hr().IvfIndex(vec, torch.arange(2 * nq + 1), vec, ids, row_tables=tables)
+    both = torch.arange(2 * nq, dtype=torch.int32, device="cuda").view(nq, 2)
+    single = [ix.scan(q, both[:, x:x + 1].contiguous(), 1, metric) for x in (0, 1)]
+    found, score = ix.scan(q, both, 1, metric)
+    best = torch.maximum(single[0][1], single[1][1]) if metric == "ip" else torch.minimum(single[0][1], single[1][1])
+    assert torch.equal(score, best)
+    won = torch.where(single[0][1] == best, single[0][0], single[1][0])
+    tie = single[0][1] == single[1][1]
+    assert bool((tie | (found == won)).all())
+    assert metric == "l2" or bool(((found == single[0][0]).any() and (found == single[1][0]).any()))
+    ix.close()
