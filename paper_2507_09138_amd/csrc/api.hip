@@ -199,6 +199,7 @@ struct PlanLimits { int item_target; size_t ckeys_bytes; bool by_length; int cap
 static constexpr PlanLimits kDefaultLimits = {kItemTarget, (size_t)512 << 20, true, 0};
 
 static constexpr int kShortSegK = 24;          // most neighbours of a search that may go in segments shorter than kMinSegRows
+static constexpr int kFullTileK = 12;          // most neighbours of float32 rows that always go in full tiles of queries
 
 static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, const PlanLimits& lim = kDefaultLimits)
 {
@@ -265,12 +266,14 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     // Many neighbours and few queries per list, float32 rows: what a wave does is select, so it has eight queries instead of 16.  Tiles
     // of 128 and 64: 700 queries over 16 of 512 lists, k 50, d = 768 277 and 245 us, d = 64 322 and 295, 3000 queries, k 100, 594
     // and 549, 607 and 614; 662 over 6 of 1703, k 23, 268 and 226; over 16 of 256 lists (187 queries per list) 671 and 817, 801 and 1089.
-    if (scan_dtype(ix) == HR_F32 && k > 12 && pairs <= 96 * nlist) p.cw_s /= 2;
+    const int narrow = scan_dtype(ix) == HR_F32 && k > kFullTileK ? p.cw_s / 2 : p.cw_s;
+    if (pairs <= 96 * nlist) p.cw_s = narrow;
     // Work items: sum over probed lists of segments x query tiles.  Segments have at least C / item_target rows, C =
     // sum of rows x tiles, so there are at most item_target items plus one per (list, tile) for the ragged ends.
-    // Result slots: sum of segments x bucket width <= cw x item_target, plus one per pair for the ragged ends.
+    // Result slots: sum of segments x bucket width <= cw x item_target, plus one per pair for the ragged ends.  (In a
+    // workspace items are bounded for the narrower tiles that fewer queries would go in: the plan of a larger batch is never the smaller.)
     p.item_target = lim.item_target;
-    p.item_cap = (int)(lim.item_target + pairs / p.cw_s + (pairs < nlist ? pairs : nlist) + 8);
+    p.item_cap = (int)(lim.item_target + pairs / (lim.by_length ? narrow : p.cw_s) + (pairs < nlist ? pairs : nlist) + 8);
     int64_t slots_most = (int64_t)p.cw_s * lim.item_target + pairs;
     // Nor has a pair more slots than the longest list has segments, whatever the batch (one query over 16 of 256 lists of
     // 65536 rows in all, k 10: 268 MB of slots without this bound, 1.3 with it).  Segments shorter than kMinSegRows are of
@@ -548,9 +551,12 @@ size_t hr_ivf_workspace_bytes(const hr_ivf_index* ix, int64_t nq, int32_t nprobe
     if (nprobe < 1 || nprobe > HR_NPROBE_MAX) { fail(HR_ERR_ARG, "nprobe=%d must be in 1..%d", nprobe, HR_NPROBE_MAX); return 0; }
     if (check_batch(ix, nq, nprobe > ix->nlist ? (int)ix->nlist : nprobe, k, HR_METRIC_IP, true)) return 0;
     // what is enough for k is enough for fewer: searches of few neighbours may take more, shorter segments, so more result slots
-    // (one request over 16 of 256 lists, the longest of 11000 rows, k 10 1386 KB of slots, k 100 1034)
-    const size_t need = make_plan(ix, nq, nprobe, k).total;
-    return k > kShortSegK ? std::max(need, make_plan(ix, nq, nprobe, kShortSegK).total) : need;
+    // (one request over 16 of 256 lists, the longest of 11000 rows, k 10 1386 KB of slots, k 100 1034), or wider tiles (1024 queries
+    // over 32 of 1024 float32 lists of up to 20000 rows, k 12 297 MB, k 13 237).  Between these k the buffers only grow.
+    size_t need = 0;
+    for (const int at : {(int)k, kShortSegK, kFullTileK})
+        if (at <= k) need = std::max(need, make_plan(ix, nq, nprobe, at).total);
+    return need;
 }
 
 }  // extern "C"

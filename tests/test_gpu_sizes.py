@@ -739,3 +739,32 @@ def test_a_long_row_does_not_hide_a_short_one(tables, d, metric):
     assert bool((tie | (found == won)).all())
     assert metric == "l2" or bool(((found == single[0][0]).any() and (found == single[1][0]).any()))
     ix.close()
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.float32, 64), (torch.float32, 1024), (torch.bfloat16, 64)])
+@pytest.mark.parametrize("nlist,N,zipf", [(1024, 300000, 0.8), (300, 30000, 0.0), (4096, 300000, 0.3)])
+def test_workspace_never_says_less_for_more(dtype, d, nlist, N, zipf):
+    """More neighbours, more queries and more probes, also where the tiles of queries change their width; a search of fewer with
+    that workspace is not refused."""
+    hr = _hr()
+    ix, cent, off, vec, ids, g = _index(N, d, nlist, dtype, d, zipf=zipf)
+    size = lambda nq, nprobe, k: hr.hr_ivf_workspace_bytes(ix.handle, nq, nprobe, k)
+    for nq, nprobe in ((1, 16), (100, 33), (1024, 32), (3000, 64)):
+        sizes = [size(nq, nprobe, k) for k in range(1, hr.HR_K_MAX + 1)]
+        assert sizes == sorted(sizes)
+    for k in (10, 13, 20, 30, 100):
+        for nprobe in (1, 16, 128):
+            edge = 96 * nlist // nprobe
+            sizes = [size(nq, nprobe, k) for nq in (edge // 2, edge - 1, edge, edge + 1, edge + 2, edge + edge // 3, 2 * edge)]
+            assert sizes == sorted(sizes)
+        for nq in (500, 96 * nlist // 64):
+            sizes = [size(nq, nprobe, k) for nprobe in (1, 2, 16, 63, 64, 65, 100, 128, 256)]
+            assert sizes == sorted(sizes)
+    q = torch.randn(1024, d, generator=g, device="cuda")
+    ws = torch.empty(size(1024, 32, 20), dtype=torch.uint8, device="cuda")
+    for nq, k in ((1024, 10), (1024, 13), (700, 20)):
+        out = torch.empty(nq, k, dtype=torch.int64, device="cuda"), torch.empty(nq, k, device="cuda")
+        hr.hr_ivf_search(ix.handle, q[:nq], nq, 32, k, hr.HR_METRIC_IP, *out, ws, ws.numel())
+        want = ix.search(q[:nq], 32, k, "ip")
+        assert torch.equal(out[0], want[0]) and torch.equal(out[1], want[1])
+    ix.close()
