@@ -288,7 +288,8 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     // queries over 32 of 512 lists, 48828 rows, 232 -> 204 us, 250 over 16 168 -> 152, 8 over 32 104 -> 96, 700 over 32 of 1024, 97656
     // rows, 246 -> 238, 700 over 16 of 512, k 50, 280 -> 247; shorter rows lose by it (d = 768, 64 over 16 of 512 141 -> 161, bfloat16 of d = 1024 116 -> 127).
     p.base_rows = scan_dtype(ix) == HR_F32 && ix->d >= 1024 ? kMinSegRows / 2 : kMinSegRows;
-    p.min_rows = k <= kShortSegK && ix->d >= 512 ? std::min(((128 << 10) / (ix->d * (ix->dtype == HR_F32 ? 4 : 2)) + 15) & ~15, kMinSegRows) : kMinSegRows;
+    p.min_rows = k <= kShortSegK && ix->d >= 512 ? ((128 << 10) / (ix->d * (ix->dtype == HR_F32 ? 4 : 2)) + 15) & ~15 : kMinSegRows;
+    p.min_rows = std::min(p.min_rows, p.base_rows);          // (what is meant to shorten segments never makes them longer)
     if (p.min_rows < 64) p.min_rows = 64;
     const int64_t in_short = std::min((int64_t)p.cw_s * p.few_items + pairs, pairs * ((ix->longest + p.min_rows - 1) / p.min_rows));
     const int64_t by_length = std::max(pairs * ((ix->longest + p.base_rows - 1) / p.base_rows), in_short);

@@ -768,3 +768,18 @@ def test_workspace_never_says_less_for_more(dtype, d, nlist, N, zipf):
         want = ix.search(q[:nq], 32, k, "ip")
         assert torch.equal(out[0], want[0]) and torch.equal(out[1], want[1])
     ix.close()
+
+
+@pytest.mark.parametrize("nq", [1, 8, 60])
+def test_small_batches_never_go_in_longer_segments(nq):
+    """Float32 rows of d = 1024, many neighbours: the segments of a small batch are no longer than those of a large one."""
+    ix, cent, off, vec, ids, g = _index(48000, 1024, 60, torch.float32, 3)
+    rows = []
+    for n in (nq, 700):
+        q = torch.randn(n, 1024, generator=g, device="cuda")
+        ix.search(q, 8, 30, "ip")
+        torch.cuda.synchronize()
+        ws = ix.workspace(n, 8, 30)
+        rows.append(_hr().hr_ivf_stats(ix.handle, ws, ws.numel(), n, 8, 30)["seg_rows"])
+    assert rows[0] <= rows[1]
+    ix.close()
