@@ -218,7 +218,9 @@ int hr_ivf_split_probes(const hr_ivf_index* index, const int32_t* probe_ids, int
  * row_end-1 in list_vectors (a cluster loaded asynchronously into the place of another one of
  * the same length: the index loading interface of Section 5), recompute what the library
  * derives from them (squared norms; with HR_F32 what bounds the scores of a list's rows, which searches with either
- * metric rely on; the binary16 row tables of HR_LOAD_ROW_TABLES).  Enqueued on
+ * metric rely on; the binary16 row tables of HR_LOAD_ROW_TABLES).  Those bounds start anew for a list whose rows are all in
+ * the range; of a list in part of it they can only become wider, so searches of a list that once held a very long row take
+ * longer until all of it is replaced in one call (the results are the same).  Enqueued on
  * `stream`: put it behind the copy, and the next search behind it.  list_ids is read at search time
  * and needs no refresh; list_offsets cannot change.  Only with a binary16 table of bfloat16 rows the
  * call also waits for the stream, to learn whether a new value exceeds 65504: HR_ERR_UNSUPPORTED

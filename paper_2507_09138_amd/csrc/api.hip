@@ -128,6 +128,7 @@ struct hr_ivf_index {
     int64_t nlist, N;
     int64_t longest;       // rows of the longest list
     int d, dtype;
+    int* h_list_off;       // [nlist+1] int32, on the host
     int* d_list_off;       // [nlist+1] int32
     float* d_row_norm;     // [N]
     float* d_cent_norm;    // [nlist]
@@ -384,7 +385,7 @@ int hr_ivf_load(const float* centroids, const int64_t* list_offsets, const void*
     if (!ix) return fail(HR_ERR_HIP, "out of host memory");
     ix->centroids = centroids; ix->vectors = list_vectors; ix->ids = list_ids;
     ix->nlist = nlist; ix->N = N; ix->d = d; ix->dtype = dtype;
-    int* h_off = new (std::nothrow) int[nlist + 1];
+    int* const h_off = ix->h_list_off = new (std::nothrow) int[nlist + 1];
     if (!h_off) { delete ix; return fail(HR_ERR_HIP, "out of host memory"); }
     for (int64_t l = 0; l <= nlist; l++) h_off[l] = (int)list_offsets[l];
     for (int64_t l = 0; l < nlist; l++) ix->longest = std::max(ix->longest, list_offsets[l + 1] - list_offsets[l]);
@@ -456,8 +457,8 @@ int hr_ivf_load(const float* centroids, const int64_t* list_offsets, const void*
         e = hipHostMalloc((void**)&ix->h_over, 64 * sizeof(int), hipHostMallocMapped | hipHostMallocCoherent);
         if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&ix->d_over, ix->h_over, 0);
     }
-    delete[] h_off;
     if (e != hipSuccess || flags[1]) {
+        delete[] h_off;
         if (ix->d_list_off) (void)hipFree(ix->d_list_off);
         if (ix->d_row_norm) (void)hipFree(ix->d_row_norm);
         if (ix->d_list_bound) (void)hipFree(ix->d_list_bound);
@@ -541,6 +542,7 @@ int hr_ivf_free(hr_ivf_index* ix)
     if (ix->d_vec16) (void)hipFree(ix->d_vec16);
     if (ix->d_flag) (void)hipFree(ix->d_flag);
     if (ix->h_over) (void)hipHostFree(ix->h_over);
+    delete[] ix->h_list_off;
     delete ix;
     return HR_OK;
 }
@@ -1012,10 +1014,13 @@ int hr_ivf_refresh_rows(hr_ivf_index* ix, int64_t row_begin, int64_t row_end, vo
                                             "replace the rows again, or load the index without HR_LOAD_ROW_TABLES");
         return HR_OK;
     }
-    // (bounds only grow: rows that were replaced count on)
-    if (ix->d_list_bound)
+    if (ix->d_list_bound) {
+        // bounds start anew in lists of which every row is replaced; in the others they only grow, as rows that were replaced count on
+        const int *off = ix->h_list_off, *end = off + ix->nlist + 1;
+        const int64_t l0 = std::lower_bound(off, end, (int)row_begin) - off, l1 = std::upper_bound(off, end, (int)row_end) - off - 1;
+        if (l0 < l1) HR_HIP(launch_fill_i32((int*)(ix->d_list_bound + l0), 2 * (l1 - l0), 0, s));
         HR_HIP(launch_list_bounds((const float*)ix->vectors, ix->d, row_begin, n, ix->d_list_off, (int)ix->nlist, ix->d_row_norm, (uint2*)ix->d_list_bound, ix->d_vec_hi, s));
-    else
+    } else
         HR_HIP(launch_row_norms(rows, ix->dtype, n, ix->d, ix->d_row_norm + row_begin, s));
     return HR_OK;
 }

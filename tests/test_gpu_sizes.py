@@ -783,3 +783,50 @@ def test_small_batches_never_go_in_longer_segments(nq):
         rows.append(_hr().hr_ivf_stats(ix.handle, ws, ws.numel(), n, 8, 30)["seg_rows"])
     assert rows[0] <= rows[1]
     ix.close()
+
+
+@pytest.mark.parametrize("tables", [False, True])
+def test_a_replaced_long_row_does_not_slow_its_list_for_good(tables):
+    """Every list once held a row a thousand times as long: once all its rows are replaced, searches take as long as before, and the
+    lists at the edges of a range and the empty ones keep bounds that hold."""
+    d, nlist, N = 128, 64, 64000
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    cent = torch.randn(nlist, d, generator=g, device="cuda")
+    off = torch.linspace(0, N, nlist + 1).long()
+    off[7:10] = off[7]                                  # two lists without rows
+    good = torch.randn(N, d, generator=g, device="cuda")
+    vec = good.clone()
+    ix = _hr().IvfIndex(cent, off, vec, torch.arange(N, device="cuda"), row_tables=tables)
+    q = torch.randn(512, d, generator=g, device="cuda")
+
+    def took():
+        spans = []
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                out = ix.search(q, 32, 10, "ip")
+            b.record()
+            b.synchronize()
+            spans.append(a.elapsed_time(b))
+        return min(spans), out
+
+    before, want = took()
+    vec[::500] *= 1000
+    ix.refresh_rows(0, N)
+    took()
+    vec.copy_(good)
+    ix.refresh_rows(0, N)
+    after, got = took()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    assert after < 2 * before
+    # parts of lists at both ends of the range, each of which has held longer rows
+    for a, b in ((int(off[3]) + 5, int(off[11]) - 5), (int(off[6]), int(off[10])), (int(off[7]), int(off[7]) + 1)):
+        vec[a:b] = 30 * torch.randn(b - a, d, generator=g, device="cuda")
+        ix.refresh_rows(a, b)
+        found, score = ix.search(q, 64, 20, "ip")
+        best = torch.topk(q.double() @ vec.double().T, 20, dim=1).values
+        # |q||x| below 16 * 16 * 30 * 1.4, a few 2^-24 of it
+        assert float((score.double() - best).abs().max()) <= 11000 * 2.0 ** -24 * 16
+    ix.close()
