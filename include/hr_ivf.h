@@ -68,10 +68,15 @@ enum {
  * centroids, list_vectors and list_ids are BORROWED: they must stay valid and unchanged until
  * hr_ivf_free.  The library allocates (hipMalloc) derived tables: device copies of the offsets,
  * 4 bytes per row / per centroid of squared norms, the centroids as two binary16 tables, 8 bytes
- * per list of access counters (HR_F32: 8 more of bounds).  Nothing the size of list_vectors, unless the caller asks for it:
+ * per list of access counters (HR_F32: 20 more of bounds).  Nothing the size of list_vectors, unless the caller asks for it:
  * with dtype = HR_F32 | HR_LOAD_ROW_TABLES the rows are also kept rounded to binary16 (N*d*2 bytes, half of
  * list_vectors) for the scan to read, which looks for candidates with the rounded rows either way and scores those that
- * may be among the best from the float32 rows: the same results, faster.
+ * may be among the best from the float32 rows: the same results, faster.  Where rows are so close to each other, or so long
+ * against the distances between them, that rounded rows tell little (a common offset that squared distances cancel, near
+ * duplicates, one row a hundred times as long as the others of its list), the scan looks for candidates with about 22 bits of
+ * every element instead, with either flag from the float32 rows: the same results again, in about 1.25 times the time of rounded
+ * rows on rows that are apart (1.5 of those with the table).  That is decided for the index at load and, for good, by
+ * hr_ivf_refresh_rows.
  * With HR_BF16 | HR_LOAD_ROW_TABLES the rows are also kept as one binary16 table (N*d*2 bytes; every
  * bfloat16 value of magnitude 2^-14 .. 65504 is a binary16 value, smaller ones are rounded to a
  * multiple of 2^-24): the lists are then multiplied with the query rounded to binary16 (as HR_F16
@@ -127,7 +132,8 @@ int hr_ivf_search(const hr_ivf_index* index, const float* queries, int64_t nq, i
  * as hr_ivf_search's.  A batch shape that needs more scratch is refused with HR_ERR_WORKSPACE and
  * a message that gives the bytes needed (what fits: e.g. 512 queries x nprobe 32, k 10 on 4096
  * lists of 768 dimensions takes about 31 MiB; the bulk are the 128 x 256 + nq x nprobe result
- * slots of 512 bytes each for k <= 24, 1024 up to k = 64, 1536 beyond).
+ * slots of 512 bytes each for k <= 24, 1024 up to k = 64, 1536 beyond; for HR_F32 512 bytes for k <= 12, 768 up to k = 24, 1024 up to
+ * k = 36, 1536 up to k = 64, 2048 beyond, shortened where that makes a shape fit).
  * All calls on one GPU share that GPU's array: two calls that overlap in time (different
  * streams, or threads) race; put them on one stream or give one of them hr_ivf_search with a
  * workspace of its own.  The array keeps what the last call left; every call clears what it
@@ -219,8 +225,8 @@ int hr_ivf_split_probes(const hr_ivf_index* index, const int32_t* probe_ids, int
  * the same length: the index loading interface of Section 5), recompute what the library
  * derives from them (squared norms; with HR_F32 what bounds the scores of a list's rows, which searches with either
  * metric rely on; the binary16 row tables of HR_LOAD_ROW_TABLES).  Those bounds start anew for a list whose rows are all in
- * the range; of a list in part of it they can only become wider, so searches of a list that once held a very long row take
- * longer until all of it is replaced in one call (the results are the same).  Enqueued on
+ * the range; of a list in part of it, or by a captured call, they can only become wider, so searches of a list that once held a
+ * very long row may take longer until all of it is replaced in one call (the results are the same).  Enqueued on
  * `stream`: put it behind the copy, and the next search behind it.  list_ids is read at search time
  * and needs no refresh; list_offsets cannot change.  Only with a binary16 table of bfloat16 rows the
  * call also waits for the stream, to learn whether a new value exceeds 65504: HR_ERR_UNSUPPORTED

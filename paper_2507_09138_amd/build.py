@@ -15,7 +15,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libhr_ivf.so")
-SOURCES = ["api.hip", "aux_kernels.hip", "scan_f16.hip", "scan_bf16.hip", "scan_f32.hip"]
+SOURCES = ["api.hip", "aux_kernels.hip", "scan_f16.hip", "scan_bf16.hip", "scan_f32.hip", "scan_f32x2.hip"]
 HEADERS = [os.path.join(CSRC, h) for h in ("common.h", "wave.h", "group.h", "scan_kernel.h")] + [os.path.join(ROOT, "include", "hr_ivf.h")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

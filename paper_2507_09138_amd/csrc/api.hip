@@ -48,6 +48,7 @@ hipError_t launch_scan_f16(int d, const ScanArgs& a, int grid, size_t lds, hipSt
 hipError_t launch_scan_bf16(int d, const ScanArgs& a, int grid, size_t lds, hipStream_t s);
 hipError_t launch_scan_f16x2(int d, const ScanArgs& a, int grid, size_t lds, hipStream_t s);
 hipError_t launch_scan_f16hi(int d, const ScanArgs& a, int grid, size_t lds, hipStream_t s);
+hipError_t launch_scan_f32x2(int d, const ScanArgs& a, int grid, size_t lds, hipStream_t s);
 
 hipError_t launch_seed_f32(int d, const SeedArgs& a, const BucketArgs* group, hipStream_t s);
 hipError_t launch_seed_f16(int d, const SeedArgs& a, const BucketArgs* group, hipStream_t s);
@@ -71,6 +72,7 @@ hipError_t launch_scan(int dtype, int d, const ScanArgs& a, int grid, size_t lds
     case HR_BF16: return launch_scan_bf16(d, a, grid, lds, s);
     case HR_F16X2: return launch_scan_f16x2(d, a, grid, lds, s);
     case HR_F16HI: return launch_scan_f16hi(d, a, grid, lds, s);
+    case HR_F32X2: return launch_scan_f32x2(d, a, grid, lds, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -80,7 +82,7 @@ hipError_t launch_scan(int dtype, int d, const ScanArgs& a, int grid, size_t lds
 size_t scan_lds_bytes(int dtype, int d, int nbuf)
 {
     const size_t rows = block_rows(dtype, d), threads = kScanWaves * 64;
-    const size_t chunks = rows * d * (dtype == HR_F32 ? 4 : 2) / 16;
+    const size_t chunks = rows * d * (stored_f32(dtype) ? 4 : 2) / 16;
     const size_t buf = (chunks + threads - 1) / threads * threads * 16 * (dtype == HR_F16X2 ? 2 : 1);
     return nbuf * (buf + rows * sizeof(float)) + 32;
 }
@@ -136,12 +138,16 @@ struct hr_ivf_index {
     void* d_cent_lo;       // [nlist, d] binary16: (centroid - hi) * 2^11
     void* d_vec_hi;        // float32 lists only, when asked for and memory allows: [N, d] the rows rounded to binary16; else null
     void* d_vec16;         // bfloat16 lists only, when memory and the value range allow: [N, d] the rows as binary16
-    int* d_flag;           // two device ints: [0] a bfloat16 value did not fit binary16, [1] a negative label
+    int* d_flag;           // device ints: [0] a bfloat16 value did not fit binary16, [1] a negative label, [2] [3] rows of lists with wide windows, by metric
     // with d_vec16: report words of hr_ivf_refresh_rows, one for each call under way (host memory that kernels write; bit i of
     // over_used: word i belongs to a call), else null
     int *h_over, *d_over;  // their address on the host and on the device
     std::atomic<uint64_t> over_used;
-    float2* d_list_bound;  // float32 lists: [nlist] what scan_slack needs to know of the list's rows, else null
+    ListBound* d_list_bound;      // float32 lists: [nlist] what scan_slack needs to know of the list's rows, else null
+    std::atomic<uint64_t> replaced;   // float32 lists: refreshes so far (ListArgs::count)
+    float* d_spread;       // float32 lists: [nlist] how far their rows lie apart (list_spread), else null
+    // float32 lists: host memory that kernels write, its address there and on the device: [metric] some list's bounds tell little
+    int *h_tight, *d_tight;
     unsigned long long* d_hits;   // [nlist] probes per list since load / last reset
     int* d_resident;       // [nlist] 1 = the list's vectors are in place (all lists, until the caller says otherwise)
     int num_cus;
@@ -153,10 +159,17 @@ struct hr_ivf_index {
     int prof_cap, prof_n;
 };
 
+// Float32 lists: are both parts of the rows multiplied?  Scores and their order are the same either way, so what a refresh has written
+// here or not yet decides nothing but the time.
+static bool both_parts(const hr_ivf_index* ix, int metric) { return ix->h_tight && ((volatile const int*)ix->h_tight)[metric == HR_METRIC_L2] != 0; }
 // storage type the list scan runs on
-static int scan_dtype(const hr_ivf_index* ix) { return ix->d_vec_hi ? (int)HR_F16HI : (ix->d_vec16 ? (int)HR_F16 : ix->dtype); }
+static int scan_dtype(const hr_ivf_index* ix, bool both)
+{
+    if (ix->dtype == HR_F32) return both ? (int)HR_F32X2 : (ix->d_vec_hi ? (int)HR_F16HI : (int)HR_F32);
+    return ix->d_vec16 ? (int)HR_F16 : ix->dtype;
+}
 // form of the query operand the list scan multiplies (what k_prep_queries is asked for)
-static int operand_dtype(const hr_ivf_index* ix) { const int s = scan_dtype(ix); return s == HR_F16HI ? (int)HR_F32 : s; }
+static int operand_dtype(const hr_ivf_index* ix) { return ix->d_vec16 ? (int)HR_F16 : ix->dtype; }
 // rows and their type for the kernels that read single rows (threshold seeding, rescoring)
 static int row_dtype(const hr_ivf_index* ix) { return ix->d_vec16 ? (int)HR_F16 : ix->dtype; }
 static const void* row_table(const hr_ivf_index* ix) { return ix->d_vec16 ? ix->d_vec16 : ix->vectors; }
@@ -173,7 +186,7 @@ struct Plan {
     // coarse step: centroid table scanned with all queries as one dense bucket
     int nbuf_c, cw_c, cols_c, nqt_c, seg_c, nseg_c;
     // list scan
-    int groups_s, nbuf_s, cap_s, cw_s, item_cap, item_target, few_items, min_rows, base_rows;
+    int dtype_s, groups_s, nbuf_s, cap_s, cw_s, item_cap, item_target, few_items, min_rows, base_rows;
     int slot_cap;                   // result slots: one per (list segment, query of the list's bucket)
     size_t o_zero, n_zero;          // ints cleared per call: list_w[nlist], dyn[DYN_COUNT], counters[8], ..., then
     size_t zoff_round, zoff_hist, zoff_hpar;   // (in ints from o_zero) round counters of the queues, per-query key histograms and their parameters
@@ -202,7 +215,8 @@ static constexpr PlanLimits kDefaultLimits = {kItemTarget, (size_t)512 << 20, tr
 static constexpr int kShortSegK = 24;          // most neighbours of a search that may go in segments shorter than kMinSegRows
 static constexpr int kFullTileK = 12;          // most neighbours of float32 rows that always go in full tiles of queries
 
-static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, const PlanLimits& lim = kDefaultLimits)
+// both: float32 lists, multiply both parts (see both_parts); the layout of a workspace is the same either way.
+static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, bool both, const PlanLimits& lim = kDefaultLimits)
 {
     Plan p{};
     const int64_t nlist = ix->nlist;
@@ -219,9 +233,9 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     const int64_t pairs = nq * nprobe;
     const bool full_tiles = k <= 24 && pairs >= 128 * nlist &&
                             (double)(ix->N / kMinSegRows + nlist) * (double)pairs >= 1024.0 * 128.0 * (double)nlist;
-    p.groups_s = full_tiles ? groups_per_cu(scan_dtype(ix), ix->d) : 1;
-    p.nbuf_s = pick_buffers(scan_dtype(ix), ix->d, p.groups_s);
-    p.cap_s = lim.cap > 0 ? lim.cap : sel_cap(scan_dtype(ix), k);
+    p.dtype_s = scan_dtype(ix, both);
+    p.groups_s = full_tiles ? groups_per_cu(p.dtype_s, ix->d) : 1;
+    p.nbuf_s = pick_buffers(p.dtype_s, ix->d, p.groups_s);
     p.nbuf_c = scan_lds_bytes(HR_F16X2, ix->d, 3) <= (size_t)kLdsLimit ? 3 : 2;
     // queries per coarse chunk: the [chunk, nlist] key table stays within its limit, 512 MiB by default (the more
     // queries per launch the better both kernels fill the device: 16384 lists, four chunks of 2048 queries 1.88 ms,
@@ -263,39 +277,51 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     const int64_t seg = per_item * kMfmaRows;
     p.seg_c = (int)seg;
     p.nseg_c = (int)((nlist + seg - 1) / seg);
-    p.cw_s = tile_cols(scan_dtype(ix), ix->d);
-    // Many neighbours and few queries per list, float32 rows: what a wave does is select, so it has eight queries instead of 16.  Tiles
-    // of 128 and 64: 700 queries over 16 of 512 lists, k 50, d = 768 277 and 245 us, d = 64 322 and 295, 3000 queries, k 100, 594
-    // and 549, 607 and 614; 662 over 6 of 1703, k 23, 268 and 226; over 16 of 256 lists (187 queries per list) 671 and 817, 801 and 1089.
-    const int narrow = scan_dtype(ix) == HR_F32 && k > kFullTileK ? p.cw_s / 2 : p.cw_s;
-    if (pairs <= 96 * nlist) p.cw_s = narrow;
-    // Work items: sum over probed lists of segments x query tiles.  Segments have at least C / item_target rows, C =
-    // sum of rows x tiles, so there are at most item_target items plus one per (list, tile) for the ragged ends.
-    // Result slots: sum of segments x bucket width <= cw x item_target, plus one per pair for the ragged ends.  (In a
-    // workspace items are bounded for the narrower tiles that fewer queries would go in: the plan of a larger batch is never the smaller.)
-    p.item_target = lim.item_target;
-    p.item_cap = (int)(lim.item_target + pairs / (lim.by_length ? narrow : p.cw_s) + (pairs < nlist ? pairs : nlist) + 8);
-    int64_t slots_most = (int64_t)p.cw_s * lim.item_target + pairs;
-    // Nor has a pair more slots than the longest list has segments, whatever the batch (one query over 16 of 256 lists of
-    // 65536 rows in all, k 10: 268 MB of slots without this bound, 1.3 with it).  Segments shorter than kMinSegRows are of
-    // min_rows rows at least, and there are at most few_items of those, and one per pair for the ragged ends.
-    // Shorter ones pay where an item takes longer to read than to start and to merge: blocks of 128 KB, vectors of 512 and more,
-    // few candidates per segment.  One request, nprobe 16, k 10: 256 lists of 256 float32 rows of d = 768 92 -> 74 us, bfloat16 of
-    // d = 1024 63 -> 55, over 2000 lists of 300 rows 67 -> 59; but 256 binary16 rows of d = 256, four requests, 54 -> 61, and k 100,
-    // 50 lists, d = 1024, 112 -> 132; and with a second round of items (segments of rows x tiles / 256 without regard to the
-    // ragged ends) 16 requests over 16 of 256 lists, d = 64, 68 -> 97.
-    p.few_items = std::min(ix->num_cus, lim.item_target);
-    // Float32 rows of d = 1024 as they are (blocks of 64 KB, two in LDS, so an item moves 30 GB/s at most): half as long.  700
-    // queries over 32 of 512 lists, 48828 rows, 232 -> 204 us, 250 over 16 168 -> 152, 8 over 32 104 -> 96, 700 over 32 of 1024, 97656
-    // rows, 246 -> 238, 700 over 16 of 512, k 50, 280 -> 247; shorter rows lose by it (d = 768, 64 over 16 of 512 141 -> 161, bfloat16 of d = 1024 116 -> 127).
-    p.base_rows = scan_dtype(ix) == HR_F32 && ix->d >= 1024 ? kMinSegRows / 2 : kMinSegRows;
-    p.min_rows = k <= kShortSegK && ix->d >= 512 ? ((128 << 10) / (ix->d * (ix->dtype == HR_F32 ? 4 : 2)) + 15) & ~15 : kMinSegRows;
-    p.min_rows = std::min(p.min_rows, p.base_rows);          // (what is meant to shorten segments never makes them longer)
-    if (p.min_rows < 64) p.min_rows = 64;
-    const int64_t in_short = std::min((int64_t)p.cw_s * p.few_items + pairs, pairs * ((ix->longest + p.min_rows - 1) / p.min_rows));
-    const int64_t by_length = std::max(pairs * ((ix->longest + p.base_rows - 1) / p.base_rows), in_short);
-    if (lim.by_length && by_length < slots_most) slots_most = by_length;
-    p.slot_cap = (int)slots_most;
+    auto sizes = [&](int dtype) {
+        p.cap_s = lim.cap > 0 ? lim.cap : sel_cap(dtype, k);
+        p.cw_s = tile_cols(dtype, ix->d);
+        // Many neighbours and few queries per list, float32 rows: what a wave does is select, so it has eight queries instead of 16.  Tiles
+        // of 128 and 64: 700 queries over 16 of 512 lists, k 50, d = 768 277 and 245 us, d = 64 322 and 295, 3000 queries, k 100, 594
+        // and 549, 607 and 614; 662 over 6 of 1703, k 23, 268 and 226; over 16 of 256 lists (187 queries per list) 671 and 817, 801 and 1089.
+        const int narrow = dtype == HR_F32 && k > kFullTileK ? p.cw_s / 2 : p.cw_s;
+        if (pairs <= 96 * nlist) p.cw_s = narrow;
+        // Work items: sum over probed lists of segments x query tiles.  Segments have at least C / item_target rows, C =
+        // sum of rows x tiles, so there are at most item_target items plus one per (list, tile) for the ragged ends.
+        // Result slots: sum of segments x bucket width <= cw x item_target, plus one per pair for the ragged ends.  (In a
+        // workspace items are bounded for the narrower tiles that fewer queries would go in: the plan of a larger batch is never the smaller.)
+        p.item_target = lim.item_target;
+        p.item_cap = (int)(lim.item_target + pairs / (lim.by_length ? narrow : p.cw_s) + (pairs < nlist ? pairs : nlist) + 8);
+        int64_t slots_most = (int64_t)p.cw_s * lim.item_target + pairs;
+        // Nor has a pair more slots than the longest list has segments, whatever the batch (one query over 16 of 256 lists of
+        // 65536 rows in all, k 10: 268 MB of slots without this bound, 1.3 with it).  Segments shorter than kMinSegRows are of
+        // min_rows rows at least, and there are at most few_items of those, and one per pair for the ragged ends.
+        // Shorter ones pay where an item takes longer to read than to start and to merge: blocks of 128 KB, vectors of 512 and more,
+        // few candidates per segment.  One request, nprobe 16, k 10: 256 lists of 256 float32 rows of d = 768 92 -> 74 us, bfloat16 of
+        // d = 1024 63 -> 55, over 2000 lists of 300 rows 67 -> 59; but 256 binary16 rows of d = 256, four requests, 54 -> 61, and k 100,
+        // 50 lists, d = 1024, 112 -> 132; and with a second round of items (segments of rows x tiles / 256 without regard to the
+        // ragged ends) 16 requests over 16 of 256 lists, d = 64, 68 -> 97.
+        p.few_items = std::min(ix->num_cus, lim.item_target);
+        // Float32 rows of d = 1024 as they are (blocks of 64 KB, two in LDS, so an item moves 30 GB/s at most): half as long.  700
+        // queries over 32 of 512 lists, 48828 rows, 232 -> 204 us, 250 over 16 168 -> 152, 8 over 32 104 -> 96, 700 over 32 of 1024, 97656
+        // rows, 246 -> 238, 700 over 16 of 512, k 50, 280 -> 247; shorter rows lose by it (d = 768, 64 over 16 of 512 141 -> 161, bfloat16 of d = 1024 116 -> 127).
+        p.base_rows = stored_f32(dtype) && ix->d >= 1024 ? kMinSegRows / 2 : kMinSegRows;
+        p.min_rows = k <= kShortSegK && ix->d >= 512 ? ((128 << 10) / (ix->d * (ix->dtype == HR_F32 ? 4 : 2)) + 15) & ~15 : kMinSegRows;
+        p.min_rows = std::min(p.min_rows, p.base_rows);          // (what is meant to shorten segments never makes them longer)
+        if (p.min_rows < 64) p.min_rows = 64;
+        const int64_t in_short = std::min((int64_t)p.cw_s * p.few_items + pairs, pairs * ((ix->longest + p.min_rows - 1) / p.min_rows));
+        const int64_t by_length = std::max(pairs * ((ix->longest + p.base_rows - 1) / p.base_rows), in_short);
+        if (lim.by_length && by_length < slots_most) slots_most = by_length;
+        p.slot_cap = (int)slots_most;
+    };
+    size_t most_items = 0, most_slots = 0, most_entries = 0;
+    auto room = [&](int dtype) {
+        sizes(dtype);
+        most_items = std::max(most_items, (size_t)p.item_cap);
+        most_slots = std::max(most_slots, (size_t)p.slot_cap);
+        most_entries = std::max(most_entries, (size_t)p.slot_cap * p.cap_s);
+    };
+    if (ix->dtype == HR_F32 && lim.by_length) room(scan_dtype(ix, !both));
+    room(p.dtype_s);
 
     size_t o = 0;
     auto take = [&](size_t bytes) {
@@ -320,11 +346,10 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, con
     p.o_bucket_off = take((size_t)(nlist + 1) * 4);
     p.o_bucket_q = take((size_t)pairs * 4);
     p.o_slot_base = take((size_t)(nlist + 1) * 4);
-    p.o_xq = take((size_t)p.item_cap * 8 * 2 * sizeof(int4));
+    p.o_xq = take(most_items * 8 * 2 * sizeof(int4));
     p.o_ckeys = take((size_t)p.cchunk * nlist * 4);
-    const size_t slots = (size_t)p.slot_cap;
-    p.o_slot_cnt = take(slots * 4);
-    p.o_slot_ent = take(slots * (size_t)p.cap_s * sizeof(Cand));
+    p.o_slot_cnt = take(most_slots * 4);
+    p.o_slot_ent = take(most_entries * sizeof(Cand));
     p.total = o;
     return p;
 }
@@ -404,16 +429,22 @@ int hr_ivf_load(const float* centroids, const int64_t* list_offsets, const void*
     }
     if (e == hipSuccess) e = hipMalloc(&ix->d_list_off, (size_t)(nlist + 1) * 4);
     if (e == hipSuccess) e = hipMalloc(&ix->d_row_norm, (size_t)(N > 0 ? N : 1) * 4);
-    if (e == hipSuccess && dtype == HR_F32) e = hipMalloc(&ix->d_list_bound, (size_t)nlist * sizeof(float2));
+    if (e == hipSuccess && dtype == HR_F32) e = hipMalloc(&ix->d_list_bound, (size_t)nlist * sizeof(ListBound));
+    if (e == hipSuccess && dtype == HR_F32) e = hipMalloc(&ix->d_spread, (size_t)nlist * sizeof(float));
+    if (e == hipSuccess && dtype == HR_F32) e = hipHostMalloc((void**)&ix->h_tight, 2 * sizeof(int), hipHostMallocMapped | hipHostMallocCoherent);
+    if (e == hipSuccess && dtype == HR_F32) {
+        ix->h_tight[0] = ix->h_tight[1] = 0;
+        e = hipHostGetDevicePointer((void**)&ix->d_tight, ix->h_tight, 0);
+    }
     if (e == hipSuccess) e = hipMalloc(&ix->d_cent_norm, (size_t)nlist * 4);
     if (e == hipSuccess) e = hipMalloc(&ix->d_cent_hi, (size_t)nlist * d * 2);
     if (e == hipSuccess) e = hipMalloc(&ix->d_cent_lo, (size_t)nlist * d * 2);
     if (e == hipSuccess) e = hipMalloc(&ix->d_hits, (size_t)nlist * 8);
-    if (e == hipSuccess) e = hipMalloc(&ix->d_flag, 2 * sizeof(int));
+    if (e == hipSuccess) e = hipMalloc(&ix->d_flag, 4 * sizeof(int));
     if (e == hipSuccess) e = hipMalloc(&ix->d_resident, (size_t)nlist * sizeof(int));
     if (e == hipSuccess) e = launch_set_resident(ix->d_resident, (int)nlist, nullptr, nlist, 1, s);
     if (e == hipSuccess) e = hipMemsetAsync(ix->d_hits, 0, (size_t)nlist * 8, s);
-    if (e == hipSuccess) e = hipMemsetAsync(ix->d_flag, 0, 2 * sizeof(int), s);
+    if (e == hipSuccess) e = hipMemsetAsync(ix->d_flag, 0, 4 * sizeof(int), s);
     if (e == hipSuccess) e = launch_check_labels(list_ids, N, ix->d_flag + 1, s);
     if (e == hipSuccess) e = hipMemcpyAsync(ix->d_list_off, h_off, (size_t)(nlist + 1) * 4, hipMemcpyHostToDevice, s);
     if (e == hipSuccess && dtype == HR_F32) {
@@ -426,8 +457,12 @@ int hr_ivf_load(const float* centroids, const int64_t* list_offsets, const void*
             if (hipMalloc(&ix->d_vec_hi, bytes) != hipSuccess) ix->d_vec_hi = nullptr;
             if (!ix->d_vec_hi) (void)hipGetLastError();          // (not an error of the load: the other path is taken)
         }
-        e = hipMemsetAsync(ix->d_list_bound, 0, (size_t)nlist * sizeof(float2), s);
-        if (e == hipSuccess) e = launch_list_bounds((const float*)list_vectors, d, 0, N, ix->d_list_off, (int)nlist, ix->d_row_norm, (uint2*)ix->d_list_bound, ix->d_vec_hi, s);
+        const ListArgs a{(const float*)list_vectors, 0, N, ix->d_list_off, (int)nlist, d, 0, (int)nlist, ix->d_row_norm, ix->d_list_bound,
+                         ix->d_vec_hi, ix->d_spread, ix->d_tight, 0, 0, 0};
+        e = hipMemsetAsync(ix->d_list_bound, 0, (size_t)nlist * sizeof(ListBound), s);
+        if (e == hipSuccess) e = hipMemsetAsync(ix->d_spread, 0x7f, (size_t)nlist * sizeof(float), s);      // (far apart, until they are known)
+        if (e == hipSuccess) e = launch_list_bounds(a, s);
+        if (e == hipSuccess && N > 0) e = launch_wide_windows(a, ix->d_flag + 2, s);
     } else if (e == hipSuccess) {
         e = launch_row_norms(list_vectors, dtype, N, d, ix->d_row_norm, s);
     }
@@ -447,8 +482,10 @@ int hr_ivf_load(const float* centroids, const int64_t* list_offsets, const void*
         }
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    int flags[2] = {0, 0};                      // [0] a bfloat16 value beyond binary16, [1] a negative label
+    int flags[4] = {0, 0, 0, 0};                // (as in d_flag)
     if (e == hipSuccess) e = hipMemcpy(flags, ix->d_flag, sizeof flags, hipMemcpyDeviceToHost);
+    for (int m = 0; m < 2 && e == hipSuccess && dtype == HR_F32; m++)
+        if ((int64_t)flags[2 + m] * kWindowShare > N) ix->h_tight[m] = 1;
     if (e == hipSuccess && ix->d_vec16 && flags[0]) {      // the lists are scanned as bfloat16
         (void)hipFree(ix->d_vec16);
         ix->d_vec16 = nullptr;
@@ -462,6 +499,8 @@ int hr_ivf_load(const float* centroids, const int64_t* list_offsets, const void*
         if (ix->d_list_off) (void)hipFree(ix->d_list_off);
         if (ix->d_row_norm) (void)hipFree(ix->d_row_norm);
         if (ix->d_list_bound) (void)hipFree(ix->d_list_bound);
+        if (ix->d_spread) (void)hipFree(ix->d_spread);
+        if (ix->h_tight) (void)hipHostFree(ix->h_tight);
         if (ix->d_cent_norm) (void)hipFree(ix->d_cent_norm);
         if (ix->d_cent_hi) (void)hipFree(ix->d_cent_hi);
         if (ix->d_cent_lo) (void)hipFree(ix->d_cent_lo);
@@ -533,6 +572,8 @@ int hr_ivf_free(hr_ivf_index* ix)
     (void)hipFree(ix->d_list_off);
     (void)hipFree(ix->d_row_norm);
     if (ix->d_list_bound) (void)hipFree(ix->d_list_bound);
+    if (ix->d_spread) (void)hipFree(ix->d_spread);
+    if (ix->h_tight) (void)hipHostFree(ix->h_tight);
     (void)hipFree(ix->d_cent_norm);
     (void)hipFree(ix->d_cent_hi);
     (void)hipFree(ix->d_cent_lo);
@@ -558,7 +599,7 @@ size_t hr_ivf_workspace_bytes(const hr_ivf_index* ix, int64_t nq, int32_t nprobe
     // over 32 of 1024 float32 lists of up to 20000 rows, k 12 297 MB, k 13 237).  Between these k the buffers only grow.
     size_t need = 0;
     for (const int at : {(int)k, kShortSegK, kFullTileK})
-        if (at <= k) need = std::max(need, make_plan(ix, nq, nprobe, at).total);
+        if (at <= k) need = std::max(need, make_plan(ix, nq, nprobe, at, false).total);
     return need;
 }
 
@@ -585,7 +626,7 @@ static PrepArgs prep_args(const hr_ivf_index* ix, const Plan& p, char* ws, const
     a.qop_scan = (scan && !f32) ? ws + p.o_qop_s : nullptr;
     a.qnorm_scan = scan ? (float*)(ws + p.o_qnorm_s) : nullptr;
     a.zero = (int*)(ws + p.o_zero); a.n_zero = (int64_t)p.n_zero;
-    a.qlo = scan && scan_bounded(scan_dtype(ix)) ? (float*)(ws + p.o_thr) : nullptr;
+    a.qlo = scan && scan_bounded(p.dtype_s) ? (float*)(ws + p.o_thr) : nullptr;
     a.neg = (int*)(ws + p.o_thr) + nq; a.n_neg = nq; a.neg_value = (int)kKeyNegInf;
     return a;
 }
@@ -647,12 +688,12 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, const f
                         int nprobe, int k, int metric, int64_t* out_ids, float* out_scores, hipStream_t s,
                         bool carried = false, int32_t* io_rows = nullptr)
 {
-    const size_t lds = scan_lds_bytes(scan_dtype(ix), ix->d, p.nbuf_s);
+    const size_t lds = scan_lds_bytes(p.dtype_s, ix->d, p.nbuf_s);
     int* zero = (int*)(ws + p.o_zero);
     BucketArgs b{};
     b.probe = probe; b.nq = (int)nq; b.nprobe = nprobe; b.nlist = (int)ix->nlist; b.cw = p.cw_s;
     b.cw_log2 = __builtin_ctz((unsigned)p.cw_s);
-    b.half_tiles = ix->d_vec_hi != nullptr || scan_dtype(ix) == HR_F32 || operand_parts(scan_dtype(ix), ix->d) == 2;
+    b.half_tiles = scan_bounded(p.dtype_s) || operand_parts(p.dtype_s, ix->d) == 2;
     b.list_off = ix->d_list_off;
     b.list_w = zero;
     b.hits = ix->d_hits;
@@ -694,7 +735,7 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, const f
     if (together && !whole) HR_HIP(launch_bucketing_behind(b, s));
 
     ScanArgs a{};
-    a.rows = ix->d_vec_hi ? ix->d_vec_hi : row_table(ix);
+    a.rows = p.dtype_s == HR_F16HI ? ix->d_vec_hi : row_table(ix);
     a.row_norm = ix->d_row_norm;
     a.row_ids = ix->ids;
     a.qop = ws + p.o_qop_s;
@@ -720,7 +761,7 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, const f
     hr_ivf_index* mix = const_cast<hr_ivf_index*>(ix);
     const bool timed = mix->prof_ev && mix->prof_n < mix->prof_cap;
     if (timed) HR_HIP(hipEventRecord(mix->prof_ev[2 * mix->prof_n], s));
-    HR_HIP(launch_scan(scan_dtype(ix), ix->d, a, scan_grid(ix, lds, p.groups_s), lds, s));
+    HR_HIP(launch_scan(p.dtype_s, ix->d, a, scan_grid(ix, lds, p.groups_s), lds, s));
     if (timed) {
         HR_HIP(hipEventRecord(mix->prof_ev[2 * mix->prof_n + 1], s));
         mix->prof_n++;
@@ -737,9 +778,10 @@ static int enqueue_scan(const hr_ivf_index* ix, const Plan& p, char* ws, const f
     m.out_ids = out_ids; m.out_scores = out_scores;
     m.carried = carried ? 1 : 0;
     m.io_rows = io_rows;
-    if (scan_bounded(scan_dtype(ix))) {
+    if (scan_bounded(p.dtype_s)) {
         m.rows_f32 = a.rows_f32;
         m.queries = queries; m.row_norm = ix->d_row_norm; m.qlo = a.qlo; m.list_bound = ix->d_list_bound; m.d = ix->d;
+        m.split = scan_split(p.dtype_s);
     }
     HR_HIP(launch_merge(m, s));
     return HR_OK;
@@ -755,7 +797,7 @@ int hr_ivf_search(const hr_ivf_index* ix, const float* queries, int64_t nq, int3
     if (int rc = check_batch(ix, nq, nprobe, k, metric, true)) return rc;
     if (nq == 0) return HR_OK;
     if (!queries || !out_ids || !out_scores) return fail(HR_ERR_ARG, "queries / out_ids / out_scores is null");
-    const Plan p = make_plan(ix, nq, nprobe, k);
+    const Plan p = make_plan(ix, nq, nprobe, k, both_parts(ix, metric));
     if (int rc = check_ws(p, workspace, workspace_bytes)) return rc;
     char* ws = (char*)workspace;
     hipStream_t s = (hipStream_t)stream;
@@ -774,20 +816,20 @@ static constexpr PlanLimits kStaticLimits[] = {{256, (size_t)4 << 20, false, 0},
 // compute units idle, so as long as they can the 256 items stay and the selection buffers, which lie in the slots,
 // become shorter instead: 256 queries over 48 of 64 lists, k 100, half a million bfloat16 rows of d = 768, tiles of 64 queries
 // 1282 us a call, of 128 with 128 items 1537, with 256 and buffers of 184 entries instead of 192 1177.
-static Plan static_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k)
+static Plan static_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, bool both)
 {
     const size_t most = HR_STATIC_SCRATCH_BYTES;
-    const Plan p = make_plan(ix, nq, nprobe, k, kStaticLimits[0]);
-    if (p.total <= most || (scan_dtype(ix) == HR_F16)) return p;
+    const Plan p = make_plan(ix, nq, nprobe, k, both, kStaticLimits[0]);
+    if (p.total <= most || p.dtype_s == HR_F16) return p;
     Plan s = p;
     for (const PlanLimits& lim : kStaticLimits) {
-        s = make_plan(ix, nq, nprobe, k, lim);
+        s = make_plan(ix, nq, nprobe, k, both, lim);
         if (s.total <= most) return s;
         const size_t column = (size_t)s.slot_cap * sizeof(Cand);                 // one entry of every slot
         PlanLimits shorter = lim;
         shorter.cap = (s.cap_s - (int)((s.total - most + column - 1) / column)) & ~3;
         if (shorter.cap < k + kAppendMax + kRoomAfterCut) continue;
-        s = make_plan(ix, nq, nprobe, k, shorter);
+        s = make_plan(ix, nq, nprobe, k, both, shorter);
         if (s.total <= most) return s;
     }
     return s;
@@ -803,7 +845,8 @@ int hr_ivf_search_static(const hr_ivf_index* ix, const float* queries, int64_t n
     int dev = -1;
     HR_HIP(hipGetDevice(&dev));
     if (dev != ix->device) return fail(HR_ERR_ARG, "current device is %d, the index lives on device %d", dev, ix->device);
-    const Plan p = static_plan(ix, nq, nprobe, k);
+    Plan p = static_plan(ix, nq, nprobe, k, both_parts(ix, metric));
+    if (p.total > (size_t)HR_STATIC_SCRATCH_BYTES) p = static_plan(ix, nq, nprobe, k, false);       // (narrower tiles)
     if (p.total > (size_t)HR_STATIC_SCRATCH_BYTES)
         return fail(HR_ERR_WORKSPACE, "this batch (nq=%lld, nprobe=%d, k=%d) needs %zu bytes of scratch, the static array has %zu: "
                                       "use hr_ivf_search with a workspace", (long long)nq, nprobe, k, p.total, (size_t)HR_STATIC_SCRATCH_BYTES);
@@ -822,7 +865,7 @@ int hr_ivf_coarse(const hr_ivf_index* ix, const float* queries, int64_t nq, int3
     if (int rc = check_batch(ix, nq, nprobe, 1, metric, false)) return rc;
     if (nq == 0) return HR_OK;
     if (!queries || !out_probe_ids) return fail(HR_ERR_ARG, "queries / out_probe_ids is null");
-    const Plan p = make_plan(ix, nq, nprobe, 1);
+    const Plan p = make_plan(ix, nq, nprobe, 1, false);
     if (int rc = check_ws(p, workspace, workspace_bytes)) return rc;
     char* ws = (char*)workspace;
     hipStream_t s = (hipStream_t)stream;
@@ -839,7 +882,7 @@ int hr_ivf_scan(const hr_ivf_index* ix, const float* queries, int64_t nq, const 
     if (int rc = check_batch(ix, nq, np_plan, k, metric, true)) return rc;
     if (nq == 0) return HR_OK;
     if (!queries || !probe_ids || !out_ids || !out_scores) return fail(HR_ERR_ARG, "queries / probe_ids / outputs null");
-    const Plan p = make_plan(ix, nq, nprobe, k);
+    const Plan p = make_plan(ix, nq, nprobe, k, both_parts(ix, metric));
     if (int rc = check_ws(p, workspace, workspace_bytes)) return rc;
     char* ws = (char*)workspace;
     hipStream_t s = (hipStream_t)stream;
@@ -857,7 +900,7 @@ static int scan_step(const hr_ivf_index* ix, const float* queries, int64_t nq, c
     if (int rc = check_batch(ix, nq, np_plan, k, metric, true)) return rc;
     if (nq == 0) return HR_OK;
     if (!queries || !probe_ids || !io_ids || !io_scores) return fail(HR_ERR_ARG, "queries / probe_ids / state null");
-    const Plan p = make_plan(ix, nq, nprobe, k);
+    const Plan p = make_plan(ix, nq, nprobe, k, both_parts(ix, metric));
     if (int rc = check_ws(p, workspace, workspace_bytes)) return rc;
     char* ws = (char*)workspace;
     hipStream_t s = (hipStream_t)stream;
@@ -1015,11 +1058,18 @@ int hr_ivf_refresh_rows(hr_ivf_index* ix, int64_t row_begin, int64_t row_end, vo
         return HR_OK;
     }
     if (ix->d_list_bound) {
-        // bounds start anew in lists of which every row is replaced; in the others they only grow, as rows that were replaced count on
+        // Bounds start anew in lists of which every row is replaced; in the others they only grow, as rows that were replaced count on.
+        // (So they do in a graph: it replays one count, whatever the calls beside it have reached.)
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &capture) != hipSuccess) { capture = hipStreamCaptureStatusActive; (void)hipGetLastError(); }
         const int *off = ix->h_list_off, *end = off + ix->nlist + 1;
-        const int64_t l0 = std::lower_bound(off, end, (int)row_begin) - off, l1 = std::upper_bound(off, end, (int)row_end) - off - 1;
-        if (l0 < l1) HR_HIP(launch_fill_i32((int*)(ix->d_list_bound + l0), 2 * (l1 - l0), 0, s));
-        HR_HIP(launch_list_bounds((const float*)ix->vectors, ix->d, row_begin, n, ix->d_list_off, (int)ix->nlist, ix->d_row_norm, (uint2*)ix->d_list_bound, ix->d_vec_hi, s));
+        const bool anew = capture == hipStreamCaptureStatusNone;
+        const int whole0 = anew ? (int)(std::lower_bound(off, end, (int)row_begin) - off) : 0;
+        const int whole1 = anew ? (int)(std::upper_bound(off, end, (int)row_end) - off) - 1 : 0;
+        const int l0 = (int)(std::upper_bound(off, end, (int)row_begin) - off) - 1, l1 = (int)(std::lower_bound(off, end, (int)row_end) - off);
+        const ListArgs a{(const float*)ix->vectors, row_begin, n, ix->d_list_off, (int)ix->nlist, ix->d, l0, l1 - l0, ix->d_row_norm, ix->d_list_bound,
+                         ix->d_vec_hi, ix->d_spread, ix->d_tight, whole0, whole1, ix->replaced.fetch_add(1) + 1};
+        HR_HIP(launch_list_bounds(a, s));
     } else
         HR_HIP(launch_row_norms(rows, ix->dtype, n, ix->d, ix->d_row_norm + row_begin, s));
     return HR_OK;
@@ -1032,7 +1082,7 @@ int hr_ivf_workspace_layout(const hr_ivf_index* ix, int64_t nq, int32_t nprobe, 
     if (!out || !n || cap < 0) return fail(HR_ERR_ARG, "out / n is null");
     if (nprobe < 1 || nprobe > HR_NPROBE_MAX) return fail(HR_ERR_ARG, "nprobe=%d must be in 1..%d", nprobe, HR_NPROBE_MAX);
     if (int rc = check_batch(ix, nq, nprobe > ix->nlist ? (int)ix->nlist : nprobe, k, HR_METRIC_IP, true)) return rc;
-    const Plan p = make_plan(ix, nq, nprobe, k);
+    const Plan p = make_plan(ix, nq, nprobe, k, false);
     *n = p.nreg;
     for (int i = 0; i < p.nreg && i < cap; i++) { out[2 * i] = (int64_t)p.reg_off[i]; out[2 * i + 1] = (int64_t)p.reg_len[i]; }
     return HR_OK;
@@ -1044,7 +1094,7 @@ int hr_ivf_stats(const hr_ivf_index* ix, const void* workspace, size_t workspace
     if (int rc = check_index(ix)) return rc;
     if (!out) return fail(HR_ERR_ARG, "out is null");
     if (int rc = check_batch(ix, nq, nprobe > ix->nlist ? (int)ix->nlist : nprobe, k, HR_METRIC_IP, true)) return rc;
-    const Plan p = make_plan(ix, nq, nprobe, k);
+    const Plan p = make_plan(ix, nq, nprobe, k, false);
     if (int rc = check_ws(p, workspace, workspace_bytes)) return rc;
     int dyn[DYN_COUNT];
     HR_HIP(hipMemcpy(dyn, (const char*)workspace + p.o_zero + (size_t)ix->nlist * 4, sizeof dyn, hipMemcpyDeviceToHost));

@@ -231,63 +231,175 @@ __global__ __launch_bounds__(256) void k_row_norms(const void* rows, int dtype, 
     if (lane == 0) out[row] = acc;
 }
 
-// float32 rows: the squared norm of every row, and of every list the largest of them and the largest squared norm of what
-// rounding a row to binary16 leaves over (hi: the rounded rows, or nullptr).  Squares are not negative, so their bits are in order; NaN counts as infinite.  A wave
-// takes `each` rows, one after the other, and asks once per list for all of them.
-__global__ __launch_bounds__(256) void k_list_bounds(const float* rows, int d, int64_t row0, int64_t nrows, const int* list_off, int nlist,
-                                                     float* row_norm, uint2* bound, _Float16* hi, int each)
+// What the bounds of a list's scores tell: the window (two slacks) that the high parts alone leave to a score, in deviations of the scores
+// of the list's rows, whose tail the best ones are.  These are |q| spread / sqrt(d) for the inner product, and sqrt(8 / d) spread^2 for
+// the squared distance of a query that is as far from the rows as they are from each other: an offset that all rows have in common
+// widens the window and not the deviation.  (What rounding leaves over of a query is about 1.4e-4 of it.)
+//
+// 1024 queries over 16 of 256 lists, high parts and both parts (HR_F32X2), us a call by window: d = 768, inner product, k 10, 0.15 260 and
+// 336, 0.55 269 and 334, 1.08 368 and 334, 2.2 683 and 334; k 50, 0.55 394 and 405, 1.08 566 and 406; squared distance, k 10, 0.40 280
+// and 348, 0.85 331 and 349, 3.2 1235 and 350, 13 2140 and 351; d = 128, 0.42 211 and 218, 0.99 263 and 201, 1.5 494 and 217; d = 1024,
+// 0.95 289 and 305, 1.2 307 and 296, 3.7 912 and 305.  So both parts are multiplied where a sixteenth of the rows (kWindowShare) is in lists with a window
+// of more than kWindow, and where one list has one of more than kWindowAny: the queries that probe it hold up the batch (a row a
+// hundred times as long as the others in one list of 256, 643 and 340).
+constexpr float kWindow = 0.9f, kWindowAny = 3.0f;
+__device__ __forceinline__ float score_window(float norm2, float left2, float spread, int d, bool l2)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t first = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * each;
-    if (first >= nrows) return;
-    const int n = (int)min((int64_t)each, nrows - first);
+    const float n = sqrtf(norm2), slacks = 4.1f * (sqrtf(left2) + 1.4e-4f * n) * sqrtf((float)d);
+    const float over = l2 ? 2.0f * n * slacks : slacks, by = l2 ? 2.8f * spread : sqrtf(spread);
+    return by > 0.f ? over / by : 0.f;                          // (rows that are all the same: both parts tell no more)
+}
+
+// rows of the lists whose window is wide, by metric (wide: two counters, zeroed before)
+__global__ __launch_bounds__(256) void k_wide_windows(ListArgs a, int* wide)
+{
+    const int l = blockIdx.x * 256 + threadIdx.x;
+    if (l >= a.nlist) return;
+    for (int m = 0; m < 2; m++) {
+        const float w = score_window(bound_value(a.bound[l].norm2), bound_value(a.bound[l].left2), a.spread[l], a.d, m == HR_METRIC_L2);
+        if (w > kWindow) atomicAdd(&wide[m], a.list_off[l + 1] - a.list_off[l]);
+        if (w > kWindowAny) ((volatile int*)a.tight)[m] = 1;
+    }
+}
+
+hipError_t launch_wide_windows(const ListArgs& a, int* wide, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_wide_windows, dim3((unsigned)((a.nlist + 255) / 256)), dim3(256), 0, s, a, wide);
+    return hipGetLastError();
+}
+
+constexpr int kBoundWaves = 16;
+// How far the rows of list l lie apart: half the median squared distance of 16 pairs of rows that are half a list from each other
+// (infinite for a list of fewer than 16 rows), a pair for each wave.
+__device__ __forceinline__ void list_spread(const ListArgs& a, int l)
+{
+    __shared__ float s_dist[kBoundWaves], s_norm[kBoundWaves];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int first = a.list_off[l], half = (a.list_off[l + 1] - first) / 2, pairs = min(half, kBoundWaves);
+    if (half < kBoundWaves / 2) {
+        if (threadIdx.x == 0) a.spread[l] = __builtin_inff();
+        return;
+    }
+    const float* const p = a.rows + (first + (int64_t)min(wave, pairs - 1) * half / pairs) * a.d;
+    float sum = 0.f, norm = 0.f;
+#pragma unroll 4
+    for (int i = lane; i < a.d; i += 64) {
+        const float x = p[i], y = x - p[i + (size_t)half * a.d];
+        sum += y * y;
+        norm += x * x;
+    }
+    sum = wave_sum(sum);
+    norm = wave_sum(norm);
+    if (lane == 0) { s_dist[wave] = sum; s_norm[wave] = norm; }
+    __syncthreads();
+    if ((int)threadIdx.x >= pairs) return;
+    const float mine = s_dist[threadIdx.x];
+    int rank = 0;
+    for (int t = 0; t < pairs; t++) {
+        rank += s_dist[t] < mine || (s_dist[t] == mine && t < (int)threadIdx.x) ? 1 : 0;
+        norm = fmaxf(norm, s_norm[t]);
+    }
+    if (rank != pairs / 2) return;
+    a.spread[l] = 0.5f * mine;
+    // (the window that these rows alone make)
+    for (int m = 0; m < 2; m++)
+        if (score_window(norm, norm * 2e-8f, 0.5f * mine, a.d, m == HR_METRIC_L2) > kWindowAny) ((volatile int*)a.tight)[m] = 1;
+}
+
+// float32 rows: the squared norm of every row and its image in the table, and of every list its bounds (the first `blocks` workgroups, `each`
+// rows a wave, one after the other) and how far its rows lie apart (the workgroups behind).  Squares are not negative, so their bits are
+// in order; NaN counts as infinite.  Additions to one address go one after the other, 25 ns each, and where all rows of a list are
+// new every one of them is above what is known: a workgroup asks once for what its sixteen waves found of a list (every wave for
+// itself, the loads of a row one after the other: lists of some 400 rows of d = 256 swapped in 13.4 us each, now 6.6).
+__global__ __launch_bounds__(kBoundWaves * 64) void k_list_bounds(ListArgs a, int each, unsigned blocks)
+{
+    if (blockIdx.x >= blocks) {
+        for (unsigned l = blockIdx.x - blocks; l < (unsigned)a.lists; l += gridDim.x - blocks) {
+            list_spread(a, a.l0 + (int)l);
+            __syncthreads();
+        }
+        return;
+    }
+    __shared__ int s_list[kBoundWaves];
+    __shared__ uint32_t s_most[kBoundWaves], s_left[kBoundWaves];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t first = ((int64_t)blockIdx.x * kBoundWaves + wave) * each;
+    _Float16* const hi = (_Float16*)a.hi;
+    const int n = (int)min((int64_t)each, a.nrows - first);     // (none: 0 or less)
     int lo = 0;                                                 // list of the row: the last one that starts at it or before
-    for (int end = nlist; end - lo > 1;) {
+    for (int end = a.nlist; end - lo > 1;) {
         const int step = (end - lo + 63) >> 6, at = lo + lane * step;
-        const int less = __builtin_popcountll(__builtin_amdgcn_ballot_w64(at < end && list_off[at] <= row0 + first));     // (at least 1)
+        const int less = __builtin_popcountll(__builtin_amdgcn_ballot_w64(at < end && a.list_off[at] <= a.row0 + first));     // (at least 1)
         lo += (less - 1) * step;
         end = min(end, lo + step);
     }
     uint32_t most = 0, most_left = 0;
+    bool any = false;
     auto bits = [](float v) __attribute__((always_inline)) { return __builtin_bit_cast(uint32_t, v < __builtin_inff() ? v : __builtin_inff()); };
-    // (additions to one address go one after the other: most rows are below what is known already)
-    auto raise = [](uint32_t* at, uint32_t v) __attribute__((always_inline)) {
-        if (v > __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(at, v);
+    auto raise = [&](u64* at, uint32_t v, bool whole) __attribute__((always_inline)) {
+        if (whole) { atomicMax(at, bound_of(v, a.count)); return; }
+        const u64 now = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), then = bound_of(v, now >> 24);
+        if (then > now) atomicMax(at, then);
     };
-    auto report = [&]() __attribute__((always_inline)) {
-        if (lane == 0) { raise(&bound[lo].x, most); raise(&bound[lo].y, most_left); }
-        most = most_left = 0;
+    auto report = [&](int l, uint32_t norm2, uint32_t left2) __attribute__((always_inline)) {
+        const bool whole = l >= a.whole0 && l < a.whole1;
+        raise(&a.bound[l].norm2, norm2, whole);
+        raise(&a.bound[l].left2, left2, whole);
+        // (a list of which all rows are new: its spread may be that of the rows before)
+        for (int m = 0; m < 2 && !whole; m++)
+            if (score_window(__builtin_bit_cast(float, norm2), __builtin_bit_cast(float, left2), a.spread[l], a.d, m == HR_METRIC_L2) > kWindowAny) ((volatile int*)a.tight)[m] = 1;
     };
     for (int i = 0; i < n; i++) {
-        const int64_t row = row0 + first + i;
-        while (row >= list_off[lo + 1]) { if (most) report(); lo++; }
-        const float* p = rows + row * d;
+        const int64_t row = a.row0 + first + i;
+        while (row >= a.list_off[lo + 1]) {
+            if (any && lane == 0) report(lo, most, most_left);
+            lo++;
+            most = most_left = 0;
+            any = false;
+        }
+        const float* p = a.rows + row * a.d;
         float sum = 0.f, left = 0.f;
-        for (int j = lane; j < d; j += 64) {
-            const float x = p[j];
-            const _Float16 h = (_Float16)x;
-            const float r = x - (float)h;
-            if (hi) hi[row * d + j] = h;
-            sum += x * x;
-            left += r * r;
+        // (four loads on their way together)
+        for (int j0 = lane; j0 < a.d; j0 += 256) {
+            float x[4];
+#pragma unroll
+            for (int t = 0; t < 4; t++) x[t] = j0 + t * 64 < a.d ? p[j0 + t * 64] : 0.f;
+#pragma unroll
+            for (int t = 0; t < 4; t++) {
+                const _Float16 h = (_Float16)x[t];
+                const float r = x[t] - (float)h;
+                if (hi && j0 + t * 64 < a.d) hi[row * a.d + j0 + t * 64] = h;
+                sum += x[t] * x[t];
+                left += r * r;
+            }
         }
         sum = wave_sum(sum);
         left = wave_sum(left);
-        if (lane == 0) row_norm[row] = sum;
+        if (lane == 0) a.row_norm[row] = sum;
         most = max(most, bits(sum));
         most_left = max(most_left, bits(left));
+        any = true;
     }
-    report();
+    if (lane == 0) { s_list[wave] = any ? lo : -1; s_most[wave] = most; s_left[wave] = most_left; }
+    __syncthreads();
+    // (the lists of the waves are in order: the first wave of each asks for all of them)
+    if (threadIdx.x < kBoundWaves) {
+        const int l = s_list[threadIdx.x];
+        if (l < 0 || (threadIdx.x > 0 && s_list[threadIdx.x - 1] == l)) return;
+        for (int t = threadIdx.x; t < kBoundWaves && s_list[t] == l; t++) { most = max(most, s_most[t]); most_left = max(most_left, s_left[t]); }
+        report(l, most, most_left);
+    }
 }
 
-hipError_t launch_list_bounds(const float* rows, int d, int64_t row0, int64_t nrows, const int* list_off, int nlist, float* row_norm, uint2* bound, void* hi, hipStream_t s)
+hipError_t launch_list_bounds(const ListArgs& a, hipStream_t s)
 {
-    if (nrows <= 0) return hipSuccess;
+    if (a.nrows <= 0) return hipSuccess;
     // (rows of a wave: as many as the device has no waves for; 84 queries with eight lists of some 70 rows of d = 256 swapped in, 16 rows
     // a wave 335 us a batch, one 181)
-    const int each = nrows <= 16384 ? 1 : (nrows <= 262144 ? 4 : 16);
-    const int64_t waves = (nrows + each - 1) / each;
-    hipLaunchKernelGGL(k_list_bounds, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, rows, d, row0, nrows, list_off, nlist, row_norm, bound, (_Float16*)hi, each);
+    const int each = a.nrows <= 16384 ? 1 : (a.nrows <= 262144 ? 4 : 16);
+    const unsigned blocks = (unsigned)((a.nrows + (int64_t)each * kBoundWaves - 1) / (each * kBoundWaves));
+    // (a launch may not have 2^32 threads or more)
+    hipLaunchKernelGGL(k_list_bounds, dim3(blocks + (unsigned)std::min(a.lists, 1 << 20)), dim3(kBoundWaves * 64), 0, s, a, each, blocks);
     return hipGetLastError();
 }
 
@@ -632,7 +744,7 @@ __global__ __launch_bounds__(256) void k_merge(MergeArgs a)
                 if (l >= 0 && l < a.nlist && a.pair_entry[q * a.nprobe + p] >= 0) {
                     int len = a.list_off[l + 1] - a.list_off[l];
                     ns = (len + seg_rows - 1) / seg_rows;
-                    if (BOUNDED) slack = fmaxf(slack, scan_slack(qn, ql, a.list_bound[l], a.l2));
+                    if (BOUNDED) slack = fmaxf(slack, scan_slack(qn, ql, a.list_bound[l], a.l2, a.split != 0, a.d));
                 }
             }
             const int inc = wave_prefix_sum(ns);

@@ -9,27 +9,31 @@ namespace hr {
 
 constexpr int kWave = 64;
 // internal storage codes next to HR_F32 / HR_F16 / HR_BF16: float32 rows already split into a
-// binary16 hi table and a 2^11-scaled binary16 lo table (the centroid table, split at load), and rounded to a binary16 table
-// (lists with row tables)
-constexpr int HR_F16X2 = 3, HR_F16HI = 4;
+// binary16 hi table and a 2^11-scaled binary16 lo table (the centroid table, split at load), rounded to a binary16 table
+// (lists with row tables), and float32 rows of which the scan splits every block in LDS
+constexpr int HR_F16X2 = 3, HR_F16HI = 4, HR_F32X2 = 5;
 constexpr int kMfmaRows = 16;              // rows per MFMA (M of 16x16x32)
 constexpr int kAppendMax = 16;             // most candidates one column can gain per group of kMfmaRows rows
 constexpr int kMinSegRows = 256;           // smallest rows-per-work-item
 constexpr int kItemTarget = 4096;          // aimed number of scan work items per batch
 constexpr int kHistBins = 64;              // per-query histogram of candidate keys (one bin per lane)
 
-// Storage of which the scan multiplies the high parts alone and keeps every row that may count with what it left out; the
-// merge computes the exact scores of the few that are left (see scan_slack)
-__host__ __device__ constexpr bool scan_bounded(int dtype) { return dtype == HR_F32 || dtype == HR_F16HI; }
+// Storage of which the scan leaves something out, the low parts (HR_F32, HR_F16HI) or what the two parts leave over (HR_F32X2), and
+// keeps every row that may count with it; the merge computes the exact scores of the few that are left (see scan_slack)
+__host__ __device__ constexpr bool scan_bounded(int dtype) { return dtype == HR_F32 || dtype == HR_F16HI || dtype == HR_F32X2; }
+
+// Storage of which both parts of rows and query are multiplied, and storage of four bytes an element
+__host__ __device__ constexpr bool scan_split(int dtype) { return dtype == HR_F16X2 || dtype == HR_F32X2; }
+__host__ __device__ constexpr bool stored_f32(int dtype) { return dtype == HR_F32 || dtype == HR_F32X2; }
 
 // Parts of a query operand that a wave keeps in registers of their own.  Two operands of d elements leave room for the rest in
 // 256 registers up to d = 768.  Beyond that they take two MFMA columns per query (8 queries per wave).
 __host__ __device__ constexpr int operand_parts(int dtype, int d)
 {
-    return (dtype == HR_BF16 || dtype == HR_F16X2) && d <= 768 ? 2 : 1;
+    return (dtype == HR_BF16 || scan_split(dtype)) && d <= 768 ? 2 : 1;
 }
 // columns (queries) per wave
-__host__ __device__ constexpr int cols_per_set(int dtype, int d) { return (dtype == HR_BF16 || dtype == HR_F16X2) && operand_parts(dtype, d) == 1 ? 8 : 16; }
+__host__ __device__ constexpr int cols_per_set(int dtype, int d) { return (dtype == HR_BF16 || scan_split(dtype)) && operand_parts(dtype, d) == 1 ? 8 : 16; }
 
 constexpr int kScanWaves = 8;              // waves of a workgroup of the scan, two per SIMD
 // queries of a work item
@@ -44,7 +48,7 @@ __host__ __device__ constexpr int tile_cols(int dtype, int d) { return kScanWave
 // 4000 queries and 2 .. 4 % slower for fewer.
 __host__ __device__ constexpr int block_groups(int dtype, int d)
 {
-    const int most = 4, long_enough = dtype == HR_F32 || dtype == HR_F16X2 ? 256 : 512;
+    const int most = 4, long_enough = dtype == HR_F32 || scan_split(dtype) ? 256 : 512;
     return d >= long_enough ? 1 : (long_enough / d < most ? long_enough / d : most);
 }
 __host__ __device__ constexpr int block_rows(int dtype, int d) { return kMfmaRows * block_groups(dtype, d); }
@@ -64,22 +68,22 @@ __host__ __device__ constexpr int groups_per_cu(int dtype, int d)
 __host__ __device__ constexpr int scan_group(int dtype, int ksteps)
 {
     // (blocks of several groups of rows: 8 or 16 k-steps in all)
-    if (ksteps < 16) return dtype == HR_F32 ? 2 : 4;
+    if (ksteps < 16) return stored_f32(dtype) ? 2 : 4;
     // (what a long operand in two parts leaves: 253 of 256 registers at 24 k-steps, none spilled)
     if (operand_parts(dtype, ksteps * 32) == 2)
-        return dtype == HR_F16X2 ? (ksteps >= 24 ? 1 : 2) : (ksteps >= 24 ? 2 : 4);
-    return (dtype == HR_F32 && ksteps >= 24) || (dtype == HR_F16X2 && ksteps >= 32) ? 2 : 4;   // (256 registers per lane)
+        return scan_split(dtype) ? (ksteps >= 24 ? 1 : 2) : (ksteps >= 24 ? 2 : 4);
+    return (dtype == HR_F32 && ksteps >= 24) || (scan_split(dtype) && ksteps >= 32) ? 2 : 4;   // (256 registers per lane)
 }
 
 // selection buffer capacity per column for a given k: room for k kept entries plus a batch of
 // new ones between two prunes (a prune costs about the same for any fill up to 64 entries per
 // lane slot, so bigger batches make each candidate cheaper), bounded by LDS
-// (bounded types keep what is within the slack of the k-th best too: half of a buffer that has just been cut, or more, is meant to be free)
+// (high parts alone: what is within their slack of the k-th best is kept too, and half of a buffer that has just been cut, or more, is meant to be free)
 constexpr int kRoomAfterCut = 4;           // free entries beyond kAppendMax that a cut has to leave
 __host__ __device__ constexpr int sel_cap(int dtype, int k)
 {
     int c = k <= 24 ? 64 : (k <= 64 ? 128 : 192);
-    if (scan_bounded(dtype)) c = k <= 12 ? 64 : (k <= 24 ? 96 : (k <= 36 ? 128 : (k <= 64 ? 192 : 256)));
+    if (scan_bounded(dtype) && !scan_split(dtype)) c = k <= 12 ? 64 : (k <= 24 ? 96 : (k <= 36 ? 128 : (k <= 64 ? 192 : 256)));
     if (c < k + kAppendMax + kRoomAfterCut) c = k + kAppendMax + kRoomAfterCut;
     return c;
 }
@@ -121,6 +125,14 @@ constexpr uint32_t kKeyNegInf = 0x007fffffu;   // enc_key(-inf)
 // One candidate: key (enc_key of the score, larger is better) and row number.
 struct Cand { uint32_t key; uint32_t row; };
 
+// What bounds the scores of a list's rows: the largest squared norm of its rows and the largest squared norm of what rounding a row to
+// binary16 leaves over, each the upper 24 bits of a float (rounded up) below 40 bits that count the times that all rows of a list
+// were replaced: a later count is larger whatever the bound, so a bound starts anew without being cleared before.
+typedef unsigned long long u64;
+struct ListBound { u64 norm2, left2; };
+__host__ __device__ inline float bound_value(u64 b) { return __builtin_bit_cast(float, (uint32_t)(b << 8)); }
+__host__ __device__ inline u64 bound_of(uint32_t bits, u64 count) { return count << 24 | ((u64)bits + 255) >> 8; }
+
 // Arguments of the scan kernel (both uses: centroid table with all queries as one dense
 // bucket, and the inverted lists with the per-list buckets).
 struct ScanArgs {
@@ -136,7 +148,7 @@ struct ScanArgs {
     // bounded types (scan_slack)
     const float* qnorm;         // [nq] squared norms of the queries
     const float* qlo;           // [nq] norms of their low parts
-    const float2* list_bound;   // [nlist]
+    const ListBound* list_bound;   // [nlist]
     const float* rows_f32;      // [nrows, d] the rows as they are
     int* work_counter;          // dense mode: items popped beyond the first of every workgroup (zeroed before launch)
     // bucket mode
@@ -172,7 +184,7 @@ struct SeedArgs {
     const int64_t* state_ids;   // [nq, k] labels and scores of a carried result, or nullptr
     const float* state_scores;
     const float* qnorm;         // [nq] squared norms of the query operands
-    const float2* list_bound;   // [nlist] float32 rows: see scan_slack
+    const ListBound* list_bound;   // [nlist] float32 rows: see scan_slack
     int nq, nprobe, nlist, k, seed_rows, l2;
 };
 
@@ -202,8 +214,8 @@ struct MergeArgs {
     const float* rows_f32;      // [nrows, d] the rows, or nullptr: the slots hold exact keys
     const float* row_norm;      // [nrows]
     const float* qlo;           // [nq]
-    const float2* list_bound;   // [nlist]
-    int d;
+    const ListBound* list_bound;   // [nlist]
+    int d, split;               // split: the scan multiplied both parts (HR_F32X2)
     int32_t* io_rows;           // [nq, k] or nullptr: row numbers of the entries, carried along with them (-1: empty place)
 };
 
@@ -229,7 +241,23 @@ hipError_t launch_row_norms(const void* rows, int dtype, int64_t nrows, int d, f
 hipError_t launch_prep_queries(const PrepArgs& a, hipStream_t s);
 hipError_t launch_fill_i32(int* p, int64_t n, int v, hipStream_t s);
 hipError_t launch_hot_lists(const unsigned long long* hits, int nlist, int gc, int32_t* out, hipStream_t s);
-hipError_t launch_list_bounds(const float* rows, int d, int64_t row0, int64_t nrows, const int* list_off, int nlist, float* row_norm, uint2* bound, void* hi, hipStream_t s);
+struct ListArgs {
+    const float* rows;          // float32 rows of the index
+    int64_t row0, nrows;        // those that are new
+    const int* list_off;        // [nlist+1]
+    int nlist, d;
+    int l0, lists;              // the lists that have some of them
+    float* row_norm;            // [N]
+    ListBound* bound;           // [nlist]
+    void* hi;                   // [N, d] rows rounded to binary16, or nullptr
+    float* spread;              // [nlist] see k_list_bounds
+    int* tight;                 // host memory, by metric: set where a list's window is too wide (see score_window)
+    int whole0, whole1;         // the lists of which all rows are new: their bounds start anew (none where bounds may only grow)
+    u64 count;                  // of this replacement, larger than all before
+};
+hipError_t launch_list_bounds(const ListArgs& a, hipStream_t s);
+constexpr int kWindowShare = 16;           // one row in so many in lists with wide windows: see score_window
+hipError_t launch_wide_windows(const ListArgs& a, int* wide, hipStream_t s);
 hipError_t launch_read_hits(unsigned long long* hits, int64_t n, int64_t* out, int reset, hipStream_t s);
 hipError_t launch_lists_of_rows(const int32_t* rows, int64_t n, const int* list_off, int nlist, int32_t* out, hipStream_t s);
 hipError_t launch_reorder_probes(const int32_t* probe, int np, const int32_t* prev, int pp, const int32_t* hot, int nh,

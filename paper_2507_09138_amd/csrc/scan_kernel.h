@@ -20,6 +20,11 @@
 //            replaces, multiplied for every row what decides for a few: 1024 queries, 32 of 1024 lists of 1024 rows,
 //            d = 768, scan 601 -> 498 us (6.4 TB/s of rows), 3000 queries over 16 of 256 lists, d = 64, k 100, 1020 -> 803 a call.
 //   HR_F16HI (internal) the same with rows that were rounded beforehand: half the bytes (600 -> 290 us of the first).
+//   HR_F32X2 (internal) float32 rows of which every block is split into binary16 hi and 2^11-scaled lo parts where it lies in LDS, by the
+//            waves that requested it, the query likewise; the four partial products as in HR_F16X2, and a bound of what those leave
+//            over, a hundredth of what HR_F32 leaves out.  For rows that are so close to each other, or so long against the distances
+//            between them, that the bounds of HR_F32 leave too many of them (see score_window): the first of the above 698 us a call
+//            instead of 613; rows within 2 % of each other, 1024 queries over 16 of 256 lists of 1024, d = 768, 803 -> 334.
 //   HR_F16X2 (internal) rows that were split into binary16 hi and 2^11-scaled lo tables beforehand, the query likewise; the
 //            four partial products are recombined with their scales, which keeps about 22 bits of each factor with
 //            float32 accumulation (the centroid table: the coarse step of Section 2.2 runs this kernel
@@ -157,6 +162,7 @@ template <> struct StoreTraits<HR_F16>  { static constexpr int esize = 2, planes
 template <> struct StoreTraits<HR_BF16> { static constexpr int esize = 2, planes = 1; };
 template <> struct StoreTraits<HR_F16HI> { static constexpr int esize = 2, planes = 1; };
 template <> struct StoreTraits<HR_F16X2> { static constexpr int esize = 2, planes = 2; };
+template <> struct StoreTraits<HR_F32X2> { static constexpr int esize = 4, planes = 1; };
 
 // Eight waves per workgroup: two per SIMD with 256 registers each, so that one wave's MFMAs run while the other selects or
 // waits, or, two workgroups on a unit, four with 128 (see groups_per_cu).  Every wave owns nc query columns, so a work item
@@ -178,7 +184,7 @@ struct ScanShape {
     static constexpr int qp = operand_parts(DT, d);                // parts of the query operand in registers of their own
     static constexpr int na = 2 * qp;                              // accumulators per group of rows (independent MFMA chains)
     static constexpr int planes = StoreTraits<DT>::planes;
-    static constexpr int raw = DT == HR_F32 ? 2 : planes;          // 16-byte reads from LDS per row fragment of a k-step
+    static constexpr int raw = stored_f32(DT) ? 2 : planes;         // 16-byte reads from LDS per row fragment of a k-step
     static constexpr int rb = block_groups(DT, d);                 // groups of 16 rows per block
     static constexpr int br = kMfmaRows * rb;                      // rows per block
     static constexpr int rowb = d * StoreTraits<DT>::esize;        // bytes of one stored row
@@ -277,8 +283,8 @@ __device__ __forceinline__ void mfma_block(const char* const (&ap)[4], const u32
         const int u = gi * G + i, t = u % KSTEPS, j = u / KSTEPS;
 #pragma unroll
         for (int r = 0; r < S::raw; r++) {
-            if constexpr (DT == HR_F32) af[gi & 1][i][r] = *(const u32x4*)(ap[(t & 1) * 2 + r] + (t >> 1) * 256 + j * kMfmaRows * S::rowb);
-            else                        af[gi & 1][i][r] = *(const u32x4*)(ap[t & 3] + r * S::plane_bytes + (t >> 2) * 256 + j * kMfmaRows * S::rowb);
+            if constexpr (stored_f32(DT)) af[gi & 1][i][r] = *(const u32x4*)(ap[(t & 1) * 2 + r] + (t >> 1) * 256 + j * kMfmaRows * S::rowb);
+            else                          af[gi & 1][i][r] = *(const u32x4*)(ap[t & 3] + r * S::plane_bytes + (t >> 2) * 256 + j * kMfmaRows * S::rowb);
         }
     };
 #pragma unroll
@@ -324,7 +330,7 @@ __device__ __forceinline__ void mfma_pair(const char* const (&ap0)[4], const cha
 #pragma unroll
             for (int r = 0; r < S::raw; r++) {
                 const int t = g0 + i;
-                const char* b = DT == HR_F32 ? (gg < NG ? ap0[(t & 1) * 2 + r] : ap1[(t & 1) * 2 + r]) + (t >> 1) * 256
+                const char* b = stored_f32(DT) ? (gg < NG ? ap0[(t & 1) * 2 + r] : ap1[(t & 1) * 2 + r]) + (t >> 1) * 256
                                              : (gg < NG ? ap0[t & 3] : ap1[t & 3]) + r * S::plane_bytes + (t >> 2) * 256;
                 af[gg & 1][i][r] = *(const u32x4*)b;
             }
@@ -362,18 +368,21 @@ __device__ __forceinline__ uint32_t select_k(Cand* buf, int n, int k, int cap, c
 
 // what is xor-ed into the address of a lane's row fragment of k-step 0 for base j of mfma_block
 template <int DT>
-__device__ __forceinline__ constexpr int frag_step(int j) { return DT == HR_F32 ? 128 * (j >> 1) + 16 * (j & 1) : 64 * j; }
+__device__ __forceinline__ constexpr int frag_step(int j) { return stored_f32(DT) ? 128 * (j >> 1) + 16 * (j & 1) : 64 * j; }
 
-// Bounded types: the scan multiplies the high parts of rows and query alone, and the key of a row is that product's plus what the
-// parts left out can add at most, |x.y| <= |x| |y|: an upper bound of its exact key, and less two slacks a lower one.
-// bound: of the list's rows the largest squared norm and the largest squared norm of what rounding them to
-// binary16 left over.  q, q_lo: norms of the query and of its low part (infinite: no bound).  Two hundredths more for the
+// Bounded types: the scan leaves parts of rows and query out, and the key of a row is that product's plus what they can
+// add at most, |x.y| <= |x| |y|: an upper bound of its exact key, and less two slacks a lower one.
+// bound: of the list's rows (ListBound).  q, q_lo: norms of the query and of its low part (infinite: no bound).  Two hundredths more for the
 // roundings of the norms and for the product of the low parts, 2^-19 |q| |x| for the float32 sums of key and exact
 // key; with squared L2 a key is twice the product less the squared norm, both rounded.
-__device__ __forceinline__ float scan_slack(float q, float q_lo, float2 bound, int l2)
+// split: both parts are multiplied (HR_F32X2).  What they leave over of an element is at most 2^-22 of it, or 2^-36 of one that is
+// small itself.
+__device__ __forceinline__ float scan_slack(float q, float q_lo, const ListBound bound, int l2, bool split, int d)
 {
-    const float n2 = fmaxf(bound.x, 1e-18f), norm = sqrtf(n2);   // (squares of smaller numbers may have vanished)
-    float s = 1.02f * (q_lo * norm + q * sqrtf(bound.y)) + 1.9073486328125e-06f * q * norm;
+    const float n2 = fmaxf(bound_value(bound.norm2), 1e-18f), norm = sqrtf(n2);   // (squares of smaller numbers may have vanished)
+    float s = split ? 4.9e-07f * q * norm + 1.5e-11f * sqrtf((float)d) * (q + norm) : 1.02f * (q_lo * norm + q * sqrtf(bound_value(bound.left2)));
+    if (!(q_lo < __builtin_inff())) s = __builtin_inff();
+    s += 1.9073486328125e-06f * q * norm;
     if (l2) s = 2.0f * s + n2 * 9.5367431640625e-07f;
     return s < __builtin_inff() ? s : __builtin_inff();          // (also for NaN)
 }
@@ -560,11 +569,11 @@ __global__ __launch_bounds__(kScanWaves * 64, groups_per_cu(DT, KSTEPS * 32) == 
         static_assert(!S::lean || S::rowb % 256 == 0, "the xor below stays inside a row");
         if constexpr (S::lean) {
             // (a row is a multiple of 256 bytes: the address of step j is that of step 0 with frag_step(j) xor-ed in)
-            abase[0] = i * S::rowb + 16 * ((DT == HR_F32 ? 2 * g : g) ^ (i & S::swz));
+            abase[0] = i * S::rowb + 16 * ((stored_f32(DT) ? 2 * g : g) ^ (i & S::swz));
             abase[1] = abase[2] = abase[3] = 0;
         } else {
 #pragma unroll
-            for (int j = 0; j < 4; j++) abase[j] = i * S::rowb + ((16 * ((DT == HR_F32 ? 2 * g : g) ^ (i & S::swz))) ^ frag_step<DT>(j));
+            for (int j = 0; j < 4; j++) abase[j] = i * S::rowb + ((16 * ((stored_f32(DT) ? 2 * g : g) ^ (i & S::swz))) ^ frag_step<DT>(j));
         }
 #pragma unroll
         for (int m = 0; m < NLD; m++) {
@@ -729,6 +738,29 @@ __global__ __launch_bounds__(kScanWaves * 64, groups_per_cu(DT, KSTEPS * 32) == 
                 }
             }
         };
+        // HR_F32X2: what this wave has requested of block blk lies in buffer buf: eight elements, 32 bytes, become their hi and
+        // their scaled lo parts in the same place, before the barrier that hands the block to all waves.  (Every wave splits an
+        // eighth; split while the fragments are read, all of them would split all of it.)
+        auto split_block = [&](int buf) __attribute__((always_inline)) {
+            if constexpr (DT == HR_F32X2) {
+                static_assert(NLD % 2 == 0, "half of the lanes for each of two requests");
+                const int ln = lane_here();
+#pragma unroll 1
+                for (int m0 = 0; m0 < NLD; m0 += 2) {
+                    const int m = m0 + (ln >> 5);
+                    const int odd = ((m * NW + wave) * 64 + (ln & 31) * 2) / S::cpr & 1;      // (odd rows: the two chunks are swapped)
+                    char* const at = stage + buf * S::buf_bytes + (m * NW + wave) * 1024 + (ln & 31) * 32;
+                    u32x4* const first = (u32x4*)(at + odd * 16);
+                    u32x4* const second = (u32x4*)(at + 16 - odd * 16);
+                    const u32x4 x[2] = {*first, *second};
+                    half8 hi, lo;
+                    split8(x, hi, lo);
+                    *first = __builtin_bit_cast(u32x4, hi);
+                    *second = __builtin_bit_cast(u32x4, lo);
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            }
+        };
         // ---- first row blocks on their way before anything else
         for (int i = 0; i < D; i++) fill(i, i);
 
@@ -771,7 +803,7 @@ __global__ __launch_bounds__(kScanWaves * 64, groups_per_cu(DT, KSTEPS * 32) == 
         if constexpr (S::bounded) {
             if (col_ok) {
                 const float lo = a.qlo[q];
-                slack = scan_slack(sqrtf(a.qnorm[q]), lo, a.list_bound[list], a.l2);
+                slack = scan_slack(sqrtf(a.qnorm[q]), lo, a.list_bound[list], a.l2, scan_split(DT), S::d);
                 if (lo != lo) thr = __builtin_inff();            // (a query beyond binary16)
             }
         }
@@ -852,10 +884,10 @@ __global__ __launch_bounds__(kScanWaves * 64, groups_per_cu(DT, KSTEPS * 32) == 
                 return best;
             };
             make_keys([](const floatx4 (&c)[S::na], int r) __attribute__((always_inline)) {
-                if constexpr (!DENSE && QP == 1) {
+                if constexpr (!scan_split(DT) && QP == 1) {
                     const float v = c[0][r] + c[1][r];
                     return NC == 8 ? v + lane_xor8(v) : v;
-                } else if constexpr (!DENSE) {
+                } else if constexpr (!scan_split(DT)) {
                     return (c[0][r] + c[1][r]) + (c[2][r] + c[3][r]);
                 } else if constexpr (QP == 2) {
                     return c[0][r] + (c[2][r] + c[1][r]) * (1.0f / 2048.0f) + c[3][r] * (1.0f / 4194304.0f);
@@ -924,7 +956,7 @@ __global__ __launch_bounds__(kScanWaves * 64, groups_per_cu(DT, KSTEPS * 32) == 
                         if (left > a.cap - kAppendMax - kRoomAfterCut) {
                             // more rows than that are within the slack of the k-th best: the best by their exact keys
                             const int qc = __builtin_amdgcn_readlane(q, col);
-                            exact_keys<4, 1>(sel + col * a.cap, left, 0, 1, a.rows_f32, a.row_norm, a.queries + (size_t)qc * S::d, S::d, a.l2);
+                            exact_keys<scan_split(DT) ? 2 : 4, 1>(sel + col * a.cap, left, 0, 1, a.rows_f32, a.row_norm, a.queries + (size_t)qc * S::d, S::d, a.l2);
                             kth = select_k(sel + col * a.cap, left, a.k, a.cap, a.row_ids, lane);
                             left = a.k;
                         }
@@ -976,6 +1008,7 @@ __global__ __launch_bounds__(kScanWaves * 64, groups_per_cu(DT, KSTEPS * 32) == 
                 default: wait_vmcnt<3 * (S::lpf - S::nnl)>(); break;
                 }
             }
+            split_block(bi);
             __builtin_amdgcn_s_barrier();
             if (DENSE) flush_keys();
             fill(blk + D, bi == 0 ? NB - 1 : bi - 1);
@@ -989,6 +1022,8 @@ __global__ __launch_bounds__(kScanWaves * 64, groups_per_cu(DT, KSTEPS * 32) == 
             if (NB != 6) wait_vmcnt<0>();
             else if (a.l2) wait_vmcnt<2 * S::lpf>();
             else wait_vmcnt<2 * (S::lpf - S::nnl)>();
+            split_block(bi);
+            split_block(bi + 1);
             __builtin_amdgcn_s_barrier();
             // (the requests of all waves at once keep the address unit busy for a while, and a
             // wave cannot go on before its own are accepted: half of the waves send theirs
@@ -1340,7 +1375,7 @@ __device__ __forceinline__ void seed_query(const SeedArgs& a, const int64_t q)
         // (the scores that count are exact ones: other sums of products of about 22 bits per factor, half of the 2^-19 |q| |x| that
         // scan_slack counts for both; and elements below 2^-36 or so vanish in the low parts.  A bound too high by that would keep
         // rows of lists with shorter rows out)
-        const float qn = a.qnorm[q], xn = a.list_bound[l].x;
+        const float qn = a.qnorm[q], xn = bound_value(a.list_bound[l].norm2);
         float lost = 2.9103830456733704e-11f * sqrtf((float)d) * (sqrtf(qn) + sqrtf(xn)) + 9.5367431640625e-07f * sqrtf(qn) * sqrtf(xn);
         if (a.l2) lost = 2.0f * lost + xn * 4.76837158203125e-07f;
         pub = qn > 1e-30f && xn > 1e-30f ? key_below(pub, lost) : 0u;

@@ -678,15 +678,25 @@ def _replaced(N, d, nlist, rows, seed, tables):
 @pytest.mark.parametrize("tables", [False, True])
 @pytest.mark.parametrize("d,k,metric", [(64, 10, "ip"), (256, 20, "l2"), (512, 10, "l2"), (768, 10, "ip"), (768, 1, "l2"), (1024, 24, "ip"), (1024, 10, "l2")])
 @pytest.mark.parametrize("spread", [1e-5, 1e-4])
-def test_close_float32_rows_are_the_same_bits_in_every_call(tables, d, k, metric, spread):
-    """Rows so close that buffers overflow with rows whose bounds say nothing: ids and scores must not depend on the batch around a
-    query, on the plan (segments and buffers of the static scratch) or on which lists are searched together."""
+@pytest.mark.parametrize("share", [1, 3])
+def test_close_float32_rows_are_the_same_bits_in_every_call(tables, d, k, metric, spread, share):
+    """Rows so close that buffers overflow with rows whose bounds say nothing, all rows of a list (both parts are multiplied then) or the
+    third of it that the queries are closest to: ids and scores must not depend on the batch around a query, on the plan (segments and
+    buffers of the static scratch) or on which lists are searched together."""
     hr = _hr()
     nlist, nq = 6, 250
     N = nlist * 1500
-    ix, vec, ids, g = _replaced(N, d, nlist, lambda g: torch.randn(1, d, generator=g, device="cuda") + spread * torch.randn(N, d, generator=g, device="cuda"),
-                                d + k, tables)
+
+    def rows(g):
+        base = torch.randn(1, d, generator=g, device="cuda")
+        close = base + spread * torch.randn(N, d, generator=g, device="cuda")
+        far = torch.randn(N, d, generator=g, device="cuda") - (0.5 if metric == "ip" else 0.0) * base
+        return torch.where((torch.arange(N, device="cuda") % 1500 < 1500 // share)[:, None], close, far)
+
+    ix, vec, ids, g = _replaced(N, d, nlist, rows, d + k, tables)
     q = torch.randn(1100, d, generator=g, device="cuda")
+    if share > 1:
+        q = q + vec[0]
     alone = ix.search(q[:nq], nlist, k, metric)
     for _ in range(3):
         again = ix.search(q[:nq], nlist, k, metric)
@@ -829,4 +839,120 @@ def test_a_replaced_long_row_does_not_slow_its_list_for_good(tables):
         best = torch.topk(q.double() @ vec.double().T, 20, dim=1).values
         # |q||x| below 16 * 16 * 30 * 1.4, a few 2^-24 of it
         assert float((score.double() - best).abs().max()) <= 11000 * 2.0 ** -24 * 16
+    ix.close()
+
+
+def _split_and_not(N, d, nlist, seed, tables, zipf=0.0, scale=1.0, hole=None):
+    """Two indexes of the same float32 rows: one that was loaded with them, and one that was loaded with rows which differ by less than
+    rounding takes from them, so that it multiplies both parts of the rows for good."""
+    hr = _hr()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    cent = torch.randn(nlist, d, generator=g, device="cuda")
+    w = torch.arange(1, nlist + 1, dtype=torch.float64) ** -zipf
+    sizes = torch.floor((N - nlist) * w / w.sum()).long() + 1
+    if hole is not None:
+        sizes[hole] = 0
+    sizes[0] += N - int(sizes.sum())
+    off = torch.zeros(nlist + 1, dtype=torch.int64)
+    off[1:] = torch.cumsum(sizes, 0)
+    good = scale * torch.randn(N, d, generator=g, device="cuda")
+    ids = torch.randperm(N, generator=g, device="cuda")
+    vec = (1 + 1e-5 * torch.randn(N, d, generator=g, device="cuda")).contiguous()
+    split = hr.IvfIndex(cent, off, vec, ids, row_tables=tables)
+    vec.copy_(good)
+    split.refresh_rows(0, N)
+    torch.cuda.synchronize()
+    return hr.IvfIndex(cent, off, good, ids, row_tables=tables), split, off, good, ids, g
+
+
+@pytest.mark.parametrize("d", [64, 128, 256, 512, 768, 1024])
+@pytest.mark.parametrize("N,nlist,nq,nprobe,k,zipf,scale", [(9000, 40, 1, 7, 10, 1.0, 1.0), (20011, 37, 333, 11, 1, 0.7, 1.0), (3000, 300, 65, 40, 100, 0.3, 100.0), (40000, 20, 1030, 9, 24, 0.5, 1.0),
+                                                            (15000, 25, 129, 25, 13, 1.2, 1e-3), (700, 9, 17, 5, 128, 0.9, 1e-6), (5000, 60, 2000, 8, 50, 0.4, 1.0)])
+@pytest.mark.parametrize("metric", ["ip", "l2"])
+def test_both_parts_of_float32_rows_give_the_same_bits(d, N, nlist, nq, nprobe, k, zipf, scale, metric):
+    """Every call that scans float32 lists, by their high parts or by both: odd sizes, empty lists, lists out of place, probes that are
+    none, carried results, the static scratch; the best rows against float64."""
+    hr = _hr()
+    a, b, off, vec, ids, g = _split_and_not(N, d, nlist, N + d, nq % 2 == 0, zipf, scale, hole=nlist // 2)
+    q = scale * torch.randn(nq, d, generator=g, device="cuda")
+    out = torch.tensor([1, nlist - 2], dtype=torch.int32, device="cuda")
+    probe = torch.rand(nq, nlist, generator=g, device="cuda").topk(nprobe, dim=1).indices.int()
+    probe[::5, 1] = -1
+    for x in (a, b):
+        x.set_resident(out, False)
+    results = []
+    for x in (a, b):
+        state = x.new_state_rows(nq, k)
+        for part in (probe[:, :2], probe[:, 2:]):
+            x.scan_step_rows(q, part.contiguous(), state, metric)
+        fixed = torch.empty(min(nq, 40), k, dtype=torch.int64, device="cuda"), torch.empty(min(nq, 40), k, device="cuda")
+        hr.hr_ivf_search_static(x.handle, q[:40].contiguous(), min(nq, 40), nprobe, k, hr.HR_METRIC_IP if metric == "ip" else hr.HR_METRIC_L2, *fixed)
+        results.append([*x.search(q, nprobe, k, metric), *x.scan(q, probe, k, metric), *state, *fixed])
+    for u, v in zip(*results):
+        assert torch.equal(u, v)
+    found, score = results[0][2:4]
+    allowed = torch.zeros(nq, nlist + 1, dtype=torch.bool, device="cuda").scatter_(1, torch.where(probe < 0, nlist, probe).long(), True)[:, :nlist]
+    allowed[:, out.long()] = False
+    of_row = torch.repeat_interleave(torch.arange(nlist), off[1:] - off[:-1]).cuda()
+    key = torch.where(allowed[:, of_row], _keys(q.double(), vec.double(), metric), -float("inf"))
+    best = torch.topk(key, min(k, N), dim=1).values
+    got = found[:, :best.shape[1]]
+    assert torch.equal(got >= 0, best > -float("inf"))
+    row = torch.empty_like(ids)
+    row[ids] = torch.arange(N, device="cuda")
+    mine = torch.where(got >= 0, key.gather(1, row[got.clamp(min=0)]), best)
+    # float32 sums of d products in chains of at most d/64 + 6 steps and a norm: 2^-24 of |q||x| (+ |x|^2) for each
+    size = q.double().norm(dim=1, keepdim=True) * vec.double().norm(dim=1).max() * 2 + (vec.double().norm(dim=1).max() ** 2 if metric == "l2" else 0)
+    assert bool(((mine - best).abs().nan_to_num(0.0) <= size * 2.0 ** -24 * 24).all())
+    a.close()
+    b.close()
+
+
+def test_both_parts_are_multiplied_where_bounds_tell_little():
+    """What the loader and hr_ivf_refresh_rows make of rows, read from the number of work items: at d = 1024 a tile holds 128 queries, of
+    which both parts are multiplied 64."""
+    hr = _hr()
+    d, N, nq = 1024, 600, 128
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4)
+    base, noise = torch.randn(1, d, generator=g, device="cuda"), torch.randn(N, d, generator=g, device="cuda")
+    q = torch.randn(nq, d, generator=g, device="cuda")
+
+    def tiles(ix, metric):
+        ix.scan(q, torch.zeros(nq, 1, dtype=torch.int32, device="cuda"), 10, metric)
+        torch.cuda.synchronize()
+        ws = ix.workspace(nq, 1, 10)
+        s = hr.hr_ivf_stats(ix.handle, ws, ws.numel(), nq, 1, 10)
+        return s["items"] // ((N + s["seg_rows"] - 1) // s["seg_rows"])
+
+    def load(rows, off=(0, N)):
+        return hr.IvfIndex(base.expand(len(off) - 1, d).contiguous(), torch.tensor(off), rows.contiguous(), torch.arange(len(rows), device="cuda"))
+
+    # windows of 0.04 and 0.03 deviations; 0.5 and 4; 4 and 270; an offset that all have; equal rows (both parts tell no more); rows of zeros
+    for rows, ip, l2 in ((noise, 1, 1), (base + 0.08 * noise, 1, 2), (base + 0.01 * noise, 2, 2), (noise * 0.05 + 10, 2, 2), (base.expand(N, d), 1, 1), (0 * noise, 1, 1)):
+        ix = load(rows)
+        assert (tiles(ix, "ip"), tiles(ix, "l2")) == (ip, l2)
+        ix.close()
+    # a row a thousand times as long; rows that are replaced later, one of them or all
+    long = noise.clone()
+    long[7] *= 1000
+    ix = load(long)
+    assert (tiles(ix, "ip"), tiles(ix, "l2")) == (2, 2)
+    ix.close()
+    for before, a, b, rows, want in ((noise, 7, 8, long, 2), (noise, 0, N, base + 0.01 * noise, 2), (0 * noise, 0, N, noise, 1), (noise, 0, N, 2 * noise, 1)):
+        vec = before.clone()
+        ix = load(vec)
+        vec[a:b] = rows[a:b]
+        ix.refresh_rows(a, b)
+        torch.cuda.synchronize()
+        assert (tiles(ix, "ip"), tiles(ix, "l2")) == (want, want)
+        ix.close()
+    # one list in twenty whose window is a little wide (1.2 deviations) does not count, one in ten does
+    many = torch.cat([noise] * 19 + [base + 0.03 * noise])
+    ix = load(many, list(range(0, 20 * N + 1, N)))
+    assert tiles(ix, "ip") == 1
+    ix.close()
+    ix = load(torch.cat([noise] * 9 + [base + 0.03 * noise]), list(range(0, 10 * N + 1, N)))
+    assert tiles(ix, "ip") == 2
     ix.close()
