@@ -68,7 +68,7 @@ enum {
  * centroids, list_vectors and list_ids are BORROWED: they must stay valid and unchanged until
  * hr_ivf_free.  The library allocates (hipMalloc) derived tables: device copies of the offsets,
  * 4 bytes per row / per centroid of squared norms, the centroids as two binary16 tables, 8 bytes
- * per list of access counters (HR_F32: 20 more of bounds).  Nothing the size of list_vectors, unless the caller asks for it:
+ * per list of access counters (HR_F32: 24 more of bounds).  Nothing the size of list_vectors, unless the caller asks for it:
  * with dtype = HR_F32 | HR_LOAD_ROW_TABLES the rows are also kept rounded to binary16 (N*d*2 bytes, half of
  * list_vectors) for the scan to read, which looks for candidates with the rounded rows either way and scores those that
  * may be among the best from the float32 rows: the same results, faster.  Where rows are so close to each other, or so long

@@ -145,7 +145,7 @@ struct hr_ivf_index {
     std::atomic<uint64_t> over_used;
     ListBound* d_list_bound;      // float32 lists: [nlist] what scan_slack needs to know of the list's rows, else null
     std::atomic<uint64_t> replaced;   // float32 lists: refreshes so far (ListArgs::count)
-    float* d_spread;       // float32 lists: [nlist] how far their rows lie apart (list_spread), else null
+    float2* d_spread;      // float32 lists: [nlist] how far the scores of their rows are apart (list_spread), else null
     // float32 lists: host memory that kernels write, its address there and on the device: [metric] some list's bounds tell little
     int *h_tight, *d_tight;
     unsigned long long* d_hits;   // [nlist] probes per list since load / last reset
@@ -430,7 +430,7 @@ int hr_ivf_load(const float* centroids, const int64_t* list_offsets, const void*
     if (e == hipSuccess) e = hipMalloc(&ix->d_list_off, (size_t)(nlist + 1) * 4);
     if (e == hipSuccess) e = hipMalloc(&ix->d_row_norm, (size_t)(N > 0 ? N : 1) * 4);
     if (e == hipSuccess && dtype == HR_F32) e = hipMalloc(&ix->d_list_bound, (size_t)nlist * sizeof(ListBound));
-    if (e == hipSuccess && dtype == HR_F32) e = hipMalloc(&ix->d_spread, (size_t)nlist * sizeof(float));
+    if (e == hipSuccess && dtype == HR_F32) e = hipMalloc(&ix->d_spread, (size_t)nlist * sizeof(float2));
     if (e == hipSuccess && dtype == HR_F32) e = hipHostMalloc((void**)&ix->h_tight, 2 * sizeof(int), hipHostMallocMapped | hipHostMallocCoherent);
     if (e == hipSuccess && dtype == HR_F32) {
         ix->h_tight[0] = ix->h_tight[1] = 0;
@@ -460,7 +460,7 @@ int hr_ivf_load(const float* centroids, const int64_t* list_offsets, const void*
         const ListArgs a{(const float*)list_vectors, 0, N, ix->d_list_off, (int)nlist, d, 0, (int)nlist, ix->d_row_norm, ix->d_list_bound,
                          ix->d_vec_hi, ix->d_spread, ix->d_tight, 0, 0, 0};
         e = hipMemsetAsync(ix->d_list_bound, 0, (size_t)nlist * sizeof(ListBound), s);
-        if (e == hipSuccess) e = hipMemsetAsync(ix->d_spread, 0x7f, (size_t)nlist * sizeof(float), s);      // (far apart, until they are known)
+        if (e == hipSuccess) e = hipMemsetAsync(ix->d_spread, 0x7f, (size_t)nlist * sizeof(float2), s);      // (far apart, until they are known)
         if (e == hipSuccess) e = launch_list_bounds(a, s);
         if (e == hipSuccess && N > 0) e = launch_wide_windows(a, ix->d_flag + 2, s);
     } else if (e == hipSuccess) {

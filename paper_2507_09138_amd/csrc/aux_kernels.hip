@@ -232,22 +232,21 @@ __global__ __launch_bounds__(256) void k_row_norms(const void* rows, int dtype, 
 }
 
 // What the bounds of a list's scores tell: the window (two slacks) that the high parts alone leave to a score, in deviations of the scores
-// of the list's rows, whose tail the best ones are.  These are |q| spread / sqrt(d) for the inner product, and sqrt(8 / d) spread^2 for
-// the squared distance of a query that is as far from the rows as they are from each other: an offset that all rows have in common
-// widens the window and not the deviation.  (What rounding leaves over of a query is about 1.4e-4 of it.)
-//
-// 1024 queries over 16 of 256 lists, high parts and both parts (HR_F32X2), us a call by window: d = 768, inner product, k 10, 0.15 260 and
-// 336, 0.55 269 and 334, 1.08 368 and 334, 2.2 683 and 334; k 50, 0.55 394 and 405, 1.08 566 and 406; squared distance, k 10, 0.40 280
-// and 348, 0.85 331 and 349, 3.2 1235 and 350, 13 2140 and 351; d = 128, 0.42 211 and 218, 0.99 263 and 201, 1.5 494 and 217; d = 1024,
-// 0.95 289 and 305, 1.2 307 and 296, 3.7 912 and 305.  So both parts are multiplied where a sixteenth of the rows (kWindowShare) is in lists with a window
-// of more than kWindow, and where one list has one of more than kWindowAny: the queries that probe it hold up the batch (a row a
-// hundred times as long as the others in one list of 256, 643 and 340).
-constexpr float kWindow = 0.9f, kWindowAny = 3.0f;
-__device__ __forceinline__ float score_window(float norm2, float left2, float spread, int d, bool l2)
+// of the list's rows, whose tail the best ones are (dev: see list_spread; norm2, left2: of the longest row and of the largest rounding
+// residue; what rounding leaves over of a query is about 1.4e-4 of it).  1024 queries over 16 lists, high parts and both parts (HR_F32X2), us
+// a call, by the window of all lists: d = 768, 256 lists of 1024 rows of norm 1, inner product, k 10, 0.37 269 and 340, 0.71 297 and 339,
+// 1.4 736 and 340, 8 2130 and 342; k 50, 0.71 422 and 415, 1.4 1463 and 415; squared distance, 0.63 293 and 352, 0.97 457 and 351; d = 1024,
+// 0.82 219 and 230, 1.6 496 and 229; d = 128, 512 lists, 0.31 197 and 209, 0.58 213 and 208, 0.90 295 and 209; d = 64, 2000 queries, k 20,
+// 0.31 229 and 226, 0.52 261 and 226.  A few lists are as slow as all, their queries hold up the batch: one in twenty, d = 768, 0.71 271 and
+// 342, 1.4 414 and 340, d = 128, 0.58 199 and 209, 0.90 241 and 208; one list, d = 768, 1.4 285 and 341, 2.2 306 and 340, 3.8 390 and 341, k
+// 50, 1.4 531 and 416; d = 128, 1.6 211 and 209.  So both parts are multiplied where a 64th of the rows (kWindowShare) is in lists whose
+// window is wider than the line, 0.7 for long rows and 0.4 for short ones, which both parts take little longer for, and where one list
+// is kWindowAny times as wide.
+constexpr float kWindowAny = 2.2f;
+__device__ __forceinline__ float score_window(float norm2, float left2, float dev, int d)      // (in units of the line)
 {
-    const float n = sqrtf(norm2), slacks = 4.1f * (sqrtf(left2) + 1.4e-4f * n) * sqrtf((float)d);
-    const float over = l2 ? 2.0f * n * slacks : slacks, by = l2 ? 2.8f * spread : sqrtf(spread);
-    return by > 0.f ? over / by : 0.f;                          // (rows that are all the same: both parts tell no more)
+    const float over = 4.1f * (sqrtf(left2) + 1.4e-4f * sqrtf(norm2)) / (d >= 512 ? 0.7f : 0.4f);
+    return dev > 0.f ? over / dev : 0.f;                          // (rows that are all the same: both parts tell no more)
 }
 
 // rows of the lists whose window is wide, by metric (wide: two counters, zeroed before)
@@ -256,8 +255,8 @@ __global__ __launch_bounds__(256) void k_wide_windows(ListArgs a, int* wide)
     const int l = blockIdx.x * 256 + threadIdx.x;
     if (l >= a.nlist) return;
     for (int m = 0; m < 2; m++) {
-        const float w = score_window(bound_value(a.bound[l].norm2), bound_value(a.bound[l].left2), a.spread[l], a.d, m == HR_METRIC_L2);
-        if (w > kWindow) atomicAdd(&wide[m], a.list_off[l + 1] - a.list_off[l]);
+        const float w = score_window(bound_value(a.bound[l].norm2), bound_value(a.bound[l].left2), m == HR_METRIC_L2 ? a.spread[l].y : a.spread[l].x, a.d);
+        if (w > 1.0f) atomicAdd(&wide[m], a.list_off[l + 1] - a.list_off[l]);
         if (w > kWindowAny) ((volatile int*)a.tight)[m] = 1;
     }
 }
@@ -269,41 +268,50 @@ hipError_t launch_wide_windows(const ListArgs& a, int* wide, hipStream_t s)
 }
 
 constexpr int kBoundWaves = 16;
-// How far the rows of list l lie apart: half the median squared distance of 16 pairs of rows that are half a list from each other
-// (infinite for a list of fewer than 16 rows), a pair for each wave.
+// How far apart the scores of the rows of list l are, in deviations for a query of norm 1, from 16 pairs of rows that are half a list from
+// each other (infinite for a list of fewer than 16 rows), a pair for each wave.  With squared distances, of a query that is as far
+// from the rows as these are from each other: sqrt(2 / d) times half the median squared distance of a pair over the norm, whatever the
+// rows have in common; with the inner product, which is half of what the two norms leave of that distance, as far as the norms are as well (1.05: the
+// deviation of one from the median difference of two).
 __device__ __forceinline__ void list_spread(const ListArgs& a, int l)
 {
-    __shared__ float s_dist[kBoundWaves], s_norm[kBoundWaves];
+    __shared__ float s_dist[kBoundWaves], s_apart[kBoundWaves], s_norm[kBoundWaves];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int first = a.list_off[l], half = (a.list_off[l + 1] - first) / 2, pairs = min(half, kBoundWaves);
     if (half < kBoundWaves / 2) {
-        if (threadIdx.x == 0) a.spread[l] = __builtin_inff();
+        if (threadIdx.x == 0) a.spread[l] = float2{__builtin_inff(), __builtin_inff()};
         return;
     }
     const float* const p = a.rows + (first + (int64_t)min(wave, pairs - 1) * half / pairs) * a.d;
-    float sum = 0.f, norm = 0.f;
+    float dist = 0.f, norm = 0.f, other = 0.f;
 #pragma unroll 4
     for (int i = lane; i < a.d; i += 64) {
-        const float x = p[i], y = x - p[i + (size_t)half * a.d];
-        sum += y * y;
+        const float x = p[i], y = p[i + (size_t)half * a.d];
+        dist += (x - y) * (x - y);
         norm += x * x;
+        other += y * y;
     }
-    sum = wave_sum(sum);
-    norm = wave_sum(norm);
-    if (lane == 0) { s_dist[wave] = sum; s_norm[wave] = norm; }
+    dist = wave_sum(dist);
+    norm = sqrtf(wave_sum(norm));
+    other = sqrtf(wave_sum(other));
+    if (lane == 0) { s_dist[wave] = dist; s_apart[wave] = fabsf(norm - other); s_norm[wave] = norm; }
     __syncthreads();
-    if ((int)threadIdx.x >= pairs) return;
-    const float mine = s_dist[threadIdx.x];
-    int rank = 0;
-    for (int t = 0; t < pairs; t++) {
-        rank += s_dist[t] < mine || (s_dist[t] == mine && t < (int)threadIdx.x) ? 1 : 0;
-        norm = fmaxf(norm, s_norm[t]);
+    if (threadIdx.x >= 64) return;
+    // (the median ones, to all lanes)
+    auto median = [&](const float* v) __attribute__((always_inline)) {
+        const float mine = lane < pairs ? v[lane] : __builtin_inff();
+        int rank = 0;
+        for (int t = 0; t < pairs; t++) rank += v[t] < mine || (v[t] == mine && t < lane) ? 1 : 0;
+        return __shfl(mine, __builtin_ctzll(__builtin_amdgcn_ballot_w64(lane < pairs && rank == pairs / 2) | 1ull << 63));
+    };
+    const float spread2 = 0.5f * median(s_dist), apart = 1.05f * median(s_apart), typical = median(s_norm);
+    const float l2 = typical > 0.f ? 1.4f * spread2 / (sqrtf((float)a.d) * typical) : 0.f, ip = sqrtf(l2 * l2 + apart * apart);
+    if (lane == 0) {
+        a.spread[l] = float2{ip, l2};
+        // (the window that these rows alone make)
+        for (int m = 0; m < 2; m++)
+            if (score_window(typical * typical, typical * typical * 2e-8f, m == HR_METRIC_L2 ? l2 : ip, a.d) > kWindowAny) ((volatile int*)a.tight)[m] = 1;
     }
-    if (rank != pairs / 2) return;
-    a.spread[l] = 0.5f * mine;
-    // (the window that these rows alone make)
-    for (int m = 0; m < 2; m++)
-        if (score_window(norm, norm * 2e-8f, 0.5f * mine, a.d, m == HR_METRIC_L2) > kWindowAny) ((volatile int*)a.tight)[m] = 1;
 }
 
 // float32 rows: the squared norm of every row and its image in the table, and of every list its bounds (the first `blocks` workgroups, `each`
@@ -347,7 +355,7 @@ __global__ __launch_bounds__(kBoundWaves * 64) void k_list_bounds(ListArgs a, in
         raise(&a.bound[l].left2, left2, whole);
         // (a list of which all rows are new: its spread may be that of the rows before)
         for (int m = 0; m < 2 && !whole; m++)
-            if (score_window(__builtin_bit_cast(float, norm2), __builtin_bit_cast(float, left2), a.spread[l], a.d, m == HR_METRIC_L2) > kWindowAny) ((volatile int*)a.tight)[m] = 1;
+            if (score_window(__builtin_bit_cast(float, norm2), __builtin_bit_cast(float, left2), m == HR_METRIC_L2 ? a.spread[l].y : a.spread[l].x, a.d) > kWindowAny) ((volatile int*)a.tight)[m] = 1;
     };
     for (int i = 0; i < n; i++) {
         const int64_t row = a.row0 + first + i;

@@ -250,13 +250,13 @@ struct ListArgs {
     float* row_norm;            // [N]
     ListBound* bound;           // [nlist]
     void* hi;                   // [N, d] rows rounded to binary16, or nullptr
-    float* spread;              // [nlist] see k_list_bounds
+    float2* spread;             // [nlist] deviations of the scores of a list's rows, by metric (list_spread)
     int* tight;                 // host memory, by metric: set where a list's window is too wide (see score_window)
     int whole0, whole1;         // the lists of which all rows are new: their bounds start anew (none where bounds may only grow)
     u64 count;                  // of this replacement, larger than all before
 };
 hipError_t launch_list_bounds(const ListArgs& a, hipStream_t s);
-constexpr int kWindowShare = 16;           // one row in so many in lists with wide windows: see score_window
+constexpr int kWindowShare = 64;           // one row in so many in lists with wide windows: see score_window
 hipError_t launch_wide_windows(const ListArgs& a, int* wide, hipStream_t s);
 hipError_t launch_read_hits(unsigned long long* hits, int64_t n, int64_t* out, int reset, hipStream_t s);
 hipError_t launch_lists_of_rows(const int32_t* rows, int64_t n, const int* list_off, int nlist, int32_t* out, hipStream_t s);

@@ -919,18 +919,18 @@ def test_both_parts_are_multiplied_where_bounds_tell_little():
     base, noise = torch.randn(1, d, generator=g, device="cuda"), torch.randn(N, d, generator=g, device="cuda")
     q = torch.randn(nq, d, generator=g, device="cuda")
 
-    def tiles(ix, metric):
+    def tiles(ix, metric, rows=N):
         ix.scan(q, torch.zeros(nq, 1, dtype=torch.int32, device="cuda"), 10, metric)
         torch.cuda.synchronize()
         ws = ix.workspace(nq, 1, 10)
         s = hr.hr_ivf_stats(ix.handle, ws, ws.numel(), nq, 1, 10)
-        return s["items"] // ((N + s["seg_rows"] - 1) // s["seg_rows"])
+        return s["items"] // ((rows + s["seg_rows"] - 1) // s["seg_rows"])
 
     def load(rows, off=(0, N)):
         return hr.IvfIndex(base.expand(len(off) - 1, d).contiguous(), torch.tensor(off), rows.contiguous(), torch.arange(len(rows), device="cuda"))
 
-    # windows of 0.04 and 0.03 deviations; 0.5 and 4; 4 and 270; an offset that all have; equal rows (both parts tell no more); rows of zeros
-    for rows, ip, l2 in ((noise, 1, 1), (base + 0.08 * noise, 1, 2), (base + 0.01 * noise, 2, 2), (noise * 0.05 + 10, 2, 2), (base.expand(N, d), 1, 1), (0 * noise, 1, 1)):
+    # windows of 0.02 and 0.03 deviations; 0.24 and 1.2; 3.6 and 270; an offset that all have; equal rows (both parts tell no more); rows of zeros
+    for rows, ip, l2 in ((noise, 1, 1), (base + 0.15 * noise, 1, 2), (base + 0.01 * noise, 2, 2), (noise * 0.05 + 10, 2, 2), (base.expand(N, d), 1, 1), (0 * noise, 1, 1)):
         ix = load(rows)
         assert (tiles(ix, "ip"), tiles(ix, "l2")) == (ip, l2)
         ix.close()
@@ -948,11 +948,11 @@ def test_both_parts_are_multiplied_where_bounds_tell_little():
         torch.cuda.synchronize()
         assert (tiles(ix, "ip"), tiles(ix, "l2")) == (want, want)
         ix.close()
-    # one list in twenty whose window is a little wide (1.2 deviations) does not count, one in ten does
-    many = torch.cat([noise] * 19 + [base + 0.03 * noise])
-    ix = load(many, list(range(0, 20 * N + 1, N)))
-    assert tiles(ix, "ip") == 1
-    ix.close()
-    ix = load(torch.cat([noise] * 9 + [base + 0.03 * noise]), list(range(0, 10 * N + 1, N)))
-    assert tiles(ix, "ip") == 2
-    ix.close()
+    # rows as long as each other: one list in a hundred whose window is a little wide (1.0 deviations) does not count, one in fifty does; one
+    # of 4 always
+    for lists, step, want in ((100, 0.163, 1), (50, 0.163, 2), (100, 0.08, 2)):
+        rows = torch.randn(64 * lists, d, generator=g, device="cuda")
+        rows[-64:] = 32 * torch.nn.functional.normalize(base + step * rows[-64:], dim=1)
+        ix = load(rows, list(range(0, 64 * lists + 1, 64)))
+        assert tiles(ix, "ip", 64) == want
+        ix.close()
