@@ -291,18 +291,23 @@ __device__ __forceinline__ void list_spread(const ListArgs& a, int l)
         norm += x * x;
         other += y * y;
     }
-    dist = wave_sum(dist);
-    norm = sqrtf(wave_sum(norm));
-    other = sqrtf(wave_sum(other));
-    if (lane == 0) { s_dist[wave] = dist; s_apart[wave] = fabsf(norm - other); s_norm[wave] = norm; }
+    dist = wave_add(dist);
+    norm = sqrtf(wave_add(norm));
+    other = sqrtf(wave_add(other));
+    if (lane == 63) { s_dist[wave] = dist; s_apart[wave] = fabsf(norm - other); s_norm[wave] = norm; }
     __syncthreads();
     if (threadIdx.x >= 64) return;
-    // (the median ones, to all lanes)
+    // (the median ones, to all lanes; none is negative, so their bits are in order)
     auto median = [&](const float* v) __attribute__((always_inline)) {
-        const float mine = lane < pairs ? v[lane] : __builtin_inff();
+        const uint32_t mine = lane < pairs ? __builtin_bit_cast(uint32_t, v[lane]) : ~0u;
         int rank = 0;
-        for (int t = 0; t < pairs; t++) rank += v[t] < mine || (v[t] == mine && t < lane) ? 1 : 0;
-        return __shfl(mine, __builtin_ctzll(__builtin_amdgcn_ballot_w64(lane < pairs && rank == pairs / 2) | 1ull << 63));
+#pragma unroll
+        for (int t = 0; t < kBoundWaves; t++) {
+            const uint32_t other = __builtin_amdgcn_readlane(mine, t);
+            rank += other < mine || (other == mine && t < lane) ? 1 : 0;
+        }
+        const unsigned long long at = __builtin_amdgcn_ballot_w64(lane < pairs && rank == pairs / 2);     // (one lane)
+        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(mine, __builtin_ctzll(at)));
     };
     const float spread2 = 0.5f * median(s_dist), apart = 1.05f * median(s_apart), typical = median(s_norm);
     const float l2 = typical > 0.f ? 1.4f * spread2 / (sqrtf((float)a.d) * typical) : 0.f, ip = sqrtf(l2 * l2 + apart * apart);
@@ -318,7 +323,7 @@ __device__ __forceinline__ void list_spread(const ListArgs& a, int l)
 // rows a wave, one after the other) and how far its rows lie apart (the workgroups behind).  Squares are not negative, so their bits are
 // in order; NaN counts as infinite.  Additions to one address go one after the other, 25 ns each, and where all rows of a list are
 // new every one of them is above what is known: a workgroup asks once for what its sixteen waves found of a list (every wave for
-// itself, the loads of a row one after the other: lists of some 400 rows of d = 256 swapped in 13.4 us each, now 6.6).
+// itself, the loads of a row one after the other: lists of some 400 rows of d = 256 swapped in 13.4 us each, now 7.2).
 __global__ __launch_bounds__(kBoundWaves * 64) void k_list_bounds(ListArgs a, int each, unsigned blocks)
 {
     if (blockIdx.x >= blocks) {
