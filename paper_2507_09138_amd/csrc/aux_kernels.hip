@@ -683,9 +683,9 @@ hipError_t launch_bucketing(const BucketArgs& a, hipStream_t s)
     }
     hipError_t e = launch_bucketing_before(a, s);
     if (e != hipSuccess) return e;
+    // (up to kWholeLists lists this rides on the seeding)
     const int per = (a.nlist + 1023) / 1024;
-    if (per <= 4) hipLaunchKernelGGL((k_bucket_scan<4, false>), dim3(1), dim3(1024), 0, s, a);
-    else if (per <= 16) hipLaunchKernelGGL((k_bucket_scan<16, false>), dim3(1), dim3(1024), 0, s, a);
+    if (per <= 16) hipLaunchKernelGGL((k_bucket_scan<16, false>), dim3(1), dim3(1024), 0, s, a);
     else hipLaunchKernelGGL((k_bucket_scan<0, false>), dim3(1), dim3(1024), 0, s, a);
     e = hipGetLastError();
     return e != hipSuccess ? e : launch_bucketing_behind(a, s);
