@@ -280,11 +280,13 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, boo
     auto sizes = [&](int dtype) {
         p.cap_s = lim.cap > 0 ? lim.cap : sel_cap(dtype, k);
         p.cw_s = tile_cols(dtype, ix->d);
-        // Many neighbours and few queries per list, float32 rows: what a wave does is select, so it has eight queries instead of 16.  Tiles
-        // of 128 and 64: 700 queries over 16 of 512 lists, k 50, d = 768 277 and 245 us, d = 64 322 and 295, 3000 queries, k 100, 594
-        // and 549, 607 and 614; 662 over 6 of 1703, k 23, 268 and 226; over 16 of 256 lists (187 queries per list) 671 and 817, 801 and 1089.
+        // Many neighbours and few queries per list, float32 rows: tiles of half the queries, half the slots.  Up to 32 queries per list
+        // they take as long (a tile that is at most half full goes on all waves either way); at 48 tiles of 128 and 64, k 20, 512 lists: d
+        // = 64 170 and 149 us, 128 180 and 165, 256 212 and 201, 768 373 and 391, 1024 270 and 264, 4096 lists, d = 64, 638 and 649; at
+        // 64 175 and 175, 195 and 196, 223 and 231, 424 and 479, 302 and 306, 747 and 843; at 96 183 and 213, d = 256 242 and 295, 768 495
+        // and 620, 1024 366 and 408; k 100 alike.
         const int narrow = dtype == HR_F32 && k > kFullTileK ? p.cw_s / 2 : p.cw_s;
-        if (pairs <= 96 * nlist) p.cw_s = narrow;
+        if (pairs <= 48 * nlist) p.cw_s = narrow;
         // Work items: sum over probed lists of segments x query tiles.  Segments have at least C / item_target rows, C =
         // sum of rows x tiles, so there are at most item_target items plus one per (list, tile) for the ragged ends.
         // Result slots: sum of segments x bucket width <= cw x item_target, plus one per pair for the ragged ends.  (In a

@@ -764,10 +764,10 @@ def test_workspace_never_says_less_for_more(dtype, d, nlist, N, zipf):
         assert sizes == sorted(sizes)
     for k in (10, 13, 20, 30, 100):
         for nprobe in (1, 16, 128):
-            edge = 96 * nlist // nprobe
+            edge = 48 * nlist // nprobe
             sizes = [size(nq, nprobe, k) for nq in (edge // 2, edge - 1, edge, edge + 1, edge + 2, edge + edge // 3, 2 * edge)]
             assert sizes == sorted(sizes)
-        for nq in (500, 96 * nlist // 64):
+        for nq in (500, 48 * nlist // 64):
             sizes = [size(nq, nprobe, k) for nprobe in (1, 2, 16, 63, 64, 65, 100, 128, 256)]
             assert sizes == sorted(sizes)
     q = torch.randn(1024, d, generator=g, device="cuda")
