@@ -589,8 +589,10 @@ def test_full_tiles_of_short_lists(storage, rows, nlist, nq, nprobe):
 @pytest.mark.parametrize("spread,scale", [(1e-5, 1.0), (1e-2, 1.0), (1.0, 1e-6), (1e-5, 1e-12)])
 def test_float32_rows_that_binary16_cannot_tell_apart(tables, d, N, nlist, nq, k, metric, spread, scale):
     """Rows so close to each other, or so small, that all of them, or many, lie within what rounding to binary16 may have taken:
-    selection buffers overflow with them in the scan and in the merge (one wave and four), and the best are still those of
-    float64.  The queries start at an odd address; a carried result goes on being merged exactly."""
+    selection buffers overflow with them in the scan and in the merge (one wave and four).  As many rows as there are, each once, with
+    the scores that float64 gives them, at a spread of 1e-2 and more those of its best (closer rows are as good as equal in float32:
+    test_rows_that_differ_by_less_than_binary16_rounds plants what tells them apart).  The queries start at an odd address; a
+    carried result goes on being merged exactly."""
     hr = _hr()
     g = torch.Generator(device="cuda")
     g.manual_seed(N + k)
@@ -956,3 +958,46 @@ def test_both_parts_are_multiplied_where_bounds_tell_little():
         ix = load(rows, list(range(0, 64 * lists + 1, 64)))
         assert tiles(ix, "ip", 64) == want
         ix.close()
+
+
+@pytest.mark.parametrize("tables", [False, True])
+@pytest.mark.parametrize("share", [1, 3])
+@pytest.mark.parametrize("d,nq,k,metric", [(64, 3, 1, "ip"), (768, 5, 10, "l2"), (1024, 130, 24, "ip"), (512, 33, 25, "l2"), (128, 40, 64, "ip"), (256, 20, 100, "l2"), (768, 1100, 128, "ip"),
+                                           (1024, 1030, 37, "l2")])
+def test_rows_that_differ_by_less_than_binary16_rounds(tables, share, d, nq, k, metric):
+    """Rows that are all the same in binary16 and differ along the queries by a thousand times what float32 sums may be off: the best of
+    them are found, whether they are all of a list (both parts are multiplied) or the third of it that the queries are closest to
+    (every one of them is within what the bounds leave, in the scan and in the merge); also list by list with a carried result."""
+    hr = _hr()
+    nlist, N = 4, 6000
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + k)
+    base = (1.1 + 0.4 * torch.rand(1, d, generator=g, device="cuda")).half().float()        # (steps of 2^-10: rounding takes up to 2^-11)
+    along = torch.randint(0, 2, (1, d), generator=g, device="cuda").float() * 2 - 1
+    step = torch.rand(N, 1, generator=g, device="cuda") * 2.0 ** -11.5
+    vec = base + step * along
+    close = torch.arange(N, device="cuda") % (N // nlist) < N // nlist // share
+    vec = torch.where(close[:, None], vec, -base + torch.randn(N, d, generator=g, device="cuda")).contiguous()
+    assert torch.equal(vec[close].half().float(), base.expand(int(close.sum()), d))
+    ids = torch.randperm(N, generator=g, device="cuda")
+    ix = hr.IvfIndex(base.expand(nlist, d).contiguous(), torch.linspace(0, N, nlist + 1).long(), vec, ids, row_tables=tables)
+    q = base + along * (0.5 + torch.rand(nq, 1, generator=g, device="cuda"))
+    probe = torch.arange(nlist, dtype=torch.int32, device="cuda").repeat(nq, 1)
+    key = _keys(q.double(), vec.double(), metric)
+    best = torch.topk(key, k, dim=1).values
+    row = torch.empty_like(ids)
+    row[ids] = torch.arange(N, device="cuda")
+    # float32 sums of d products in chains of at most d/64 + 6 steps, and a norm: 2^-24 of |q||x| (+ |x|^2) for each
+    size = q.double().norm(dim=1, keepdim=True) * vec.double().norm(dim=1).max() * 2 + (vec.double().norm(dim=1).max() ** 2 if metric == "l2" else 0)
+    tol = 2 * size * 2.0 ** -24 * (d / 64 + 6)
+    some = key[:, close][:, torch.randint(0, int(close.sum()), (k,), generator=g, device="cuda")].sort(dim=1, descending=True).values
+    assert bool(((some - best).abs().max(1, keepdim=True).values > 4 * tol).all())       # (any k of the close rows would not do)
+    state = ix.new_state_rows(nq, k)
+    for x in range(nlist):
+        ix.scan_step_rows(q, probe[:, x:x + 1].contiguous(), state, metric)
+    for found, score in (ix.search(q, nlist, k, metric), ix.scan(q, probe, k, metric), state[:2]):
+        assert bool(((key.gather(1, row[found]) - best).abs() <= tol).all())
+        want = best if metric == "ip" else (q.double() ** 2).sum(1, keepdim=True) - best
+        assert bool(((score.double() - want).abs() <= 2 * tol).all())
+        assert all(len(set(r)) == k for r in found.cpu().tolist())
+    ix.close()
