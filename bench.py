@@ -20,21 +20,13 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 F16_MFMA_PEAK_TFLOPS = 2500.0      # dense binary16 / bfloat16 MFMA
-F32_PEAK_TFLOPS = 157.3            # float32 (vector or MFMA): what float32 storage is priced against
 ESIZE = {"f32": 4, "f16": 2, "bf16": 2}
-
-
-def mfma_peak(cfg, ix):
-    """float32 lists are a float32 contraction to the caller (that its candidates come from a binary16 product on the matrix
-    pipes is this library's choice): its 2 d flops per (query, row) pair are priced against the float32 peak; 16-bit lists
-    against the dense 16-bit MFMA peak."""
-    return F32_PEAK_TFLOPS if cfg.dtype == "f32" else F16_MFMA_PEAK_TFLOPS
 
 
 def operand_name(cfg, ix):
     """The type the list scan multiplies in (accumulation is float32 throughout)."""
     if cfg.dtype == "f32":
-        return "f16"                                # rows and queries rounded to binary16; exact float32 scores of the candidates
+        return "f16"                                # rows and queries rounded to binary16 (these rows are apart); exact float32 scores of the candidates
     if cfg.dtype == "bf16":
         return "f16" if ix.row_tables else "bf16"   # binary16 row table asked for at load, else bfloat16 rows x (hi, lo) query
     return "f16"
@@ -179,7 +171,7 @@ def bench_width_split(args, cfg, hr, ix, idx, rounds, metric):
     flops = 2.0 * cfg.d * pair_rows
     tf = flops / (scan_ms * 1e-3) / 1e12
     gbs = nbytes / (scan_ms * 1e-3) / 1e9
-    peak = mfma_peak(cfg, ix)
+    peak = F16_MFMA_PEAK_TFLOPS
     ix.close()
     roof = ({"bound": "mfma", "achieved": tf, "peak": peak, "unit": "TFLOP/s", "frac": tf / peak} if wide else
             {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS})
@@ -454,8 +446,8 @@ def main():
                      "traffic": traffic, "traffic_source": traffic_src, "scan_ms_avg": scan_ms, "launches_timed": n_timed,
                      "algorithmic_bytes_per_launch": scan_bytes,
                      "mfma_tflops": scan_flops / (scan_ms * 1e-3) / 1e12 if scan_ms > 0 else 0.0,
-                     "mfma_frac": (scan_flops / (scan_ms * 1e-3) / 1e12 / mfma_peak(cfg, ix)) if scan_ms > 0 else 0.0,
-                     "mfma_peak_tflops": mfma_peak(cfg, ix),
+                     "mfma_frac": (scan_flops / (scan_ms * 1e-3) / 1e12 / F16_MFMA_PEAK_TFLOPS) if scan_ms > 0 else 0.0,
+                     "mfma_peak_tflops": F16_MFMA_PEAK_TFLOPS,
                      "mfma_flops_executed_over_algorithmic": executed_rows / max(pair_rows, 1)},
     }
     if len(rounds) > 1:

@@ -68,7 +68,7 @@ enum {
  * centroids, list_vectors and list_ids are BORROWED: they must stay valid and unchanged until
  * hr_ivf_free.  The library allocates (hipMalloc) derived tables: device copies of the offsets,
  * 4 bytes per row / per centroid of squared norms, the centroids as two binary16 tables, 8 bytes
- * per list of access counters (HR_F32: 24 more of bounds).  Nothing the size of list_vectors, unless the caller asks for it:
+ * per list of access counters (HR_F32: 16 more of bounds).  Nothing the size of list_vectors, unless the caller asks for it:
  * with dtype = HR_F32 | HR_LOAD_ROW_TABLES the rows are also kept rounded to binary16 (N*d*2 bytes, half of
  * list_vectors) for the scan to read, which looks for candidates with the rounded rows either way and scores those that
  * may be among the best from the float32 rows: the same results, faster.  Where rows are so close to each other, or so long
@@ -224,8 +224,8 @@ int hr_ivf_split_probes(const hr_ivf_index* index, const int32_t* probe_ids, int
  * row_end-1 in list_vectors (a cluster loaded asynchronously into the place of another one of
  * the same length: the index loading interface of Section 5), recompute what the library
  * derives from them (squared norms; with HR_F32 what bounds the scores of a list's rows, which searches with either
- * metric rely on; the binary16 row tables of HR_LOAD_ROW_TABLES).  Those bounds start anew for a list whose rows are all in
- * the range; of a list in part of it, or by a captured call, they can only become wider, so searches of a list that once held a
+ * metric rely on; the binary16 row tables of HR_LOAD_ROW_TABLES).  Those bounds start anew for a list of 16 rows or more that
+ * are all in the range and half as long, or shorter; else they can only become wider, so searches of a list that once held a
  * very long row may take longer until all of it is replaced in one call (the results are the same).  Enqueued on
  * `stream`: put it behind the copy, and the next search behind it.  list_ids is read at search time
  * and needs no refresh; list_offsets cannot change.  Only with a binary16 table of bfloat16 rows the

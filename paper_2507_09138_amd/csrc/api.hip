@@ -144,7 +144,6 @@ struct hr_ivf_index {
     int *h_over, *d_over;  // their address on the host and on the device
     std::atomic<uint64_t> over_used;
     ListBound* d_list_bound;      // float32 lists: [nlist] what scan_slack needs to know of the list's rows, else null
-    std::atomic<uint64_t> replaced;   // float32 lists: refreshes so far (ListArgs::count)
     float2* d_spread;      // float32 lists: [nlist] how far the scores of their rows are apart (list_spread), else null
     // float32 lists: host memory that kernels write, its address there and on the device: [metric] some list's bounds tell little
     int *h_tight, *d_tight;
@@ -285,7 +284,7 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, boo
         // = 64 170 and 149 us, 128 180 and 165, 256 212 and 201, 768 373 and 391, 1024 270 and 264, 4096 lists, d = 64, 638 and 649; at
         // 64 175 and 175, 195 and 196, 223 and 231, 424 and 479, 302 and 306, 747 and 843; at 96 183 and 213, d = 256 242 and 295, 768 495
         // and 620, 1024 366 and 408; k 100 alike.
-        const int narrow = dtype == HR_F32 && k > kFullTileK ? p.cw_s / 2 : p.cw_s;
+        const int narrow = stored_f32(dtype) && cols_per_set(dtype, ix->d) == 16 && k > kFullTileK ? p.cw_s / 2 : p.cw_s;
         if (pairs <= 48 * nlist) p.cw_s = narrow;
         // Work items: sum over probed lists of segments x query tiles.  Segments have at least C / item_target rows, C =
         // sum of rows x tiles, so there are at most item_target items plus one per (list, tile) for the ragged ends.
@@ -460,7 +459,7 @@ int hr_ivf_load(const float* centroids, const int64_t* list_offsets, const void*
             if (!ix->d_vec_hi) (void)hipGetLastError();          // (not an error of the load: the other path is taken)
         }
         const ListArgs a{(const float*)list_vectors, 0, N, ix->d_list_off, (int)nlist, d, 0, (int)nlist, ix->d_row_norm, ix->d_list_bound,
-                         ix->d_vec_hi, ix->d_spread, ix->d_tight, 0, 0, 0};
+                         ix->d_vec_hi, ix->d_spread, ix->d_tight, 0, 0};
         e = hipMemsetAsync(ix->d_list_bound, 0, (size_t)nlist * sizeof(ListBound), s);
         if (e == hipSuccess) e = hipMemsetAsync(ix->d_spread, 0x7f, (size_t)nlist * sizeof(float2), s);      // (far apart, until they are known)
         if (e == hipSuccess) e = launch_list_bounds(a, s);
@@ -1060,17 +1059,12 @@ int hr_ivf_refresh_rows(hr_ivf_index* ix, int64_t row_begin, int64_t row_end, vo
         return HR_OK;
     }
     if (ix->d_list_bound) {
-        // Bounds start anew in lists of which every row is replaced; in the others they only grow, as rows that were replaced count on.
-        // (So they do in a graph: it replays one count, whatever the calls beside it have reached.)
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(s, &capture) != hipSuccess) { capture = hipStreamCaptureStatusActive; (void)hipGetLastError(); }
+        // the lists that have some of the rows, and those of which all rows are new
         const int *off = ix->h_list_off, *end = off + ix->nlist + 1;
-        const bool anew = capture == hipStreamCaptureStatusNone;
-        const int whole0 = anew ? (int)(std::lower_bound(off, end, (int)row_begin) - off) : 0;
-        const int whole1 = anew ? (int)(std::upper_bound(off, end, (int)row_end) - off) - 1 : 0;
         const int l0 = (int)(std::upper_bound(off, end, (int)row_begin) - off) - 1, l1 = (int)(std::lower_bound(off, end, (int)row_end) - off);
+        const int whole0 = (int)(std::lower_bound(off, end, (int)row_begin) - off), whole1 = (int)(std::upper_bound(off, end, (int)row_end) - off) - 1;
         const ListArgs a{(const float*)ix->vectors, row_begin, n, ix->d_list_off, (int)ix->nlist, ix->d, l0, l1 - l0, ix->d_row_norm, ix->d_list_bound,
-                         ix->d_vec_hi, ix->d_spread, ix->d_tight, whole0, whole1, ix->replaced.fetch_add(1) + 1};
+                         ix->d_vec_hi, ix->d_spread, ix->d_tight, whole0, whole1};
         HR_HIP(launch_list_bounds(a, s));
     } else
         HR_HIP(launch_row_norms(rows, ix->dtype, n, ix->d, ix->d_row_norm + row_begin, s));

@@ -267,42 +267,100 @@ hipError_t launch_wide_windows(const ListArgs& a, int* wide, hipStream_t s)
     return hipGetLastError();
 }
 
-constexpr int kBoundWaves = 16;
+constexpr int kBoundWaves = 8, kPairs = 16;
+// squared norms of row p and of what rounding it to binary16 leaves over (hi: its place in the table, or nullptr), four loads on their
+// way together
+__device__ __forceinline__ float2 row_squares(const float* p, _Float16* hi, int d, int lane)
+{
+    float sum = 0.f, left = 0.f;
+    for (int j0 = lane; j0 < d; j0 += 256) {
+        float x[4];
+#pragma unroll
+        for (int t = 0; t < 4; t++) x[t] = j0 + t * 64 < d ? p[j0 + t * 64] : 0.f;
+#pragma unroll
+        for (int t = 0; t < 4; t++) {
+            const _Float16 h = (_Float16)x[t];
+            const float r = x[t] - (float)h;
+            if (hi && j0 + t * 64 < d) hi[j0 + t * 64] = h;
+            sum += x[t] * x[t];
+            left += r * r;
+        }
+    }
+    return float2{wave_sum(sum), wave_sum(left)};
+}
+// their bits (NaN counts as infinite)
+__device__ __forceinline__ uint32_t square_bits(float v) { return __builtin_bit_cast(uint32_t, v < __builtin_inff() ? v : __builtin_inff()); }
+
 // How far apart the scores of the rows of list l are, in deviations for a query of norm 1, from 16 pairs of rows that are half a list from
-// each other (infinite for a list of fewer than 16 rows), a pair for each wave.  With squared distances, of a query that is as far
+// each other (infinite for a list of fewer than 16 rows), two for each wave.  With squared distances, of a query that is as far
 // from the rows as these are from each other: sqrt(2 / d) times half the median squared distance of a pair over the norm, whatever the
 // rows have in common; with the inner product, which is half of what the two norms leave of that distance, as far as the norms are as well (1.05: the
 // deviation of one from the median difference of two).
 __device__ __forceinline__ void list_spread(const ListArgs& a, int l)
 {
-    __shared__ float s_dist[kBoundWaves], s_apart[kBoundWaves], s_norm[kBoundWaves];
+    __shared__ float s_dist[kPairs], s_apart[kPairs], s_norm[kPairs];
+    __shared__ float s_longest;
+    __shared__ uint32_t s_most[2];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int first = a.list_off[l], half = (a.list_off[l + 1] - first) / 2, pairs = min(half, kBoundWaves);
-    if (half < kBoundWaves / 2) {
+    const int first = a.list_off[l], half = (a.list_off[l + 1] - first) / 2, pairs = min(half, kPairs);
+    if (half < kPairs / 2) {
         if (threadIdx.x == 0) a.spread[l] = float2{__builtin_inff(), __builtin_inff()};
         return;
     }
-    const float* const p = a.rows + (first + (int64_t)min(wave, pairs - 1) * half / pairs) * a.d;
-    float dist = 0.f, norm = 0.f, other = 0.f;
-#pragma unroll 4
-    for (int i = lane; i < a.d; i += 64) {
-        const float x = p[i], y = p[i + (size_t)half * a.d];
-        dist += (x - y) * (x - y);
-        norm += x * x;
-        other += y * y;
+    const bool whole = l >= a.whole0 && l < a.whole1;
+    // (one thread asks: other workgroups may raise it meanwhile, and the branch on it has barriers)
+    if (threadIdx.x == 0) s_longest = whole ? bound_value(__hip_atomic_load(&a.bound[l].norm2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) : 0.f;
+    constexpr int P = kPairs / kBoundWaves;
+    const float* p[P];
+    float dist[P], norm[P], other[P];
+#pragma unroll
+    for (int j = 0; j < P; j++) {
+        p[j] = a.rows + (first + (int64_t)min(wave * P + j, pairs - 1) * half / pairs) * a.d;
+        dist[j] = norm[j] = other[j] = 0.f;
     }
-    dist = wave_add(dist);
-    norm = sqrtf(wave_add(norm));
-    other = sqrtf(wave_add(other));
-    if (lane == 63) { s_dist[wave] = dist; s_apart[wave] = fabsf(norm - other); s_norm[wave] = norm; }
+#pragma unroll 4
+    for (int i = lane; i < a.d; i += 64)
+#pragma unroll
+        for (int j = 0; j < P; j++) {
+            const float x = p[j][i], y = p[j][i + (size_t)half * a.d];
+            dist[j] += (x - y) * (x - y);
+            norm[j] += x * x;
+            other[j] += y * y;
+        }
+#pragma unroll
+    for (int j = 0; j < P; j++) {
+        dist[j] = wave_add(dist[j]);
+        norm[j] = sqrtf(wave_add(norm[j]));
+        other[j] = sqrtf(wave_add(other[j]));
+        if (lane == 63) { s_dist[wave * P + j] = dist[j]; s_apart[wave * P + j] = fabsf(norm[j] - other[j]); s_norm[wave * P + j] = norm[j]; }
+    }
     __syncthreads();
+    // Bounds only grow, row by row.  Where all rows of a list are new and its bound is that of rows twice as long as those met here, it
+    // starts anew, from all of them.  (In whichever order the waves that see the rows one by one raise it: none is above this one.)
+    if (whole) {
+        float met = 0.f;
+        for (int t = 0; t < kPairs; t++) met = fmaxf(met, s_norm[t]);
+        if (s_longest > 4.0f * met * met) {
+            if (threadIdx.x == 0) s_most[0] = s_most[1] = 0;
+            __syncthreads();
+            uint32_t most = 0, most_left = 0;
+            for (int64_t row = first + wave; row < a.list_off[l + 1]; row += kBoundWaves) {
+                const float2 v = row_squares(a.rows + row * a.d, nullptr, a.d, lane);
+                most = max(most, square_bits(v.x));
+                most_left = max(most_left, square_bits(v.y));
+            }
+            if (lane == 0) { atomicMax(&s_most[0], most); atomicMax(&s_most[1], most_left); }
+            __syncthreads();
+            if (threadIdx.x == 0) { atomicExch(&a.bound[l].norm2, s_most[0]); atomicExch(&a.bound[l].left2, s_most[1]); }
+        }
+    }
     if (threadIdx.x >= 64) return;
     // (the median ones, to all lanes; none is negative, so their bits are in order)
     auto median = [&](const float* v) __attribute__((always_inline)) {
         const uint32_t mine = lane < pairs ? __builtin_bit_cast(uint32_t, v[lane]) : ~0u;
         int rank = 0;
 #pragma unroll
-        for (int t = 0; t < kBoundWaves; t++) {
+        for (int t = 0; t < kPairs; t++) {
             const uint32_t other = __builtin_amdgcn_readlane(mine, t);
             rank += other < mine || (other == mine && t < lane) ? 1 : 0;
         }
@@ -319,26 +377,23 @@ __device__ __forceinline__ void list_spread(const ListArgs& a, int l)
     }
 }
 
-// float32 rows: the squared norm of every row and its image in the table, and of every list its bounds (the first `blocks` workgroups, `each`
-// rows a wave, one after the other) and how far its rows lie apart (the workgroups behind).  Squares are not negative, so their bits are
-// in order; NaN counts as infinite.  Additions to one address go one after the other, 25 ns each, and where all rows of a list are
-// new every one of them is above what is known: a workgroup asks once for what its sixteen waves found of a list (every wave for
-// itself, the loads of a row one after the other: lists of some 400 rows of d = 256 swapped in 13.4 us each, now 7.2).
+// float32 rows: how far the scores of every list are apart (the first `blocks` workgroups, whose chain is the longest), and the squared norm of
+// every row, its image in the table and the bounds of its list (the others, `each` rows a wave, one after the other, asking once per
+// list for all of them).  A refresh of some 400 rows of d = 256 takes 5.8 us (6.0 without the spread, one load of a row after the other).
 __global__ __launch_bounds__(kBoundWaves * 64) void k_list_bounds(ListArgs a, int each, unsigned blocks)
 {
-    if (blockIdx.x >= blocks) {
-        for (unsigned l = blockIdx.x - blocks; l < (unsigned)a.lists; l += gridDim.x - blocks) {
+    if (blockIdx.x < blocks) {
+        for (unsigned l = blockIdx.x; l < (unsigned)a.lists; l += blocks) {
             list_spread(a, a.l0 + (int)l);
             __syncthreads();
         }
         return;
     }
-    __shared__ int s_list[kBoundWaves];
-    __shared__ uint32_t s_most[kBoundWaves], s_left[kBoundWaves];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t first = ((int64_t)blockIdx.x * kBoundWaves + wave) * each;
+    const int lane = threadIdx.x & 63;
+    const int64_t first = ((int64_t)(blockIdx.x - blocks) * kBoundWaves + (threadIdx.x >> 6)) * each;
+    if (first >= a.nrows) return;
     _Float16* const hi = (_Float16*)a.hi;
-    const int n = (int)min((int64_t)each, a.nrows - first);     // (none: 0 or less)
+    const int n = (int)min((int64_t)each, a.nrows - first);
     int lo = 0;                                                 // list of the row: the last one that starts at it or before
     for (int end = a.nlist; end - lo > 1;) {
         const int step = (end - lo + 63) >> 6, at = lo + lane * step;
@@ -347,61 +402,29 @@ __global__ __launch_bounds__(kBoundWaves * 64) void k_list_bounds(ListArgs a, in
         end = min(end, lo + step);
     }
     uint32_t most = 0, most_left = 0;
-    bool any = false;
-    auto bits = [](float v) __attribute__((always_inline)) { return __builtin_bit_cast(uint32_t, v < __builtin_inff() ? v : __builtin_inff()); };
-    auto raise = [&](u64* at, uint32_t v, bool whole) __attribute__((always_inline)) {
-        if (whole) { atomicMax(at, bound_of(v, a.count)); return; }
-        const u64 now = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), then = bound_of(v, now >> 24);
-        if (then > now) atomicMax(at, then);
+    // (additions to one address go one after the other: most rows are below what is known already)
+    auto raise = [](uint32_t* at, uint32_t v) __attribute__((always_inline)) {
+        if (v > __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(at, v);
     };
-    auto report = [&](int l, uint32_t norm2, uint32_t left2) __attribute__((always_inline)) {
-        const bool whole = l >= a.whole0 && l < a.whole1;
-        raise(&a.bound[l].norm2, norm2, whole);
-        raise(&a.bound[l].left2, left2, whole);
-        // (a list of which all rows are new: its spread may be that of the rows before)
-        for (int m = 0; m < 2 && !whole; m++)
-            if (score_window(__builtin_bit_cast(float, norm2), __builtin_bit_cast(float, left2), m == HR_METRIC_L2 ? a.spread[l].y : a.spread[l].x, a.d) > kWindowAny) ((volatile int*)a.tight)[m] = 1;
+    auto report = [&]() __attribute__((always_inline)) {
+        if (lane == 0) {
+            raise(&a.bound[lo].norm2, most);
+            raise(&a.bound[lo].left2, most_left);
+            // (a list of which all rows are new: its spread may be that of the rows before)
+            for (int m = 0; m < 2 && !(lo >= a.whole0 && lo < a.whole1); m++)
+                if (score_window(bound_value(most), bound_value(most_left), m == HR_METRIC_L2 ? a.spread[lo].y : a.spread[lo].x, a.d) > kWindowAny) ((volatile int*)a.tight)[m] = 1;
+        }
+        most = most_left = 0;
     };
     for (int i = 0; i < n; i++) {
         const int64_t row = a.row0 + first + i;
-        while (row >= a.list_off[lo + 1]) {
-            if (any && lane == 0) report(lo, most, most_left);
-            lo++;
-            most = most_left = 0;
-            any = false;
-        }
-        const float* p = a.rows + row * a.d;
-        float sum = 0.f, left = 0.f;
-        // (four loads on their way together)
-        for (int j0 = lane; j0 < a.d; j0 += 256) {
-            float x[4];
-#pragma unroll
-            for (int t = 0; t < 4; t++) x[t] = j0 + t * 64 < a.d ? p[j0 + t * 64] : 0.f;
-#pragma unroll
-            for (int t = 0; t < 4; t++) {
-                const _Float16 h = (_Float16)x[t];
-                const float r = x[t] - (float)h;
-                if (hi && j0 + t * 64 < a.d) hi[row * a.d + j0 + t * 64] = h;
-                sum += x[t] * x[t];
-                left += r * r;
-            }
-        }
-        sum = wave_sum(sum);
-        left = wave_sum(left);
-        if (lane == 0) a.row_norm[row] = sum;
-        most = max(most, bits(sum));
-        most_left = max(most_left, bits(left));
-        any = true;
+        while (row >= a.list_off[lo + 1]) { if (most) report(); lo++; }
+        const float2 v = row_squares(a.rows + row * a.d, hi ? hi + row * a.d : nullptr, a.d, lane);
+        if (lane == 0) a.row_norm[row] = v.x;
+        most = max(most, square_bits(v.x));
+        most_left = max(most_left, square_bits(v.y));
     }
-    if (lane == 0) { s_list[wave] = any ? lo : -1; s_most[wave] = most; s_left[wave] = most_left; }
-    __syncthreads();
-    // (the lists of the waves are in order: the first wave of each asks for all of them)
-    if (threadIdx.x < kBoundWaves) {
-        const int l = s_list[threadIdx.x];
-        if (l < 0 || (threadIdx.x > 0 && s_list[threadIdx.x - 1] == l)) return;
-        for (int t = threadIdx.x; t < kBoundWaves && s_list[t] == l; t++) { most = max(most, s_most[t]); most_left = max(most_left, s_left[t]); }
-        report(l, most, most_left);
-    }
+    report();
 }
 
 hipError_t launch_list_bounds(const ListArgs& a, hipStream_t s)
@@ -410,9 +433,9 @@ hipError_t launch_list_bounds(const ListArgs& a, hipStream_t s)
     // (rows of a wave: as many as the device has no waves for; 84 queries with eight lists of some 70 rows of d = 256 swapped in, 16 rows
     // a wave 335 us a batch, one 181)
     const int each = a.nrows <= 16384 ? 1 : (a.nrows <= 262144 ? 4 : 16);
-    const unsigned blocks = (unsigned)((a.nrows + (int64_t)each * kBoundWaves - 1) / (each * kBoundWaves));
     // (a launch may not have 2^32 threads or more)
-    hipLaunchKernelGGL(k_list_bounds, dim3(blocks + (unsigned)std::min(a.lists, 1 << 20)), dim3(kBoundWaves * 64), 0, s, a, each, blocks);
+    const unsigned blocks = (unsigned)std::min(a.lists, 1 << 20), rows = (unsigned)((a.nrows + (int64_t)each * kBoundWaves - 1) / (each * kBoundWaves));
+    hipLaunchKernelGGL(k_list_bounds, dim3(blocks + rows), dim3(kBoundWaves * 64), 0, s, a, each, blocks);
     return hipGetLastError();
 }
 

@@ -54,7 +54,7 @@ __host__ __device__ constexpr int block_groups(int dtype, int d)
 __host__ __device__ constexpr int block_rows(int dtype, int d) { return kMfmaRows * block_groups(dtype, d); }
 
 // Most workgroups of eight waves on a compute unit: two where a wave can do with 128 registers (binary16 rows of up to 256
-// elements, of which d = 128 spills two registers, 12 bytes a lane; float32 rows of 128 with fragments fetched two steps at a
+// elements, of which d = 128 spills four registers, 20 bytes a lane; float32 rows of 128 with fragments fetched two steps at a
 // time; the other short ones could, with blocks of 32 rows instead of 64, which cost them 3 .. 7 % where two workgroups do not
 // pay).  The waves of one wait for each other at every pair of blocks; the other's fill the pipes meanwhile.  Where that pays is
 // in make_plan.  The bound on registers holds for all launches of the kernel: without it binary16 searches of d = 128 that put
@@ -69,7 +69,8 @@ __host__ __device__ constexpr int scan_group(int dtype, int ksteps)
 {
     // (blocks of several groups of rows: 8 or 16 k-steps in all)
     if (ksteps < 16) return stored_f32(dtype) ? 2 : 4;
-    // (what a long operand in two parts leaves: 253 of 256 registers at 24 k-steps, none spilled)
+    // (what a long operand in two parts leaves: 253 of 256 registers at 24 k-steps, none spilled; HR_F32X2, which selects too, spills
+    // three, 16 bytes a lane.  The bounded kernels keep some hundred scalar registers in vector ones, the others sixty.)
     if (operand_parts(dtype, ksteps * 32) == 2)
         return scan_split(dtype) ? (ksteps >= 24 ? 1 : 2) : (ksteps >= 24 ? 2 : 4);
     return (dtype == HR_F32 && ksteps >= 24) || (scan_split(dtype) && ksteps >= 32) ? 2 : 4;   // (256 registers per lane)
@@ -126,12 +127,9 @@ constexpr uint32_t kKeyNegInf = 0x007fffffu;   // enc_key(-inf)
 struct Cand { uint32_t key; uint32_t row; };
 
 // What bounds the scores of a list's rows: the largest squared norm of its rows and the largest squared norm of what rounding a row to
-// binary16 leaves over, each the upper 24 bits of a float (rounded up) below 40 bits that count the times that all rows of a list
-// were replaced: a later count is larger whatever the bound, so a bound starts anew without being cleared before.
-typedef unsigned long long u64;
-struct ListBound { u64 norm2, left2; };
-__host__ __device__ inline float bound_value(u64 b) { return __builtin_bit_cast(float, (uint32_t)(b << 8)); }
-__host__ __device__ inline u64 bound_of(uint32_t bits, u64 count) { return count << 24 | ((u64)bits + 255) >> 8; }
+// binary16 leaves over (their bits, which are in order, as squares are not negative)
+struct ListBound { uint32_t norm2, left2; };
+__host__ __device__ inline float bound_value(uint32_t b) { return __builtin_bit_cast(float, b); }
 
 // Arguments of the scan kernel (both uses: centroid table with all queries as one dense
 // bucket, and the inverted lists with the per-list buckets).
@@ -252,8 +250,7 @@ struct ListArgs {
     void* hi;                   // [N, d] rows rounded to binary16, or nullptr
     float2* spread;             // [nlist] deviations of the scores of a list's rows, by metric (list_spread)
     int* tight;                 // host memory, by metric: set where a list's window is too wide (see score_window)
-    int whole0, whole1;         // the lists of which all rows are new: their bounds start anew (none where bounds may only grow)
-    u64 count;                  // of this replacement, larger than all before
+    int whole0, whole1;         // the lists of which all rows are new
 };
 hipError_t launch_list_bounds(const ListArgs& a, hipStream_t s);
 constexpr int kWindowShare = 64;           // one row in so many in lists with wide windows: see score_window
