@@ -284,12 +284,13 @@ static Plan make_plan(const hr_ivf_index* ix, int64_t nq, int nprobe, int k, boo
         // = 64 170 and 149 us, 128 180 and 165, 256 212 and 201, 768 373 and 391, 1024 270 and 264, 4096 lists, d = 64, 638 and 649; at
         // 64 175 and 175, 195 and 196, 223 and 231, 424 and 479, 302 and 306, 747 and 843; at 96 183 and 213, d = 256 242 and 295, 768 495
         // and 620, 1024 366 and 408; k 100 alike.
-        const int narrow = stored_f32(dtype) && cols_per_set(dtype, ix->d) == 16 && k > kFullTileK ? p.cw_s / 2 : p.cw_s;
-        if (pairs <= 48 * nlist) p.cw_s = narrow;
+        const int narrow = stored_f32(dtype) && cols_per_set(dtype, ix->d) == 16 ? p.cw_s / 2 : p.cw_s;
+        if (k > kFullTileK && pairs <= 48 * nlist) p.cw_s = narrow;
         // Work items: sum over probed lists of segments x query tiles.  Segments have at least C / item_target rows, C =
         // sum of rows x tiles, so there are at most item_target items plus one per (list, tile) for the ragged ends.
         // Result slots: sum of segments x bucket width <= cw x item_target, plus one per pair for the ragged ends.  (In a
-        // workspace items are bounded for the narrower tiles that fewer queries would go in: the plan of a larger batch is never the smaller.)
+        // workspace items are bounded for the narrower tiles whatever the batch and k: the plan of a larger batch is never the smaller, and
+        // what lies before the slots lies at the same place for every k.)
         p.item_target = lim.item_target;
         p.item_cap = (int)(lim.item_target + pairs / (lim.by_length ? narrow : p.cw_s) + (pairs < nlist ? pairs : nlist) + 8);
         int64_t slots_most = (int64_t)p.cw_s * lim.item_target + pairs;
@@ -846,8 +847,7 @@ int hr_ivf_search_static(const hr_ivf_index* ix, const float* queries, int64_t n
     int dev = -1;
     HR_HIP(hipGetDevice(&dev));
     if (dev != ix->device) return fail(HR_ERR_ARG, "current device is %d, the index lives on device %d", dev, ix->device);
-    Plan p = static_plan(ix, nq, nprobe, k, both_parts(ix, metric));
-    if (p.total > (size_t)HR_STATIC_SCRATCH_BYTES) p = static_plan(ix, nq, nprobe, k, false);       // (narrower tiles)
+    const Plan p = static_plan(ix, nq, nprobe, k, both_parts(ix, metric));      // (both parts: tiles and buffers that are no larger)
     if (p.total > (size_t)HR_STATIC_SCRATCH_BYTES)
         return fail(HR_ERR_WORKSPACE, "this batch (nq=%lld, nprobe=%d, k=%d) needs %zu bytes of scratch, the static array has %zu: "
                                       "use hr_ivf_search with a workspace", (long long)nq, nprobe, k, p.total, (size_t)HR_STATIC_SCRATCH_BYTES);

@@ -772,6 +772,8 @@ def test_workspace_never_says_less_for_more(dtype, d, nlist, N, zipf):
         for nq in (500, 48 * nlist // 64):
             sizes = [size(nq, nprobe, k) for nprobe in (1, 2, 16, 63, 64, 65, 100, 128, 256)]
             assert sizes == sorted(sizes)
+    # (the coarse step takes the plan of one neighbour: it must stay inside the regions of any other)
+    assert len({tuple(map(tuple, hr.hr_ivf_workspace_layout(ix.handle, 1024, 32, k)[:-2])) for k in (1, 12, 13, 30, 100)}) == 1
     q = torch.randn(1024, d, generator=g, device="cuda")
     ws = torch.empty(size(1024, 32, 20), dtype=torch.uint8, device="cuda")
     for nq, k in ((1024, 10), (1024, 13), (700, 20)):
