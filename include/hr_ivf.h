@@ -74,9 +74,10 @@ enum {
  * may be among the best from the float32 rows: the same results, faster.  Where rows are so close to each other, or so long
  * against the distances between them, that rounded rows tell little (a common offset that squared distances cancel, near
  * duplicates, one row a hundred times as long as the others of its list), the scan looks for candidates with about 22 bits of
- * every element instead, with either flag from the float32 rows: the same results again, in about 1.25 times the time of rounded
- * rows on rows that are apart (1.5 of those with the table).  That is decided for the index at load and, for good, by
- * hr_ivf_refresh_rows.
+ * every element instead, with either flag from the float32 rows: the same results again, in 1.1 to 1.4 times the time of rounded
+ * rows on rows that are apart (up to 2.1 times that with the table).  That is decided for the index at load and by
+ * hr_ivf_refresh_rows: such rows at once, and that there are none left when a 64th of all rows or more have been replaced in whole
+ * lists.
  * With HR_BF16 | HR_LOAD_ROW_TABLES the rows are also kept as one binary16 table (N*d*2 bytes; every
  * bfloat16 value of magnitude 2^-14 .. 65504 is a binary16 value, smaller ones are rounded to a
  * multiple of 2^-24): the lists are then multiplied with the query rounded to binary16 (as HR_F16

@@ -138,15 +138,16 @@ struct hr_ivf_index {
     void* d_cent_lo;       // [nlist, d] binary16: (centroid - hi) * 2^11
     void* d_vec_hi;        // float32 lists only, when asked for and memory allows: [N, d] the rows rounded to binary16; else null
     void* d_vec16;         // bfloat16 lists only, when memory and the value range allow: [N, d] the rows as binary16
-    int* d_flag;           // device ints: [0] a bfloat16 value did not fit binary16, [1] a negative label, [2] [3] rows of lists with wide windows, by metric, [4] [5] h_tight is set, by metric
+    int* d_flag;           // device ints: [0] a bfloat16 value did not fit binary16, [1] a negative label, [2] [3] h_tight has been set, by metric
     // with d_vec16: report words of hr_ivf_refresh_rows, one for each call under way (host memory that kernels write; bit i of
     // over_used: word i belongs to a call), else null
     int *h_over, *d_over;  // their address on the host and on the device
     std::atomic<uint64_t> over_used;
     ListBound* d_list_bound;      // float32 lists: [nlist] what scan_slack needs to know of the list's rows, else null
     float2* d_spread;      // float32 lists: [nlist] how far the scores of their rows are apart (list_spread), else null
-    // float32 lists: host memory that kernels write, its address there and on the device: [metric] some list's bounds tell little
+    // float32 lists: host memory that kernels write, its address there and on the device: [metric] lists' bounds tell little
     int *h_tight, *d_tight;
+    std::atomic<int64_t> replaced;     // rows of wholly replaced lists since these were last looked over, while they tell little
     unsigned long long* d_hits;   // [nlist] probes per list since load / last reset
     int* d_resident;       // [nlist] 1 = the list's vectors are in place (all lists, until the caller says otherwise)
     int num_cus;
@@ -442,11 +443,11 @@ int hr_ivf_load(const float* centroids, const int64_t* list_offsets, const void*
     if (e == hipSuccess) e = hipMalloc(&ix->d_cent_hi, (size_t)nlist * d * 2);
     if (e == hipSuccess) e = hipMalloc(&ix->d_cent_lo, (size_t)nlist * d * 2);
     if (e == hipSuccess) e = hipMalloc(&ix->d_hits, (size_t)nlist * 8);
-    if (e == hipSuccess) e = hipMalloc(&ix->d_flag, 6 * sizeof(int));
+    if (e == hipSuccess) e = hipMalloc(&ix->d_flag, 4 * sizeof(int));
     if (e == hipSuccess) e = hipMalloc(&ix->d_resident, (size_t)nlist * sizeof(int));
     if (e == hipSuccess) e = launch_set_resident(ix->d_resident, (int)nlist, nullptr, nlist, 1, s);
     if (e == hipSuccess) e = hipMemsetAsync(ix->d_hits, 0, (size_t)nlist * 8, s);
-    if (e == hipSuccess) e = hipMemsetAsync(ix->d_flag, 0, 6 * sizeof(int), s);
+    if (e == hipSuccess) e = hipMemsetAsync(ix->d_flag, 0, 4 * sizeof(int), s);
     if (e == hipSuccess) e = launch_check_labels(list_ids, N, ix->d_flag + 1, s);
     if (e == hipSuccess) e = hipMemcpyAsync(ix->d_list_off, h_off, (size_t)(nlist + 1) * 4, hipMemcpyHostToDevice, s);
     if (e == hipSuccess && dtype == HR_F32) {
@@ -460,11 +461,11 @@ int hr_ivf_load(const float* centroids, const int64_t* list_offsets, const void*
             if (!ix->d_vec_hi) (void)hipGetLastError();          // (not an error of the load: the other path is taken)
         }
         const ListArgs a{(const float*)list_vectors, 0, N, ix->d_list_off, (int)nlist, d, 0, (int)nlist, ix->d_row_norm, ix->d_list_bound,
-                         ix->d_vec_hi, ix->d_spread, ix->d_tight, ix->d_flag + 4, 0, 0};
+                         ix->d_vec_hi, ix->d_spread, ix->d_tight, ix->d_flag + 2, 0, 0};
         e = hipMemsetAsync(ix->d_list_bound, 0, (size_t)nlist * sizeof(ListBound), s);
         if (e == hipSuccess) e = hipMemsetAsync(ix->d_spread, 0x7f, (size_t)nlist * sizeof(float2), s);      // (far apart, until they are known)
         if (e == hipSuccess) e = launch_list_bounds(a, s);
-        if (e == hipSuccess && N > 0) e = launch_wide_windows(a, ix->d_flag + 2, s);
+        if (e == hipSuccess && N > 0) e = launch_wide_windows(a, s);
     } else if (e == hipSuccess) {
         e = launch_row_norms(list_vectors, dtype, N, d, ix->d_row_norm, s);
     }
@@ -484,10 +485,8 @@ int hr_ivf_load(const float* centroids, const int64_t* list_offsets, const void*
         }
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    int flags[4] = {0, 0, 0, 0};                // (the first of d_flag)
+    int flags[2] = {0, 0};                      // (the first of d_flag)
     if (e == hipSuccess) e = hipMemcpy(flags, ix->d_flag, sizeof flags, hipMemcpyDeviceToHost);
-    for (int m = 0; m < 2 && e == hipSuccess && dtype == HR_F32; m++)
-        if ((int64_t)flags[2 + m] * kWindowShare > N) ix->h_tight[m] = 1;
     if (e == hipSuccess && ix->d_vec16 && flags[0]) {      // the lists are scanned as bfloat16
         (void)hipFree(ix->d_vec16);
         ix->d_vec16 = nullptr;
@@ -1064,8 +1063,14 @@ int hr_ivf_refresh_rows(hr_ivf_index* ix, int64_t row_begin, int64_t row_end, vo
         const int l0 = (int)(std::upper_bound(off, end, (int)row_begin) - off) - 1, l1 = (int)(std::lower_bound(off, end, (int)row_end) - off);
         const int whole0 = (int)(std::lower_bound(off, end, (int)row_begin) - off), whole1 = (int)(std::upper_bound(off, end, (int)row_end) - off) - 1;
         const ListArgs a{(const float*)ix->vectors, row_begin, n, ix->d_list_off, (int)ix->nlist, ix->d, l0, l1 - l0, ix->d_row_norm, ix->d_list_bound,
-                         ix->d_vec_hi, ix->d_spread, ix->d_tight, ix->d_flag + 4, whole0, whole1};
+                         ix->d_vec_hi, ix->d_spread, ix->d_tight, ix->d_flag + 2, whole0, whole1};
         HR_HIP(launch_list_bounds(a, s));
+        // (looked over when a 64th of the rows are new, or more: 16 us for 1024 lists)
+        if (whole1 > whole0 && (both_parts(ix, HR_METRIC_IP) || both_parts(ix, HR_METRIC_L2)) &&
+            (ix->replaced += off[whole1] - off[whole0]) * kWindowShare >= ix->N) {
+            ix->replaced = 0;
+            HR_HIP(launch_wide_windows(a, s));
+        }
     } else
         HR_HIP(launch_row_norms(rows, ix->dtype, n, ix->d, ix->d_row_norm + row_begin, s));
     return HR_OK;

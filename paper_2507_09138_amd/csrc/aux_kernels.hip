@@ -256,21 +256,50 @@ __device__ __forceinline__ void tell_wide(const ListArgs& a, int m)
     if (__hip_atomic_load(&a.told[m], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0 && atomicExch(&a.told[m], 1) == 0) ((volatile int*)a.tight)[m] = 1;
 }
 
-// rows of the lists whose window is wide, by metric (wide: two counters, zeroed before)
-__global__ __launch_bounds__(256) void k_wide_windows(ListArgs a, int* wide)
+// Whether both parts are multiplied, from the windows of all lists as they are now: at load, and where whole lists have been replaced since
+// (see hr_ivf_refresh_rows): one cluster of close rows that has come and gone would leave an index with row tables at half its speed for
+// good.  One workgroup: what has been said so far is taken back before it looks, and said again if a refresh on another stream has said
+// so meanwhile.
+__global__ __launch_bounds__(1024) void k_wide_windows(ListArgs a)
 {
-    const int l = blockIdx.x * 256 + threadIdx.x;
-    if (l >= a.nlist) return;
+    __shared__ unsigned long long s_rows[2];
+    __shared__ int s_any[2];
+    if (threadIdx.x < 2) {
+        s_rows[threadIdx.x] = 0;
+        s_any[threadIdx.x] = 0;
+        atomicExch(&a.told[threadIdx.x], 0);
+    }
+    __threadfence();
+    __syncthreads();
+    unsigned long long rows[2] = {0, 0};
+    bool any[2] = {false, false};
+    for (int64_t l = threadIdx.x; l < a.nlist; l += 1024) {
+        const float norm2 = bound_value(__hip_atomic_load(&a.bound[l].norm2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        const float left2 = bound_value(__hip_atomic_load(&a.bound[l].left2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        for (int m = 0; m < 2; m++) {
+            const float w = score_window(norm2, left2, m == HR_METRIC_L2 ? a.spread[l].y : a.spread[l].x, a.d);
+            if (w > 1.0f) rows[m] += a.list_off[l + 1] - a.list_off[l];
+            any[m] |= w > kWindowAny;
+        }
+    }
     for (int m = 0; m < 2; m++) {
-        const float w = score_window(bound_value(a.bound[l].norm2), bound_value(a.bound[l].left2), m == HR_METRIC_L2 ? a.spread[l].y : a.spread[l].x, a.d);
-        if (w > 1.0f) atomicAdd(&wide[m], a.list_off[l + 1] - a.list_off[l]);
-        if (w > kWindowAny) tell_wide(a, m);
+        if (rows[m]) atomicAdd(&s_rows[m], rows[m]);
+        if (any[m]) s_any[m] = 1;
+    }
+    __syncthreads();
+    if (threadIdx.x >= 2) return;
+    const int m = threadIdx.x;
+    if (s_any[m] || s_rows[m] * kWindowShare > (unsigned long long)a.list_off[a.nlist]) tell_wide(a, m);
+    else {
+        ((volatile int*)a.tight)[m] = 0;
+        __threadfence_system();
+        if (__hip_atomic_load(&a.told[m], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) ((volatile int*)a.tight)[m] = 1;
     }
 }
 
-hipError_t launch_wide_windows(const ListArgs& a, int* wide, hipStream_t s)
+hipError_t launch_wide_windows(const ListArgs& a, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_wide_windows, dim3((unsigned)((a.nlist + 255) / 256)), dim3(256), 0, s, a, wide);
+    hipLaunchKernelGGL(k_wide_windows, dim3(1), dim3(1024), 0, s, a);
     return hipGetLastError();
 }
 

@@ -249,13 +249,13 @@ struct ListArgs {
     ListBound* bound;           // [nlist]
     void* hi;                   // [N, d] rows rounded to binary16, or nullptr
     float2* spread;             // [nlist] deviations of the scores of a list's rows, by metric (list_spread)
-    int* tight;                 // host memory, by metric: set where a list's window is too wide (see score_window)
+    int* tight;                 // host memory, by metric: set where lists' windows are too wide (see score_window)
     int* told;                  // by metric: that has been done
     int whole0, whole1;         // the lists of which all rows are new
 };
 hipError_t launch_list_bounds(const ListArgs& a, hipStream_t s);
 constexpr int kWindowShare = 64;           // one row in so many in lists with wide windows: see score_window
-hipError_t launch_wide_windows(const ListArgs& a, int* wide, hipStream_t s);
+hipError_t launch_wide_windows(const ListArgs& a, hipStream_t s);
 hipError_t launch_read_hits(unsigned long long* hits, int64_t n, int64_t* out, int reset, hipStream_t s);
 hipError_t launch_lists_of_rows(const int32_t* rows, int64_t n, const int* list_off, int nlist, int32_t* out, hipStream_t s);
 hipError_t launch_reorder_probes(const int32_t* probe, int np, const int32_t* prev, int pp, const int32_t* hot, int nh,

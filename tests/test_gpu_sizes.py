@@ -848,7 +848,7 @@ def test_a_replaced_long_row_does_not_slow_its_list_for_good(tables):
 
 def _split_and_not(N, d, nlist, seed, tables, zipf=0.0, scale=1.0, hole=None):
     """Two indexes of the same float32 rows: one that was loaded with them, and one that was loaded with rows which differ by less than
-    rounding takes from them, so that it multiplies both parts of the rows for good."""
+    rounding takes from them and has had no list replaced in one call since, so that it multiplies both parts of the rows."""
     hr = _hr()
     g = torch.Generator(device="cuda")
     g.manual_seed(seed)
@@ -865,7 +865,9 @@ def _split_and_not(N, d, nlist, seed, tables, zipf=0.0, scale=1.0, hole=None):
     vec = (1 + 1e-5 * torch.randn(N, d, generator=g, device="cuda")).contiguous()
     split = hr.IvfIndex(cent, off, vec, ids, row_tables=tables)
     vec.copy_(good)
-    split.refresh_rows(0, N)
+    ends = [0, *((off[:-1] + off[1:]) // 2).tolist(), N]
+    for at, end in zip(ends[:-1], ends[1:]):
+        split.refresh_rows(at, end)
     torch.cuda.synchronize()
     return hr.IvfIndex(cent, off, good, ids, row_tables=tables), split, off, good, ids, g
 
@@ -952,6 +954,31 @@ def test_both_parts_are_multiplied_where_bounds_tell_little():
         torch.cuda.synchronize()
         assert (tiles(ix, "ip"), tiles(ix, "l2")) == (want, want)
         ix.close()
+    # lists that come and go: parts of them change nothing, nor fewer rows than a 64th
+    def replaced(ix, vec, a, b, rows):
+        vec[a:b] = rows[a:b]
+        ix.refresh_rows(a, b)
+        torch.cuda.synchronize()
+        return tiles(ix, "ip"), tiles(ix, "l2")
+
+    close = base + 0.01 * noise
+    vec = close.clone()
+    ix = load(vec)
+    assert replaced(ix, vec, 0, N // 2, noise) == (2, 2) and replaced(ix, vec, N // 2, N, noise) == (2, 2)
+    assert replaced(ix, vec, 0, N, noise) == (1, 1) and replaced(ix, vec, 0, N, close) == (2, 2) and replaced(ix, vec, 0, N, noise) == (1, 1)
+    ix.close()
+    # (a list of 600 rows, 400, 300 and the rest: 786 rows are a 64th)
+    at = [0, N, N + 400, N + 700, 50300]
+    many = torch.randn(at[-1], d, generator=g, device="cuda")
+    near = base + 0.01 * many[:at[3]]
+    vec = many.clone()
+    ix = load(vec, at)
+    assert replaced(ix, vec, 0, N, near) == (2, 2)
+    assert replaced(ix, vec, 0, N, many) == (2, 2) and replaced(ix, vec, N, at[2], many) == (1, 1)
+    assert replaced(ix, vec, 0, N, near) == (2, 2)
+    assert replaced(ix, vec, 0, N, many) == (2, 2) and replaced(ix, vec, N, at[2], near) == (2, 2)
+    assert replaced(ix, vec, N, at[2], many) == (2, 2) and replaced(ix, vec, at[2], at[3], many) == (2, 2) and replaced(ix, vec, 0, N, many) == (1, 1)
+    ix.close()
     # rows as long as each other: one list in a hundred whose window is a little wide (1.0 deviations) does not count, one in fifty does; one
     # of 4 always
     for lists, step, want in ((100, 0.163, 1), (50, 0.163, 2), (100, 0.08, 2)):
